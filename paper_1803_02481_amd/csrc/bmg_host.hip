@@ -268,6 +268,10 @@ struct hipbmg_hier {
     double *d_scal = nullptr;   // [0] ||b||, [1] relres, [2] ||r|| (mixed outer), [3] inner relres
     double *h_scal = nullptr;   // pinned mirror
     int lstar = 0;
+    // levels 0..dense_top as one dense operator instead of the collapsed
+    // workgroup (-1: not in use); formed by the first solve
+    int dense_top = -1, dense_n = 0, dense_ld = 0, dense_built = 0;
+    double *d_dense = nullptr;
     // agglomeration stages between the grid-wide kernels and the collapse
     int cl_nstage = 0;
     int cl_wg[CLUSTER_MAX_STAGES] = {}, cl_hi[CLUSTER_MAX_STAGES] = {};
@@ -632,6 +636,41 @@ static bool rc_on_the_fly(const hipbmg_hier *h, int nx, int ny, bool fine)
     return !fine && h->prm.nu1 == 2 && !h->no_fuse2 && (long long)nx * ny >= lim;
 }
 
+// LDS of a dense-operator column's workgroup with its highest level `top`:
+// offsets (in doubles) of x, r, b per level, then the coarse solve's vector
+static size_t dense_lds(const std::vector<int> &sx, const std::vector<int> &sy, int top, int *off)
+{
+    size_t t = 0;
+    for (int l = 0; l <= top; ++l) {
+        if (off) off[l] = (int)t;
+        t += 3 * (size_t)sx[l] * sy[l];
+    }
+    return t;
+}
+
+// Highest level run as one dense operator with everything below it (-1: none):
+// the largest below the finest with at most DENSE_UNKNOWNS unknowns whose
+// columns' workgroups fit their LDS.  Only where the caller leaves the coarse
+// levels to the library: a forced collapse level, forced stages or
+// cluster_wg = 0 (also what a batch uses: its problems' collapses run side by
+// side, one workgroup each) keep the collapsed workgroup.
+constexpr int DENSE_UNKNOWNS = 1024;
+
+static int choose_dense(const hipbmg_params &prm, const std::vector<int> &sx, const std::vector<int> &sy, int *n)
+{
+    *n = 0;
+    if (prm.collapse_level >= 0 || prm.cluster_wg != -1 || std::getenv("HIPBMG_STAGES")) return -1;
+    int top = -1;
+    for (int l = 0; l + 1 < (int)sx.size() && l < COLLAPSE_MAX_LEVELS; ++l) {
+        const long long m = (long long)(sx[l] - 2) * (sy[l] - 2);
+        const size_t lds = (dense_lds(sx, sy, l, nullptr) + (size_t)(sx[0] - 2) * (sy[0] - 2)) * sizeof(double);
+        if (m > DENSE_UNKNOWNS || lds > (size_t)DENSE_LDS) break;
+        top = l;
+        *n = (int)m;
+    }
+    return top;
+}
+
 // The model's view of level l: launch geometry of its down and up kernels and
 // whether it is staged in LDS when collapsed (levels fill the LDS budget from
 // the coarsest up, as the collapse launch stages them).
@@ -782,12 +821,15 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
         delete h;
         return st;
     };
+    const int dense_top = choose_dense(prm, sx, sy, &h->dense_n);
+    h->dense_ld = (h->dense_n + 127) / 128 * 128;
     {
         const bool mixed = prm.precision == HIPBMG_MIXED;
         const size_t fplane = (size_t)ny * pitch_for(nx);
         size_t need = levels_bytes<double>(sx, sy) + (mixed ? levels_bytes<float>(sx, sy) : 0) + (size_t(1) << 20);
         if (npt == 5 && prm.nu1 == 2 && prm.nu2 == 1 && L >= 2)
             need += dalloc_bytes(fplane, sizeof(double)) + (mixed ? dalloc_bytes(fplane, sizeof(float)) : 0);
+        if (dense_top >= 0) need += dalloc_bytes((size_t)h->dense_n * h->dense_ld, sizeof(double));
         const hipbmg_status rs = arena_reserve(h, need, s);
         if (rs != HIPBMG_OK) return bail(rs);
     }
@@ -1111,7 +1153,12 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
     } else {
         h->path_us = h->model_us[h->lstar];
     }
-    if (h->lstar >= L - 1) h->fused3 = 0;   // the finest level itself is collapsed
+    if (dense_top >= 0 && h->cl_nstage == 0) {
+        st = dalloc(h, &h->d_dense, (size_t)h->dense_n * h->dense_ld, s);
+        if (st != HIPBMG_OK) return bail(st);
+        h->dense_top = dense_top;
+    }
+    if (h->dense_top < 0 && h->lstar >= L - 1) h->fused3 = 0;   // the finest level itself is collapsed
     if (hipStreamSynchronize(s) != hipSuccess) return bail(fail(HIPBMG_EHIP, "setup failed: %s",
                                                              hipGetErrorString(hipGetLastError())));
     h->setup_ms = now_ms() - t0;
@@ -1239,7 +1286,9 @@ static hipError_t enqueue_vcycle(hipbmg_hier *h, const std::vector<LevelDev<T>> 
     const int L = skip_finest ? h->L - 1 : h->L, ls = h->lstar;
     const int nu1 = h->prm.nu1, nu2 = h->prm.nu2, rc = h->prm.residual_correction;
     // highest level below the grid-wide kernels: the first stage's, or l*
-    const int gtop = h->cl_nstage > 0 ? h->cl_hi[0] : ls;
+    // (or the dense operator's)
+    const bool dense = h->dense_top >= 0;
+    const int gtop = dense ? h->dense_top : h->cl_nstage > 0 ? h->cl_hi[0] : ls;
     int xb_after[HIPBMG_MAX_LEVELS], xres[HIPBMG_MAX_LEVELS];
     hipError_t e = hipSuccess;
     for (int l = L - 1; l > gtop; --l) {
@@ -1287,7 +1336,14 @@ static hipError_t enqueue_vcycle(hipbmg_hier *h, const std::vector<LevelDev<T>> 
         }
         xb_after[l] = xb;
     }
-    if (h->cl_nstage > 0) {
+    if (dense) {
+        // levels 0..gtop: one matrix-vector product
+        const int pk = prof_begin(h, -1, PrecIdx<T>::v, gtop, 2, false, s);
+        if ((e = launch_dense_apply<T>(h->d_dense, h->dense_n, h->dense_ld, lv[gtop], 1, active, s)) != hipSuccess)
+            return e;
+        prof_end(h, pk, s);
+        xres[gtop] = 1;
+    } else if (h->cl_nstage > 0) {
         // levels 0..gtop in one launch: the stages, then the collapse
         const ClusterArgs<T> c = cluster_args<T>(h, lv, d_lv, ls, h->cl_nstage, h->cl_wg, h->cl_hi, active);
         const int pk = prof_begin(h, -1, PrecIdx<T>::v, gtop, 2, false, s);
@@ -1357,6 +1413,36 @@ static hipError_t enqueue_vcycle(hipbmg_hier *h, const std::vector<LevelDev<T>> 
     return hipSuccess;
 }
 
+// Form the dense operator of levels 0..dense_top from the FP64 levels (the
+// FP32 cycles of a mixed solve use the same one), on the first solve's stream:
+// a hierarchy that is never solved with does not pay for it.  Every solve
+// synchronises its stream before it returns, so later solves on other streams
+// see it complete.
+static hipbmg_status ensure_dense(hipbmg_hier *h, hipStream_t s)
+{
+    if (h->dense_top < 0 || h->dense_built) return HIPBMG_OK;
+    DenseBuildArgs a{};
+    a.levels = h->d_lv;
+    a.top = h->dense_top;
+    a.nu1 = h->prm.nu1;
+    a.nu2 = h->prm.nu2;
+    a.rescorr = h->prm.residual_correction;
+    a.chol = h->d_chol;
+    a.nc = h->nc;
+    std::vector<int> sx(h->L), sy(h->L);
+    for (int l = 0; l < h->L; ++l) {
+        sx[l] = h->lv[l].nx;
+        sy[l] = h->lv[l].ny;
+    }
+    a.lds_y = (int)dense_lds(sx, sy, a.top, a.lds_off);
+    a.lds_doubles = a.lds_y + h->nc;
+    a.M = h->d_dense;
+    a.ld = h->dense_ld;
+    HIPCHK(launch_dense_build(a, h->dense_n, s));
+    h->dense_built = 1;
+    return HIPBMG_OK;
+}
+
 template <typename T> static T *&x3_of(hipbmg_hier *h);
 template <> double *&x3_of<double>(hipbmg_hier *h) { return h->x3_64; }
 template <> float *&x3_of<float>(hipbmg_hier *h) { return h->x3_32; }
@@ -1381,6 +1467,7 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
     const LevelDev<T> &F = lv[L - 1];
     const int *act = h->d_flags;
     const bool pipe = h->fused3 != 0;
+    STCHK(ensure_dense(h, s));
     T *xb[3] = {F.x[0], F.x[1], pipe ? x3_of<T>(h) : nullptr};
     // the convergence-test events, made on the handle's first solve (the
     // hierarchies of a batch never need them)

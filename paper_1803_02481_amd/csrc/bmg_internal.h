@@ -202,6 +202,26 @@ struct CollapseArgs {
 template <typename T>
 hipError_t launch_collapse(const CollapseArgs<T> &a, hipStream_t s);
 
+// Levels 0..top as one dense operator (bmg_dense.hip): M (n rows of ld columns,
+// ld = n rounded up to 128, the columns past n zero) with x_top = M b_top, the
+// V-cycle of levels top..0 from zero; n = (nx-2)(ny-2) of level top.
+constexpr int DENSE_MAX = 2048;               // largest ld
+constexpr int DENSE_LDS = 64 * 1024;          // bytes of LDS a column's workgroup may take
+struct DenseBuildArgs {
+    const LevelDev<double> *levels;           // device array, index = level
+    int top, nu1, nu2, rescorr;
+    const double *chol;                       // as in CollapseArgs
+    int nc;
+    int lds_off[COLLAPSE_MAX_LEVELS];         // doubles: x, r, b of each level at compact pitch
+    int lds_y, lds_doubles;
+    double *M;
+    int ld;
+};
+hipError_t launch_dense_build(const DenseBuildArgs &a, int n, hipStream_t s);
+template <typename T>
+hipError_t launch_dense_apply(const double *M, int n, int ld, const LevelDev<T> &lv, int xb, const int *active,
+                              hipStream_t s);
+
 // Agglomeration stages between the grid-wide kernels and the collapsed
 // workgroup (section 4: the coarse grid moves onto fewer and fewer
 // processors).  One launch of wg[0] workgroups: stage s runs levels
