@@ -128,12 +128,17 @@ hipbmg_status hipbmg3d_op_coarse_solve(hipbmg3d_handle h, const double *b, doubl
 /* Kernel timing of the solve phase: with enable = 1 every later solve
  * brackets its finest-level relaxation, residual, restriction and
  * interpolation launches with HIP events and accumulates their durations;
- * profile_read returns, for kernel class k (0 relaxation colours of the
- * finest level, 1 finest residual, with or without the norm, 2
- * finest-to-next restriction, 3 next-to-finest interpolation, 4 everything
- * below the finest level), the summed duration in ms, the number of launches
- * and the mean algorithmic bytes of one launch (FP64 values read and written
- * once each; 0 for class 4).  A 7-point finest level whose every interior
+ * profile_read returns, for kernel class k (0 relaxation of the finest level, 1
+ * its residual norm, 2 finest-to-next restriction with the residual it needs,
+ * 3 next-to-finest interpolation, 4 everything below the finest level), the
+ * summed duration in ms, the number of launches and the mean algorithmic bytes
+ * of one launch (FP64 values read and written once each; 0 for class 4).  A
+ * relaxation is two launches, the planes of even and of odd index, each
+ * counted as two of its four colour groups {0}, {1,2,4}, {3,5,6}, {7}, so a
+ * class-0 launch is a quarter of a sweep.  The odd planes' residual comes with
+ * the relaxation launch before it and the even planes' is a launch of half a
+ * level, counted as half a residual.  Outside profiling a cycle's norm is
+ * taken in the next cycle's first launch instead, the same bits.  A 7-point finest level whose every interior
  * diagonal is bitwise the sum of its six connections (finite volumes of pure
  * diffusion, hipbmg3d_fv7_from_cells) has that sum formed in its relaxation
  * and residual kernels instead of the C plane loaded, which shows as 8 bytes

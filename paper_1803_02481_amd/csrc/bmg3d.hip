@@ -27,6 +27,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 namespace {
@@ -443,8 +444,7 @@ struct LArgs {
     double *bc;
     double *partials;
     int rescorr;
-    double *xcz;       // restriction: the coarse iterate, cleared alongside
-    int zc;            // 7-point level whose diagonal is the sum of its connections
+    double *xcz;       // restriction: the coarse iterate, cleared alongside (or null)
 };
 
 // index of the neighbour at (DX,DY,DZ) of thread t of octant O
@@ -457,52 +457,85 @@ __device__ __forceinline__ long long nbr(const Oct &g, long long t)
     return on * g.oct + t + sz * g.plane + sy * g.px + sx;
 }
 
-template <bool NT>
-__device__ __forceinline__ double ldc(const double *p)
-{
-    if (NT) return __builtin_nontemporal_load(p);
-    return *p;
-}
-
-// sum_q A(p,q) x_q over the whole stencil of vertex t of octant O (NT: the
-// 7-point coefficients as nontemporal loads; ZC: the 7-point diagonal formed
-// as W_p + W_e + S_p + S_n + B_p + B_t in this order instead of loaded, which
-// the setup checked is bitwise the stored one; diag receives the diagonal)
-template <int NPT, int O, bool NT = false, bool ZC = false>
-__device__ __forceinline__ double apply_at(const Oct &g, const double *st, const double *x, long long t,
-                                           double *diag = nullptr)
+// The residual of row p, b_p - (A x)_p, as every kernel (grid-wide or
+// collapsed) forms it: b_p - A_pp x_p, plus the sum of the terms of the planes
+// above and below (off_plane, a chain of its own), then the terms of p's own
+// plane (in_plane), each one fused multiply-add in a fixed order.  The
+// relaxation adds it over A_pp to x_p.  Starting from the diagonal the partial
+// sums shrink towards the residual, so their rounding does too.
+template <int NPT, int O>
+__device__ __forceinline__ double off_plane(const Oct &g, const double *st, const double *x, long long t)
 {
     const long long F = g.field;
     const long long v = O * g.oct + t;
+    double s = 0.0;
     if (NPT == 7) {
-        // in a relaxation the coefficients stream through once per sweep
-        // (nontemporal); the iterate's octants are read again by the
-        // neighbouring colours
-        const double *C = st, *W = st + F, *S = st + 2 * F, *B = st + 3 * F;
-        const long long xw = nbr<O, -1, 0, 0>(g, t), xe = nbr<O, 1, 0, 0>(g, t);
-        const long long ys = nbr<O, 0, -1, 0>(g, t), yn = nbr<O, 0, 1, 0>(g, t);
+        const double *B = st + 3 * F;
         const long long zb = nbr<O, 0, 0, -1>(g, t), zt = nbr<O, 0, 0, 1>(g, t);
-        const double wv = ldc<NT>(W + v), we = ldc<NT>(W + xe), sv = ldc<NT>(S + v), sn = ldc<NT>(S + yn),
-                     bv = ldc<NT>(B + v), bt = ldc<NT>(B + zt);
-        const double cv = ZC ? wv + we + sv + sn + bv + bt : ldc<NT>(C + v);
-        if (diag) *diag = cv;
-        return cv * x[v] - wv * x[xw] - we * x[xe] - sv * x[ys] - sn * x[yn] - bv * x[zb] - bt * x[zt];
+        s += B[v] * x[zb];
+        s += B[zt] * x[zt];
     } else {
-        double s = ldc<NT>(st + v) * x[v];
 #define HB3_PAIR(o, dx, dy, dz)                                                                      \
     {                                                                                                \
         const long long qm = nbr<O, dx, dy, dz>(g, t), qp = nbr<O, -(dx), -(dy), -(dz)>(g, t);      \
-        s -= ldc<NT>(st + (1 + o) * F + v) * x[qm];                                                  \
-        s -= ldc<NT>(st + (1 + o) * F + qp) * x[qp];                                                 \
+        s += st[(1 + o) * F + v] * x[qm];                                                            \
+        s += st[(1 + o) * F + qp] * x[qp];                                                           \
     }
         HB3_PAIR(0, -1, -1, -1) HB3_PAIR(1, 0, -1, -1) HB3_PAIR(2, 1, -1, -1)
         HB3_PAIR(3, -1, 0, -1) HB3_PAIR(4, 0, 0, -1) HB3_PAIR(5, 1, 0, -1)
         HB3_PAIR(6, -1, 1, -1) HB3_PAIR(7, 0, 1, -1) HB3_PAIR(8, 1, 1, -1)
-        HB3_PAIR(9, -1, -1, 0) HB3_PAIR(10, 0, -1, 0) HB3_PAIR(11, 1, -1, 0)
-        HB3_PAIR(12, -1, 0, 0)
 #undef HB3_PAIR
-        return s;
     }
+    return s;
+}
+
+// the in-plane connections of vertex t in the order in_plane takes them:
+// west, east, south, north (7-point); south-west, north-east, south, north,
+// south-east, north-west, west, east (27-point)
+template <int NPT> struct InPlane { enum { n = NPT == 7 ? 4 : 8 }; };
+
+template <int NPT, int O>
+__device__ __forceinline__ void in_plane_coefs(const Oct &g, const double *st, long long t, double *k)
+{
+    const long long F = g.field;
+    const long long v = O * g.oct + t;
+    if (NPT == 7) {
+        k[0] = st[F + v];
+        k[1] = st[F + nbr<O, 1, 0, 0>(g, t)];
+        k[2] = st[2 * F + v];
+        k[3] = st[2 * F + nbr<O, 0, 1, 0>(g, t)];
+    } else {
+        k[0] = st[10 * F + v];
+        k[1] = st[10 * F + nbr<O, 1, 1, 0>(g, t)];
+        k[2] = st[11 * F + v];
+        k[3] = st[11 * F + nbr<O, 0, 1, 0>(g, t)];
+        k[4] = st[12 * F + v];
+        k[5] = st[12 * F + nbr<O, -1, 1, 0>(g, t)];
+        k[6] = st[13 * F + v];
+        k[7] = st[13 * F + nbr<O, 1, 0, 0>(g, t)];
+    }
+}
+
+// xn: the neighbours' values, as a function of their offset (dx, dy)
+template <int NPT, typename X>
+__device__ __forceinline__ double in_plane(const double *k, double s, X xn)
+{
+    if (NPT == 7) {
+        s += k[0] * xn(-1, 0);
+        s += k[1] * xn(1, 0);
+        s += k[2] * xn(0, -1);
+        s += k[3] * xn(0, 1);
+    } else {
+        s += k[0] * xn(-1, -1);
+        s += k[1] * xn(1, 1);
+        s += k[2] * xn(0, -1);
+        s += k[3] * xn(0, 1);
+        s += k[4] * xn(1, -1);
+        s += k[5] * xn(-1, 1);
+        s += k[6] * xn(-1, 0);
+        s += k[7] * xn(1, 0);
+    }
+    return s;
 }
 
 template <int O>
@@ -516,101 +549,444 @@ __device__ __forceinline__ bool thread_vertex(const Oct &g, long long t, int &i,
     return a < g.mx && inner(g, i, j, k);
 }
 
-// x_p += (b_p - (A x)_p) / A_pp at vertex t of octant O
-template <int NPT, int O, bool ZC = false>
-__device__ __forceinline__ void gs_point(const LArgs &a, long long t)
+// ---------------------------------------------------------------------------
+// relaxation by planes.  Colours 0..3 are the planes of even k, 4..7 those of
+// odd k, and a plane couples only to the planes above and below, which are of
+// the other parity.  So a sweep is two launches, the even planes (four colours
+// in turn) and then the odd ones, and within a launch every plane is a
+// two-dimensional four-colour relaxation whose terms of the neighbouring
+// planes do not change: a thread loads its vertex's row of the operator and
+// sums those terms before the first colour, the plane's iterate waits in LDS,
+// and a colour costs four or eight LDS reads and a barrier.
+//
+// Small levels are bound by latency: a half sweep takes one memory round trip
+// and four short phases, 6-7 us for a level of 9^3 to 65^3 where four launches
+// of one colour each took 16-19 us.  All loads of a row go out before anything
+// waits (a thread with the four rows of its cell kept them in batches: 15-20
+// us).  Large ones are bound by memory: at 257^3 (7-point) a half sweep moves
+// 622 MB in 125 us (5.0 TB/s; 543 MB if every value crossed once), at 129^3
+// (27-point) 255 MB in 62 us.  Coefficients are plain loads: marked
+// nontemporal, the connections that two rows of a tile share are fetched twice
+// (257^3 102 -> 105-111 ms a solve).
+//
+// A workgroup owns tr rows of tc cells of a plane (a cell: the vertices of
+// the plane's four octants with one sub-grid position).  What it needs from
+// beyond its tile it relaxes itself: a chain of colours reaches one cell to
+// the left, two to the right and one row up (its even-row colours only), and
+// one cell and one row further down where the residual follows.  Rows and
+// columns beyond that are read as they were before the half sweep, which is
+// why the relaxed planes go to a second buffer.
+// ---------------------------------------------------------------------------
+struct Tile {
+    int ncol, nrow, nk, kk0;   // cells and planes with interior vertices
+    int tc, tr, ntx, nty;      // tiles of a plane
+    int hx, hy;                // halo cells to the left, rows below
+    int cw, rw;                // cells x rows relaxed
+    int n01, n23;              // threads of an even-row and of an odd-row group
+    unsigned ntiles;
+};
+
+struct PArgs {
+    Oct g;
+    const double *st, *b;
+    const double *xs, *xo;     // the planes' own iterate, the other parity's
+    double *xd;                // the relaxed planes
+    double *r;
+    const double *w;           // restriction
+    Oct c;
+    double *bc, *xcz;
+    double *partials;
+    Tile t;
+};
+
+// a thread's vertex: its row of the operator as loaded, then its off-plane sum
+template <int NPT>
+struct Row {
+    enum { noff = NPT == 7 ? 2 : 18 };
+    double b, off, d, k[InPlane<NPT>::n];
+    double oc[noff], ox[noff];
+    bool in;
+};
+
+// every load of the row of vertex (i, j) of octant O, none of them waited
+// for: at a vertex that is not interior they stay inside the fields, and are
+// not used
+template <int NPT, int O, bool ZC, bool OFF>
+__device__ __forceinline__ void load_row(const PArgs &a, int i, int j, long long t, Row<NPT> &R)
 {
-    int i, j, k;
-    if (!thread_vertex<O>(a.g, t, i, j, k)) return;
-    const long long v = O * a.g.oct + t;
-    if (ZC && NPT == 7) {
-        double d;
-        const double s = apply_at<NPT, O, true, true>(a.g, a.st, a.x, t, &d);
-        a.x[v] += (a.b[v] - s) / d;
+    R.in = i >= 1 && i <= a.g.nx - 2 && j >= 1 && j <= a.g.ny - 2;
+    const long long F = a.g.field, v = O * a.g.oct + t;
+    if (NPT == 7) {
+        if (OFF || ZC) {
+            R.oc[0] = a.st[3 * F + v];
+            R.oc[1] = a.st[3 * F + nbr<O, 0, 0, 1>(a.g, t)];
+        }
+        if (OFF) {
+            R.ox[0] = a.xo[nbr<O, 0, 0, -1>(a.g, t)];
+            R.ox[1] = a.xo[nbr<O, 0, 0, 1>(a.g, t)];
+        }
+    } else if (OFF) {
+#define HB3_PAIR(o, dx, dy)                                                                          \
+    {                                                                                                \
+        const long long qm = nbr<O, dx, dy, -1>(a.g, t), qp = nbr<O, -(dx), -(dy), 1>(a.g, t);       \
+        R.oc[2 * o] = a.st[(1 + o) * F + v];                                                         \
+        R.ox[2 * o] = a.xo[qm];                                                                      \
+        R.oc[2 * o + 1] = a.st[(1 + o) * F + qp];                                                    \
+        R.ox[2 * o + 1] = a.xo[qp];                                                                  \
+    }
+        HB3_PAIR(0, -1, -1) HB3_PAIR(1, 0, -1) HB3_PAIR(2, 1, -1)
+        HB3_PAIR(3, -1, 0) HB3_PAIR(4, 0, 0) HB3_PAIR(5, 1, 0)
+        HB3_PAIR(6, -1, 1) HB3_PAIR(7, 0, 1) HB3_PAIR(8, 1, 1)
+#undef HB3_PAIR
+    }
+    in_plane_coefs<NPT, O>(a.g, a.st, t, R.k);
+    if (!(NPT == 7 && ZC)) R.d = a.st[v];
+    R.b = a.b[v];
+}
+
+// the off-plane sum (a chain in the order of the pairs) and, where it is
+// formed, the diagonal W_p + W_e + S_p + S_n + B_p + B_t (in this order the
+// setup found it bitwise the stored one)
+template <int NPT, bool ZC, bool OFF>
+__device__ __forceinline__ void finish_row(Row<NPT> &R)
+{
+    R.off = 0.0;
+    if (OFF) {
+#pragma unroll
+        for (int q = 0; q < Row<NPT>::noff; ++q) R.off += R.oc[q] * R.ox[q];
+    }
+    if (NPT == 7 && ZC) R.d = R.k[0] + R.k[1] + R.k[2] + R.k[3] + R.oc[0] + R.oc[1];
+}
+
+// the plane's iterate in LDS: one array per octant of the plane, rows lr0..,
+// cells la0.. of the window
+struct Window {
+    double *x;
+    int stride, size;
+};
+
+// value at (dx, dy) from the vertex of octant O (its plane's parity dropped) in cell `at`
+template <int O>
+__device__ __forceinline__ double win(const Window &w, int at, int dx, int dy)
+{
+    const int ox = (O & 1) + dx, oy = ((O >> 1) & 1) + dy;
+    const int q = (ox & 1) | ((oy & 1) << 1);
+    return w.x[q * w.size + at + (oy >> 1) * w.stride + (ox >> 1)];
+}
+
+template <int NPT, int Q>
+__device__ __forceinline__ double row_resid(const Window &w, int at, const Row<NPT> &R)
+{
+    double s = R.b - R.d * w.x[Q * w.size + at];
+    s += R.off;
+    return in_plane<NPT>(R.k, s, [&](int dx, int dy) { return win<Q>(w, at, dx, dy); });
+}
+
+template <int NPT, int Q>
+__device__ __forceinline__ void relax_colour(const Window &w, int at, const Row<NPT> &R)
+{
+    if (R.in) w.x[Q * w.size + at] += row_resid<NPT, Q>(w, at, R) / R.d;
+}
+
+// the window's iterate into LDS: zero, or as stored
+template <int PZ, bool ZERO>
+__device__ __forceinline__ void fill_window(const PArgs &a, const Window &w, int la0, int lr0, int kk)
+{
+    for (int e = threadIdx.x; e < (ZERO ? 4 * w.size : w.size); e += blockDim.x) {
+        if (ZERO) {
+            w.x[e] = 0.0;
+            continue;
+        }
+        const int row = e / w.stride, ca = la0 + e - row * w.stride, cr = lr0 + row;
+        const double *x = a.xs + 4 * PZ * a.g.oct + (long long)kk * a.g.plane + (long long)cr * a.g.px + ca;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w.x[q * w.size + e] = x[q * a.g.oct];
+    }
+}
+
+// fixed-order sum over the workgroup (up to 16 waves) into partials[blk]
+__device__ __forceinline__ void block_partial(double sq, double *partials, unsigned blk)
+{
+    __shared__ double ws[16];
+    for (int off = 32; off >= 1; off >>= 1) sq += __shfl_xor(sq, off, 64);
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = ws[0];
+        for (unsigned q = 1; q < (blockDim.x + 63) / 64; ++q) s += ws[q];
+        partials[blk] = s;
+    }
+}
+
+constexpr int PLANE_THREADS = 1024;
+
+// a tile of a plane and a thread's part in it.  Threads come in groups by
+// colour, padded to whole waves so that a wave's vertices are of one octant:
+// 7-point levels have two (even rows: colours 0 and 1, both on one thread; odd
+// rows: 2 and 3), 27-point levels, whose rows take 46 loads, one per colour.
+template <int NPT>
+struct Place {
+    int kk, a0, a1, r0, r1;      // plane, owned cells and rows
+    int la0, lr0, lr;            // window origin and rows
+    Window w;
+    int group, ca, cr, at;       // this thread's cell
+    long long t;
+    bool valid, own;
+
+    __device__ __forceinline__ Place(const PArgs &a, unsigned lb, double *sx)
+    {
+        const Tile &T = a.t;
+        const int tx = lb % T.ntx, ty = (lb / T.ntx) % T.nty;
+        kk = T.kk0 + (int)(lb / (T.ntx * T.nty));
+        a0 = tx * T.tc;
+        a1 = min(a0 + T.tc, T.ncol);
+        r0 = ty * T.tr;
+        r1 = min(r0 + T.tr, T.nrow);
+        const int ca0 = max(a0 - T.hx, 0), ca1 = min(a1 + 2, T.ncol), cr0 = max(r0 - T.hy, 0),
+                  cr1 = min(r1 + 1, T.nrow);
+        la0 = max(ca0 - 1, 0);
+        lr0 = max(cr0 - 1, 0);
+        lr = min(cr1, a.g.my - 1) - lr0 + 1;
+        w.x = sx;
+        w.stride = min(ca1, a.g.mx - 1) - la0 + 1;
+        w.size = w.stride * lr;
+        int e = threadIdx.x;
+        if (NPT == 7) {
+            group = e >= T.n01 ? 1 : 0;
+            e -= group * T.n01;
+        } else {
+            group = e < T.n01 ? 0 : e < 2 * T.n01 ? 1 : e < 2 * T.n01 + T.n23 ? 2 : 3;
+            e -= group < 2 ? group * T.n01 : 2 * T.n01 + (group - 2) * T.n23;
+        }
+        group = __builtin_amdgcn_readfirstlane(group);
+        const bool odd = group >= (NPT == 7 ? 1 : 2);   // the row above the tile: even vertices only
+        const int row = e / T.cw;
+        ca = ca0 + e - row * T.cw;
+        cr = cr0 + row;
+        valid = ca < ca1 && cr < (odd ? r1 : cr1);
+        own = valid && ca >= a0 && ca < a1 && cr >= r0 && cr < r1;
+        // threads without a vertex load the tile's last
+        ca = min(ca, ca1 - 1);
+        cr = min(cr, (odd ? r1 : cr1) - 1);
+        at = (cr - lr0) * w.stride + ca - la0;
+        t = (long long)kk * a.g.plane + (long long)cr * a.g.px + ca;
+    }
+};
+
+template <int NPT> struct Pts { enum { n = NPT == 7 ? 2 : 1 }; };   // vertices of a thread
+
+template <int NPT, int PZ, bool ZC, bool OFF>
+__device__ __forceinline__ void load_rows(const PArgs &a, const Place<NPT> &P, Row<NPT> *R)
+{
+    const int i = 2 * P.ca, j = 2 * P.cr;
+    if (NPT == 7) {
+        if (P.group == 0) {
+            load_row<NPT, 4 * PZ + 0, ZC, OFF>(a, i, j, P.t, R[0]);
+            load_row<NPT, 4 * PZ + 1, ZC, OFF>(a, i + 1, j, P.t, R[Pts<NPT>::n - 1]);
+        } else {
+            load_row<NPT, 4 * PZ + 2, ZC, OFF>(a, i, j + 1, P.t, R[0]);
+            load_row<NPT, 4 * PZ + 3, ZC, OFF>(a, i + 1, j + 1, P.t, R[Pts<NPT>::n - 1]);
+        }
+    } else {
+        if (P.group == 0) load_row<NPT, 4 * PZ + 0, ZC, OFF>(a, i, j, P.t, R[0]);
+        else if (P.group == 1) load_row<NPT, 4 * PZ + 1, ZC, OFF>(a, i + 1, j, P.t, R[0]);
+        else if (P.group == 2) load_row<NPT, 4 * PZ + 2, ZC, OFF>(a, i, j + 1, P.t, R[0]);
+        else load_row<NPT, 4 * PZ + 3, ZC, OFF>(a, i + 1, j + 1, P.t, R[0]);
+    }
+#pragma unroll
+    for (int q = 0; q < Pts<NPT>::n; ++q) R[q].in = R[q].in && P.valid;
+}
+
+// f(colour constant, row) for this thread's vertices
+template <int NPT, typename Fn>
+__device__ __forceinline__ void each_vertex(const Place<NPT> &P, const Row<NPT> *R, Fn f)
+{
+    if (NPT == 7) {
+        if (P.group == 0) {
+            f(std::integral_constant<int, 0>{}, R[0]);
+            f(std::integral_constant<int, 1>{}, R[Pts<NPT>::n - 1]);
+        } else {
+            f(std::integral_constant<int, 2>{}, R[0]);
+            f(std::integral_constant<int, 3>{}, R[Pts<NPT>::n - 1]);
+        }
+    } else {
+        if (P.group == 0) f(std::integral_constant<int, 0>{}, R[0]);
+        else if (P.group == 1) f(std::integral_constant<int, 1>{}, R[0]);
+        else if (P.group == 2) f(std::integral_constant<int, 2>{}, R[0]);
+        else f(std::integral_constant<int, 3>{}, R[0]);
+    }
+}
+
+template <int NPT, int Q>
+__device__ __forceinline__ void colour_phase(const Place<NPT> &P, const Row<NPT> *R)
+{
+    constexpr int grp = NPT == 7 ? Q >> 1 : Q, q = NPT == 7 ? Q & 1 : 0;
+    if (P.group == grp) relax_colour<NPT, Q>(P.w, P.at, R[q]);
+}
+
+// squares of the residual at this thread's own vertices
+template <int NPT>
+__device__ __forceinline__ double squares(const Place<NPT> &P, const Row<NPT> *R)
+{
+    double sq = 0.0;
+    if (P.own)
+        each_vertex<NPT>(P, R, [&](auto c, const Row<NPT> &r) {
+            constexpr int Q = decltype(c)::value;
+            if (!r.in) return;
+            const double q = row_resid<NPT, Q>(P.w, P.at, r);
+            sq += q * q;
+        });
+    return sq;
+}
+
+// Half a sweep: colours 4 PZ .. 4 PZ + 3 on the planes of parity PZ.
+// ZERO: the sweep starts from x = 0 (the even planes then read no iterate and
+// no coefficient towards other planes).  RES: 1 stores the residual the relaxed
+// planes end with, 2 sums its squares (both only right for PZ = 1, the end of
+// the sweep); 3 sums the squares of the residual they start with.
+template <int NPT, int PZ, bool ZC, bool ZERO, int RES>
+__global__ __launch_bounds__(PLANE_THREADS) void k3_plane(PArgs a)
+{
+    extern __shared__ double sx[];
+    const unsigned lb = xcd_block(blockIdx.x, gridDim.x);
+    if (lb >= a.t.ntiles) {
+        if (RES >= 2 && threadIdx.x == 0) a.partials[lb] = 0.0;
         return;
     }
-    const double s = apply_at<NPT, O, true>(a.g, a.st, a.x, t);
-    a.x[v] += (a.b[v] - s) / a.st[v];
-}
-
-// one colour of the relaxation on octant O.  On the coarse levels a launch
-// holds a wave or less per SIMD; a four-wave occupancy target leaves the
-// registers to issue every load of a 27-point row before the first use (at
-// the default target they go out in three or four dependent batches)
-template <int NPT, int O>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k3_gs(LArgs a)
-{
-    const long long t = xcd_block(blockIdx.x, gridDim.x) * 256LL + threadIdx.x;
-    if (t >= a.g.oct) return;
-    gs_point<NPT, O>(a, t);
-}
-
-// 7-point operators: a colour couples only to the three colours that differ
-// from it in one index parity, so colours 1, 2, 4 do not couple to each other,
-// nor do 3, 5, 6.  Running {0}, {1,2,4}, {3,5,6}, {7} as four launches updates
-// every vertex from the same values as the colour order 0..7 (bitwise the
-// same sweep), and one thread's three vertices share their neighbours' loads.
-template <int G, bool ZC = false>
-__global__ __launch_bounds__(256) void k3_gs7g(LArgs a)
-{
-    const long long t = xcd_block(blockIdx.x, gridDim.x) * 256LL + threadIdx.x;
-    if (t >= a.g.oct) return;
-    if (G == 0) {
-        gs_point<7, 0, ZC>(a, t);
-    } else if (G == 1) {
-        gs_point<7, 1, ZC>(a, t);
-        gs_point<7, 2, ZC>(a, t);
-        gs_point<7, 4, ZC>(a, t);
-    } else if (G == 2) {
-        gs_point<7, 3, ZC>(a, t);
-        gs_point<7, 5, ZC>(a, t);
-        gs_point<7, 6, ZC>(a, t);
-    } else {
-        gs_point<7, 7, ZC>(a, t);
+    const Place<NPT> P(a, lb, sx);
+    constexpr bool OFF = !(ZERO && PZ == 0);
+    Row<NPT> R[Pts<NPT>::n];
+    load_rows<NPT, PZ, ZC, OFF>(a, P, R);
+    fill_window<PZ, ZERO>(a, P.w, P.la0, P.lr0, P.kk);
+#pragma unroll
+    for (int q = 0; q < Pts<NPT>::n; ++q) finish_row<NPT, ZC, OFF>(R[q]);
+    __syncthreads();
+    double sq = 0.0;
+    if (RES == 3) {
+        sq = squares(P, R);
+        __syncthreads();
     }
+    colour_phase<NPT, 0>(P, R);
+    __syncthreads();
+    colour_phase<NPT, 1>(P, R);
+    __syncthreads();
+    colour_phase<NPT, 2>(P, R);
+    __syncthreads();
+    colour_phase<NPT, 3>(P, R);
+    if (RES == 1 || RES == 2) __syncthreads();
+    if (P.own) {
+        const long long v = 4 * PZ * a.g.oct + P.t;
+        each_vertex<NPT>(P, R, [&](auto c, const Row<NPT> &r) {
+            constexpr int Q = decltype(c)::value;
+            if (!r.in) return;
+            a.xd[v + Q * a.g.oct] = P.w.x[Q * P.w.size + P.at];
+            if (RES == 1) a.r[v + Q * a.g.oct] = row_resid<NPT, Q>(P.w, P.at, r);
+        });
+    }
+    if (RES == 2) sq = squares(P, R);
+    if (RES >= 2) block_partial(sq, a.partials, lb);
 }
 
-// residual r = b - A x (STORE) and/or block sums of r^2 (NORM); blockIdx.y = octant
-template <int NPT, int O, bool STORE, bool NORM, bool ZC = false>
-__device__ __forceinline__ double resid_at(const LArgs &a, long long t)
+// Residual on the planes of parity PZ with the same tiles.  NORM: its squares'
+// block sums, over the same threads and in the same order as k3_plane does
+// with RES 2 (PZ = 1) and 3 (PZ = 0).
+// Otherwise (PZ = 0): with the odd planes' residual in a.r already, the
+// restriction as well: coarse vertex (I, J, K) sits in cell (I, J) of the even
+// plane K and gathers this plane's residual from LDS (a halo cell to the left
+// and a halo row below) and its neighbours' from memory, so the even planes'
+// is written only for the interpolation's r/C and never read back here.
+template <int NPT, int PZ, bool ZC, bool NORM>
+__global__ __launch_bounds__(PLANE_THREADS) void k3_plane_resid(PArgs a)
+{
+    extern __shared__ double sx[];
+    const unsigned lb = xcd_block(blockIdx.x, gridDim.x);
+    if (lb >= a.t.ntiles) {
+        if (NORM && threadIdx.x == 0) a.partials[lb] = 0.0;
+        return;
+    }
+    const Place<NPT> P(a, lb, sx);
+    Row<NPT> R[Pts<NPT>::n];
+    load_rows<NPT, PZ, ZC, true>(a, P, R);
+    fill_window<PZ, false>(a, P.w, P.la0, P.lr0, P.kk);
+#pragma unroll
+    for (int q = 0; q < Pts<NPT>::n; ++q) finish_row<NPT, ZC, true>(R[q]);
+    __syncthreads();
+    if (NORM) {
+        block_partial(squares(P, R), a.partials, lb);
+        return;
+    }
+    const long long v = 4 * PZ * a.g.oct + P.t;
+    double rv[Pts<NPT>::n];
+    each_vertex<NPT>(P, R, [&](auto c, const Row<NPT> &r) {
+        constexpr int Q = decltype(c)::value;
+        const double q = r.in ? row_resid<NPT, Q>(P.w, P.at, r) : 0.0;
+        if (Q != 0 && P.own && r.in) a.r[v + Q * a.g.oct] = q;
+        rv[(NPT == 7 ? Q & 1 : 0)] = q;
+    });
+    __syncthreads();   // every read of the iterate is done: its window takes the residual
+    each_vertex<NPT>(P, R, [&](auto c, const Row<NPT> &) {
+        constexpr int Q = decltype(c)::value;
+        if (P.valid) P.w.x[Q * P.w.size + P.at] = rv[(NPT == 7 ? Q & 1 : 0)];
+    });
+    __syncthreads();
+    if (P.group != 0 || !P.own || !inner(a.c, P.ca, P.cr, P.kk)) return;
+    const Oct &g = a.g;
+    double s = 0.0;
+#pragma unroll
+    for (int ez = -1; ez <= 1; ++ez)
+#pragma unroll
+        for (int ey = -1; ey <= 1; ++ey)
+#pragma unroll
+            for (int ex = -1; ex <= 1; ++ex) {
+                const int pi = 2 * P.ca + ex, pj = 2 * P.cr + ey, pk = 2 * P.kk + ez;
+                const int mI = (ex == -1 ? 1 : 0) | (ey == -1 ? 2 : 0) | (ez == -1 ? 4 : 0);
+                const double q = ez == 0 ? win<0>(P.w, P.at, ex, ey) : a.r[vid(g, pi, pj, pk)];
+                s += weight_on(g, a.w, pi, pj, pk, mI) * q;
+            }
+    const long long vc = vid(a.c, P.ca, P.cr, P.kk);
+    a.bc[vc] = s;
+    if (a.xcz) a.xcz[vc] = 0.0;
+}
+
+// residual r = b - A x of a whole level; blocks interleave the octants
+// (octant = block mod 8), so that the eight octants of one region run together
+// and share their neighbours in L2
+template <int NPT, int O>
+__device__ __forceinline__ void resid_at(const LArgs &a, long long t)
 {
     int i, j, k;
-    if (!thread_vertex<O>(a.g, t, i, j, k)) {
-        if (STORE) a.r[O * a.g.oct + t] = 0.0;
-        return 0.0;
+    const Oct &g = a.g;
+    if (!thread_vertex<O>(g, t, i, j, k)) {
+        a.r[O * g.oct + t] = 0.0;
+        return;
     }
-    const long long v = O * a.g.oct + t;
-    const double r = a.b[v] - apply_at<NPT, O, false, ZC>(a.g, a.st, a.x, t);
-    if (STORE) a.r[v] = r;
-    return NORM ? r * r : 0.0;
+    const long long v = O * g.oct + t;
+    double kc[InPlane<NPT>::n];
+    in_plane_coefs<NPT, O>(g, a.st, t, kc);
+    double s = a.b[v] - a.st[v] * a.x[v];
+    s += off_plane<NPT, O>(g, a.st, a.x, t);
+    a.r[v] = in_plane<NPT>(kc, s, [&](int dx, int dy) {
+        const int ox = (O & 1) + dx, oy = ((O >> 1) & 1) + dy;
+        const long long q = ((ox & 1) | ((oy & 1) << 1) | (O & 4)) * g.oct + t;
+        return a.x[q + (oy >> 1) * g.px + (ox >> 1)];
+    });
 }
 
-// blocks interleave the octants (octant = block mod 8), so that the eight
-// octants of one region run together and share their neighbours in L2
-template <int NPT, bool STORE, bool NORM, bool ZC = false>
+template <int NPT>
 __global__ __launch_bounds__(256) void k3_resid(LArgs a)
 {
     const unsigned lb = xcd_block(blockIdx.x, gridDim.x);
     const long long t = (lb >> 3) * 256LL + threadIdx.x;
-    double sq = 0.0;
-    if (t < a.g.oct) {
-        switch (lb & 7) {
-        case 0: sq = resid_at<NPT, 0, STORE, NORM, ZC>(a, t); break;
-        case 1: sq = resid_at<NPT, 1, STORE, NORM, ZC>(a, t); break;
-        case 2: sq = resid_at<NPT, 2, STORE, NORM, ZC>(a, t); break;
-        case 3: sq = resid_at<NPT, 3, STORE, NORM, ZC>(a, t); break;
-        case 4: sq = resid_at<NPT, 4, STORE, NORM, ZC>(a, t); break;
-        case 5: sq = resid_at<NPT, 5, STORE, NORM, ZC>(a, t); break;
-        case 6: sq = resid_at<NPT, 6, STORE, NORM, ZC>(a, t); break;
-        default: sq = resid_at<NPT, 7, STORE, NORM, ZC>(a, t); break;
-        }
-    }
-    if (NORM) {
-        for (int off = 32; off >= 1; off >>= 1) sq += __shfl_xor(sq, off, 64);
-        __shared__ double ws[4];
-        if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sq;
-        __syncthreads();
-        if (threadIdx.x == 0) a.partials[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
+    if (t >= a.g.oct) return;
+    switch (lb & 7) {
+    case 0: resid_at<NPT, 0>(a, t); break;
+    case 1: resid_at<NPT, 1>(a, t); break;
+    case 2: resid_at<NPT, 2>(a, t); break;
+    case 3: resid_at<NPT, 3>(a, t); break;
+    case 4: resid_at<NPT, 4>(a, t); break;
+    case 5: resid_at<NPT, 5>(a, t); break;
+    case 6: resid_at<NPT, 6>(a, t); break;
+    default: resid_at<NPT, 7>(a, t); break;
     }
 }
 
@@ -702,7 +1078,7 @@ __global__ __launch_bounds__(256) void k3_restrict(LArgs a)
     sub_coords(c, ts, ca, cb, cc);
     const int I = 2 * ca + (oc & 1), J = 2 * cb + ((oc >> 1) & 1), K = 2 * cc + (oc >> 2);
     // the coarse level's iterate starts at zero (every entry, boundary included)
-    a.xcz[t] = 0.0;
+    if (a.xcz) a.xcz[t] = 0.0;
     if (ca >= c.mx || !inner(c, I, J, K)) {
         a.bc[t] = 0.0;
         return;
@@ -796,28 +1172,42 @@ __device__ __forceinline__ int nbr_rt(const Oct &g, int o, int t, int dx, int dy
     return on * (int)g.oct + t + (oz >> 1) * (int)g.plane + (oy >> 1) * g.px + (ox >> 1);
 }
 
-// apply_at with the octant at run time (same expressions, same order)
-__device__ __forceinline__ double apply_rt(const CLev &L, int o, int t)
+// the residual of a row with the octant at run time (same terms, same order)
+__device__ __forceinline__ double row_rt(const CLev &L, int o, int t)
 {
     const Oct &g = L.g;
     const int F = (int)g.field;
     const int v = o * (int)g.oct + t;
     const double *st = L.st, *x = L.x;
+    double s = L.b[v] - st[v] * x[v], off = 0.0;
     if (L.npt == 7) {
-        const double *C = st, *W = st + F, *S = st + 2 * F, *B = st + 3 * F;
+        const double *W = st + F, *S = st + 2 * F, *B = st + 3 * F;
         const int xw = nbr_rt(g, o, t, -1, 0, 0), xe = nbr_rt(g, o, t, 1, 0, 0);
         const int ys = nbr_rt(g, o, t, 0, -1, 0), yn = nbr_rt(g, o, t, 0, 1, 0);
         const int zb = nbr_rt(g, o, t, 0, 0, -1), zt = nbr_rt(g, o, t, 0, 0, 1);
-        const double cv = C[v], wv = W[v], we = W[xe], sv = S[v], sn = S[yn], bv = B[v], bt = B[zt];
-        return cv * x[v] - wv * x[xw] - we * x[xe] - sv * x[ys] - sn * x[yn] - bv * x[zb] - bt * x[zt];
+        off += B[v] * x[zb];
+        off += B[zt] * x[zt];
+        s += off;
+        s += W[v] * x[xw];
+        s += W[xe] * x[xe];
+        s += S[v] * x[ys];
+        s += S[yn] * x[yn];
+        return s;
     }
-    double s = st[v] * x[v];
 #pragma unroll
-    for (int q = 0; q < 13; ++q) {
-        const int dx = q % 3 - 1, dy = (q / 3) % 3 - 1, dz = q / 9 - 1;
-        const int qm = nbr_rt(g, o, t, dx, dy, dz), qp = nbr_rt(g, o, t, -dx, -dy, -dz);
-        s -= st[(1 + q) * F + v] * x[qm];
-        s -= st[(1 + q) * F + qp] * x[qp];
+    for (int q = 0; q < 9; ++q) {
+        const int dx = q % 3 - 1, dy = q / 3 - 1;
+        const int qm = nbr_rt(g, o, t, dx, dy, -1), qp = nbr_rt(g, o, t, -dx, -dy, 1);
+        off += st[(1 + q) * F + v] * x[qm];
+        off += st[(1 + q) * F + qp] * x[qp];
+    }
+    s += off;
+#pragma unroll
+    for (int q = 9; q < 13; ++q) {
+        const int dx = q % 3 - 1, dy = (q / 3) % 3 - 1;
+        const int qm = nbr_rt(g, o, t, dx, dy, 0), qp = nbr_rt(g, o, t, -dx, -dy, 0);
+        s += st[(1 + q) * F + v] * x[qm];
+        s += st[(1 + q) * F + qp] * x[qp];
     }
     return s;
 }
@@ -849,8 +1239,7 @@ __device__ __forceinline__ void wg_relax(const CLev &L, int sweeps)
                 int i, j, k;
                 if (!vertex_rt(L.g, o, t, i, j, k)) continue;
                 const int v = o * (int)L.g.oct + t;
-                const double s = apply_rt(L, o, t);
-                L.x[v] += (L.b[v] - s) / L.st[v];
+                L.x[v] += row_rt(L, o, t) / L.st[v];
             }
             __syncthreads();
         }
@@ -867,7 +1256,7 @@ __device__ __forceinline__ void wg_residual(const CLev &L)
             L.r[u] = 0.0;
             continue;
         }
-        L.r[u] = L.b[u] - apply_rt(L, o, t);
+        L.r[u] = row_rt(L, o, t);
     }
     __syncthreads();
 }
@@ -1005,7 +1394,10 @@ struct Lev3 {
     int zc = 0;             // 7-point: the diagonal is formed from the connections
     double *st = nullptr;   // npt == 7: 4 fields; 27: 14 fields
     double *w = nullptr;    // NWSLOT octant slots: weights onto the next coarser level
-    double *x = nullptr, *b = nullptr, *r = nullptr;
+    // the iterate's two buffers: a half sweep reads the planes it relaxes from
+    // one and writes them to the other (tiles of a plane read each other's old
+    // rows); x[0] holds the iterate at the start of a visit of the level
+    double *x[2] = {nullptr, nullptr}, *b = nullptr, *r = nullptr;
 };
 
 constexpr int NPROF3 = 5;
@@ -1027,19 +1419,21 @@ struct hipbmg3d_hier {
     double *h_sum = nullptr;   // pinned
     double *d_nat = nullptr;   // plain-layout staging of the op_* entry points
     std::vector<void *> allocs;
-    hipGraph_t graph = nullptr;        // one V-cycle and the residual norm, captured
-    hipGraphExec_t exec = nullptr;
+    int cur = 0;                       // the finest iterate's buffer
+    // one V-cycle and the residual norm, captured, per buffer it starts from
+    hipGraph_t graph[2] = {nullptr, nullptr};
+    hipGraphExec_t exec[2] = {nullptr, nullptr};
     hipStream_t cap = nullptr;         // the stream the graph is captured on (the caller's may be the null stream)
     int prof = 0;
     std::vector<hipEvent_t> evpool;
     struct ProfMark {
         int k;
-        double bytes;
+        double bytes, launches;
         hipEvent_t e0, e1;
     };
     std::vector<ProfMark> marks;
     double prof_ms[NPROF3] = {0};
-    long long prof_n[NPROF3] = {0};
+    double prof_n[NPROF3] = {0};
     double prof_b[NPROF3] = {0};   // algorithmic bytes of the launches timed
 };
 
@@ -1066,20 +1460,24 @@ void free3(hipbmg3d_hier *h)
         hbmg::pinned_small_free(h->h_sum);
     }
     for (hipEvent_t e : h->evpool) (void)hipEventDestroy(e);
-    if (h->exec) (void)hipGraphExecDestroy(h->exec);
-    if (h->graph) (void)hipGraphDestroy(h->graph);
+    for (int k = 0; k < 2; ++k) {
+        if (h->exec[k]) (void)hipGraphExecDestroy(h->exec[k]);
+        if (h->graph[k]) (void)hipGraphDestroy(h->graph[k]);
+    }
     if (h->cap) (void)hipStreamDestroy(h->cap);
     delete h;
 }
 
 // kernel-class timing: an event pair around launches of class k, which
-// move `bytes` algorithmic bytes
+// move `bytes` algorithmic bytes and count as `launches` launches of the class
+// (a half sweep as two of a sweep's four colour groups, the norm of the even
+// planes as half a residual)
 struct Mark {
     hipbmg3d_hier *h;
     int k;
     hipStream_t s;
     hipEvent_t e1 = nullptr;
-    Mark(hipbmg3d_hier *h_, int k_, hipStream_t s_, double bytes = 0.0) : h(h_), k(k_), s(s_)
+    Mark(hipbmg3d_hier *h_, int k_, hipStream_t s_, double bytes = 0.0, double launches = 1.0) : h(h_), k(k_), s(s_)
     {
         if (!h->prof) return;
         const size_t need = 2 * (h->marks.size() + 1);
@@ -1095,7 +1493,7 @@ struct Mark {
         hipEvent_t e0 = h->evpool[2 * h->marks.size()];
         e1 = h->evpool[2 * h->marks.size() + 1];
         (void)hipEventRecord(e0, s);
-        h->marks.push_back({k, bytes, e0, e1});
+        h->marks.push_back({k, bytes, launches, e0, e1});
     }
     ~Mark()
     {
@@ -1110,7 +1508,7 @@ hipbmg_status prof_collect(hipbmg3d_hier *h)
         HIP3(hipEventSynchronize(m.e1));
         HIP3(hipEventElapsedTime(&ms, m.e0, m.e1));
         h->prof_ms[m.k] += ms;
-        h->prof_n[m.k] += 1;
+        h->prof_n[m.k] += m.launches;
         h->prof_b[m.k] += m.bytes;
     }
     h->marks.clear();
@@ -1129,73 +1527,147 @@ double sweep_bytes_per_vertex(const Lev3 &f)
 
 double grid_vertices(const Lev3 &f) { return (double)f.g.nx * f.g.ny * f.g.nz; }
 
-LArgs largs(const Lev3 &f, const Lev3 *c)
+LArgs largs(const Lev3 &f, const Lev3 *c, int cur, int ccur)
 {
     LArgs a{};
     a.g = f.g;
     a.st = f.st;
     a.b = f.b;
-    a.x = f.x;
+    a.x = f.x[cur];
     a.r = f.r;
     a.w = f.w;
-    a.zc = f.zc;
     if (c) {
         a.c = c->g;
-        a.xc = c->x;
+        a.xc = c->x[ccur];
         a.bc = c->b;
     }
     return a;
 }
 
-// one colour of a 27-point level (7-point levels run the colour groups)
-hipError_t launch_gs_colour27(int o, const LArgs &a, hipStream_t s)
+// The tiles of a level's planes of parity pz, hx halo cells to the left and hy
+// halo rows below (two cells to the right and a row above always).  Whole rows
+// up to PLANE_COLS cells, even shares of them beyond; as many rows as the
+// workgroup holds, halved (down to two) while the launch has fewer than
+// PLANE_TILES workgroups.  The large levels are bound by the bytes the tiles
+// load, halo included, so their tiles are near square: 257^3 (7-point, rows of
+// 128 cells) takes 89.0 ms a solve with thirds of a row by 10 rows, 91.1 with
+// halves by 7; 129^3 (27-point, whole rows of 64 by 3) loses 2-6% with halves
+// or smaller workgroups.  The small ones are bound by latency: 129 x 97 x 65
+// takes 8.90 ms with the line at 128 or 256 workgroups, 8.97 at 512, 9.15 at
+// 1024, and 3% more with tiles of one row.
+constexpr int PLANE_COLS7 = 48, PLANE_COLS27 = 64, PLANE_TILES = 256;
+
+Tile make_tile(const Oct &g, int npt, int pz, int hx, int hy)
 {
-    const dim3 grid(round8(nblk(a.g.oct))), block(256);
-#define HB3_GS(O) hipLaunchKernelGGL((k3_gs<27, O>), grid, block, 0, s, a)
-    switch (o) {
-    case 0: HB3_GS(0); break;
-    case 1: HB3_GS(1); break;
-    case 2: HB3_GS(2); break;
-    case 3: HB3_GS(3); break;
-    case 4: HB3_GS(4); break;
-    case 5: HB3_GS(5); break;
-    case 6: HB3_GS(6); break;
-    default: HB3_GS(7); break;
+    Tile t{};
+    t.ncol = (g.nx - 2) / 2 + 1;
+    t.nrow = (g.ny - 2) / 2 + 1;
+    t.nk = pz ? (g.nz - 1) / 2 : (g.nz - 2) / 2;
+    t.kk0 = pz ? 0 : 1;
+    t.hx = hx;
+    t.hy = hy;
+    const int cols = npt == 7 ? PLANE_COLS7 : PLANE_COLS27;
+    t.ntx = (t.ncol + cols - 1) / cols;
+    t.tc = (t.ncol + t.ntx - 1) / t.ntx;
+    t.ntx = (t.ncol + t.tc - 1) / t.tc;
+    t.cw = std::min(t.ncol, t.tc + hx + 2);
+    // points of a thread: two of a row (7-point), one
+    const int groups = npt == 7 ? 1 : 2;
+    auto shape = [&](int tr) {
+        t.tr = tr;
+        t.nty = (t.nrow + tr - 1) / tr;
+        t.ntiles = (unsigned)((long long)t.ntx * t.nty * t.nk);
+        t.rw = std::min(t.nrow, tr + hy + 1);
+        t.n01 = (t.cw * t.rw + 63) / 64 * 64;
+        t.n23 = (t.cw * std::min(t.nrow, tr + hy) + 63) / 64 * 64;
+        return groups * (t.n01 + t.n23);
+    };
+    int tr = t.nrow;
+    while (tr > 1 && shape(tr) > PLANE_THREADS) --tr;
+    shape(tr);
+    while (t.ntiles < (unsigned)PLANE_TILES && tr > 2) {
+        tr = (tr + 1) / 2;
+        shape(tr);
     }
-#undef HB3_GS
+    return t;
+}
+
+int tile_threads(const Tile &t, int npt) { return (npt == 7 ? 1 : 2) * (t.n01 + t.n23); }
+
+// LDS of a tile's workgroup: the window of four octants, a cell and a row more
+// than is relaxed on each side
+size_t tile_lds(const Tile &t) { return 4 * (size_t)(t.cw + 2) * (t.rw + 2) * sizeof(double); }
+
+// the norm's tiles are the last half sweep's
+Tile norm_tile(const Lev3 &f, int pz) { return make_tile(f.g, f.npt, pz, pz ? 2 : 1, pz ? 1 : 0); }
+long long norm_partials(const Lev3 &f)
+{
+    return (long long)round8(norm_tile(f, 0).ntiles) + round8(norm_tile(f, 1).ntiles);
+}
+
+template <int NPT, typename K>
+hipError_t launch_tiles(K kernel, const PArgs &a, hipStream_t s)
+{
+    if (a.t.ntiles == 0) return hipSuccess;
+    hipLaunchKernelGGL(kernel, dim3(round8(a.t.ntiles)), dim3(tile_threads(a.t, NPT)), tile_lds(a.t), s, a);
     return hipGetLastError();
 }
 
-hipbmg_status relax(hipbmg3d_hier *h, int l, int sweeps, hipStream_t s)
+PArgs pargs(const Lev3 &f)
+{
+    PArgs a{};
+    a.g = f.g;
+    a.st = f.st;
+    a.b = f.b;
+    a.r = f.r;
+    a.w = f.w;
+    return a;
+}
+
+template <int NPT, bool ZC>
+hipError_t launch_half(int pz, bool zero, int res, const PArgs &a, hipStream_t s)
+{
+    if (pz == 0) {
+        if (zero) return launch_tiles<NPT>(k3_plane<NPT, 0, ZC, true, 0>, a, s);
+        if (res == 3) return launch_tiles<NPT>(k3_plane<NPT, 0, ZC, false, 3>, a, s);
+        return launch_tiles<NPT>(k3_plane<NPT, 0, ZC, false, 0>, a, s);
+    }
+    if (zero)
+        return res == 1 ? launch_tiles<NPT>(k3_plane<NPT, 1, ZC, true, 1>, a, s)
+                        : launch_tiles<NPT>(k3_plane<NPT, 1, ZC, true, 0>, a, s);
+    if (res == 1) return launch_tiles<NPT>(k3_plane<NPT, 1, ZC, false, 1>, a, s);
+    if (res == 2) return launch_tiles<NPT>(k3_plane<NPT, 1, ZC, false, 2>, a, s);
+    return launch_tiles<NPT>(k3_plane<NPT, 1, ZC, false, 0>, a, s);
+}
+
+// half of a relaxation of level l, the planes of parity pz from x[cur] to
+// x[1 - cur]; zero: x[cur] counts as zero; res as in k3_plane (2 and 3: block
+// sums into d_part)
+hipbmg_status half_sweep(hipbmg3d_hier *h, int l, int cur, int pz, bool zero, int res, hipStream_t s)
 {
     const Lev3 &f = h->lv[l];
-    const LArgs a = largs(f, nullptr);
-    const dim3 grid(round8(nblk(f.g.oct))), block(256);
+    PArgs a = pargs(f);
+    a.xs = f.x[cur];
+    a.xo = pz ? f.x[1 - cur] : f.x[cur];
+    a.xd = f.x[1 - cur];
+    a.partials = h->d_part + (res == 3 ? round8(norm_tile(f, 1).ntiles) : 0);
+    const bool end = res == 1 || res == 2;
+    a.t = make_tile(f.g, f.npt, pz, end ? 2 : 1, end ? 1 : 0);
+    // half of the sweep's vertices: two of its four colour groups {0},
+    // {1,2,4}, {3,5,6}, {7}
+    Mark mk(h, l == h->L - 1 ? 0 : 4, s, sweep_bytes_per_vertex(f) * grid_vertices(f) * 0.5, 2.0);
+    if (f.npt == 7 && f.zc) HIP3((launch_half<7, true>(pz, zero, res, a, s)));
+    else if (f.npt == 7) HIP3((launch_half<7, false>(pz, zero, res, a, s)));
+    else HIP3((launch_half<27, false>(pz, zero, res, a, s)));
+    return HIPBMG_OK;
+}
+
+hipbmg_status relax(hipbmg3d_hier *h, int l, int *cur, int sweeps, hipStream_t s)
+{
     for (int it = 0; it < sweeps; ++it) {
-        if (f.npt == 7) {
-            for (int gq = 0; gq < 4; ++gq) {
-                // colour groups {0}, {1,2,4}, {3,5,6}, {7}: 1/8, 3/8, 3/8, 1/8 of the vertices
-                Mark mk(h, l == h->L - 1 ? 0 : 4, s,
-                        sweep_bytes_per_vertex(f) * grid_vertices(f) * ((gq == 0 || gq == 3) ? 0.125 : 0.375));
-                if (f.zc) {
-                    if (gq == 0) hipLaunchKernelGGL((k3_gs7g<0, true>), grid, block, 0, s, a);
-                    else if (gq == 1) hipLaunchKernelGGL((k3_gs7g<1, true>), grid, block, 0, s, a);
-                    else if (gq == 2) hipLaunchKernelGGL((k3_gs7g<2, true>), grid, block, 0, s, a);
-                    else hipLaunchKernelGGL((k3_gs7g<3, true>), grid, block, 0, s, a);
-                } else {
-                    if (gq == 0) hipLaunchKernelGGL(k3_gs7g<0>, grid, block, 0, s, a);
-                    else if (gq == 1) hipLaunchKernelGGL(k3_gs7g<1>, grid, block, 0, s, a);
-                    else if (gq == 2) hipLaunchKernelGGL(k3_gs7g<2>, grid, block, 0, s, a);
-                    else hipLaunchKernelGGL(k3_gs7g<3>, grid, block, 0, s, a);
-                }
-                HIP3(hipGetLastError());
-            }
-            continue;
-        }
-        for (int o = 0; o < 8; ++o) {
-            Mark mk(h, l == h->L - 1 ? 0 : 4, s, sweep_bytes_per_vertex(f) * grid_vertices(f) * 0.125);
-            HIP3(launch_gs_colour27(o, a, s));
-        }
+        ST3(half_sweep(h, l, *cur, 0, false, 0, s));
+        ST3(half_sweep(h, l, *cur, 1, false, 0, s));
+        *cur = 1 - *cur;
     }
     return HIPBMG_OK;
 }
@@ -1211,36 +1683,50 @@ hipbmg_status reduce_sum(hipbmg3d_hier *h, const double *partials, long long n, 
     return HIPBMG_OK;
 }
 
-// residual of level l: store r (store), or only the squared norm's block
-// sums and their sum in d_sum[0] (norm)
-hipbmg_status residual(hipbmg3d_hier *h, int l, bool store, bool norm, hipStream_t s)
+// residual r = b - A x[cur] of level l
+hipbmg_status residual(hipbmg3d_hier *h, int l, int cur, hipStream_t s)
 {
-    if (store == norm) return fail3(HIPBMG_EINVAL, "residual: store or norm, not both");
     const Lev3 &f = h->lv[l];
-    LArgs a = largs(f, nullptr);
-    a.partials = h->d_part;
+    const LArgs a = largs(f, nullptr, cur, 0);
     const dim3 grid(8 * nblk(f.g.oct)), block(256);   // a multiple of 8, octants interleaved
-    Mark mk(h, l == h->L - 1 ? 1 : 4, s, (sweep_bytes_per_vertex(f) - (store ? 0.0 : 8.0)) * grid_vertices(f));
-    if (f.npt == 7 && f.zc) {
-        if (store) hipLaunchKernelGGL((k3_resid<7, true, false, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k3_resid<7, false, true, true>), grid, block, 0, s, a);
-    } else if (f.npt == 7) {
-        if (store) hipLaunchKernelGGL((k3_resid<7, true, false>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k3_resid<7, false, true>), grid, block, 0, s, a);
-    } else {
-        if (store) hipLaunchKernelGGL((k3_resid<27, true, false>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k3_resid<27, false, true>), grid, block, 0, s, a);
-    }
+    Mark mk(h, 4, s);
+    if (f.npt == 7) hipLaunchKernelGGL((k3_resid<7>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k3_resid<27>), grid, block, 0, s, a);
     HIP3(hipGetLastError());
-    if (norm) ST3(reduce_sum(h, h->d_part, (long long)grid.x, s));
     return HIPBMG_OK;
 }
 
-// b_{l-1} = P^T r_l, and x_{l-1} = 0
-hipbmg_status restrict_to(hipbmg3d_hier *h, int l, hipStream_t s)
+// ||b - A x[cur]||^2 of the finest level into d_sum[0].  The block sums of the
+// planes of a parity that a half sweep has left in d_part already (have_odd,
+// have_even) are the same bits this forms.
+hipbmg_status norm(hipbmg3d_hier *h, int cur, bool have_odd, bool have_even, hipStream_t s)
 {
-    LArgs a = largs(h->lv[l], &h->lv[l - 1]);
-    a.xcz = h->lv[l - 1].x;
+    const Lev3 &f = h->lv[h->L - 1];
+    PArgs a = pargs(f);
+    a.xs = a.xo = f.x[cur];
+    for (int pz = 0; pz < 2; ++pz) {
+        if (pz ? have_odd : have_even) continue;
+        a.t = norm_tile(f, pz);
+        a.partials = h->d_part + (pz ? 0 : round8(norm_tile(f, 1).ntiles));
+        Mark mk(h, 1, s, (sweep_bytes_per_vertex(f) - 8.0) * grid_vertices(f) * 0.5, 0.5);
+        if (f.npt == 7 && f.zc)
+            HIP3(pz ? launch_tiles<7>(k3_plane_resid<7, 1, true, true>, a, s)
+                    : launch_tiles<7>(k3_plane_resid<7, 0, true, true>, a, s));
+        else if (f.npt == 7)
+            HIP3(pz ? launch_tiles<7>(k3_plane_resid<7, 1, false, true>, a, s)
+                    : launch_tiles<7>(k3_plane_resid<7, 0, false, true>, a, s));
+        else
+            HIP3(pz ? launch_tiles<27>(k3_plane_resid<27, 1, false, true>, a, s)
+                    : launch_tiles<27>(k3_plane_resid<27, 0, false, true>, a, s));
+    }
+    return reduce_sum(h, h->d_part, norm_partials(f), s);
+}
+
+// b_{l-1} = P^T r_l, and x_{l-1} = 0 if zero
+hipbmg_status restrict_to(hipbmg3d_hier *h, int l, bool zero, hipStream_t s)
+{
+    LArgs a = largs(h->lv[l], &h->lv[l - 1], 0, 0);
+    if (zero) a.xcz = h->lv[l - 1].x[0];
     // reads r and the 26 weights per coarse cell (3.25 per fine vertex),
     // writes the coarse right-hand side and the zero coarse iterate
     Mark mk(h, l == h->L - 1 ? 2 : 4, s, 8.0 * (1.0 + 3.25 + 0.25) * grid_vertices(h->lv[l]));
@@ -1249,10 +1735,30 @@ hipbmg_status restrict_to(hipbmg3d_hier *h, int l, hipStream_t s)
     return HIPBMG_OK;
 }
 
-hipbmg_status interp_from(hipbmg3d_hier *h, int l, int rescorr, hipStream_t s)
+// the same, with the even planes' residual of x[cur] formed on the way (the
+// odd planes' is in r)
+hipbmg_status residual_restrict(hipbmg3d_hier *h, int l, int cur, bool zero, hipStream_t s)
+{
+    const Lev3 &f = h->lv[l], &c = h->lv[l - 1];
+    PArgs a = pargs(f);
+    a.xs = a.xo = f.x[cur];
+    a.c = c.g;
+    a.bc = c.b;
+    a.xcz = zero ? c.x[0] : nullptr;
+    a.t = make_tile(f.g, f.npt, 0, 1, 1);
+    Mark mk(h, l == h->L - 1 ? 2 : 4, s,
+            (0.5 * sweep_bytes_per_vertex(f) + 8.0 * (0.5 + 3.25 + 0.125)) * grid_vertices(f));
+    if (f.npt == 7 && f.zc) HIP3((launch_tiles<7>(k3_plane_resid<7, 0, true, false>, a, s)));
+    else if (f.npt == 7) HIP3((launch_tiles<7>(k3_plane_resid<7, 0, false, false>, a, s)));
+    else HIP3((launch_tiles<27>(k3_plane_resid<27, 0, false, false>, a, s)));
+    return HIPBMG_OK;
+}
+
+// x[cur] += P x_{l-1}[ccur] (+ r/C)
+hipbmg_status interp_from(hipbmg3d_hier *h, int l, int cur, int ccur, int rescorr, hipStream_t s)
 {
     const Lev3 &f = h->lv[l];
-    LArgs a = largs(f, &h->lv[l - 1]);
+    LArgs a = largs(f, &h->lv[l - 1], cur, ccur);
     a.rescorr = rescorr;
     const dim3 grid(round8(nblk(f.g.oct)), 8), block(256);
     // reads and writes x, reads r, C, the weights and the coarse iterate
@@ -1269,7 +1775,7 @@ hipbmg_status collapse(hipbmg3d_hier *h, int top, hipStream_t s)
     CArgs a{};
     for (int l = 0; l <= top; ++l) {
         const Lev3 &v = h->lv[l];
-        a.lv[l] = CLev{v.g, v.npt, v.st, v.w, v.x, v.b, v.r};
+        a.lv[l] = CLev{v.g, v.npt, v.st, v.w, v.x[0], v.b, v.r};
     }
     a.top = top;
     a.chol = h->d_chol;
@@ -1284,43 +1790,88 @@ hipbmg_status collapse(hipbmg3d_hier *h, int top, hipStream_t s)
     return HIPBMG_OK;
 }
 
-// Algorithm 1 on level l: x_l and b_l are the level's own fields
-hipbmg_status vcycle(hipbmg3d_hier *h, int l, hipStream_t s)
+// Algorithm 1 on level l; the iterate starts in x[0] (on the finest level in
+// x[h->cur], and from zero on all others) and ends in x[*end].  begun: the
+// first half sweep has been done; norm_odd: the last one also leaves the odd
+// planes' part of the norm in d_part.
+hipbmg_status vcycle(hipbmg3d_hier *h, int l, hipStream_t s, int *end = nullptr, bool begun = false,
+                     bool norm_odd = false)
 {
+    const bool fine = l == h->L - 1;
+    int cur = fine ? h->cur : 0;
+    if (end) *end = cur;
     if (l <= h->lstar) return collapse(h, l, s);
-    ST3(relax(h, l, h->prm.nu1, s));
-    ST3(residual(h, l, true, false, s));
-    ST3(restrict_to(h, l, s));
-    ST3(vcycle(h, l - 1, s));
-    ST3(interp_from(h, l, h->prm.residual_correction, s));
-    ST3(relax(h, l, h->prm.nu2, s));
+    const int nu1 = h->prm.nu1, nu2 = h->prm.nu2;
+    for (int it = 0; it < nu1; ++it) {
+        const bool zero = !fine && it == 0;
+        if (!(begun && it == 0)) ST3(half_sweep(h, l, cur, 0, zero, 0, s));
+        ST3(half_sweep(h, l, cur, 1, zero, it == nu1 - 1 ? 1 : 0, s));
+        cur = 1 - cur;
+    }
+    // the coarse iterate's zeros are stored only for what reads them: the
+    // collapsed workgroup, or a level without pre-relaxations
+    const bool zero = l - 1 <= h->lstar || nu1 == 0;
+    if (nu1 > 0) {
+        ST3(residual_restrict(h, l, cur, zero, s));
+    } else {
+        ST3(residual(h, l, cur, s));
+        ST3(restrict_to(h, l, zero, s));
+    }
+    int ccur = 0;
+    ST3(vcycle(h, l - 1, s, &ccur));
+    ST3(interp_from(h, l, cur, ccur, h->prm.residual_correction, s));
+    for (int it = 0; it < nu2; ++it) {
+        ST3(half_sweep(h, l, cur, 0, false, 0, s));
+        ST3(half_sweep(h, l, cur, 1, false, norm_odd && it == nu2 - 1 ? 2 : 0, s));
+        cur = 1 - cur;
+    }
+    if (end) *end = cur;
     return HIPBMG_OK;
 }
 
+// the finest level's cycles overlap: a cycle ends with the first half sweep of
+// the next one, which writes the other buffer (the iterate stays whole where a
+// cycle was the last) and sums the squares of the residual it starts from, so
+// the norm's even planes cost no pass of their own.  Not where kernel timing
+// is on, which times the norm as a launch of its own.
+bool overlapped(const hipbmg3d_hier *h) { return h->L - 1 > h->lstar && h->prm.nu1 > 0 && !h->prof; }
+
+hipbmg_status enqueue_cycle(hipbmg3d_hier *h, hipStream_t s, int *end)
+{
+    const bool norm_odd = h->L - 1 > h->lstar && h->prm.nu2 > 0, over = overlapped(h);
+    ST3(vcycle(h, h->L - 1, s, end, over, norm_odd));
+    if (over) ST3(half_sweep(h, h->L - 1, *end, 0, false, 3, s));
+    return norm(h, *end, norm_odd, over, s);
+}
+
 // one cycle and the finest residual norm (into d_sum); replayed from a
-// captured graph unless use_graph is 0 or kernel timing is on
+// captured graph (one per buffer the finest iterate starts from) unless
+// use_graph is 0 or kernel timing is on
 hipbmg_status cycle_and_norm(hipbmg3d_hier *h, hipStream_t s)
 {
+    const int k = h->cur;
+    int end = k;
     if (!h->prm.use_graph || h->prof) {
-        ST3(vcycle(h, h->L - 1, s));
-        return residual(h, h->L - 1, false, true, s);
+        ST3(enqueue_cycle(h, s, &end));
+        h->cur = end;
+        return HIPBMG_OK;
     }
-    if (!h->exec) {
+    if (!h->exec[k]) {
         if (!h->cap) HIP3(hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking));
         hipStream_t c = h->cap;
         HIP3(hipStreamBeginCapture(c, hipStreamCaptureModeThreadLocal));
-        hipbmg_status st = vcycle(h, h->L - 1, c);
-        if (st == HIPBMG_OK) st = residual(h, h->L - 1, false, true, c);
+        const hipbmg_status st = enqueue_cycle(h, c, &end);
         hipGraph_t g = nullptr;
         const hipError_t e2 = hipStreamEndCapture(c, &g);
         if (st != HIPBMG_OK || e2 != hipSuccess) {
             if (g) (void)hipGraphDestroy(g);
             return st != HIPBMG_OK ? st : fail3(HIPBMG_EHIP, "graph capture failed: %s", hipGetErrorString(e2));
         }
-        h->graph = g;
-        HIP3(hipGraphInstantiate(&h->exec, g, nullptr, nullptr, 0));
+        h->graph[k] = g;
+        HIP3(hipGraphInstantiate(&h->exec[k], g, nullptr, nullptr, 0));
     }
-    HIP3(hipGraphLaunch(h->exec, s));
+    HIP3(hipGraphLaunch(h->exec[k], s));
+    if (h->L - 1 > h->lstar) h->cur = k ^ ((h->prm.nu1 + h->prm.nu2) & 1);
     return HIPBMG_OK;
 }
 
@@ -1564,7 +2115,8 @@ extern "C" hipbmg_status hipbmg3d_setup(int nx, int ny, int nz, int npt, const d
         v.npt = (l == L - 1) ? npt : 27;
         const int nf = v.npt == 7 ? 4 : 14;
         if ((st = dalloc3(h, &v.st, nf * v.g.field)) != HIPBMG_OK) return bail(st);
-        if ((st = dalloc3(h, &v.x, v.g.field)) != HIPBMG_OK) return bail(st);
+        for (int k = 0; k < 2; ++k)
+            if ((st = dalloc3(h, &v.x[k], v.g.field)) != HIPBMG_OK) return bail(st);
         if ((st = dalloc3(h, &v.b, v.g.field)) != HIPBMG_OK) return bail(st);
         if ((st = dalloc3(h, &v.r, v.g.field)) != HIPBMG_OK) return bail(st);
         if (l >= 1 && (st = dalloc3(h, &v.w, NWSLOT * v.g.oct)) != HIPBMG_OK) return bail(st);
@@ -1572,7 +2124,7 @@ extern "C" hipbmg_status hipbmg3d_setup(int nx, int ny, int nz, int npt, const d
     const Lev3 &top = h->lv[L - 1];
     const long long nnat = (long long)nx * ny * nz;
     if ((st = dalloc3(h, &h->d_nat, nnat)) != HIPBMG_OK) return bail(st);
-    h->npart = 8 * (long long)nblk(top.g.oct) + 8;
+    h->npart = (long long)nblk(top.g.field) + norm_partials(top) + 8;
     if ((st = dalloc3(h, &h->d_part, h->npart)) != HIPBMG_OK) return bail(st);
     if ((st = dalloc3(h, &h->d_sum, 8 + 256)) != HIPBMG_OK) return bail(st);
     if (hbmg::pinned_small((void **)&h->h_sum, nullptr, 8 * sizeof(double)) != hipSuccess) {
@@ -1700,7 +2252,9 @@ extern "C" hipbmg_status hipbmg3d_solve(hipbmg3d_handle h, const double *b, doub
     auto t0 = std::chrono::steady_clock::now();
     Lev3 &f = h->lv[h->L - 1];
     ST3(to_oct(f.g, b, f.b, 1, s));
-    ST3(to_oct(f.g, u, f.x, 1, s));
+    ST3(to_oct(f.g, u, f.x[0], 1, s));
+    h->cur = 0;
+    if (overlapped(h)) ST3(half_sweep(h, h->L - 1, 0, 0, false, 0, s));
     hipLaunchKernelGGL(k3_sumsq, dim3(nblk(f.g.field)), dim3(256), 0, s, f.g, (const double *)f.b, h->d_part);
     HIP3(hipGetLastError());
     ST3(reduce_sum(h, h->d_part, (long long)nblk(f.g.field), s));
@@ -1737,7 +2291,7 @@ extern "C" hipbmg_status hipbmg3d_solve(hipbmg3d_handle h, const double *b, doub
                 break;
             }
         }
-        ST3(from_oct(f.g, f.x, u, s));
+        ST3(from_oct(f.g, f.x[h->cur], u, s));
         HIP3(hipStreamSynchronize(s));
         if (rc == HIPBMG_ENOCONV) fail3(rc, "tolerance not reached in %d cycles", cycles);
     }
@@ -1759,9 +2313,10 @@ extern "C" hipbmg_status hipbmg3d_op_smooth(hipbmg3d_handle h, int l, const doub
     hipStream_t s = (hipStream_t)stream;
     Lev3 &v = h->lv[l];
     ST3(to_oct(v.g, b, v.b, 1, s));
-    ST3(to_oct(v.g, x, v.x, 1, s));
-    ST3(relax(h, l, sweeps, s));
-    ST3(from_oct(v.g, v.x, x, s));
+    ST3(to_oct(v.g, x, v.x[0], 1, s));
+    int cur = 0;
+    ST3(relax(h, l, &cur, sweeps, s));
+    ST3(from_oct(v.g, v.x[cur], x, s));
     HIP3(hipStreamSynchronize(s));
     h->marks.clear();
     return HIPBMG_OK;
@@ -1775,8 +2330,8 @@ extern "C" hipbmg_status hipbmg3d_op_residual(hipbmg3d_handle h, int l, const do
     hipStream_t s = (hipStream_t)stream;
     Lev3 &v = h->lv[l];
     ST3(to_oct(v.g, b, v.b, 1, s));
-    ST3(to_oct(v.g, x, v.x, 1, s));
-    ST3(residual(h, l, true, false, s));
+    ST3(to_oct(v.g, x, v.x[0], 1, s));
+    ST3(residual(h, l, 0, s));
     ST3(from_oct(v.g, v.r, r, s));
     HIP3(hipStreamSynchronize(s));
     h->marks.clear();
@@ -1790,7 +2345,7 @@ extern "C" hipbmg_status hipbmg3d_op_restrict(hipbmg3d_handle h, int l, const do
     hipStream_t s = (hipStream_t)stream;
     Lev3 &v = h->lv[l];
     ST3(to_oct(v.g, r, v.r, 1, s));
-    ST3(restrict_to(h, l, s));
+    ST3(restrict_to(h, l, true, s));
     ST3(from_oct(h->lv[l - 1].g, h->lv[l - 1].b, bc, s));
     HIP3(hipStreamSynchronize(s));
     h->marks.clear();
@@ -1804,11 +2359,11 @@ extern "C" hipbmg_status hipbmg3d_op_interp_correct(hipbmg3d_handle h, int l, do
     if (l < 1 || l >= h->L) return fail3(HIPBMG_EINVAL, "bad level");
     hipStream_t s = (hipStream_t)stream;
     Lev3 &v = h->lv[l];
-    ST3(to_oct(v.g, x, v.x, 1, s));
+    ST3(to_oct(v.g, x, v.x[0], 1, s));
     ST3(to_oct(v.g, r, v.r, 1, s));
-    ST3(to_oct(h->lv[l - 1].g, xc, h->lv[l - 1].x, 1, s));
-    ST3(interp_from(h, l, rescorr, s));
-    ST3(from_oct(v.g, v.x, x, s));
+    ST3(to_oct(h->lv[l - 1].g, xc, h->lv[l - 1].x[0], 1, s));
+    ST3(interp_from(h, l, 0, 0, rescorr, s));
+    ST3(from_oct(v.g, v.x[0], x, s));
     HIP3(hipStreamSynchronize(s));
     h->marks.clear();
     return HIPBMG_OK;
@@ -1820,11 +2375,11 @@ extern "C" hipbmg_status hipbmg3d_op_coarse_solve(hipbmg3d_handle h, const doubl
     hipStream_t s = (hipStream_t)stream;
     Lev3 &c = h->lv[0];
     ST3(to_oct(c.g, b, c.b, 1, s));
-    hipLaunchKernelGGL(k3_fill0, dim3((unsigned)std::min<long long>(nblk(c.g.field), 2048)), dim3(256), 0, s, c.x,
-                       c.g.field);
+    hipLaunchKernelGGL(k3_fill0, dim3((unsigned)std::min<long long>(nblk(c.g.field), 2048)), dim3(256), 0, s,
+                       c.x[0], c.g.field);
     HIP3(hipGetLastError());
     ST3(collapse(h, 0, s));
-    ST3(from_oct(c.g, c.x, x, s));
+    ST3(from_oct(c.g, c.x[0], x, s));
     HIP3(hipStreamSynchronize(s));
     h->marks.clear();
     return HIPBMG_OK;
@@ -1836,7 +2391,7 @@ extern "C" hipbmg_status hipbmg3d_profile(hipbmg3d_handle h, int enable)
     h->prof = enable ? 1 : 0;
     for (int k = 0; k < NPROF3; ++k) {
         h->prof_ms[k] = 0.0;
-        h->prof_n[k] = 0;
+        h->prof_n[k] = 0.0;
         h->prof_b[k] = 0.0;
     }
     h->marks.clear();
@@ -1849,7 +2404,7 @@ extern "C" hipbmg_status hipbmg3d_profile_read(hipbmg3d_handle h, int k, double 
     if (!h) return fail3(HIPBMG_EINVAL, "null argument");
     if (k < 0 || k >= NPROF3) return fail3(HIPBMG_EINVAL, "kernel class %d out of range", k);
     if (ms_host) *ms_host = h->prof_ms[k];
-    if (launches_host) *launches_host = h->prof_n[k];
-    if (bytes_per_launch_host) *bytes_per_launch_host = h->prof_n[k] ? h->prof_b[k] / (double)h->prof_n[k] : 0.0;
+    if (launches_host) *launches_host = (long long)(h->prof_n[k] + 0.5);
+    if (bytes_per_launch_host) *bytes_per_launch_host = h->prof_n[k] > 0.0 ? h->prof_b[k] / h->prof_n[k] : 0.0;
     return HIPBMG_OK;
 }

@@ -367,24 +367,22 @@ double model_path_us(const ModelLevel *lv, int L, int nu1, int nu2, int nc, int 
 // ---------------------------------------------------------------------------
 namespace {
 
-// loaded FP64 words per vertex of one relaxation or residual (stencil entries,
-// the iterate at every stencil point, b, one store)
-double words3_sweep(int npt) { return npt == 7 ? 16.0 : 56.0; }
+// loaded FP64 words per vertex of one relaxation or residual: the row of the
+// operator, b, the iterate of the planes above and below at every stencil
+// point and of the vertex's own plane once, one store
+double words3_sweep(int npt) { return npt == 7 ? 12.0 : 48.0; }
 
 struct Kernels3 {
-    int n;             // launches
-    double bytes[4];   // relaxation launch, residual, restriction + zeroing, interpolation
-    int nrelax;
+    double bytes[4];   // half a sweep, residual, restriction + zeroing, interpolation
+    int nrelax;        // half sweeps (the even planes, the odd planes)
 };
 
 Kernels3 kernels3(const ModelLevel3 &lv, int nu1, int nu2)
 {
     const double nv = (double)lv.nx * lv.ny * lv.nz;
     Kernels3 k;
-    const int per = lv.npt == 7 ? 4 : 8;
-    k.nrelax = (nu1 + nu2) * per;
-    k.n = k.nrelax + 4;
-    k.bytes[0] = nv * words3_sweep(lv.npt) * 8.0 / per;
+    k.nrelax = (nu1 + nu2) * 2;
+    k.bytes[0] = nv * words3_sweep(lv.npt) * 8.0 / 2.0;
     k.bytes[1] = nv * words3_sweep(lv.npt) * 8.0;
     k.bytes[2] = nv * (54.0 / 8.0 + 1.0 / 8.0) * 8.0;   // 27 (r, weight) pairs per coarse vertex; zeroing
     k.bytes[3] = nv * 8.25 * 8.0;                       // x in and out, r, C, 3.25 weights, x_c
@@ -400,8 +398,9 @@ double model3_grid_level_us(const ModelLevel3 &lv, int nu1, int nu2, const Model
     const double ws = (double)lv.nx * lv.ny * lv.nz * ((lv.npt == 7 ? 4.0 : 14.0) + 3.0 + 3.25) * 8.0;
     const double beta = ws > p.cache_bytes ? p.beta_hbm_us_per_B : p.beta_cache_us_per_B;
     const double t0 = p.t0_dn_us[0];
-    // the zeroing launch moves little; count it as its fixed cost
-    return k.nrelax * (t0 + k.bytes[0] * beta) + (t0 + k.bytes[1] * beta) + (2.0 * t0 + k.bytes[2] * beta) +
+    // the odd planes' residual comes with the last half sweep, the even planes'
+    // with the restriction
+    return k.nrelax * (t0 + k.bytes[0] * beta) + (t0 + (0.5 * k.bytes[1] + k.bytes[2]) * beta) +
            (t0 + k.bytes[3] * beta);
 }
 

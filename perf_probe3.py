@@ -20,24 +20,23 @@ sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 
 # finest-level kernels of the 3D path and their algorithmic bytes per vertex
 # of the whole grid (FP64, 7-point, zero-excess operator: the diagonal is
-# formed from the six connections, so C is not read): a colour group reads x,
-# b, W, S, B and writes x at its share of the vertices (1/8 or 3/8); the
-# residual reads the same and writes r; the interpolation reads x, r, C, the
-# 3.25 weights per vertex and the coarse x (1/8) and writes x; the restriction
-# reads r and the weights and writes the coarse rhs and the zero coarse
-# iterate (1/8 each)
+# formed from the six connections, so C is not read): half a sweep reads x, b,
+# W, S, B and writes x at its half of the vertices, and at the end of the
+# pre-relaxations writes r there too; the residual with the restriction does
+# so at the even planes, reads the odd planes' r (1/2) and the 3.25 weights per
+# vertex and writes the coarse rhs (1/8); the interpolation reads x, r, C, the
+# weights and the coarse x (1/8) and writes x
 SWEEP_B = 48.0
 KERNELS3 = {
-    "gs7g<0>": ("k3_gs7g<0, true>", SWEEP_B / 8),
-    "gs7g<1>": ("k3_gs7g<1, true>", SWEEP_B * 3 / 8),
-    "gs7g<2>": ("k3_gs7g<2, true>", SWEEP_B * 3 / 8),
-    "gs7g<3>": ("k3_gs7g<3, true>", SWEEP_B / 8),
-    "resid": ("k3_resid<7, true, false, true>", 48.0),
-    "resid_norm": ("k3_resid<7, false, true, true>", 40.0),
-    "restrict": ("k3_restrict", 8.0 + 26.0 + 2.0),
+    "even": ("k3_plane<7, 0, true, false, 0>", SWEEP_B / 2),
+    "odd": ("k3_plane<7, 1, true, false, 0>", SWEEP_B / 2),
+    "odd_resid": ("k3_plane<7, 1, true, false, 1>", SWEEP_B / 2 + 4.0),
+    "odd_norm": ("k3_plane<7, 1, true, false, 2>", SWEEP_B / 2),
+    "even_norm": ("k3_plane<7, 0, true, false, 3>", SWEEP_B / 2),
+    "resid_restrict": ("k3_plane_resid<7, 0, true, false>", SWEEP_B / 2 + 8.0 * (0.5 + 3.25 + 0.125)),
     "interp": ("k3_interp<7>", 8.0 * (2 + 1 + 1 + 3.25 + 0.125)),
 }
-SWEEP = ("gs7g<0>", "gs7g<1>", "gs7g<2>", "gs7g<3>")
+SWEEP = ("even", "odd")
 
 
 def source_sha():
@@ -102,7 +101,7 @@ def summarize(fetch_dir, write_dir, n=257, copy_bytes=1 << 30):
                                                                     (f + w) / algo))
     sweep = sum(total[k] for k in SWEEP) if all(k in total for k in SWEEP) else None
     if sweep is not None:
-        lines += ["", "One relaxation sweep (the four colour-group launches): %.1f MB of HBM traffic against "
+        lines += ["", "One relaxation sweep (the even planes, then the odd ones): %.1f MB of HBM traffic against "
                       "%.1f MB algorithmic (%.3f)." % (sweep / 1e6, SWEEP_B * npts / 1e6, sweep / (SWEEP_B * npts))]
     lines += ["", "Source hash of bmg3d.hip when taken: `%s`." % sha]
     with open(os.path.join(root, "profiles", "traffic_fp64_257cubed_blocks.md"), "w") as fh:

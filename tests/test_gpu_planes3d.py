@@ -1,0 +1,59 @@
+"""The 3D relaxation by planes (tiles of a plane, halos, remainders) against
+the same iteration in one workgroup.
+
+With collapse_level = L-1 every level runs vertex by vertex in a single
+workgroup, without tiles; with collapse_level = 0 every level above the
+coarsest runs by planes.  Both form every value from the same terms in the
+same order, so iterate and history are the same bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1803_02481_amd import hipbmg as HB
+from paper_1803_02481_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def g(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def planes_of(npt, shape, seed):
+    nz, ny, nx = shape
+    if npt == 7:
+        return HB.fv7_from_cells(g(inputs.cells3_lognormal(nx, ny, nz, sigma=1.0, seed=seed)))
+    # 27 points: random connections, a diagonal a little above their sum
+    conn = np.random.default_rng(seed).uniform(0.1, 1.0, size=(13,) + shape)
+    C = np.full(shape, 0.5)
+    for o in range(13):
+        d = (o // 9 - 1, (o // 3) % 3 - 1, o % 3 - 1)
+        at = tuple(slice(max(0, -s), n - max(0, s)) for s, n in zip(d, shape))   # p with p + d on the grid
+        to = tuple(slice(max(0, s), n + min(0, s)) for s, n in zip(d, shape))    # those p + d
+        C += conn[o]
+        C[to] += conn[o][at]
+    return g(np.concatenate([C[None], conn]))
+
+
+# rows of cells: one tile, just over one (49, 65 cells), three; single rows and
+# planes; more rows than a workgroup holds
+@pytest.mark.parametrize("shape", [(5, 5, 5), (3, 9, 9), (9, 3, 17), (5, 9, 97), (5, 7, 99), (5, 9, 129), (5, 7, 131),
+                                   (9, 9, 259), (7, 85, 35), (17, 49, 101)])
+@pytest.mark.parametrize("npt", [7, 27])
+@pytest.mark.parametrize("nu", [(2, 1), (1, 2), (0, 2), (2, 0)])
+def test_planes_are_the_single_workgroup(shape, npt, nu):
+    nz, ny, nx = shape
+    planes = planes_of(npt, shape, 71)
+    b = g(inputs.load3_uniform(nx, ny, nz, seed=72))
+    u0 = g(np.random.default_rng(73).standard_normal(shape))
+    got = []
+    L = HB.Hierarchy3(planes).L
+    for ls in (0, L - 1):
+        if ls > 7:
+            continue
+        h = HB.Hierarchy3(planes, collapse_level=ls, nu1=nu[0], nu2=nu[1], max_cycles=3)
+        u, info = h.solve(b, u0=u0, tol=1e-30, check=False)
+        assert bool(torch.isfinite(u).all())
+        got.append((u, info.history()))
+    assert torch.equal(got[0][0], got[-1][0])
+    assert got[0][1] == got[-1][1]
