@@ -1361,6 +1361,233 @@ __global__ __launch_bounds__(CWG3) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
 }
 
 // ---------------------------------------------------------------------------
+// The collapse of levels whose octants hold at most 64 interior vertices (9^3
+// and smaller) above a coarsest level of at most SMALL_NC unknowns: the usual
+// case.  Wave o holds octant o, a vertex per lane, with its whole row of the
+// operator and its interpolation weights in registers, loaded once for the
+// launch; the iterates and residuals live in LDS.  Such a launch is nothing but
+// dependent phases, so what a phase waits for is kept out of it: the off-plane
+// sums of four colours are formed together before their first, and no phase
+// reads memory.  Same terms and order as above, so the same bits; at 257^3
+// (levels 9^3, 5^3, 3^3) the launch takes 25-30 us instead of 153.
+// ---------------------------------------------------------------------------
+constexpr int SMALL_NC = 48, SMALL_MAXTOP = 2;
+
+struct SRow {
+    double oc[18], k[8], d, b, w[8], off, r;
+    int at;
+    bool in;
+};
+
+__device__ __forceinline__ int small_count(int n, int odd) { return odd ? (n - 1) / 2 : (n - 3) / 2; }
+
+// vertex `lane` of octant o of a level (odd sides): its row and weights, all
+// loads in flight
+__device__ __forceinline__ void small_load(const CLev &L, int o, int lane, SRow &R)
+{
+    const Oct &g = L.g;
+    const int na = small_count(g.nx, o & 1), nb = small_count(g.ny, (o >> 1) & 1), nc = small_count(g.nz, o >> 2);
+    R.in = lane < na * nb * nc;
+    const int p = R.in ? lane : 0;
+    const int a = na > 0 ? p % na : 0, q = na > 0 ? p / na : 0, b = nb > 0 ? q % nb : 0, c = nb > 0 ? q / nb : 0;
+    const int i = 2 * a + ((o & 1) ? 1 : 2), j = 2 * b + (((o >> 1) & 1) ? 1 : 2), k = 2 * c + ((o >> 2) ? 1 : 2);
+    R.at = (k * g.ny + j) * g.nx + i;
+    if (!R.in) return;
+    const int F = (int)g.field;
+    const int t = (k >> 1) * (int)g.plane + (j >> 1) * g.px + (i >> 1), v = o * (int)g.oct + t;
+#pragma unroll
+    for (int s = 0; s < 9; ++s) {
+        R.oc[2 * s] = L.st[(1 + s) * F + v];
+        R.oc[2 * s + 1] = L.st[(1 + s) * F + nbr_rt(g, o, t, 1 - s % 3, 1 - s / 3, 1)];
+    }
+#pragma unroll
+    for (int s = 9; s < 13; ++s) {
+        R.k[2 * (s - 9)] = L.st[(1 + s) * F + v];
+        R.k[2 * (s - 9) + 1] = L.st[(1 + s) * F + nbr_rt(g, o, t, 1 - s % 3, 1 - (s / 3) % 3, 0)];
+    }
+    R.d = L.st[v];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        R.w[m] = 1.0;
+        if (!(m & ~o) && o != 0) R.w[m] = L.w[(wbase(o) + wrank(o, m)) * (int)g.oct + t];
+    }
+}
+
+__device__ __forceinline__ void small_off(const SRow &R, const double *x, int nx, int nxy, double &off)
+{
+    off = 0.0;
+#pragma unroll
+    for (int s = 0; s < 9; ++s) {
+        const int dx = s % 3 - 1, dy = s / 3 - 1;
+        off += R.oc[2 * s] * x[R.at + dx + dy * nx - nxy];
+        off += R.oc[2 * s + 1] * x[R.at - dx - dy * nx + nxy];
+    }
+}
+
+__device__ __forceinline__ double small_resid(const SRow &R, const double *x, int nx)
+{
+    double s = R.b - R.d * x[R.at];
+    s += R.off;
+#pragma unroll
+    for (int q = 9; q < 13; ++q) {
+        const int dx = q % 3 - 1, dy = (q / 3) % 3 - 1;
+        s += R.k[2 * (q - 9)] * x[R.at + dx + dy * nx];
+        s += R.k[2 * (q - 9) + 1] * x[R.at - dx - dy * nx];
+    }
+    return s;
+}
+
+__device__ __forceinline__ void small_relax(SRow &R, double *x, int nx, int nxy, int o, int sweeps)
+{
+    for (int it = 0; it < sweeps; ++it)
+#pragma unroll
+        for (int pz = 0; pz < 2; ++pz) {
+            if ((o >> 2) == pz && R.in) small_off(R, x, nx, nxy, R.off);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (o == 4 * pz + q && R.in) x[R.at] += small_resid(R, x, nx) / R.d;
+                __syncthreads();
+            }
+        }
+}
+
+// the weights of fine level F towards its coarse vertex t, slot by slot in the
+// order of the restriction's sum, into LDS
+__device__ __forceinline__ void small_stage_weights(const CLev &F, const Oct &c, double *wr)
+{
+    const Oct &g = F.g;
+    const int ni = c.nx - 2, nj = c.ny - 2, n = ni * nj * (c.nz - 2);
+    for (int e = threadIdx.x; e < 27 * n; e += CWG3) {
+        const int s = e / n, t = e - s * n;
+        const int I = 1 + t % ni, J = 1 + (t / ni) % nj, K = 1 + t / (ni * nj);
+        const int ex = s % 3 - 1, ey = (s / 3) % 3 - 1, ez = s / 9 - 1;
+        const int mI = (ex == -1 ? 1 : 0) | (ey == -1 ? 2 : 0) | (ez == -1 ? 4 : 0);
+        wr[s * 64 + t] = weight_on(g, F.w, 2 * I + ex, 2 * J + ey, 2 * K + ez, mI);
+    }
+}
+
+// b_c = P^T r: coarse vertices on the first wave's lanes
+__device__ __forceinline__ void small_restrict(const Oct &g, const Oct &c, const double *r, const double *wr, double *bc)
+{
+    const int ni = c.nx - 2, nj = c.ny - 2, n = ni * nj * (c.nz - 2), t = threadIdx.x;
+    if (t < n) {
+        const int I = 1 + t % ni, J = 1 + (t / ni) % nj, K = 1 + t / (ni * nj);
+        const int f = (2 * K * g.ny + 2 * J) * g.nx + 2 * I;
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < 27; ++e)
+            s += wr[e * 64 + t] * r[f + e % 3 - 1 + ((e / 3) % 3 - 1) * g.nx + (e / 9 - 1) * g.nx * g.ny];
+        bc[(K * c.ny + J) * c.nx + I] = s;
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ void small_interp(const Oct &g, const Oct &c, const SRow &R, double *x, const double *xc,
+                                             int o, int rescorr)
+{
+    if (R.in) {
+        const int k = R.at / (g.nx * g.ny), j = (R.at / g.nx) % g.ny, i = R.at % g.nx;
+        const int f = ((k >> 1) * c.ny + (j >> 1)) * c.nx + (i >> 1);
+        double s = 0.0;
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+            if (!(m & ~o)) s += R.w[m] * xc[f + (m & 1) + ((m >> 1) & 1) * c.nx + (m >> 2) * c.nx * c.ny];
+        double xv = x[R.at] + s;
+        if (o != 0 && rescorr) xv += R.r / R.d;
+        x[R.at] = xv;
+    }
+    __syncthreads();
+}
+
+// the Cholesky substitutions of at most 64 unknowns on one wave, an unknown per lane
+__device__ __forceinline__ void small_coarse(const Oct &g, const double *Lf, int n, const double *b, double *x)
+{
+    if (threadIdx.x < 64) {
+        const int r = threadIdx.x, ni = g.nx - 2, nj = g.ny - 2;
+        const int at = r < n ? ((1 + r / (ni * nj)) * g.ny + 1 + (r / ni) % nj) * g.nx + 1 + r % ni : 0;
+        double y = r < n ? b[at] : 0.0;
+        for (int k = 0; k < n; ++k) {
+            const double yk = __shfl(y, k, 64) / Lf[k * n + k];
+            if (r > k && r < n) y -= Lf[r * n + k] * yk;
+            if (r == k) y = yk;
+        }
+        for (int k = n - 1; k >= 0; --k) {
+            const double yk = __shfl(y, k, 64) / Lf[k * n + k];
+            if (r < k) y -= Lf[k * n + r] * yk;
+            if (r == k) y = yk;
+        }
+        if (r < n) x[at] = y;
+    }
+    __syncthreads();
+}
+
+struct SmallLds {
+    int x[SMALL_MAXTOP + 1], r[SMALL_MAXTOP + 1], b[SMALL_MAXTOP + 1], w[SMALL_MAXTOP + 1], chol, total;
+};
+
+template <int TOP>
+__global__ __launch_bounds__(CWG3) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3_collapse_small(CArgs a,
+                                                                                                     SmallLds s)
+{
+    extern __shared__ double sm[];
+    const int o = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    SRow R[TOP > 0 ? TOP : 1];
+#pragma unroll
+    for (int l = TOP; l >= 1; --l) small_load(a.lv[l], o, lane, R[l - 1]);
+    for (int e = threadIdx.x; e < s.w[0]; e += CWG3) sm[e] = 0.0;   // iterates, residuals, right-hand sides
+    for (int e = threadIdx.x; e < a.nc * a.nc; e += CWG3) sm[s.chol + e] = a.chol[e];
+#pragma unroll
+    for (int l = TOP; l >= 1; --l) small_stage_weights(a.lv[l], a.lv[l - 1].g, sm + s.w[l]);
+    __syncthreads();
+    {   // the top level's right-hand side and iterate
+        const CLev &T = a.lv[TOP];
+        const Oct &g = T.g;
+        const int ni = g.nx - 2, nj = g.ny - 2, n = ni * nj * (g.nz - 2);
+        for (int e = threadIdx.x; e < n; e += CWG3) {
+            const int i = 1 + e % ni, j = 1 + (e / ni) % nj, k = 1 + e / (ni * nj);
+            const int q = (k * g.ny + j) * g.nx + i, v = (int)vid(g, i, j, k);
+            sm[s.x[TOP] + q] = T.x[v];
+            sm[s.b[TOP] + q] = T.b[v];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = TOP; l >= 1; --l) {
+        const Oct &g = a.lv[l].g;
+        SRow &Q = R[l - 1];
+        double *x = sm + s.x[l];
+        const int nxy = g.nx * g.ny;
+        Q.b = Q.in ? sm[s.b[l] + Q.at] : 0.0;
+        small_relax(Q, x, g.nx, nxy, o, a.nu1);
+        if (Q.in) {
+            small_off(Q, x, g.nx, nxy, Q.off);
+            Q.r = small_resid(Q, x, g.nx);
+            sm[s.r[l] + Q.at] = Q.r;
+        }
+        __syncthreads();
+        small_restrict(g, a.lv[l - 1].g, sm + s.r[l], sm + s.w[l], sm + s.b[l - 1]);
+    }
+    small_coarse(a.lv[0].g, sm + s.chol, a.nc, sm + s.b[0], sm + s.x[0]);
+#pragma unroll
+    for (int l = 1; l <= TOP; ++l) {
+        const Oct &g = a.lv[l].g;
+        SRow &Q = R[l - 1];
+        double *x = sm + s.x[l];
+        small_interp(g, a.lv[l - 1].g, Q, x, sm + s.x[l - 1], o, a.rescorr);
+        small_relax(Q, x, g.nx, g.nx * g.ny, o, a.nu2);
+    }
+    {
+        const CLev &T = a.lv[TOP];
+        const Oct &g = T.g;
+        const int ni = g.nx - 2, nj = g.ny - 2, n = ni * nj * (g.nz - 2);
+        for (int e = threadIdx.x; e < n; e += CWG3) {
+            const int i = 1 + e % ni, j = 1 + (e / ni) % nj, k = 1 + e / (ni * nj);
+            T.x[vid(g, i, j, k)] = sm[s.x[TOP] + (k * g.ny + j) * g.nx + i];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 hipbmg_status fail3(hipbmg_status st, const char *fmt, ...)
@@ -1769,6 +1996,38 @@ hipbmg_status interp_from(hipbmg3d_hier *h, int l, int cur, int ccur, int rescor
     return HIPBMG_OK;
 }
 
+// whether levels 0..top take the register-resident collapse, and its LDS: every
+// level above the coarsest with 27 points, odd sides and at most 64 interior
+// vertices in its largest octant (the one of all odd indices), which caps top
+// at 2; at most SMALL_NC unknowns on the coarsest; 64 KB of LDS
+bool small_collapse(const hipbmg3d_hier *h, int top, SmallLds *s)
+{
+    if (top > SMALL_MAXTOP || h->nc > SMALL_NC || h->nc < 1) return false;
+    for (int l = 1; l <= top; ++l) {
+        const Oct &g = h->lv[l].g;
+        if (h->lv[l].npt != 27 || !(g.nx & 1) || !(g.ny & 1) || !(g.nz & 1) ||
+            (long long)((g.nx - 1) / 2) * ((g.ny - 1) / 2) * ((g.nz - 1) / 2) > 64)
+            return false;
+    }
+    int at = 0;
+    for (int l = 0; l <= top; ++l) {
+        const Oct &g = h->lv[l].g;
+        const int n = g.nx * g.ny * g.nz;
+        s->x[l] = at;
+        s->b[l] = at + n;
+        s->r[l] = at + 2 * n;
+        at += (l > 0 ? 3 : 2) * n;
+    }
+    s->w[0] = at;   // what starts as zero ends here
+    for (int l = 1; l <= top; ++l) {
+        s->w[l] = at;
+        at += 27 * 64;
+    }
+    s->chol = at;
+    s->total = at + h->nc * h->nc;
+    return (size_t)s->total * sizeof(double) <= 64 * 1024;
+}
+
 // levels 0..top in one workgroup (top = 0: the coarse solve alone)
 hipbmg_status collapse(hipbmg3d_hier *h, int top, hipStream_t s)
 {
@@ -1785,6 +2044,16 @@ hipbmg_status collapse(hipbmg3d_hier *h, int top, hipStream_t s)
     a.nu2 = h->prm.nu2;
     a.rescorr = h->prm.residual_correction;
     Mark mk(h, 4, s);
+    SmallLds sl;
+    if (small_collapse(h, top, &sl)) {
+        const dim3 one(1), wg(CWG3);
+        const size_t lds = (size_t)sl.total * sizeof(double);
+        if (top == 0) hipLaunchKernelGGL(k3_collapse_small<0>, one, wg, lds, s, a, sl);
+        else if (top == 1) hipLaunchKernelGGL(k3_collapse_small<1>, one, wg, lds, s, a, sl);
+        else hipLaunchKernelGGL(k3_collapse_small<2>, one, wg, lds, s, a, sl);
+        HIP3(hipGetLastError());
+        return HIPBMG_OK;
+    }
     hipLaunchKernelGGL(k3_collapse, dim3(1), dim3(CWG3), (size_t)std::max(h->nc, 1) * sizeof(double), s, a);
     HIP3(hipGetLastError());
     return HIPBMG_OK;

@@ -57,3 +57,24 @@ def test_planes_are_the_single_workgroup(shape, npt, nu):
         got.append((u, info.history()))
     assert torch.equal(got[0][0], got[-1][0])
     assert got[0][1] == got[-1][1]
+
+
+# octants of exactly 64 vertices (9^3, 33 x 5 x 5) and just more (11 x 9 x 9),
+# two levels and one above the coarsest, an even coarsest side, 1, 15, 36 and
+# 216 coarsest unknowns (the last beyond the small workgroup)
+@pytest.mark.parametrize("shape", [(17, 17, 17), (9, 9, 65), (17, 17, 21), (17, 29, 13), (9, 9, 101), (15, 15, 15),
+                                   (9, 17, 33)])
+@pytest.mark.parametrize("prm", [{}, {"nu1": 1, "nu2": 2, "residual_correction": 0}, {"nu1": 0}])
+def test_register_resident_collapse_is_the_general_one(shape, prm):
+    nz, ny, nx = shape
+    planes = planes_of(7, shape, 81)
+    b = g(inputs.load3_uniform(nx, ny, nz, seed=82))
+    L = HB.Hierarchy3(planes).L
+    ref = None
+    for ls in [L - 1] + list(range(min(L, 3))):
+        h = HB.Hierarchy3(planes, collapse_level=ls, max_cycles=3, **prm)
+        u, info = h.solve(b, tol=1e-30, check=False)
+        if ref is None:
+            ref = (u, info.history())
+        assert torch.equal(u, ref[0]), ls
+        assert info.history() == ref[1], ls
