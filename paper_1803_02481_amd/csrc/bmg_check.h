@@ -1,0 +1,58 @@
+// bmg_check.h -- the convergence test of a cycle, as a device function: it runs
+// as a launch of its own (k_finalize_check) or as an extra workgroup of the
+// next cycle's first coarse kernel.
+#pragma once
+#include "bmg_internal.h"
+
+namespace hbmg {
+
+// Sum of the first 256 threads' values (every thread of the workgroup calls):
+// a butterfly within each wave, then the four wave sums in turn.  The result is
+// thread 0's.
+__device__ __forceinline__ double sum256(double acc, double *sh)
+{
+    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if ((threadIdx.x & 63) == 0 && threadIdx.x < 256) sh[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    return ((sh[0] + sh[1]) + sh[2]) + sh[3];
+}
+
+// values to a host-mapped slot, then the tag the host polls for: the fence
+// orders the two
+__device__ __forceinline__ void slot_write(double *slot, double v0, double v1, double v2, double tag)
+{
+    volatile double *v = slot;
+    v[0] = v0;
+    v[1] = v1;
+    v[2] = v2;
+    __threadfence_system();
+    v[3] = tag;
+}
+
+// the whole workgroup (at least 256 threads) calls
+__device__ __forceinline__ void cycle_check(const CheckArgs &c)
+{
+    __shared__ double sh[4];
+    if (c.flags[0] == 0) return;   // an earlier cycle met the test
+    double acc = 0.0;
+    if (threadIdx.x < 256)
+        for (int m = threadIdx.x; m < c.n; m += 256) acc += c.partials[m];
+    const double sum = sum256(acc, sh);
+    if (threadIdx.x == 0) {
+        const double rel = sqrt(sum) / c.denom[0];
+        int run = 1;
+        if (!isfinite(rel)) {
+            run = 0;
+            c.flags[1] = c.k;
+            c.flags[2] = 2;
+        } else if (rel <= c.tol) {
+            run = 0;
+            c.flags[1] = c.k;
+            c.flags[2] = 1;
+        }
+        c.flags[0] = run;
+        slot_write(c.slot, rel, (double)run, (double)c.flags[1], c.tag);
+    }
+}
+
+}  // namespace hbmg

@@ -13,7 +13,7 @@
 // in LDS while they fit; the rest are addressed in global memory (L2
 // resident).  The coarsest level is solved with the Cholesky factor computed
 // at setup (section 3, coarse-solve cost), in FP64.
-#include "bmg_internal.h"
+#include "bmg_check.h"
 
 namespace hbmg {
 
@@ -615,103 +615,39 @@ template hipError_t launch_collapse<double>(const CollapseArgs<double> &, hipStr
 template hipError_t launch_collapse<float>(const CollapseArgs<float> &, hipStream_t);
 
 // ---------------------------------------------------------------------------
-// Norm helpers: per-block partial sums of squares over interior vertices, then
-// one workgroup adds the partials in a fixed order.
+// Norm helpers: one workgroup adds the per-block partial sums of squares in a
+// fixed order.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_sumsq(const double *__restrict__ v, int nx, int ny,
-                                               int pitch, double *__restrict__ partials)
+__global__ __launch_bounds__(256) void k_finalize(const double *__restrict__ partials, int n,
+                                                  double *__restrict__ out, int *flags, double *slot, double tag)
 {
     __shared__ double sh[4];
-    const int ni = nx - 2;
-    const long long n = (long long)ni * (ny - 2);
-    double acc = 0.0;
-    for (long long idx = (long long)blockIdx.x * 256 + threadIdx.x; idx < n;
-         idx += (long long)gridDim.x * 256) {
-        const double a = v[(size_t)(1 + idx / ni) * pitch + 1 + idx % ni];
-        acc += a * a;
-    }
-    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) partials[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
-}
-
-hipError_t launch_sumsq(const double *v, int nx, int ny, int pitch, double *partials, int nparts,
-                        hipStream_t s)
-{
-    hipLaunchKernelGGL(k_sumsq, dim3(nparts), dim3(256), 0, s, v, nx, ny, pitch, partials);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_finalize(const double *__restrict__ partials, int n,
-                                                  const double *__restrict__ denom,
-                                                  double *__restrict__ out)
-{
-    __shared__ double sh[256];
     double acc = 0.0;
     for (int k = threadIdx.x; k < n; k += 256) acc += partials[k];
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int h = 128; h >= 1; h >>= 1) {
-        if ((int)threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
-        __syncthreads();
+    const double sum = sum256(acc, sh);
+    if (threadIdx.x == 0) {
+        const double v = sqrt(sum);
+        out[0] = v;
+        if (flags) {
+            flags[0] = 1;
+            flags[1] = flags[2] = 0;
+        }
+        if (slot) slot_write(slot, v, 0.0, 0.0, tag);
     }
-    if (threadIdx.x == 0) out[0] = denom ? sqrt(sh[0]) / denom[0] : sqrt(sh[0]);
 }
 
-hipError_t launch_finalize_norm(const double *partials, int n, const double *denom, double *out,
-                                hipStream_t s)
+hipError_t launch_finalize_norm(const double *partials, int n, double *out, hipStream_t s, int *flags, double *slot,
+                                double tag)
 {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, s, partials, n, denom, out);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, s, partials, n, out, flags, slot, tag);
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_finalize_check(const double *__restrict__ partials, int n,
-                                                        const double *__restrict__ denom, double tol, int k,
-                                                        double *__restrict__ hist, int hist_cap, double *last,
-                                                        int *flags, double *slot)
-{
-    __shared__ double sh[4];
-    if (flags[0] == 0) return;   // an earlier cycle met the test
-    // fixed order: a strided sum per lane, a butterfly within each wave, then
-    // the four wave sums in turn
-    double acc = 0.0;
-    for (int m = threadIdx.x; m < n; m += 256) acc += partials[m];
-    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const double rel = sqrt(((sh[0] + sh[1]) + sh[2]) + sh[3]) / denom[0];
-        if (k - 1 < hist_cap) hist[k - 1] = rel;
-        last[0] = rel;
-        int run = 1;
-        if (!isfinite(rel)) {
-            run = 0;
-            flags[1] = k;
-            flags[2] = 2;
-        } else if (rel <= tol) {
-            run = 0;
-            flags[1] = k;
-            flags[2] = 1;
-        }
-        flags[0] = run;
-        // host-mapped slot: the host reads it after synchronising on an event
-        // recorded behind this kernel, whose system-scope release makes these
-        // writes visible
-        volatile double *v = slot;
-        v[0] = rel;
-        v[1] = (double)run;
-        v[2] = (double)flags[1];
-        v[3] = (double)k;
-    }
-}
+__global__ __launch_bounds__(256) void k_finalize_check(CheckArgs c) { cycle_check(c); }
 
-hipError_t launch_finalize_check(const double *partials, int n, const double *denom, double tol, int k,
-                                 double *hist, int hist_cap, double *last, int *flags, double *slot,
-                                 hipStream_t s)
+hipError_t launch_finalize_check(const CheckArgs &c, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_finalize_check, dim3(1), dim3(256), 0, s, partials, n, denom, tol, k, hist, hist_cap,
-                       last, flags, slot);
+    hipLaunchKernelGGL(k_finalize_check, dim3(1), dim3(256), 0, s, c);
     return hipGetLastError();
 }
 

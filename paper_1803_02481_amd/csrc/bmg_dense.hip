@@ -8,7 +8,7 @@
 // is one launch without a single dependent step.  M is formed once per
 // hierarchy, in FP64, by the same relaxations, transfers and Cholesky
 // substitutions as the collapse, one workgroup per column.
-#include "bmg_internal.h"
+#include "bmg_check.h"
 
 namespace hbmg {
 
@@ -207,9 +207,13 @@ constexpr int DENSE_PRE = DENSE_MAX / 128;   // a row's loads, all in flight
 template <typename T>
 __global__ __launch_bounds__(64 * DENSE_ROWS) void k_dense_apply(const double *__restrict__ M, int n, int ld,
                                                                 const T *__restrict__ b, T *__restrict__ x, int nx,
-                                                                int pitch, const int *active)
+                                                                int pitch, const int *active, CheckArgs chk)
 {
     __shared__ __align__(16) double bs[DENSE_MAX];
+    if ((int)blockIdx.x * DENSE_ROWS >= n) {   // the extra workgroup
+        cycle_check(chk);
+        return;
+    }
     if (active && *active == 0) return;
     const int lane = threadIdx.x & 63, row = blockIdx.x * DENSE_ROWS + (threadIdx.x >> 6);
     const int nch = ld >> 7, mine = row < n ? row : n - 1;
@@ -241,15 +245,17 @@ __global__ __launch_bounds__(64 * DENSE_ROWS) void k_dense_apply(const double *_
 
 template <typename T>
 hipError_t launch_dense_apply(const double *M, int n, int ld, const LevelDev<T> &lv, int xb, const int *active,
-                              hipStream_t s)
+                              hipStream_t s, const CheckArgs *chk)
 {
-    hipLaunchKernelGGL((k_dense_apply<T>), dim3((n + DENSE_ROWS - 1) / DENSE_ROWS), dim3(64 * DENSE_ROWS), 0, s, M, n,
-                       ld, lv.b, lv.x[xb], lv.nx, lv.pitch, active);
+    static_assert(64 * DENSE_ROWS >= 256, "cycle_check needs 256 threads");
+    const int extra = chk && chk->partials ? 1 : 0;
+    hipLaunchKernelGGL((k_dense_apply<T>), dim3((n + DENSE_ROWS - 1) / DENSE_ROWS + extra), dim3(64 * DENSE_ROWS), 0,
+                       s, M, n, ld, lv.b, lv.x[xb], lv.nx, lv.pitch, active, extra ? *chk : CheckArgs{});
     return hipGetLastError();
 }
 template hipError_t launch_dense_apply<double>(const double *, int, int, const LevelDev<double> &, int, const int *,
-                                               hipStream_t);
+                                               hipStream_t, const CheckArgs *);
 template hipError_t launch_dense_apply<float>(const double *, int, int, const LevelDev<float> &, int, const int *,
-                                              hipStream_t);
+                                              hipStream_t, const CheckArgs *);
 
 }  // namespace hbmg

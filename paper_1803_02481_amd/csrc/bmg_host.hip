@@ -9,6 +9,7 @@
 #include <atomic>
 #include <thread>
 #include <algorithm>
+#include <functional>
 #include <map>
 #include <chrono>
 #include <cmath>
@@ -265,12 +266,12 @@ struct hipbmg_hier {
     int nc = 0;
     double *d_partials = nullptr;
     size_t n_partials = 0;
-    double *d_scal = nullptr;   // [0] ||b||, [1] relres, [2] ||r|| (mixed outer), [3] inner relres
+    double *d_scal = nullptr;   // [0] ||b||, [2] ||r|| (mixed outer), [5] an operation's norm
     double *h_scal = nullptr;   // pinned mirror
     int lstar = 0;
     // levels 0..dense_top as one dense operator instead of the collapsed
     // workgroup (-1: not in use); formed by the first solve
-    int dense_top = -1, dense_n = 0, dense_ld = 0, dense_built = 0;
+    int dense_top = -1, dense_n = 0, dense_ld = 0, dense_built = 0, dense_xb = 0;
     double *d_dense = nullptr;
     // agglomeration stages between the grid-wide kernels and the collapse
     int cl_nstage = 0;
@@ -301,13 +302,15 @@ struct hipbmg_hier {
     int wform = 0;              // the FP64 pipelined pass forms the interpolation weights
     double *x3_64 = nullptr;    // third iterate buffer of the pipelined finest level
     float *x3_32 = nullptr;
-    // device-side stopping: run flag, residual history, and a ring of
-    // host-mapped slots through which the host sees each cycle's test
+    // device-side stopping: run flag, and a ring of host-mapped slots through
+    // which the host sees each cycle's test
     int *d_flags = nullptr;               // [0] run, [1] stopping cycle, [2] reason
-    int *h_flags = nullptr;               // pinned mirror of d_flags
-    double *d_hist = nullptr;             // relres after each cycle of the current solve
-    double *ring_host = nullptr, *ring_dev = nullptr;   // RING x {relres, run, stop, k}
-    hipEvent_t ring_ev[RING] = {};
+    std::vector<double> hist;             // relres after each cycle of the current run
+    int stop_reason = 0;                  // of that run: 1 test met, 2 not finite, 0 neither
+    // RING x {relres, run, stopping cycle, tag}, then one {norm, -, -, tag};
+    // a tag names a run and a cycle, so a slot of an earlier one never matches
+    double *ring_host = nullptr, *ring_dev = nullptr;
+    unsigned run_id = 0;
     int ahead = 2;                        // cycles enqueued beyond the last test seen
     // live timing of the finest-level streaming kernels (HIP events on the
     // solve stream), kept in a ring and collected in order once complete
@@ -333,14 +336,11 @@ struct hipbmg_hier {
             if (ev0[k]) (void)hipEventDestroy(ev0[k]);
             if (ev1[k]) (void)hipEventDestroy(ev1[k]);
         }
-        for (int k = 0; k < RING; ++k)
-            if (ring_ev[k]) (void)hipEventDestroy(ring_ev[k]);
         dev_free_all(allocs);
         // the pinned slots go back to the pool for the next handle: nothing
         // of this handle may still write them
-        if (h_scal || h_flags || ring_host) (void)hipDeviceSynchronize();
+        if (h_scal || ring_host) (void)hipDeviceSynchronize();
         pinned_small_free(h_scal);
-        pinned_small_free(h_flags);
         pinned_small_free(ring_host);
     }
 };
@@ -1009,17 +1009,15 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
     if (st != HIPBMG_OK) return bail(st);
     st = dalloc(h, &h->d_scal, 8, s);
     if (st != HIPBMG_OK) return bail(st);
-    if (pinned_small((void **)&h->h_scal, nullptr, 8 * sizeof(double)) != hipSuccess ||
-        pinned_small((void **)&h->h_flags, nullptr, 4 * sizeof(int)) != hipSuccess)
+    if (pinned_small((void **)&h->h_scal, nullptr, 8 * sizeof(double)) != hipSuccess)
         return bail(fail(HIPBMG_ENOMEM, "pinned host allocation failed"));
-    // device-side stopping: run flag, residual history, host-mapped test slots
+    // device-side stopping: run flag, host-mapped test slots
     st = dalloc(h, &h->d_flags, 4, s);
-    if (st == HIPBMG_OK) st = dalloc(h, &h->d_hist, HIPBMG_MAX_HIST, s);
     if (st != HIPBMG_OK) return bail(st);
-    if (pinned_small((void **)&h->ring_host, (void **)&h->ring_dev, RING * 4 * sizeof(double)) != hipSuccess ||
+    if (pinned_small((void **)&h->ring_host, (void **)&h->ring_dev, (RING + 1) * 4 * sizeof(double)) != hipSuccess ||
         !h->ring_dev)
         return bail(fail(HIPBMG_ENOMEM, "host-mapped allocation failed"));
-    for (int k = 0; k < RING * 4; ++k) h->ring_host[k] = 0.0;
+    for (int k = 0; k < (RING + 1) * 4; ++k) h->ring_host[k] = 0.0;
     if (const char *e = std::getenv("HIPBMG_AHEAD")) {   // cycles enqueued ahead of the last test seen
         const int v = std::atoi(e);
         if (v >= 0 && v < RING) h->ahead = v;
@@ -1278,8 +1276,10 @@ template <typename T>
 static hipError_t enqueue_vcycle(hipbmg_hier *h, const std::vector<LevelDev<T>> &lv,
                                  const LevelDev<T> *d_lv, int cur, bool zero_start, int *new_cur,
                                  int *nparts, hipStream_t s, bool skip_finest = false,
-                                 const int *active = nullptr)
+                                 const int *active = nullptr, const CheckArgs *chk = nullptr)
 {
+    // chk: the previous cycle's test (or none), taken along by the first launch
+    // where check_rides says it can be
     // skip_finest: run levels L-2..0 only (the finest level's kernels are
     // issued by the caller); *new_cur then receives the buffer of level L-2's
     // correction
@@ -1327,7 +1327,7 @@ static hipError_t enqueue_vcycle(hipbmg_hier *h, const std::vector<LevelDev<T>> 
                 a.rb = tile_steps(nw, 1);
                 tile_geometry(A.nx, A.ny, A.npt, nw, 1, &a.nstrips, &nbl, &a.ntiles);
                 a.nblocks = nbl;
-                if ((e = launch_tile<T>(1, nw, a, s)) != hipSuccess) return e;
+                if ((e = launch_tile<T>(1, nw, a, s, l == L - 1 ? chk : nullptr)) != hipSuccess) return e;
             } else if ((e = run_stream(A, v, a, s)) != hipSuccess) {
                 return e;
             }
@@ -1339,10 +1339,14 @@ static hipError_t enqueue_vcycle(hipbmg_hier *h, const std::vector<LevelDev<T>> 
     if (dense) {
         // levels 0..gtop: one matrix-vector product
         const int pk = prof_begin(h, -1, PrecIdx<T>::v, gtop, 2, false, s);
-        if ((e = launch_dense_apply<T>(h->d_dense, h->dense_n, h->dense_ld, lv[gtop], 1, active, s)) != hipSuccess)
+        // into either buffer in turn: a stopping cycle's correction outlasts the
+        // launch that takes that cycle's test along
+        const int xb = h->dense_xb ^= 1;
+        if ((e = launch_dense_apply<T>(h->d_dense, h->dense_n, h->dense_ld, lv[gtop], xb, active, s,
+                                       gtop == L - 1 ? chk : nullptr)) != hipSuccess)
             return e;
         prof_end(h, pk, s);
-        xres[gtop] = 1;
+        xres[gtop] = xb;
     } else if (h->cl_nstage > 0) {
         // levels 0..gtop in one launch: the stages, then the collapse
         const ClusterArgs<T> c = cluster_args<T>(h, lv, d_lv, ls, h->cl_nstage, h->cl_wg, h->cl_hi, active);
@@ -1447,21 +1451,72 @@ template <typename T> static T *&x3_of(hipbmg_hier *h);
 template <> double *&x3_of<double>(hipbmg_hier *h) { return h->x3_64; }
 template <> float *&x3_of<float>(hipbmg_hier *h) { return h->x3_32; }
 
+// A fresh tag: the run's number in the high bits, room for a cycle number below
+static double next_tag(hipbmg_hier *h) { return (double)(++h->run_id & 0xfffffu) * 4294967296.0; }
+
+// Wait until slot `idx` of the ring carries `tag`.  The kernel that writes it is
+// on stream s, so a stream that has drained without it means a failed launch.
+static hipbmg_status wait_slot(hipbmg_hier *h, int idx, double tag, hipStream_t s)
+{
+    const volatile double *v = h->ring_host + 4 * idx;
+    for (unsigned spins = 1;; ++spins) {
+        if (v[3] == tag) break;
+        __builtin_ia32_pause();
+        if (spins % 4096) continue;
+        const hipError_t e = hipStreamQuery(s);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        if (e == hipSuccess && v[3] == tag) break;
+        return fail(HIPBMG_EHIP, "a test's result did not arrive: %s", hipGetErrorString(e));
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    return HIPBMG_OK;
+}
+
+// ||b||, written by the launch tagged `tag`
+static hipbmg_status wait_bnorm(hipbmg_hier *h, double tag, hipStream_t s, double *bnorm)
+{
+    STCHK(wait_slot(h, RING, tag, s));
+    *bnorm = h->ring_host[4 * RING];
+    if (!std::isfinite(*bnorm)) return fail(HIPBMG_ENAN, "||b|| is not finite");
+    return HIPBMG_OK;
+}
+
+// Whether the first launch below the finest level can take the previous cycle's
+// test along as one more workgroup: the dense operator, or a tile kernel.  The
+// launch then runs once after the stopping cycle too (16 us at most, on 513^2),
+// where a test of its own costs 4 us and a gap of 4-5 us every cycle; a
+// streaming down leg of a larger level would be 28 us or more.  Nothing it
+// writes is read again: the stopping cycle's correction is in the level's
+// other buffer.
+static bool check_rides(const hipbmg_hier *h)
+{
+    const int top = h->L - 2;
+    const int gtop = h->dense_top >= 0 ? h->dense_top : h->cl_nstage > 0 ? h->cl_hi[0] : h->lstar;
+    return gtop == top ? h->dense_top == top : h->tile_dn[top] != 0;
+}
+
 // Run up to max_cycles V-cycles on the hierarchy lv (FP64 levels, or the FP32
 // levels of a mixed solve) from its finest iterate x[0] (or from zero), with
 // the convergence test ||r|| / denom[0] <= tol after every cycle taken on the
-// device.  The host enqueues up to `ahead` cycles beyond the last test it has
-// seen; once a test is met the device clears the run flag and every launch of
-// later cycles returns at once, so the iterate stays the one of the stopping
-// cycle.  With the finest level pipelined, cycle k's post-relaxation, norm and
-// cycle k+1's pre-relaxations and restriction are one pass over three
-// iterate buffers.  On return *result is the finest buffer holding the
-// iterate after the last cycle run, *cycles_done their number, and the
-// residual history of the run is in d_hist.
+// device.  The caller has set the run flag.  The host enqueues up to `ahead`
+// cycles beyond the last test it has seen; once a test is met the device clears
+// the run flag and every launch of later cycles returns at once, so the iterate
+// stays the one of the stopping cycle.  The host polls host-mapped slots for
+// the tests and never waits for the stream.  With the finest level pipelined,
+// cycle k's post-relaxation, norm and cycle k+1's pre-relaxations and
+// restriction are one pass over three iterate buffers.  gate (or null) is
+// called once the first cycle is enqueued and ends the run unless it returns
+// OK.  On return *result is the finest buffer that holds the iterate after the
+// last cycle run (once the stream gets there), *cycles_done their number,
+// h->hist the residual history and h->stop_reason why it stopped.
 template <typename T>
 static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &lv, const LevelDev<T> *d_lv,
                                 bool zero_start, int max_cycles, double tol, const double *d_denom,
-                                hipStream_t s, const T **result, int *cycles_done)
+                                hipStream_t s, const T **result, int *cycles_done,
+                                const std::function<hipbmg_status()> &gate)
 {
     const int L = h->L;
     const LevelDev<T> &F = lv[L - 1];
@@ -1469,20 +1524,15 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
     const bool pipe = h->fused3 != 0;
     STCHK(ensure_dense(h, s));
     T *xb[3] = {F.x[0], F.x[1], pipe ? x3_of<T>(h) : nullptr};
-    // the convergence-test events, made on the handle's first solve (the
-    // hierarchies of a batch never need them)
-    for (int k = 0; k < RING; ++k)
-        if (!h->ring_ev[k] && hipEventCreateWithFlags(&h->ring_ev[k], hipEventDisableTiming) != hipSuccess) {
-            h->ring_ev[k] = nullptr;
-            return fail(HIPBMG_EHIP, "event creation failed");
-        }
+    h->hist.clear();
+    h->stop_reason = 0;
+    const double tag0 = next_tag(h);
 
     std::vector<const T *> res_after((size_t)max_cycles + 1, F.x[0]);
     // pipelined: the inputs of each cycle's finest pass (iterate buffer,
     // coarse correction), to rebuild the stopping cycle's iterate
     std::vector<int> in_i((size_t)max_cycles + 1, 0);
     std::vector<const T *> in_xc((size_t)max_cycles + 1, nullptr);
-    HIPCHK(launch_flags_reset(h->d_flags, s));
     if (pipe) {
         // pre-relaxations of cycle 1 and the restriction of its residual
         const LevelDev<T> &Cl = lv[L - 2];
@@ -1498,8 +1548,26 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
         a.cplane = (long long)Cl.plane;
         HIPCHK(run_stream(F, zero_start ? SV_SWEEP2_RQ_ZX : SV_SWEEP2_RQ, a, s));
     }
-    int k = 0, seen = 0, i = 1, cur = 0;
+    int k = 0, seen = 0, i = 1, cur = 0, kdone = 0;
     bool stopped = false;
+    const bool ride = pipe && check_rides(h);
+    const int ahead = std::max(h->ahead, ride ? 1 : 0);
+    CheckArgs pending{};   // the last cycle's test, for the next cycle's first launch
+    // the next test's outcome
+    auto look = [&]() -> hipbmg_status {
+        ++seen;
+        const int idx = seen % RING;
+        STCHK(wait_slot(h, idx, tag0 + seen, s));
+        const volatile double *slot = h->ring_host + 4 * idx;
+        const double rel = slot[0];
+        h->hist.push_back(rel);
+        if (slot[1] == 0.0) {
+            stopped = true;
+            kdone = (int)slot[2];
+            h->stop_reason = std::isfinite(rel) ? 1 : 2;
+        }
+        return HIPBMG_OK;
+    };
     // a cycle known to be the last (the cap) runs stage P alone, storing its
     // iterate and forming its norm, instead of also relaxing for a next cycle
     // that never comes and then rebuilding (HIPBMG_NO_LAST_PASS=1 keeps the
@@ -1514,7 +1582,7 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
         if (pipe) {
             const LevelDev<T> &Cl = lv[L - 2];
             int cc = 0, dummy = 0;
-            hipError_t e = enqueue_vcycle<T>(h, lv, d_lv, 0, false, &cc, &dummy, s, true, act);
+            hipError_t e = enqueue_vcycle<T>(h, lv, d_lv, 0, false, &cc, &dummy, s, true, act, &pending);
             if (e != hipSuccess) return fail(HIPBMG_EHIP, "V-cycle launch failed: %s", hipGetErrorString(e));
             StreamArgs<T> a = base_args(F, h->rb3);
             a.zexc = h->zexc[PrecIdx<T>::v];
@@ -1548,22 +1616,22 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
             cur = nc;
             res_after[k] = F.x[cur];
         }
-        HIPCHK(launch_finalize_check(h->d_partials, np, d_denom, tol, k, h->d_hist, HIPBMG_MAX_HIST, h->d_scal + 1,
-                                     h->d_flags, h->ring_dev + 4 * (k % RING), s));
-        HIPCHK(hipEventRecord(h->ring_ev[k % RING], s));
+        pending = CheckArgs{h->d_partials, np, k, d_denom, tol, h->d_flags,
+                            h->ring_dev + 4 * (k % RING), tag0 + k};
+        if (!ride || k == max_cycles) {
+            HIPCHK(launch_finalize_check(pending, s));
+            pending = CheckArgs{};
+        }
+        if (k == 1 && gate) STCHK(gate());
         // the tests of earlier cycles, `ahead` cycles behind the newest
-        while (seen < k - h->ahead && !stopped) {
-            ++seen;
-            HIPCHK(hipEventSynchronize(h->ring_ev[seen % RING]));
+        while (seen < k - ahead && !stopped) {
+            STCHK(look());
             prof_collect(h, false, seen, false);
-            const volatile double *slot = h->ring_host + 4 * (seen % RING);
-            if (slot[1] == 0.0) stopped = true;
         }
     }
-    // the flags come back with the same synchronisation that ends the cycles
-    HIPCHK(hipMemcpyAsync(h->h_flags, h->d_flags, 4 * sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    const int kdone = h->h_flags[0] ? k : h->h_flags[1];
+    while (!stopped && seen < k) STCHK(look());
+    if (!stopped) kdone = k;
+    if (h->prof_on) HIPCHK(hipStreamSynchronize(s));
     prof_collect(h, true, kdone);
     if (pipe && kdone > 0 && kdone != stored_last) {
         // the pipelined pass does not store the iterate after its cycle; the
@@ -1637,24 +1705,27 @@ static hipbmg_status check_stage_barriers(hipbmg_hier *h, hipStream_t s)
 }
 
 static hipbmg_status solve_fp64(hipbmg_hier *h, double tol, hipStream_t s, hipbmg_info *info,
-                                const double **res_out)
+                                const double **res_out, double bn_tag, double *bnorm)
 {
     int cycles = 0;
-    STCHK(run_cycles<double>(h, h->lv, h->d_lv, false, h->prm.max_cycles, tol, h->d_scal, s, res_out, &cycles));
-    std::vector<double> hist(std::min(cycles, HIPBMG_MAX_HIST));
-    if (!hist.empty())
-        HIPCHK(hipMemcpy(hist.data(), h->d_hist, hist.size() * sizeof(double), hipMemcpyDeviceToHost));
-    STCHK(read_scalars(h, 1, 1, s));
-    const double rel = cycles > 0 ? h->h_scal[1] : 1.0;
+    // ||b|| is waited for once the first relaxations are under way
+    auto gate = [&]() -> hipbmg_status {
+        STCHK(wait_bnorm(h, bn_tag, s, bnorm));
+        return *bnorm == 0.0 ? HIPBMG_EINVAL : HIPBMG_OK;   // nothing to solve: ends the run
+    };
+    const hipbmg_status st =
+        run_cycles<double>(h, h->lv, h->d_lv, false, h->prm.max_cycles, tol, h->d_scal, s, res_out, &cycles, gate);
+    if (*bnorm == 0.0) return HIPBMG_OK;
+    if (st != HIPBMG_OK) return st;
+    const double rel = h->hist[cycles - 1];
     if (info) {
         info->cycles = cycles;
         info->outer_steps = cycles;
         info->relres = rel;
-        for (size_t m = 0; m < hist.size(); ++m) info->relres_hist[m] = hist[m];
+        for (int m = 0; m < std::min(cycles, HIPBMG_MAX_HIST); ++m) info->relres_hist[m] = h->hist[m];
     }
-    if (h->h_flags[0] == 0 && h->h_flags[2] == 2)
-        return fail(HIPBMG_ENAN, "residual norm is not finite after cycle %d", cycles);
-    if (h->h_flags[0] != 0)
+    if (h->stop_reason == 2) return fail(HIPBMG_ENAN, "residual norm is not finite after cycle %d", cycles);
+    if (h->stop_reason == 0)
         return fail(HIPBMG_ENOCONV, "relres %.3e > tol %.3e after %d cycles", rel, tol, cycles);
     return HIPBMG_OK;
 }
@@ -1662,7 +1733,8 @@ static hipbmg_status solve_fp64(hipbmg_hier *h, double tol, hipStream_t s, hipbm
 // FP64 iterative refinement: the outer residual r = b - A u in FP64 (demoted
 // into the FP32 right-hand side), inner FP32 V-cycles on A e = r from e = 0 to
 // a relative residual of inner_tol, u += e.
-static hipbmg_status solve_mixed(hipbmg_hier *h, double tol, hipStream_t s, hipbmg_info *info)
+static hipbmg_status solve_mixed(hipbmg_hier *h, double tol, hipStream_t s, hipbmg_info *info, double bn_tag,
+                                 double *bnorm_out)
 {
     const int L = h->L;
     const LevelDev<double> &F = h->lv[L - 1];
@@ -1670,13 +1742,20 @@ static hipbmg_status solve_mixed(hipbmg_hier *h, double tol, hipStream_t s, hipb
     int cycles = 0, steps = 0;
     double rel = 1.0;
     hipbmg_status st = HIPBMG_ENOCONV;
-    const double bnorm = h->h_scal[0];
+    double bnorm = 0.0;
     for (;;) {
         int np = 0;
         HIPCHK(launch_ir_residual(F, F.x[0], F32.b, F32.pitch, h->d_partials, &np, s));
-        HIPCHK(launch_finalize_norm(h->d_partials, np, nullptr, h->d_scal + 2, s));
-        STCHK(read_scalars(h, 2, 1, s));
-        const double rnorm = h->h_scal[2];
+        if (steps == 0) {
+            STCHK(wait_bnorm(h, bn_tag, s, bnorm_out));
+            bnorm = *bnorm_out;
+            if (bnorm == 0.0) return HIPBMG_OK;
+        }
+        // the norm's launch starts the inner run's flags as well
+        const double tag = next_tag(h);
+        HIPCHK(launch_finalize_norm(h->d_partials, np, h->d_scal + 2, s, h->d_flags, h->ring_dev + 4 * RING, tag));
+        STCHK(wait_slot(h, RING, tag, s));
+        const double rnorm = h->ring_host[4 * RING];
         rel = rnorm / bnorm;
         if (info && steps < HIPBMG_MAX_HIST) info->relres_hist[steps] = rel;
         if (!std::isfinite(rel)) {
@@ -1697,7 +1776,7 @@ static hipbmg_status solve_mixed(hipbmg_hier *h, double tol, hipStream_t s, hipb
         int done = 0;
         double itol = h->prm.inner_tol;
         if (h->inner_adapt) itol = std::max(itol, 0.5 * tol / rel);
-        STCHK(run_cycles<float>(h, h->lv32, h->d_lv32, true, cap, itol, h->d_scal + 2, s, &e32, &done));
+        STCHK(run_cycles<float>(h, h->lv32, h->d_lv32, true, cap, itol, h->d_scal + 2, s, &e32, &done, nullptr));
         cycles += done;
         HIPCHK(launch_ir_update(F.x[0], F.pitch, e32, F32.pitch, F.nx, F.ny, s));
     }
@@ -1726,32 +1805,25 @@ extern "C" hipbmg_status hipbmg_solve(hipbmg_handle h, const double *b, double *
         memset(info, 0, sizeof *info);
         fill_info_common(h, info);
     }
-    HIPCHK(hipMemcpy2DAsync(F.b, F.pitch * sizeof(double), b, nx * sizeof(double), nx * sizeof(double),
-                            ny, hipMemcpyDeviceToDevice, s));
-    HIPCHK(hipMemcpy2DAsync(F.x[0], F.pitch * sizeof(double), u, nx * sizeof(double),
-                            nx * sizeof(double), ny, hipMemcpyDeviceToDevice, s));
-    HIPCHK(launch_zero_ring(F.x[0], nx, ny, F.pitch, s));
-    HIPCHK(launch_zero_ring(F.b, nx, ny, F.pitch, s));
-    const int nparts = 1024;
-    HIPCHK(launch_sumsq(F.b, nx, ny, F.pitch, h->d_partials, nparts, s));
-    HIPCHK(launch_finalize_norm(h->d_partials, nparts, nullptr, h->d_scal, s));
-    STCHK(read_scalars(h, 0, 1, s));
-    const double bnorm = h->h_scal[0];
-    if (!std::isfinite(bnorm)) return fail(HIPBMG_ENAN, "||b|| is not finite");
-    if (bnorm == 0.0) {
+    int nparts = 0;
+    HIPCHK(launch_stage_in(b, u, F.b, F.x[0], nx, ny, F.pitch, h->d_partials, &nparts, s));
+    const double bn_tag = next_tag(h);
+    HIPCHK(launch_finalize_norm(h->d_partials, nparts, h->d_scal, s, h->d_flags, h->ring_dev + 4 * RING, bn_tag));
+    double bnorm = 1.0;
+    const double *res = F.x[0];
+    hipbmg_status st = h->prm.precision == HIPBMG_MIXED ? solve_mixed(h, tol, s, info, bn_tag, &bnorm)
+                                                         : solve_fp64(h, tol, s, info, &res, bn_tag, &bnorm);
+    if (!std::isfinite(bnorm)) return st;
+    if (bnorm == 0.0 && st == HIPBMG_OK) {
         HIPCHK(hipMemsetAsync(u, 0, (size_t)nx * ny * sizeof(double), s));
         HIPCHK(hipStreamSynchronize(s));
         if (info) info->solve_ms = now_ms() - t0;
         return HIPBMG_OK;
     }
-    const double *res = F.x[0];
-    hipbmg_status st = h->prm.precision == HIPBMG_MIXED ? solve_mixed(h, tol, s, info)
-                                                         : solve_fp64(h, tol, s, info, &res);
     if (st != HIPBMG_OK && st != HIPBMG_ENOCONV && st != HIPBMG_ENAN) return st;
     STCHK(check_stage_barriers(h, s));
     std::string msg = g_err;
-    HIPCHK(hipMemcpy2DAsync(u, nx * sizeof(double), res, F.pitch * sizeof(double),
-                            nx * sizeof(double), ny, hipMemcpyDeviceToDevice, s));
+    HIPCHK(launch_stage_out(res, u, nx, ny, F.pitch, s));
     HIPCHK(hipStreamSynchronize(s));
     if (info) info->solve_ms = now_ms() - t0;
     g_err = msg;
@@ -1904,7 +1976,7 @@ static hipbmg_status op_interp_smooth(hipbmg_hier *h, int l, const T *b, T *x, c
     int nt = 0;
     HIPCHK(run_stream(A, sumsq_host ? SV_INTERP_NORM : SV_INTERP, a, s, &nt));
     if (sumsq_host) {
-        HIPCHK(launch_finalize_norm(h->d_partials, nt, nullptr, h->d_scal + 5, s));
+        HIPCHK(launch_finalize_norm(h->d_partials, nt, h->d_scal + 5, s));
         STCHK(read_scalars(h, 5, 1, s));
         *sumsq_host = h->h_scal[5] * h->h_scal[5];
     }
@@ -1995,9 +2067,10 @@ extern "C" hipbmg_status hipbmg_op32_inner(hipbmg_handle h, const float *r, floa
     HIPCHK(hipStreamSynchronize(s));
     const float *res = nullptr;
     int done = 0;
-    STCHK(run_cycles<float>(h, h->lv32, h->d_lv32, true, cycles, inner_tol, h->d_scal + 2, s, &res, &done));
-    if (hist_host && done > 0)
-        HIPCHK(hipMemcpyAsync(hist_host, h->d_hist, done * sizeof(double), hipMemcpyDeviceToHost, s));
+    HIPCHK(launch_flags_reset(h->d_flags, s));
+    STCHK(run_cycles<float>(h, h->lv32, h->d_lv32, true, cycles, inner_tol, h->d_scal + 2, s, &res, &done, nullptr));
+    if (hist_host)
+        for (int m = 0; m < done; ++m) hist_host[m] = h->hist[m];
     STCHK(from_pitched(e, res, F.pitch, F.nx, F.ny, s));
     HIPCHK(hipStreamSynchronize(s));
     if (cycles_host) *cycles_host = done;

@@ -142,6 +142,21 @@ hipError_t launch_stream3_batched(int variant, int zc, const StreamArgs<T> *args
 hipError_t launch_rowsum_diag(const LevelDev<double> &A, int *flag, int set, hipStream_t s);
 hipError_t launch_zero_excess9(const LevelDev<float> &A, int *flag, hipStream_t s);
 
+// Convergence test after cycle k of a solve: ||r|| / denom[0] from the n norm
+// partials goes, with the flag state, to the slot {relres, run flag, stopping
+// cycle, tag} (host-mapped memory the host polls for the tag).
+// When relres <= tol, or is not finite, the run flag flags[0] is cleared and
+// flags[1] = k, flags[2] = 1 (met) or 2 (not finite).  Nothing is written once
+// the flag is clear.
+struct CheckArgs {
+    const double *partials;   // null: no test in this launch
+    int n, k;
+    const double *denom;
+    double tol;
+    int *flags;
+    double *slot, tag;
+};
+
 // Tile kernels of the small 9-point coarse levels (V(2,1)): a workgroup of nw
 // waves (4 or 8) owns a strip by tile_steps(nw, down) row-pair steps.  down:
 // two relaxations from zero, residual, r/C and restriction (the work of
@@ -149,8 +164,9 @@ hipError_t launch_zero_excess9(const LevelDev<float> &A, int *flag, hipStream_t 
 // a.nstrips / a.ntiles come from tile_geometry; one workgroup per tile.
 int tile_steps(int nw, int down);
 void tile_geometry(int nx, int ny, int npt, int nw, int down, int *nstrips, int *nblocks, int *ntiles);
+// chk: the test of the previous cycle, as one more workgroup (down only).
 template <typename T>
-hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s);
+hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s, const CheckArgs *chk = nullptr);
 
 // 1 if every interior vertex of a 5-point level has C exactly equal to
 // ((W_p + W_e) + S_p) + S_n (FP64), or an FP32 edge-form excess of exactly 0;
@@ -220,7 +236,7 @@ struct DenseBuildArgs {
 hipError_t launch_dense_build(const DenseBuildArgs &a, int n, hipStream_t s);
 template <typename T>
 hipError_t launch_dense_apply(const double *M, int n, int ld, const LevelDev<T> &lv, int xb, const int *active,
-                              hipStream_t s);
+                              hipStream_t s, const CheckArgs *chk = nullptr);
 
 // Agglomeration stages between the grid-wide kernels and the collapsed
 // workgroup (section 4: the coarse grid moves onto fewer and fewer
@@ -267,22 +283,11 @@ hipError_t launch_finalize_batched(const double *partials, const int *off, const
                                    const double *tol_dev, int nprob, hipStream_t s, int tol_stride = 0);
 hipError_t launch_count_active(const int *active, int n, int *count, hipStream_t s);
 
-// Sum of squares of interior entries of a pitched field -> partials.
-hipError_t launch_sumsq(const double *v, int nx, int ny, int pitch, double *partials, int nparts,
-                        hipStream_t s);
-// out[0] = sqrt(sum(partials)) / denom_src[0] (denom_src may be null -> plain norm).
-hipError_t launch_finalize_norm(const double *partials, int n, const double *denom, double *out,
-                                hipStream_t s);
-// Convergence test after cycle k of a solve: ||r|| / denom[0] from the norm
-// partials (the same fixed-order reduction as launch_finalize_norm) goes to
-// last[0], to hist[k-1] (if k <= hist_cap) and, with the flag state, to the four doubles
-// at slot {relres, run flag, stopping cycle, k} (host-mapped memory read by
-// the host a few cycles later).  When relres <= tol, or is not finite, the run
-// flag flags[0] is cleared and flags[1] = k, flags[2] = 1 (met) or 2 (not
-// finite).  Nothing is written once the flag is clear.
-hipError_t launch_finalize_check(const double *partials, int n, const double *denom, double tol, int k,
-                                 double *hist, int hist_cap, double *last, int *flags, double *slot,
-                                 hipStream_t s);
+// out[0] = sqrt(sum(partials)).  flags (or null): starts a solve, flags[0] = 1
+// (run), flags[1] = flags[2] = 0.  slot (or null): host-mapped {norm, -, -, tag}.
+hipError_t launch_finalize_norm(const double *partials, int n, double *out, hipStream_t s, int *flags = nullptr,
+                                double *slot = nullptr, double tag = 0.0);
+hipError_t launch_finalize_check(const CheckArgs &c, hipStream_t s);
 // flags[0] = 1 (run), flags[1] = flags[2] = 0: the start of a solve
 hipError_t launch_flags_reset(int *flags, hipStream_t s);
 

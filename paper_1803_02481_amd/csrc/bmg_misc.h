@@ -6,6 +6,12 @@ namespace hbmg {
 
 hipError_t launch_zero_ring(double *v, int nx, int ny, int pitch, hipStream_t s);
 hipError_t launch_zero_ring(float *v, int nx, int ny, int pitch, hipStream_t s);
+// the caller's b and u ([ny][nx]) into a level's padded planes, 0 on the boundary
+// ring, with block sums of b^2 (interior) to partials (*nparts of them, at most
+// 4096 + ceil(nx / 256)); and a padded plane back to the caller's array
+hipError_t launch_stage_in(const double *b, const double *u, double *bdst, double *xdst, int nx, int ny, int pitch,
+                           double *partials, int *nparts, hipStream_t s);
+hipError_t launch_stage_out(const double *src, double *u, int nx, int ny, int pitch, hipStream_t s);
 // FP64 level -> FP32 edge-form level (and its interpolation weights)
 hipError_t launch_demote_level(const LevelDev<double> &d, const LevelDev<float> &f, int cnx,
                                int cny, hipStream_t s);

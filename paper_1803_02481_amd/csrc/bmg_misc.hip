@@ -3,6 +3,7 @@
 // mixed-precision iterative refinement, and a batch's copies of the caller's
 // arrays to and from its finest levels.
 #include "bmg_misc.h"
+#include "bmg_check.h"
 
 #include <algorithm>
 
@@ -33,6 +34,68 @@ hipError_t launch_zero_ring(float *v, int nx, int ny, int pitch, hipStream_t s)
 {
     const int n = nx > ny ? nx : ny;
     hipLaunchKernelGGL(k_zero_ring<float>, dim3((n + 255) / 256), dim3(256), 0, s, v, nx, ny, pitch);
+    return hipGetLastError();
+}
+
+// A solve's arrays in and out, 256 columns by a run of rows per workgroup: one
+// launch each way, where the runtime's pitched copies, the ring clearing and
+// the norm's own pass over b took five and its copy out another (4097^2: 230
+// and 92 us, at 2.9 TB/s for the copies).
+__global__ __launch_bounds__(256) void k_stage_in(const double *__restrict__ b, const double *__restrict__ u,
+                                                  double *__restrict__ bdst, double *__restrict__ xdst, int nx,
+                                                  int ny, int pitch, int rows, double *__restrict__ partials)
+{
+    __shared__ double sh[4];
+    const int i = blockIdx.x * 256 + threadIdx.x, j0 = blockIdx.y * rows, j1 = min(j0 + rows, ny);
+    double acc = 0.0;
+    if (i < nx) {
+        const bool ci = i >= 1 && i <= nx - 2;
+#pragma unroll 4
+        for (int j = j0; j < j1; ++j) {
+            const size_t q = (size_t)j * nx + i, p = (size_t)j * pitch + i;
+            const bool in = ci && j >= 1 && j <= ny - 2;
+            const double bv = in ? b[q] : 0.0, uv = in ? u[q] : 0.0;
+            bdst[p] = bv;
+            xdst[p] = uv;
+            acc += bv * bv;
+        }
+    }
+    const double s = sum256(acc, sh);
+    if (threadIdx.x == 0) partials[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+}
+
+__global__ __launch_bounds__(256) void k_stage_out(const double *__restrict__ src, double *__restrict__ u, int nx,
+                                                   int ny, int pitch, int rows)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x, j0 = blockIdx.y * rows, j1 = min(j0 + rows, ny);
+    if (i >= nx) return;
+#pragma unroll 4
+    for (int j = j0; j < j1; ++j) u[(size_t)j * nx + i] = src[(size_t)j * pitch + i];
+}
+
+// rows of a workgroup: one, or what keeps the launch at 4096 workgroups
+static dim3 stage_grid(int nx, int ny, int *rows)
+{
+    const int nxb = (nx + 255) / 256;
+    *rows = (int)(((long long)ny * nxb + 4095) / 4096);
+    return dim3(nxb, (ny + *rows - 1) / *rows);
+}
+
+hipError_t launch_stage_in(const double *b, const double *u, double *bdst, double *xdst, int nx, int ny, int pitch,
+                           double *partials, int *nparts, hipStream_t s)
+{
+    int rows = 1;
+    const dim3 g = stage_grid(nx, ny, &rows);
+    *nparts = (int)(g.x * g.y);
+    hipLaunchKernelGGL(k_stage_in, g, dim3(256), 0, s, b, u, bdst, xdst, nx, ny, pitch, rows, partials);
+    return hipGetLastError();
+}
+
+hipError_t launch_stage_out(const double *src, double *u, int nx, int ny, int pitch, hipStream_t s)
+{
+    int rows = 1;
+    const dim3 g = stage_grid(nx, ny, &rows);
+    hipLaunchKernelGGL(k_stage_out, g, dim3(256), 0, s, src, u, nx, ny, pitch, rows);
     return hipGetLastError();
 }
 

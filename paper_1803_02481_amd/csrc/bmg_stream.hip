@@ -29,7 +29,7 @@
 //
 // The tile index is remapped so that the 8 XCDs (WG i runs on XCD i mod 8)
 // each get a contiguous band of strips and share halo rows in their own L2.
-#include "bmg_internal.h"
+#include "bmg_check.h"
 
 #include <map>
 #include <mutex>
@@ -1462,7 +1462,7 @@ __device__ __forceinline__ void tile_load_above(Row<T> &r, int j, const LaneCtx 
 // Two relaxations from x = 0, residual, r/C and restriction onto the coarse
 // right-hand side (the down leg of a coarse level; stream2_tile's work).
 template <typename T, int NW>
-__global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a)
+__global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArgs chk)
 {
     constexpr int NPT = 9;
     constexpr int HA = 1 + (NPT == 9);
@@ -1472,9 +1472,12 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a)
     constexpr int R = (NW * TILE_RPW - 10) / 2;
     __shared__ T xs[2][NW][64][2];   // x of each wave's first [0] and last [1] row
     __shared__ T rs[NW][64][2];      // residual of each wave's last row
-    if (a.active && *a.active == 0) return;
     const int tile = blockIdx.x;
-    if (tile >= a.ntiles) return;
+    if (tile >= a.ntiles) {   // the extra workgroup
+        cycle_check(chk);
+        return;
+    }
+    if (a.active && *a.active == 0) return;
     const int strip = tile % a.nstrips, blk = tile / a.nstrips;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int t = strip * OWN + lane - HL;
@@ -1725,21 +1728,23 @@ __global__ __launch_bounds__(64 * NW) void k_tile_up(StreamArgs<T> a)
 }
 
 template <typename T>
-hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s)
+hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s, const CheckArgs *chk)
 {
-    if (a.ntiles <= 0) return hipSuccess;
+    if (a.ntiles <= 0) return hipErrorInvalidValue;
+    const int extra = down && chk && chk->partials ? 1 : 0;
+    const CheckArgs c = extra ? *chk : CheckArgs{};
     if (nw == 8) {
-        if (down) hipLaunchKernelGGL((k_tile_down<T, 8>), dim3(a.ntiles), dim3(512), 0, s, a);
+        if (down) hipLaunchKernelGGL((k_tile_down<T, 8>), dim3(a.ntiles + extra), dim3(512), 0, s, a, c);
         else hipLaunchKernelGGL((k_tile_up<T, 8>), dim3(a.ntiles), dim3(512), 0, s, a);
     } else if (nw == 4) {
-        if (down) hipLaunchKernelGGL((k_tile_down<T, 4>), dim3(a.ntiles), dim3(256), 0, s, a);
+        if (down) hipLaunchKernelGGL((k_tile_down<T, 4>), dim3(a.ntiles + extra), dim3(256), 0, s, a, c);
         else hipLaunchKernelGGL((k_tile_up<T, 4>), dim3(a.ntiles), dim3(256), 0, s, a);
     } else {
         return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
-template hipError_t launch_tile<double>(int, int, const StreamArgs<double> &, hipStream_t);
-template hipError_t launch_tile<float>(int, int, const StreamArgs<float> &, hipStream_t);
+template hipError_t launch_tile<double>(int, int, const StreamArgs<double> &, hipStream_t, const CheckArgs *);
+template hipError_t launch_tile<float>(int, int, const StreamArgs<float> &, hipStream_t, const CheckArgs *);
 
 }  // namespace hbmg

@@ -58,3 +58,35 @@ def test_dense_operator_is_the_collapse(shape, prm, precision):
             bound = 5e-6
         assert bool(torch.isfinite(u).all())
         assert float((u - v).abs().max()) <= bound * float(v.abs().max())
+
+
+# the previous cycle's test rides along with the first coarse launch: the dense
+# operator (35^2, 65^2), a tile kernel of four or eight waves (129^2, 513 x 257,
+# 1025^2); 2049 x 257 has it in a launch of its own
+@pytest.mark.parametrize("shape", [(35, 35), (65, 65), (129, 129), (257, 513), (1025, 1025), (257, 2049)])
+@pytest.mark.parametrize("ahead", ["0", "2", "7"])
+def test_stopping_cycle_is_the_capped_one(shape, ahead, monkeypatch):
+    # a solve that meets its tolerance after k cycles returns the bits of one
+    # capped at k, and its history, whatever ran after the test was met
+    monkeypatch.setenv("HIPBMG_AHEAD", ahead)
+    ny, nx = shape
+    planes = HB.fv5_from_cells(g(inputs.cells_lognormal(nx, ny, 1.0, seed=5)))
+    b = g(inputs.load_uniform(nx, ny, seed=6))
+    h = HB.Hierarchy(planes)
+    u, info = h.solve(b, tol=1e-8)
+    again, _ = h.solve(b, tol=1e-8)
+    assert torch.equal(u, again)
+    capped = HB.Hierarchy(planes, max_cycles=info.cycles)
+    v, capped_info = capped.solve(b, tol=1e-30, check=False)
+    assert torch.equal(u, v)
+    assert info.history() == capped_info.history() and info.cycles >= 3
+    # a right-hand side of zeros and one that is not finite, between solves
+    z, zi = h.solve(torch.zeros_like(b), u=torch.ones_like(b), tol=1e-8)
+    assert zi.cycles == 0 and float(z.abs().max()) == 0.0
+    bad = b.clone()
+    bad[1, 1] = float("nan")
+    with pytest.raises(HB.HipBMGError) as e:
+        h.solve(bad, tol=1e-8)
+    assert e.value.status == HB.ENAN
+    after, _ = h.solve(b, tol=1e-8)
+    assert torch.equal(u, after)
