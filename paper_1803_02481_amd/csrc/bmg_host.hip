@@ -2612,6 +2612,7 @@ hipbmg_status hbmg::calibrate_on_kernels(void *stream, ModelParams &p)
 // ---------------------------------------------------------------------------
 struct BLaunch {
     int kind;            // 0 streaming stage, 1 collapse, 2 pipelined finest pass
+    int key;             // stage_key of a streaming stage or the pass
     int npt, variant;
     int wpg;             // streaming stage: strips (waves) per workgroup
     int zc;              // pipelined pass: every problem forms its diagonal
@@ -2620,6 +2621,16 @@ struct BLaunch {
     int nmap;
     int lds_bytes;
 };
+
+// tile shape of a batched launch
+struct TileShape {
+    int cap = 0;   // cap on row-pair steps per tile (0: the per-level rule)
+    int wpg = 1;   // strips (one wave each) per workgroup
+};
+
+// a stage of the batched cycle: down (0) or up (1) leg, depth below the finest
+// level, kernel of the leg
+static int stage_key(int leg, int depth, int k) { return (leg * 64 + depth) * 64 + k; }
 
 struct BPlan {
     std::vector<BLaunch> launches;
@@ -2666,8 +2677,10 @@ struct hipbmg_batch {
     double *d_itol = nullptr, *h_itol = nullptr; // each problem's inner FP32 tolerance of the current step
     int max_nx = 0, max_ny = 0, fine_npt = 5;
     BPlan plan64[2], plan32[2][2];
-    int rb_cap = 0;                           // row blocks of the batched launches (0: per-level rule)
-    int wpg = 1;                              // strips (one wave each) per workgroup of the batched launches
+    // tile shapes: every stage's own once the tuner has run, else (and for the
+    // stages it does not time) one for all
+    TileShape base;
+    std::map<int, TileShape> shapes;          // by stage_key
     // pipelined finest level: every problem's finest post-relaxation and the
     // next cycle's pre-relaxations run as one pass (as for a single problem)
     bool pipe = false;
@@ -2749,18 +2762,27 @@ const LevelDev<double> *dlevels_of<double>(hipbmg_hier *h) { return h->d_lv; }
 template <>
 const LevelDev<float> *dlevels_of<float>(hipbmg_hier *h) { return h->d_lv32; }
 
+// the shape of a stage; the finest level's first pre-relaxations of a pipelined
+// batch, which run once a solve, take the pass's
+static TileShape batch_shape(const hipbmg_batch *B, int leg, int depth, int k)
+{
+    auto it = B->shapes.find(stage_key(leg, depth, k));
+    if (it == B->shapes.end() && depth == 0) it = B->shapes.find(stage_key(1, 0, 0));
+    return it == B->shapes.end() ? B->base : it->second;
+}
+
 // Row blocks of the batched launches: the tiles of all problems share the
 // device, so the single-problem residency rounds do not apply; the longest
 // of 64, 32, ... 4 that gives a level 1024 tiles of its own keeps the
 // prologue overhead low.
 template <typename T>
-static int batch_rb(const hipbmg_batch *B, const LevelDev<T> &A)
+static int batch_rb(const TileShape &sh, const LevelDev<T> &A)
 {
     if (const char *e = std::getenv("HIPBMG_RB")) {
         const int v = std::atoi(e);
         if (v >= 1 && v <= 4096) return v;
     }
-    if (B->rb_cap > 0) return std::max(1, std::min(B->rb_cap, (A.ny - 1) / 2));
+    if (sh.cap > 0) return std::max(1, std::min(sh.cap, (A.ny - 1) / 2));
     return pick_rb(A.nx, A.ny, A.npt);
 }
 
@@ -2805,7 +2827,7 @@ static hipbmg_status build_plan(hipbmg_batch *B, int cur, bool zero_start, BPlan
                 const bool last = k == nk, zx = zero && k == 1, two = last && nk < nu1;
                 const int v = last ? (two ? (zx ? SV_SWEEP2_RQ_ZX : SV_SWEEP2_RQ) : (zx ? SV_SWEEP_RQ_ZX : SV_SWEEP_RQ))
                                    : (zx ? SV_SWEEP_ZX : SV_SWEEP);
-                StreamArgs<T> a = base_args(A, batch_rb(B, A));
+                StreamArgs<T> a = base_args(A, batch_rb(batch_shape(B, 0, d, k - 1), A));
                 a.x_in = A.x[xb];
                 a.x_out = A.x[1 - xb];
                 if (last) {
@@ -2840,7 +2862,7 @@ static hipbmg_status build_plan(hipbmg_batch *B, int cur, bool zero_start, BPlan
                 // this cycle's interpolation, relaxation and norm, and the
                 // next cycle's pre-relaxations and restriction, in one pass
                 T *x3[3] = {A.x[0], A.x[1], x3_of<T>(h)};
-                StreamArgs<T> a = base_args(A, batch_rb(B, A));
+                StreamArgs<T> a = base_args(A, batch_rb(batch_shape(B, 1, 0, 0), A));
                 a.x_in = x3[pipe_i];
                 a.x_out = x3[(pipe_i + 1) % 3];
                 a.x_out2 = x3[(pipe_i + 2) % 3];
@@ -2867,7 +2889,7 @@ static hipbmg_status build_plan(hipbmg_batch *B, int cur, bool zero_start, BPlan
             for (int k = 1; k <= nu2; ++k) {
                 const bool first = k == 1, last = k == nu2;
                 const int v = first ? (fine && last ? SV_INTERP_NORM : SV_INTERP) : (fine && last ? SV_SWEEP_NORM : SV_SWEEP);
-                StreamArgs<T> a = base_args(A, batch_rb(B, A));
+                StreamArgs<T> a = base_args(A, batch_rb(batch_shape(B, 1, d, k - 1), A));
                 a.x_in = A.x[xb];
                 a.x_out = A.x[1 - xb];
                 if (first) {
@@ -2928,7 +2950,7 @@ static hipbmg_status build_plan(hipbmg_batch *B, int cur, bool zero_start, BPlan
         std::memcpy(tab.data() + o, src, bytes);
         return o;
     };
-    auto add_stage = [&](std::vector<Rec> &recs) -> hipbmg_status {
+    auto add_stage = [&](std::vector<Rec> &recs, int leg, int depth, int k) -> hipbmg_status {
         if (recs.empty()) return HIPBMG_OK;
         std::vector<StreamArgs<T>> args(n);
         std::vector<int2> map;
@@ -2942,7 +2964,8 @@ static hipbmg_status build_plan(hipbmg_batch *B, int cur, bool zero_start, BPlan
         bl.kind = recs[0].variant == SV_FUSED3 ? 2 : 0;
         bl.npt = recs[0].npt;
         bl.variant = recs[0].variant;
-        bl.wpg = B->wpg;
+        bl.key = stage_key(leg, depth, k);
+        bl.wpg = batch_shape(B, leg, depth, k).wpg;
         bl.zc = B->zc[PrecIdx<T>::v];
         const size_t oa = put(args.data(), n * sizeof(StreamArgs<T>));
         const size_t om = put(map.data(), map.size() * sizeof(int2));
@@ -2952,7 +2975,7 @@ static hipbmg_status build_plan(hipbmg_batch *B, int cur, bool zero_start, BPlan
         return HIPBMG_OK;
     };
     for (size_t d = 0; d < down.size(); ++d)
-        for (auto &kk : down[d]) STCHK(add_stage(kk));
+        for (size_t k = 0; k < down[d].size(); ++k) STCHK(add_stage(down[d][k], 0, (int)d, (int)k));
     {
         BLaunch bl{};
         bl.kind = 1;
@@ -2961,7 +2984,7 @@ static hipbmg_status build_plan(hipbmg_batch *B, int cur, bool zero_start, BPlan
         plan.launches.push_back(bl);
     }
     for (int d = (int)up.size() - 1; d >= 0; --d)
-        for (auto &kk : up[d]) STCHK(add_stage(kk));
+        for (size_t k = 0; k < up[d].size(); ++k) STCHK(add_stage(up[d][k], 1, d, (int)k));
     char *dt = nullptr;
     STCHK(balloc_to(plan.allocs, &dt, tab.size(), s));
     HIPCHK(hipMemcpyAsync(dt, tab.data(), tab.size(), hipMemcpyHostToDevice, s));
@@ -2977,26 +3000,27 @@ static hipbmg_status build_plan(hipbmg_batch *B, int cur, bool zero_start, BPlan
 }
 
 template <typename T>
-static hipError_t run_plan_launches(hipbmg_batch *B, BPlan &plan, const int *active, hipStream_t s)
+static hipError_t run_launch(hipbmg_batch *B, const BLaunch &bl, const int *active, hipStream_t s)
 {
-    hipError_t e = hipSuccess;
-    for (BLaunch &bl : plan.launches) {
-        if (bl.kind == 0)
-            e = launch_stream_batched<T>(bl.npt, bl.variant, static_cast<const StreamArgs<T> *>(bl.d_args),
-                                         bl.d_map, bl.nmap, active, bl.wpg, s);
-        else if (bl.kind == 2)
-            e = launch_stream3_batched<T>(bl.variant, bl.zc, static_cast<const StreamArgs<T> *>(bl.d_args),
-                                          bl.d_map, bl.nmap, active, bl.wpg, s);
-        else
-            e = launch_collapse_batched<T>(static_cast<const CollapseArgs<T> *>(bl.d_args), B->n,
-                                           bl.lds_bytes, active, s);
-        if (e != hipSuccess) return e;
-    }
-    return e;
+    if (bl.kind == 0)
+        return launch_stream_batched<T>(bl.npt, bl.variant, static_cast<const StreamArgs<T> *>(bl.d_args), bl.d_map,
+                                        bl.nmap, active, bl.wpg, s);
+    if (bl.kind == 2)
+        return launch_stream3_batched<T>(bl.variant, bl.zc, static_cast<const StreamArgs<T> *>(bl.d_args), bl.d_map,
+                                         bl.nmap, active, bl.wpg, s);
+    return launch_collapse_batched<T>(static_cast<const CollapseArgs<T> *>(bl.d_args), B->n, bl.lds_bytes, active, s);
 }
 
-// one V-cycle of all active problems plus their residual norms and
-// retirement; replayed from a captured graph when use_graph is set
+template <typename T>
+static hipError_t run_plan_launches(hipbmg_batch *B, BPlan &plan, const int *active, hipStream_t s)
+{
+    for (const BLaunch &bl : plan.launches) {
+        const hipError_t e = run_launch<T>(B, bl, active, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <typename T>
 static hipbmg_status batch_cycle(hipbmg_batch *B, BPlan &plan, int *active, const double *denom, double *out,
                                  const double *tol_dev, hipStream_t s, int tol_stride = 0)
@@ -3084,40 +3108,59 @@ static hipbmg_status build_plans(hipbmg_batch *B, hipStream_t s)
     return st;
 }
 
+// Time (us, best of three) of every launch of one V-cycle of the batch, every
+// problem active; ev holds one event more than the plan has launches.
 template <typename T>
-static double time_plan_us(hipbmg_batch *B, BPlan &plan, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+static hipbmg_status time_stages(hipbmg_batch *B, BPlan &plan, hipStream_t s, std::vector<hipEvent_t> &ev,
+                                 std::vector<double> &us)
 {
-    (void)run_plan_launches<T>(B, plan, B->d_active, s);   // warm-up
-    double best = 1e30;
-    for (int r = 0; r < 3; ++r) {
-        (void)hipEventRecord(e0, s);
-        (void)run_plan_launches<T>(B, plan, B->d_active, s);
-        (void)hipEventRecord(e1, s);
-        (void)hipEventSynchronize(e1);
-        float ms = 0.f;
-        (void)hipEventElapsedTime(&ms, e0, e1);
-        best = std::min(best, 1e3 * (double)ms);
+    const size_t n = plan.launches.size();
+    while (ev.size() < n + 1) {
+        hipEvent_t e = nullptr;
+        HIPCHK(hipEventCreate(&e));
+        ev.push_back(e);
     }
-    return best;
+    us.assign(n, 1e30);
+    HIPCHK(run_plan_launches<T>(B, plan, B->d_active, s));   // warm-up
+    for (int r = 0; r < 3; ++r) {
+        HIPCHK(hipEventRecord(ev[0], s));
+        for (size_t k = 0; k < n; ++k) {
+            HIPCHK(run_launch<T>(B, plan.launches[k], B->d_active, s));
+            HIPCHK(hipEventRecord(ev[k + 1], s));
+        }
+        HIPCHK(hipEventSynchronize(ev[n]));
+        for (size_t k = 0; k < n; ++k) {
+            float ms = 0.f;
+            HIPCHK(hipEventElapsedTime(&ms, ev[k], ev[k + 1]));
+            us[k] = std::min(us[k], 1e3 * (double)ms);
+        }
+    }
+    return HIPBMG_OK;
 }
 
-// Autotuner of the batched tile shape.  A workgroup's tile is W neighbouring
+// Autotuner of the batched tile shapes.  A workgroup's tile is W neighbouring
 // strips of column pairs (one wave each, 54-62 owned pairs per strip by the
 // kernel's halo) times a block of rb row-pair steps; in a batched launch the
 // tiles of every problem share the device, so the best shape is not the
 // single-problem one.  Each candidate (W in {1, 2, 4}) x (cap on rb in
-// {1, ..., 64}, or the single-problem rule) is built into plans and one
-// steady-state V-cycle of the batch is timed (every problem active, on the
-// zero data of a fresh hierarchy); the fastest is kept.  The choice is
-// remembered per batch signature (sizes, stencil, precision, cycle) for the
-// life of the process.  HIPBMG_BATCH_TUNE=0 keeps one strip per workgroup
-// and the single-problem rule; HIPBMG_BATCH_WPG=1, 2 or 4 fixes W.
+// {2, ..., 128}, or the single-problem rule) is built into plans and the launches
+// of one steady-state V-cycle of the batch are timed one by one (every problem
+// active, on the zero data of a fresh hierarchy); every stage keeps its own
+// fastest.  They differ: the finest FP64 pass holds one wave per SIMD and
+// rebuilds four row-pair steps below a tile, so it wants few long tiles, the
+// coarse levels short ones.  On 64 problems of 1025^2 in FP64 one shape for all
+// kept a cap of 16 (finest pass 1250 us a cycle) where the pass alone takes
+// 1036 us at 128: forward and adjoint solve 57.8 -> 52.5 ms; 256 problems of
+// 128^2..512^2 in mixed precision 32.9 -> 30.9 ms.  The choice is remembered per batch signature (sizes, stencil,
+// precision, cycle) for the life of the process.  HIPBMG_BATCH_TUNE=0 keeps one
+// strip per workgroup and the single-problem rule; HIPBMG_BATCH_WPG=1, 2 or 4
+// fixes W.
 static hipbmg_status tune_batch(hipbmg_batch *B, hipStream_t s)
 {
     // shared by every thread that sets up batches: guarded; the key holds
     // every parameter that shapes the plans
     static std::mutex cache_mu;
-    static std::map<std::string, std::pair<int, int>> cache;
+    static std::map<std::string, std::map<int, TileShape>> cache;
     std::vector<std::pair<int, int>> sz;
     for (hipbmg_hier *h : B->hs) sz.push_back({h->nx, h->ny});
     std::sort(sz.begin(), sz.end());
@@ -3134,71 +3177,68 @@ static hipbmg_status tune_batch(hipbmg_batch *B, hipStream_t s)
         if (v == 1 || v == 2 || v == 4) wfix = v;
     }
     key += "w" + std::to_string(wfix) + "p" + std::to_string(B->pipe ? 1 : 0);
+    B->shapes.clear();
     if (!tune) {
-        B->rb_cap = 0;
-        B->wpg = wfix ? wfix : 1;
+        B->base = TileShape{0, wfix ? wfix : 1};
         return build_plans(B, s);
     }
+    bool hit = false;
     {
         std::lock_guard<std::mutex> lk(cache_mu);
         auto it = cache.find(key);
         if (it != cache.end()) {
-            B->rb_cap = it->second.first;
-            B->wpg = it->second.second;
-        } else {
-            B->rb_cap = -1;
+            B->shapes = it->second;
+            B->base = TileShape{0, wfix ? wfix : 1};
+            hit = true;
         }
     }
-    if (B->rb_cap >= 0) return build_plans(B, s);
+    if (hit) return build_plans(B, s);
     std::vector<int> ones(B->n, 1);
     HIPCHK(hipMemcpyAsync(B->d_active, ones.data(), B->n * sizeof(int), hipMemcpyHostToDevice, s));
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    HIPCHK(hipEventCreate(&e0));
-    if (hipEventCreate(&e1) != hipSuccess) {
-        (void)hipEventDestroy(e0);
-        return fail(HIPBMG_EHIP, "event creation failed");
-    }
     const bool mixed = B->prm.precision == HIPBMG_MIXED;
-    int best = 0, best_w = 1;
-    double tbest = 1e30;
+    std::vector<hipEvent_t> ev;
+    std::vector<double> us;
+    std::map<int, std::pair<double, TileShape>> best;
     hipbmg_status st = HIPBMG_OK;
     for (int w : {1, 2, 4}) {
         if (wfix && w != wfix) continue;
-        B->wpg = w;
-        for (int cap : {0, 1, 2, 4, 8, 16, 32, 64}) {
-            B->rb_cap = cap;
+        for (int cap : {0, 2, 4, 8, 16, 32, 64, 128}) {
+            B->base = TileShape{cap, w};
             if ((st = build_plans(B, s)) != HIPBMG_OK) break;
-            double us;
-            if (B->pipe) {
-                us = mixed ? time_plan_us<float>(B, B->pipe32[0], s, e0, e1)
-                           : time_plan_us<double>(B, B->pipe64[0], s, e0, e1);
-            } else if (mixed) {
-                const int c1 = B->plan32[1][0].end_cur;
-                us = time_plan_us<float>(B, B->plan32[0][c1], s, e0, e1);
-            } else {
-                us = time_plan_us<double>(B, B->plan64[0], s, e0, e1);
+            BPlan *plan;
+            if (B->pipe) plan = mixed ? &B->pipe32[0] : &B->pipe64[0];
+            else plan = mixed ? &B->plan32[0][B->plan32[1][0].end_cur] : &B->plan64[0];
+            if ((st = mixed ? time_stages<float>(B, *plan, s, ev, us) : time_stages<double>(B, *plan, s, ev, us)) !=
+                HIPBMG_OK)
+                break;
+            double total = 0.0;
+            for (size_t k = 0; k < us.size(); ++k) {
+                total += us[k];
+                if (plan->launches[k].kind == 1) continue;
+                auto it = best.find(plan->launches[k].key);
+                if (it == best.end() || us[k] < it->second.first)
+                    best[plan->launches[k].key] = {us[k], B->base};
             }
             if (std::getenv("HIPBMG_VERBOSE"))
                 std::fprintf(stderr, "hipbmg: batch of %d, %d strips per workgroup, row-block cap %d: %.1f us per cycle\n",
-                             B->n, w, cap, us);
-            if (us < tbest) {
-                tbest = us;
-                best = cap;
-                best_w = w;
-            }
+                             B->n, w, cap, total);
         }
         if (st != HIPBMG_OK) break;
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
+    for (hipEvent_t e : ev) (void)hipEventDestroy(e);
     if (st != HIPBMG_OK) return st;
     HIPCHK(hipMemsetAsync(B->d_active, 0, B->n * sizeof(int), s));
+    for (auto &q : best) {
+        B->shapes[q.first] = q.second.second;
+        if (std::getenv("HIPBMG_VERBOSE"))
+            std::fprintf(stderr, "hipbmg: stage %d: %d strips, cap %d, %.1f us\n", q.first, q.second.second.wpg,
+                         q.second.second.cap, q.second.first);
+    }
+    B->base = TileShape{0, wfix ? wfix : 1};
     {
         std::lock_guard<std::mutex> lk(cache_mu);
-        cache[key] = {best, best_w};
+        cache[key] = B->shapes;
     }
-    B->rb_cap = best;
-    B->wpg = best_w;
     return build_plans(B, s);
 }
 
@@ -3420,9 +3460,10 @@ extern "C" hipbmg_status hipbmg_batch_tile_shape(hipbmg_batch_handle B, int prob
     if (problem < 0 || problem >= B->n) return fail(HIPBMG_EINVAL, "problem %d out of range [0, %d)", problem, B->n);
     const hipbmg_hier *h = B->hs[problem];
     if (level < 0 || level >= h->L) return fail(HIPBMG_EINVAL, "level %d out of range [0, %d)", level, h->L);
-    if (strips_per_group) *strips_per_group = B->wpg;
-    if (rb_cap) *rb_cap = B->rb_cap;
-    if (rb) *rb = level > h->lstar ? batch_rb<double>(B, h->lv[level]) : 0;
+    const TileShape sh = batch_shape(B, 1, level > h->lstar ? h->L - 1 - level : 0, 0);
+    if (strips_per_group) *strips_per_group = sh.wpg;
+    if (rb_cap) *rb_cap = sh.cap;
+    if (rb) *rb = level > h->lstar ? batch_rb<double>(sh, h->lv[level]) : 0;
     return HIPBMG_OK;
 }
 
@@ -3470,7 +3511,7 @@ static hipbmg_status batch_rebuild(hipbmg_batch *B, const BPlan &plan, const std
         if (kstop[p] <= 0) continue;
         any = true;
         const int i = (1 + 2 * (kstop[p] - 1)) % 3;
-        StreamArgs<T> a = base_args(F, batch_rb(B, F));
+        StreamArgs<T> a = base_args(F, batch_rb(batch_shape(B, 1, 0, 0), F));
         a.x_in = x3[i];
         a.x_out = x3[(i + 1) % 3];
         a.xc = Cl.x[(PrecIdx<T>::v ? B->cc32 : B->cc64)[p]];
@@ -3522,8 +3563,11 @@ extern "C" hipbmg_status hipbmg_solve_batched(hipbmg_batch_handle B, const doubl
         if (infos) {
             memset(&infos[p], 0, sizeof(hipbmg_info));
             fill_info_common(h, &infos[p]);
-            for (int l = 0; l < h->L; ++l) infos[p].rb_down[l] = infos[p].rb_up[l] = batch_rb(B, h->lv[l]);
-            infos[p].rb_pipelined = B->pipe ? batch_rb(B, F) : 0;
+            for (int l = 0; l < h->L; ++l) {
+                infos[p].rb_down[l] = batch_rb(batch_shape(B, 0, h->L - 1 - l, 0), h->lv[l]);
+                infos[p].rb_up[l] = batch_rb(batch_shape(B, 1, h->L - 1 - l, 0), h->lv[l]);
+            }
+            infos[p].rb_pipelined = B->pipe ? batch_rb(batch_shape(B, 1, 0, 0), F) : 0;
         }
     }
     STCHK(batch_bnorm(B, s));
