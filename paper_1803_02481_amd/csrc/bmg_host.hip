@@ -298,6 +298,7 @@ struct hipbmg_hier {
     int no_fuse2 = 0;           // HIPBMG_NO_FUSE2=1: run the two pre-relaxations as two passes
     int fused3 = 0;             // finest post-relaxation fused with the next cycle's pre-relaxations
     int rb3 = 0;                // row-block steps of the pipelined finest kernel
+    bool pass_tile = false;     // the pass runs as tiles
     int zexc[2] = {0, 0};       // the pipelined pass forms the finest diagonal ([0] FP64, [1] FP32)
     int wform = 0;              // the FP64 pipelined pass forms the interpolation weights
     double *x3_64 = nullptr;    // third iterate buffer of the pipelined finest level
@@ -622,6 +623,15 @@ static int tile_waves(const hipbmg_hier *h, int nx, int ny, int npt, bool fine, 
     int nst, nbl, nt;
     tile_geometry(nx, ny, npt, 8, 1, &nst, &nbl, &nt);
     return nt >= 64 ? 8 : 4;
+}
+
+// The pipelined finest pass of a small grid runs as tiles: up to 3 * 2^17
+// vertices in FP64 and 2^20 in FP32 (HIPBMG_PASS_TILE_MAX), where the streaming pass's
+// time is its chain of row-pair steps and not its bytes (figures at
+// k_tile_pass; the tiles load half their rows twice).
+static bool pass_tiles(int nx, int ny, bool fp32)
+{
+    return (long long)nx * ny <= tile_limit("HIPBMG_PASS_TILE_MAX", fp32 ? 1LL << 20 : 3LL << 17);
 }
 
 // Levels whose up leg forms r/C from the rows it loads instead of reading the
@@ -1002,6 +1012,11 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
         int nst, nbl, nt, g;
         stream_geometry(sx[L - 1], sy[L - 1], npt, SV_FUSED3, h->rb3, &nst, &nbl, &nt, &g);
         np = std::max(np, (size_t)nt);
+        h->pass_tile = !std::getenv("HIPBMG_RB_FUSED3") && pass_tiles(nx, ny, prm.precision == HIPBMG_MIXED);
+        if (h->pass_tile) {
+            pass_tile_geometry(nx, ny, &nst, &nbl, &nt);
+            np = std::max(np, (size_t)nt);
+        }
     }
     np = std::max(np, (size_t)((nx + 255) / 256) * ny);   // refinement residual partials
     h->n_partials = np;
@@ -1603,7 +1618,13 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
             const int vf = last_pass && k == max_cycles ? SV_FUSED3_PN : SV_FUSED3;
             if (vf == SV_FUSED3_PN) stored_last = k;
             const int pk = prof_begin(h, vf, PrecIdx<T>::v, L - 1, 1, true, s);
-            HIPCHK(run_stream(F, vf, a, s, &np));
+            if (h->pass_tile) {
+                int nst, nbl;
+                pass_tile_geometry(F.nx, F.ny, &nst, &nbl, &np);
+                HIPCHK(launch_tile_pass<T>(vf, a, s));
+            } else {
+                HIPCHK(run_stream(F, vf, a, s, &np));
+            }
             prof_end(h, pk, s);
             res_after[k] = xb[(i + 1) % 3];
             in_i[k] = i;
@@ -1677,7 +1698,7 @@ static void fill_info_common(hipbmg_hier *h, hipbmg_info *info)
         info->rb_down[l] = l < h->L ? h->rb[l] : 0;
         info->rb_up[l] = l < h->L ? h->rb_up[l] : 0;
     }
-    info->rb_pipelined = h->fused3 ? h->rb3 : 0;
+    info->rb_pipelined = h->fused3 ? (h->pass_tile ? pass_tile_steps() : h->rb3) : 0;
     info->setup_ms = h->setup_ms;
     info->cluster_stages = h->cl_nstage;
     for (int k = 0; k < 4; ++k) {

@@ -168,6 +168,14 @@ void tile_geometry(int nx, int ny, int npt, int nw, int down, int *nstrips, int 
 template <typename T>
 hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s, const CheckArgs *chk = nullptr);
 
+// The pipelined finest pass (SV_FUSED3, SV_FUSED3_PN) of a small grid as tiles: a workgroup
+// owns a strip by pass_tile_steps() row-pair steps and writes one norm partial.
+// a.wform is ignored (the stored weights are read, the same values).
+int pass_tile_steps();
+void pass_tile_geometry(int nx, int ny, int *nstrips, int *nblocks, int *ntiles);
+template <typename T>
+hipError_t launch_tile_pass(int variant, StreamArgs<T> a, hipStream_t s);
+
 // 1 if every interior vertex of a 5-point level has C exactly equal to
 // ((W_p + W_e) + S_p) + S_n (FP64), or an FP32 edge-form excess of exactly 0;
 // the result goes to *flag (device int, written by the check)

@@ -1416,15 +1416,15 @@ void tile_geometry(int nx, int ny, int npt, int nw, int down, int *nstrips, int 
     *ntiles = *nstrips * *nblocks;
 }
 
-template <typename T>
+template <typename T, int NPT = 9>
 __device__ __forceinline__ void tile_relax_row(const Row<T> &bl, Row<T> &cu, const Row<T> &ab, int j,
                                                const LaneCtx &L)
 {
     const bool rj = j >= 1 && j <= L.ny - 2;
     T d;
-    T r = res_even<T, 9>(bl, cu, ab, d);
+    T r = res_even<T, NPT>(bl, cu, ab, d);
     if (rj && L.ie) cu.x0 += r / d;
-    r = res_odd<T, 9>(bl, cu, ab, d);
+    r = res_odd<T, NPT>(bl, cu, ab, d);
     if (rj && L.io) cu.x1 += r / d;
 }
 
@@ -1726,6 +1726,302 @@ __global__ __launch_bounds__(64 * NW) void k_tile_up(StreamArgs<T> a)
         }
     }
 }
+
+// The pipelined finest pass (SV_FUSED3, stream3_tile's work) of a small 5-point
+// grid in the same manner: interpolate and correct with r/C formed from the
+// loaded iterate, one relaxation and its residual norm (P), the next cycle's
+// two relaxations (A, B), residual and restriction.  A 5-point even row depends
+// only on odd rows and on itself, an odd row only on even rows and on itself,
+// so each of the three relaxations is again two phases.  A tile owning
+// row-pair steps [s0, s1) loads rows 2 s0 - 8 .. 2 s1 + 7: B's residual of row
+// 2 s0 - 1 reaches down to raw row 2 s0 - 8 and B's row 2 s1 up to raw row
+// 2 s1 + 6.  Half the rows of an 8-wave tile are such halo, which a grid that
+// cannot fill the device has the lanes for.  Every expression is that of the
+// streaming pass: iterates and restricted residuals are the same bits, only the
+// norm's partial sums are in another order.
+//
+// Bound by latency: load, eight phases of two dependent updates (a division
+// each) and barriers; tiles of 12 and 16 waves own more of their rows but
+// spill.  us a cycle of a solve, streaming pass -> this one:
+//         65^2          257^2         513^2         769 x 641     1025^2
+//   FP64  20.6 -> 17.7  43.2 -> 41.5  60.5 -> 57.5  77.0 -> 76.7  91.7 -> 101
+//   FP32  30.8 -> 27.6  48.0 -> 44.7  64.1 -> 59.3  78.9 -> 74.5  84.7 -> 83.3
+constexpr int PASS_NW = 8;
+
+// PN: P and its norm alone, storing the iterate (SV_FUSED3_PN), in the same
+// tiles, so that a capped solve's last norm is summed as the others are.
+template <typename T, bool ZC, bool PN>
+__global__ __launch_bounds__(64 * PASS_NW) void k_tile_pass(StreamArgs<T> a)
+{
+    constexpr int NPT = 5, NW = PASS_NW;
+    constexpr int HL = 5, HR = 5, OWN = 64 - HL - HR;
+    constexpr int R = (NW * TILE_RPW - 16) / 2;
+    // x of each wave's first [0] and last [1] row after the sweeps, alternating
+    __shared__ T xs[2][2][NW][64][2];
+    __shared__ T rs[NW][64][2];      // residual of each wave's last row
+    __shared__ double accs[NW];
+    if (a.active && *a.active == 0) return;
+    const int tile = blockIdx.x;
+    const int strip = tile % a.nstrips, blk = tile / a.nstrips;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int t = strip * OWN + lane - HL;
+    const int e = 2 * t, o = 2 * t + 1;
+    const int nx = a.nx, ny = a.ny, pitch = a.pitch;
+    const bool colv = t >= 0 && e < nx;
+    const bool own = lane >= HL && lane < 64 - HR && colv;
+    const bool ie = e >= 1 && e <= nx - 2;
+    const bool io = o >= 1 && o <= nx - 2;
+    const bool cv = t >= 0 && t < a.cnx;
+    const LaneCtx L{t, e, o, pitch, ny, own, ie, io, cv};
+    const int nsteps = (ny - 1) / 2;
+    const int s0 = blk * R, s1 = min(s0 + R, nsteps);
+    const int jw0 = 2 * s0 - 8 + TILE_RPW * w;   // even
+
+    // all loads first: rows, the raw iterate below, the raw iterate and S above
+    Row<T> rw[TILE_RPW], dn{}, up{};
+#pragma unroll
+    for (int k = 0; k < TILE_RPW; ++k) {
+        Row<T> &r = rw[k];
+        const int j = jw0 + k;
+        r = Row<T>{};
+        if (colv && j >= 0 && j < ny) {
+            const size_t off = (size_t)j * pitch + e;
+            ld2(a.x_in + off, r.x0, r.x1);
+            ld2(a.b + off, r.b0, r.b1);
+            if (!ZC) ld2(a.C + off, r.C0, r.C1);
+            ld2(a.W + off, r.W0, r.W1);
+            ld2(a.S + off, r.S0, r.S1);
+        }
+        if (cv && j >= 1 && j <= ny - 2) {
+            const size_t co = (size_t)(j >> 1) * a.cpitch + t;
+            const T *wt = a.wt;
+            const long long cp = a.cplane;
+            r.ca = a.xc[co];
+            if (j & 1) {
+                r.cu = a.xc[co + a.cpitch];
+                r.w0 = wt[WYB * cp + co];
+                r.w1 = wt[WYT * cp + co];
+                r.w2 = wt[WCSW * cp + co];
+                r.w3 = wt[WCSE * cp + co];
+                r.w4 = wt[WCNW * cp + co];
+                r.w5 = wt[WCNE * cp + co];
+            } else {
+                r.w0 = wt[WXL * cp + co];
+                r.w1 = wt[WXR * cp + co];
+            }
+        }
+    }
+    if (colv && jw0 - 1 >= 0 && jw0 - 1 < ny) ld2(a.x_in + (size_t)(jw0 - 1) * pitch + e, dn.x0, dn.x1);
+    if (colv && jw0 + TILE_RPW >= 0 && jw0 + TILE_RPW < ny) {
+        const size_t off = (size_t)(jw0 + TILE_RPW) * pitch + e;
+        ld2(a.x_in + off, up.x0, up.x1);
+        ld2(a.S + off, up.S0, up.S1);
+    }
+    // restriction weights of the odd row below this wave's rows
+    T ytp0 = T(0), cnwp0 = T(0), cnep0 = T(0);
+    if (cv && jw0 - 1 >= 1 && jw0 - 1 <= ny - 2) {
+        const size_t co = (size_t)((jw0 - 1) >> 1) * a.cpitch + t;
+        ytp0 = a.wt[WYT * a.cplane + co];
+        cnwp0 = a.wt[WCNW * a.cplane + co];
+        cnep0 = a.wt[WCNE * a.cplane + co];
+    }
+    if (ZC && !IsEdge<T>::value) {
+#pragma unroll
+        for (int k = 0; k < TILE_RPW; ++k) {
+            Row<T> &r = rw[k];
+            const Row<T> &ab = k == TILE_RPW - 1 ? up : rw[k + 1];
+            const T we = fromR(r.W0);
+            r.C0 = r.W0 + r.W1 + r.S0 + ab.S0;
+            r.C1 = r.W1 + we + r.S1 + ab.S1;
+        }
+    }
+    // x += P x_c, + r/C of the raw iterate at fine-only vertices
+    {
+        const bool rc = a.rescorr != 0;
+        T q0[TILE_RPW], q1[TILE_RPW];
+#pragma unroll
+        for (int k = 0; k < TILE_RPW; ++k) {
+            const Row<T> &bl = k == 0 ? dn : rw[k - 1];
+            const Row<T> &ab = k == TILE_RPW - 1 ? up : rw[k + 1];
+            T d;
+            T r = res_odd<T, NPT>(bl, rw[k], ab, d);
+            q1[k] = rc ? r / d : T(0);
+            q0[k] = T(0);
+            if (k & 1) {
+                r = res_even<T, NPT>(bl, rw[k], ab, d);
+                q0[k] = rc ? r / d : T(0);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < TILE_RPW; ++k) {
+            Row<T> &r = rw[k];
+            const int j = jw0 + k;
+            const bool rin = j >= 1 && j <= ny - 2;
+            const T xb = fromR(r.ca);
+            if ((k & 1) == 0) {
+                if (rin && ie) r.x0 += r.ca;
+                if (rin && io) r.x1 += r.w0 * r.ca + r.w1 * xb + q1[k];
+            } else {
+                const T xd = fromR(r.cu);
+                if (rin && ie) r.x0 += r.w0 * r.ca + r.w1 * r.cu + q0[k];
+                if (rin && io) r.x1 += r.w2 * r.ca + r.w3 * xb + r.w4 * r.cu + r.w5 * xd + q1[k];
+            }
+        }
+    }
+    auto below = [&](int p) {
+        Row<T> r{};
+        if (w > 0) {
+            r.x0 = xs[p][1][w - 1][lane][0];
+            r.x1 = xs[p][1][w - 1][lane][1];
+        }
+        return r;
+    };
+    auto above = [&](int p) {
+        Row<T> r = up;
+        if (w < NW - 1) {
+            r.x0 = xs[p][0][w + 1][lane][0];
+            r.x1 = xs[p][0][w + 1][lane][1];
+        }
+        return r;
+    };
+    xs[1][1][w][lane][0] = rw[TILE_RPW - 1].x0;
+    xs[1][1][w][lane][1] = rw[TILE_RPW - 1].x1;
+    __syncthreads();
+    // the first and last wave hold only rows that A and B no longer need
+    const bool inner = w > 0 && w < NW - 1;
+    double acc = 0.0;
+#pragma unroll
+    for (int sweep = 0; sweep < (PN ? 2 : 3); ++sweep) {
+        const bool live = sweep == 0 || inner;
+        const int p = sweep & 1;
+        if (sweep == 1) {
+            // norm of the residual after P
+            if (inner) {
+                const Row<T> b0 = below(0), a3 = above(0);
+#pragma unroll
+                for (int k = 0; k < TILE_RPW; ++k) {
+                    const Row<T> &bl = k == 0 ? b0 : rw[k - 1];
+                    const Row<T> &ab = k == TILE_RPW - 1 ? a3 : rw[k + 1];
+                    T d;
+                    const T re = res_even<T, NPT>(bl, rw[k], ab, d);
+                    const T ro = res_odd<T, NPT>(bl, rw[k], ab, d);
+                    const int j = jw0 + k;
+                    const bool rr = own && j >= 2 * s0 && j <= 2 * s1 - 1 && j >= 1 && j <= ny - 2;
+                    if (rr && ie) acc += (double)re * re;
+                    if (rr && io) acc += (double)ro * ro;
+                }
+                for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+            }
+            if (lane == 0) accs[w] = acc;
+            if (PN) {
+#pragma unroll
+                for (int k = 0; k < TILE_RPW; ++k) {
+                    const int j = jw0 + k;
+                    if (own && j >= 2 * s0 + 1 && j <= 2 * s1 && j >= 1 && j <= ny - 2)
+                        st2(a.x_out + (size_t)j * pitch + e, rw[k].x0, rw[k].x1);
+                }
+                __syncthreads();
+                break;
+            }
+        }
+        if (live) {   // even rows: colours 0 and 1
+            const Row<T> b0 = below(1 - p);
+            tile_relax_row<T, NPT>(b0, rw[0], rw[1], jw0, L);
+            tile_relax_row<T, NPT>(rw[1], rw[2], rw[3], jw0 + 2, L);
+            xs[p][0][w][lane][0] = rw[0].x0;
+            xs[p][0][w][lane][1] = rw[0].x1;
+        }
+        __syncthreads();
+        if (live) {   // odd rows: colours 2 and 3
+            tile_relax_row<T, NPT>(rw[0], rw[1], rw[2], jw0 + 1, L);
+            const Row<T> a3 = above(p);
+            tile_relax_row<T, NPT>(rw[2], rw[3], a3, jw0 + 3, L);
+            xs[p][1][w][lane][0] = rw[3].x0;
+            xs[p][1][w][lane][1] = rw[3].x1;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) s += accs[k];
+        a.partials[tile] = s;
+    }
+    if (PN) return;
+    // residuals of the final rows, zero outside the interior
+    T res_e[TILE_RPW], res_o[TILE_RPW];
+    if (inner) {
+        const Row<T> b0 = below(0), a3 = above(0);
+#pragma unroll
+        for (int k = 0; k < TILE_RPW; ++k) {
+            const Row<T> &bl = k == 0 ? b0 : rw[k - 1];
+            const Row<T> &ab = k == TILE_RPW - 1 ? a3 : rw[k + 1];
+            T d;
+            res_e[k] = res_even<T, NPT>(bl, rw[k], ab, d);
+            res_o[k] = res_odd<T, NPT>(bl, rw[k], ab, d);
+            const int j = jw0 + k;
+            const bool rr = j >= 1 && j <= ny - 2;
+            if (!(rr && ie)) res_e[k] = T(0);
+            if (!(rr && io)) res_o[k] = T(0);
+            if (own && j >= 2 * s0 + 1 && j <= 2 * s1 && rr)
+                st2(a.x_out2 + (size_t)j * pitch + e, rw[k].x0, rw[k].x1);
+        }
+        rs[w][lane][0] = res_e[TILE_RPW - 1];
+        rs[w][lane][1] = res_o[TILE_RPW - 1];
+    }
+    __syncthreads();
+    if (w < 2 || w > NW - 3) return;   // rows below 2 s0 or from 2 s1 on restrict nothing
+    T r3e = rs[w - 1][lane][0], r3o = rs[w - 1][lane][1];
+    T ytp = ytp0, cnwp = cnwp0, cnep = cnep0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int jc = (jw0 >> 1) + h, k = 2 * h;   // row 2jc is rw[k], 2jc+1 is rw[k+1]
+        const T xl = rw[k].w0, xr = rw[k].w1, yb = rw[k + 1].w0, csw = rw[k + 1].w2, cse = rw[k + 1].w3;
+        const T ae = res_e[k], ao = res_o[k], be = res_e[k + 1], bo = res_o[k + 1];
+        T lxr = fromL(xr), lcse = fromL(cse), lcnep = fromL(cnep);
+        T lao = fromL(ao), lbo = fromL(bo), lr3o = fromL(r3o);
+        T bcv = ae + xl * ao + lxr * lao + yb * be + ytp * r3e + csw * bo + lcse * lbo + cnwp * r3o +
+                lcnep * lr3o;
+        if (own && jc >= s0 && jc < s1 && jc >= 1 && jc <= a.cny - 2 && t >= 1 && t <= a.cnx - 2)
+            a.bc[(size_t)jc * a.cpitch + t] = bcv;
+        r3e = be;
+        r3o = bo;
+        ytp = rw[k + 1].w1;
+        cnwp = rw[k + 1].w4;
+        cnep = rw[k + 1].w5;
+    }
+}
+
+int pass_tile_steps() { return (PASS_NW * TILE_RPW - 16) / 2; }
+
+void pass_tile_geometry(int nx, int ny, int *nstrips, int *nblocks, int *ntiles)
+{
+    const int own = stream_owned_pairs(5, SV_FUSED3), r = pass_tile_steps();
+    *nstrips = ((nx + 1) / 2 + own - 1) / own;
+    *nblocks = ((ny - 1) / 2 + r - 1) / r;
+    *ntiles = *nstrips * *nblocks;
+}
+
+template <typename T, bool PN>
+static void launch_pass(const StreamArgs<T> &a, hipStream_t s)
+{
+    if (a.zexc) hipLaunchKernelGGL((k_tile_pass<T, true, PN>), dim3(a.ntiles), dim3(64 * PASS_NW), 0, s, a);
+    else hipLaunchKernelGGL((k_tile_pass<T, false, PN>), dim3(a.ntiles), dim3(64 * PASS_NW), 0, s, a);
+}
+
+template <typename T>
+hipError_t launch_tile_pass(int variant, StreamArgs<T> a, hipStream_t s)
+{
+    pass_tile_geometry(a.nx, a.ny, &a.nstrips, &a.nblocks, &a.ntiles);
+    a.rb = pass_tile_steps();
+    if (a.ntiles <= 0) return hipErrorInvalidValue;
+    if (variant == SV_FUSED3) launch_pass<T, false>(a, s);
+    else if (variant == SV_FUSED3_PN) launch_pass<T, true>(a, s);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+template hipError_t launch_tile_pass<double>(int, StreamArgs<double>, hipStream_t);
+template hipError_t launch_tile_pass<float>(int, StreamArgs<float>, hipStream_t);
 
 template <typename T>
 hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s, const CheckArgs *chk)
