@@ -1112,7 +1112,8 @@ __global__ __launch_bounds__(64 * W) void k_stream_batched(const StreamArgs<T> *
                                                            const int2 *__restrict__ map, int nmap,
                                                            const int *__restrict__ active)
 {
-    const int w = (int)blockIdx.x * W + (int)(threadIdx.x >> 6);
+    // one wave, one entry: the problem's arguments stay in scalar registers
+    const int w = __builtin_amdgcn_readfirstlane((int)blockIdx.x * W + (int)(threadIdx.x >> 6));
     if (w >= nmap) return;
     const int2 m = map[w];
     if (!active[m.x]) return;
@@ -1342,7 +1343,8 @@ __global__ __launch_bounds__(64 * W) void k_stream3_batched(const StreamArgs<T> 
                                                             const int2 *__restrict__ map, int nmap,
                                                             const int *__restrict__ active)
 {
-    const int w = (int)blockIdx.x * W + (int)(threadIdx.x >> 6);
+    // one wave, one entry: the problem's arguments stay in scalar registers
+    const int w = __builtin_amdgcn_readfirstlane((int)blockIdx.x * W + (int)(threadIdx.x >> 6));
     if (w >= nmap) return;
     const int2 m = map[w];
     if (active && !active[m.x]) return;
