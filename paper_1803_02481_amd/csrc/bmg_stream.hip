@@ -35,6 +35,7 @@
 #include <mutex>
 #include <type_traits>
 #include "bmg_weights.h"
+#include "bmg_quot.h"
 
 namespace hbmg {
 
@@ -84,24 +85,26 @@ __device__ __forceinline__ int xcd_tile_fn()
 }
 
 // One row of the lane's column pair.  The c*/w*/q* fields hold the raw inputs
-// of the interpolate-and-correct step until the row is finished.
+// of the interpolate-and-correct step until the row is finished; d* (FP32) and
+// y* are the relaxation's diagonal and its reciprocal (set_diag).
 template <typename T>
 struct Row {
     T x0, x1, b0, b1, C0, C1, W0, W1, S0, S1, SW0, SW1, SE0, SE1;
     T ca, cu, w0, w1, w2, w3, w4, w5, q0, q1;
+    T d0, d1, y0, y1;
 };
 
 // Residual b - (A x) at the even column of row `cu` (rows `bl` below and `ab`
-// above), and the diagonal used by the relaxation.  All lanes must call: the
-// functions shuffle.  FP64 levels hold C in the C plane (standard form); FP32
-// levels hold the excess E = C - sum(connections) there and use the edge form
+// above).  All lanes must call: the functions shuffle.  FP64 levels hold C in
+// the C plane (standard form); FP32 levels hold the excess E = C -
+// sum(connections) there and use the edge form
 //   (A x)_p = sum_q conn_pq (x_p - x_q) + E_p x_p,   diag = sum_q conn_pq + E_p,
 // which keeps zero row sums exact after rounding to FP32.
 template <typename T> struct IsEdge { enum { value = 0 }; };
 template <> struct IsEdge<float> { enum { value = 1 }; };
 
 template <typename T, int NPT>
-__device__ __forceinline__ T res_even(const Row<T> &bl, const Row<T> &cu, const Row<T> &ab, T &diag)
+__device__ __forceinline__ T res_even(const Row<T> &bl, const Row<T> &cu, const Row<T> &ab)
 {
     const T xw = fromL(cu.x1);
     T xsw = T(0), xnw = T(0), cnw = T(0);
@@ -114,22 +117,16 @@ __device__ __forceinline__ T res_even(const Row<T> &bl, const Row<T> &cu, const 
     if (!IsEdge<T>::value) {
         T s = cu.b0 + cu.W0 * xw + cu.W1 * cu.x1 + cu.S0 * bl.x0 + ab.S0 * ab.x0;
         if (NPT == 9) s += cu.SW0 * xsw + ab.SW1 * ab.x1 + cu.SE0 * bl.x1 + cnw * xnw;
-        diag = cu.C0;
         return s - cu.C0 * x;
     } else {
         T s = cu.b0 + cu.W0 * (xw - x) + cu.W1 * (cu.x1 - x) + cu.S0 * (bl.x0 - x) + ab.S0 * (ab.x0 - x);
-        T d = cu.W0 + cu.W1 + cu.S0 + ab.S0 + cu.C0;
-        if (NPT == 9) {
-            s += cu.SW0 * (xsw - x) + ab.SW1 * (ab.x1 - x) + cu.SE0 * (bl.x1 - x) + cnw * (xnw - x);
-            d += cu.SW0 + ab.SW1 + cu.SE0 + cnw;
-        }
-        diag = d;
+        if (NPT == 9) s += cu.SW0 * (xsw - x) + ab.SW1 * (ab.x1 - x) + cu.SE0 * (bl.x1 - x) + cnw * (xnw - x);
         return s - cu.C0 * x;
     }
 }
 
 template <typename T, int NPT>
-__device__ __forceinline__ T res_odd(const Row<T> &bl, const Row<T> &cu, const Row<T> &ab, T &diag)
+__device__ __forceinline__ T res_odd(const Row<T> &bl, const Row<T> &cu, const Row<T> &ab)
 {
     const T xe = fromR(cu.x0), we = fromR(cu.W0);
     T xne = T(0), xse = T(0), cne = T(0);
@@ -142,18 +139,38 @@ __device__ __forceinline__ T res_odd(const Row<T> &bl, const Row<T> &cu, const R
     if (!IsEdge<T>::value) {
         T s = cu.b1 + cu.W1 * cu.x0 + we * xe + cu.S1 * bl.x1 + ab.S1 * ab.x1;
         if (NPT == 9) s += cu.SW1 * bl.x0 + cne * xne + cu.SE1 * xse + ab.SE0 * ab.x0;
-        diag = cu.C1;
         return s - cu.C1 * x;
     } else {
         T s = cu.b1 + cu.W1 * (cu.x0 - x) + we * (xe - x) + cu.S1 * (bl.x1 - x) + ab.S1 * (ab.x1 - x);
-        T d = cu.W1 + we + cu.S1 + ab.S1 + cu.C1;
-        if (NPT == 9) {
-            s += cu.SW1 * (bl.x0 - x) + cne * (xne - x) + cu.SE1 * (xse - x) + ab.SE0 * (ab.x0 - x);
-            d += cu.SW1 + cne + cu.SE1 + ab.SE0;
-        }
-        diag = d;
+        if (NPT == 9) s += cu.SW1 * (bl.x0 - x) + cne * (xne - x) + cu.SE1 * (xse - x) + ab.SE0 * (ab.x0 - x);
         return s - cu.C1 * x;
     }
+}
+
+// The diagonals of row `cu` and their reciprocals, once the row above it (ab)
+// is loaded and the C plane complete; every lane calls.  A row is relaxed up
+// to three times and its residual divided once more: one division each and
+// none in the chain of dependent updates.  us a launch, with divisions ->
+// this: pass of 4097^2 in FP64 230 -> 228 (bandwidth), of 769 x 641 19.2 ->
+// 18.3; down leg of 513^2 14.1 -> 13.6; 2049^2 blocks in mixed precision 8.46
+// -> 8.06 ms a solve.
+template <typename T, int NPT>
+__device__ __forceinline__ void set_diag(Row<T> &cu, const Row<T> &ab)
+{
+    if (!IsEdge<T>::value) {
+        cu.d0 = cu.C0;
+        cu.d1 = cu.C1;
+    } else {
+        const T we = fromR(cu.W0);
+        T d = cu.W0 + cu.W1 + cu.S0 + ab.S0 + cu.C0;
+        if (NPT == 9) d += cu.SW0 + ab.SW1 + cu.SE0 + fromL(ab.SE1);
+        cu.d0 = d;
+        d = cu.W1 + we + cu.S1 + ab.S1 + cu.C1;
+        if (NPT == 9) d += cu.SW1 + fromR(ab.SW0) + cu.SE1 + ab.SE0;
+        cu.d1 = d;
+    }
+    cu.y0 = T(1) / cu.d0;
+    cu.y1 = T(1) / cu.d1;
 }
 
 // ZC9: on a 9-point level whose rows at least two vertices from the boundary
@@ -221,6 +238,7 @@ __device__ __forceinline__ void stage_rotate(Stage<T> &S)
 }
 
 // One step j of a relaxation stage whose rows j and j+1 are in S.r0, S.rp1
+// and whose rows j-1 and j have their diagonals set
 // (mode 0: colours 0, 1 only; 1: full step, nothing stored; 2: full step,
 // stores if WRITE).  With RES the residual of the final rows j-2 and j-1 is
 // formed, with RQ stored as q = r/C and restricted onto coarse row (j-2)/2,
@@ -234,19 +252,17 @@ __device__ __forceinline__ void stage_step(Stage<T> &S, int j, int mode, const L
     const bool rjm = j - 1 >= 1 && j - 1 <= L.ny - 2;
     // colours 0 and 1 on row j
     {
-        T d;
-        T r = res_even<T, NPT>(S.rm1, S.r0, S.rp1, d);
-        if (rj && L.ie) S.r0.x0 += r / d;
-        r = res_odd<T, NPT>(S.rm1, S.r0, S.rp1, d);
-        if (rj && L.io) S.r0.x1 += r / d;
+        T r = res_even<T, NPT>(S.rm1, S.r0, S.rp1);
+        if (rj && L.ie) S.r0.x0 += div_by(r, S.r0.d0, S.r0.y0);
+        r = res_odd<T, NPT>(S.rm1, S.r0, S.rp1);
+        if (rj && L.io) S.r0.x1 += div_by(r, S.r0.d1, S.r0.y1);
     }
     if (mode != 0) {
         // colours 2 and 3 on row j-1
-        T d;
-        T r = res_even<T, NPT>(S.rm2, S.rm1, S.r0, d);
-        if (rjm && L.ie) S.rm1.x0 += r / d;
-        r = res_odd<T, NPT>(S.rm2, S.rm1, S.r0, d);
-        if (rjm && L.io) S.rm1.x1 += r / d;
+        T r = res_even<T, NPT>(S.rm2, S.rm1, S.r0);
+        if (rjm && L.ie) S.rm1.x0 += div_by(r, S.rm1.d0, S.rm1.y0);
+        r = res_odd<T, NPT>(S.rm2, S.rm1, S.r0);
+        if (rjm && L.io) S.rm1.x1 += div_by(r, S.rm1.d1, S.rm1.y1);
 
         if (WRITE && STOREX && mode == 2 && L.own) {
             if (rjm) st2(a.x_out + (size_t)(j - 1) * L.pitch + L.e, S.rm1.x0, S.rm1.x1);
@@ -255,11 +271,10 @@ __device__ __forceinline__ void stage_step(Stage<T> &S, int j, int mode, const L
         if (RES) {
             // residuals of the final rows j-2 (even) and j-1 (odd)
             const bool rA = j - 2 >= 1 && j - 2 <= L.ny - 2;
-            T dae, dao, dbe, dbo;
-            T ae = res_even<T, NPT>(S.rm3, S.rm2, S.rm1, dae);
-            T ao = res_odd<T, NPT>(S.rm3, S.rm2, S.rm1, dao);
-            T be = res_even<T, NPT>(S.rm2, S.rm1, S.r0, dbe);
-            T bo = res_odd<T, NPT>(S.rm2, S.rm1, S.r0, dbo);
+            T ae = res_even<T, NPT>(S.rm3, S.rm2, S.rm1);
+            T ao = res_odd<T, NPT>(S.rm3, S.rm2, S.rm1);
+            T be = res_even<T, NPT>(S.rm2, S.rm1, S.r0);
+            T bo = res_odd<T, NPT>(S.rm2, S.rm1, S.r0);
             if (!(rA && L.ie)) ae = T(0);
             if (!(rA && L.io)) ao = T(0);
             if (!(rjm && L.ie)) be = T(0);
@@ -268,9 +283,11 @@ __device__ __forceinline__ void stage_step(Stage<T> &S, int j, int mode, const L
                 S.acc += (double)ae * ae + (double)ao * ao + (double)be * be + (double)bo * bo;
             if (RQ) {
                 if (WRITE && STOREQ && mode == 2 && L.own) {
-                    if (rA && L.io) a.q_out[(size_t)(j - 2) * L.pitch + L.o] = ao / dao;
+                    if (rA && L.io)
+                        a.q_out[(size_t)(j - 2) * L.pitch + L.o] = div_by(ao, S.rm2.d1, S.rm2.y1);
                     if (rjm) st2(a.q_out + (size_t)(j - 1) * L.pitch + L.e,
-                                 L.ie ? be / dbe : T(0), L.io ? bo / dbo : T(0));
+                                 L.ie ? div_by(be, S.rm1.d0, S.rm1.y0) : T(0),
+                                 L.io ? div_by(bo, S.rm1.d1, S.rm1.y1) : T(0));
                 }
                 // restriction onto coarse row jc = (j-2)/2, coarse column L.t
                 const int jc = (j - 2) >> 1;
@@ -431,6 +448,8 @@ __device__ __forceinline__ void stream_tile(const StreamArgs<T> &a, const int ti
         }
         finish_row(r0, j);
         finish_row(rp1, j + 1);
+        set_diag<T, NPT>(rm1, r0);
+        set_diag<T, NPT>(r0, rp1);
         stage_step<T, NPT, true, F::RES, F::RQ, F::NORM>(S, j, mode, L, a);
         stage_rotate(S);
     }
@@ -513,6 +532,8 @@ __device__ __forceinline__ void stream2_tile(const StreamArgs<T> &a, const int t
             complete_C9(A.rm1, A.r0, deep9(ja - 1, e, o, nx, ny));
             complete_C9(A.r0, A.rp1, deep9(ja, e, o, nx, ny));
         }
+        set_diag<T, NPT>(A.rm1, A.r0);
+        set_diag<T, NPT>(A.r0, A.rp1);
         stage_step<T, NPT, false, false, false, false>(A, ja, AM, L, a);
         const int jb = ja - 2;
         if constexpr (BM >= 0) {
@@ -703,14 +724,12 @@ __device__ __forceinline__ void stream3_tile(const StreamArgs<T> &a, const int t
     // of an odd row cu (bl, ab: the raw rows below and above)
     const bool rc = a.rescorr != 0;
     auto rc_odd = [&](const Row<T> &bl, const Row<T> &cu, const Row<T> &ab) {
-        T d;
-        const T r = res_odd<T, NPT>(bl, cu, ab, d);
-        return rc ? r / d : T(0);
+        const T r = res_odd<T, NPT>(bl, cu, ab);
+        return rc ? div_by(r, cu.d1, cu.y1) : T(0);
     };
     auto rc_even = [&](const Row<T> &bl, const Row<T> &cu, const Row<T> &ab) {
-        T d;
-        const T r = res_even<T, NPT>(bl, cu, ab, d);
-        return rc ? r / d : T(0);
+        const T r = res_even<T, NPT>(bl, cu, ab);
+        return rc ? div_by(r, cu.d0, cu.y0) : T(0);
     };
 
     const int nsteps = (ny - 1) / 2;
@@ -742,6 +761,7 @@ __device__ __forceinline__ void stream3_tile(const StreamArgs<T> &a, const int t
             xline_row(Rn, jp0, N1.S1);
             odd_row_weights(Rm1, jp0 - 1, Ra, Rn);
         }
+        set_diag<T, NPT>(Rm1, Rn);
         P.rm1 = Rm1;
         finish_row(P.rm1, jp0 - 1, rc_even(Ra, Rm1, Rn), rc_odd(Ra, Rm1, Rn));
     }
@@ -778,6 +798,8 @@ __device__ __forceinline__ void stream3_tile(const StreamArgs<T> &a, const int t
             complete_C(Rn, R1);
             complete_C(R1, R2);
         }
+        set_diag<T, NPT>(Rn, R1);
+        set_diag<T, NPT>(R1, R2);
         const T q1_even_row = rc_odd(Rm1, Rn, R1);
         const T q0_odd_row = rc_even(Rn, R1, R2), q1_odd_row = rc_odd(Rn, R1, R2);
         P.r0 = Rn;
@@ -1030,14 +1052,12 @@ __device__ __forceinline__ void interp_rc_tile(const StreamArgs<T> &a, const int
     };
     const bool rc = a.rescorr != 0;
     auto rc_odd = [&](const Row<T> &bl, const Row<T> &cu, const Row<T> &ab) {
-        T d;
-        const T r = res_odd<T, NPT>(bl, cu, ab, d);
-        return rc ? r / d : T(0);
+        const T r = res_odd<T, NPT>(bl, cu, ab);
+        return rc ? div_by(r, cu.d1, cu.y1) : T(0);
     };
     auto rc_even = [&](const Row<T> &bl, const Row<T> &cu, const Row<T> &ab) {
-        T d;
-        const T r = res_even<T, NPT>(bl, cu, ab, d);
-        return rc ? r / d : T(0);
+        const T r = res_even<T, NPT>(bl, cu, ab);
+        return rc ? div_by(r, cu.d0, cu.y0) : T(0);
     };
 
     const int nsteps = (ny - 1) / 2;
@@ -1058,6 +1078,7 @@ __device__ __forceinline__ void interp_rc_tile(const StreamArgs<T> &a, const int
             complete_C9(Ra, Rm1, deep9(jp0 - 2, e, o, nx, ny));
             complete_C9(Rm1, Rn, deep9(jp0 - 1, e, o, nx, ny));
         }
+        set_diag<T, NPT>(Rm1, Rn);
         P.rm1 = Rm1;
         finish_row(P.rm1, jp0 - 1, rc_even(Ra, Rm1, Rn), rc_odd(Ra, Rm1, Rn));
     }
@@ -1076,6 +1097,8 @@ __device__ __forceinline__ void interp_rc_tile(const StreamArgs<T> &a, const int
             complete_C9(Rn, R1, deep9(jp, e, o, nx, ny));
             complete_C9(R1, R2, deep9(jp + 1, e, o, nx, ny));
         }
+        set_diag<T, NPT>(Rn, R1);
+        set_diag<T, NPT>(R1, R2);
         const T q1_even_row = rc_odd(Rm1, Rn, R1);
         const T q0_odd_row = rc_even(Rn, R1, R2), q1_odd_row = rc_odd(Rn, R1, R2);
         P.r0 = Rn;
@@ -1256,6 +1279,10 @@ int stream_resident(int npt, int variant, int fp32)
         (void)hipGetLastError();
         return 0;
     }
+    // two waves of this one fit on a SIMD, but its levels are bandwidth-bound
+    // and tiles for one wave are twice as long, with half the prologue steps
+    // (up leg of 2049^2 64 us against 69, of 1025^2 18.2 against 21.3)
+    if (npt == 9 && variant == SV_INTERP_RC && !fp32) per = std::min(per, 4);
     std::lock_guard<std::mutex> g(mu);
     cache[{dev, k}] = ncu * per;
     return ncu * per;
@@ -1423,11 +1450,10 @@ __device__ __forceinline__ void tile_relax_row(const Row<T> &bl, Row<T> &cu, con
                                                const LaneCtx &L)
 {
     const bool rj = j >= 1 && j <= L.ny - 2;
-    T d;
-    T r = res_even<T, NPT>(bl, cu, ab, d);
-    if (rj && L.ie) cu.x0 += r / d;
-    r = res_odd<T, NPT>(bl, cu, ab, d);
-    if (rj && L.io) cu.x1 += r / d;
+    T r = res_even<T, NPT>(bl, cu, ab);
+    if (rj && L.ie) cu.x0 += div_by(r, cu.d0, cu.y0);
+    r = res_odd<T, NPT>(bl, cu, ab);
+    if (rj && L.io) cu.x1 += div_by(r, cu.d1, cu.y1);
 }
 
 template <typename T>
@@ -1525,6 +1551,8 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArg
             }
         }
     }
+#pragma unroll
+    for (int k = 0; k < TILE_RPW; ++k) set_diag<T, NPT>(rw[k], k == TILE_RPW - 1 ? up : rw[k + 1]);
     auto below = [&](bool zero) {
         Row<T> r{};
         if (w > 0 && !zero) {
@@ -1561,15 +1589,15 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArg
         __syncthreads();
     }
     // residuals of the final rows, zero outside the interior
-    T res_e[TILE_RPW], res_o[TILE_RPW], dg_e[TILE_RPW], dg_o[TILE_RPW];
+    T res_e[TILE_RPW], res_o[TILE_RPW];
     {
         const Row<T> b0 = below(false), a3 = above();
 #pragma unroll
         for (int k = 0; k < TILE_RPW; ++k) {
             const Row<T> &bl = k == 0 ? b0 : rw[k - 1];
             const Row<T> &ab = k == TILE_RPW - 1 ? a3 : rw[k + 1];
-            res_e[k] = res_even<T, NPT>(bl, rw[k], ab, dg_e[k]);
-            res_o[k] = res_odd<T, NPT>(bl, rw[k], ab, dg_o[k]);
+            res_e[k] = res_even<T, NPT>(bl, rw[k], ab);
+            res_o[k] = res_odd<T, NPT>(bl, rw[k], ab);
             const int j = jw0 + k;
             const bool rr = j >= 1 && j <= ny - 2;
             if (!(rr && ie)) res_e[k] = T(0);
@@ -1587,10 +1615,10 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArg
                 st2(a.x_out + (size_t)j * pitch + e, rw[k].x0, rw[k].x1);
             if (j >= 2 * s0 && j <= 2 * s1 - 1 && j >= 1 && j <= ny - 2) {
                 if ((k & 1) == 0) {
-                    if (io) a.q_out[(size_t)j * pitch + o] = res_o[k] / dg_o[k];
+                    if (io) a.q_out[(size_t)j * pitch + o] = div_by(res_o[k], rw[k].d1, rw[k].y1);
                 } else {
-                    st2(a.q_out + (size_t)j * pitch + e, ie ? res_e[k] / dg_e[k] : T(0),
-                        io ? res_o[k] / dg_o[k] : T(0));
+                    st2(a.q_out + (size_t)j * pitch + e, ie ? div_by(res_e[k], rw[k].d0, rw[k].y0) : T(0),
+                        io ? div_by(res_o[k], rw[k].d1, rw[k].y1) : T(0));
                 }
             }
         }
@@ -1676,6 +1704,8 @@ __global__ __launch_bounds__(64 * NW) void k_tile_up(StreamArgs<T> a)
     }
     tile_load_above(up, jw0 + TILE_RPW, L, colv, a);
     if (w == NW - 1) up = Row<T>{};
+#pragma unroll
+    for (int k = 0; k < TILE_RPW; ++k) set_diag<T, NPT>(rw[k], k == TILE_RPW - 1 ? up : rw[k + 1]);
     // x += P x_c (+ r/C at fine-only vertices)
 #pragma unroll
     for (int k = 0; k < TILE_RPW; ++k) {
@@ -1837,6 +1867,8 @@ __global__ __launch_bounds__(64 * PASS_NW) void k_tile_pass(StreamArgs<T> a)
             r.C1 = r.W1 + we + r.S1 + ab.S1;
         }
     }
+#pragma unroll
+    for (int k = 0; k < TILE_RPW; ++k) set_diag<T, NPT>(rw[k], k == TILE_RPW - 1 ? up : rw[k + 1]);
     // x += P x_c, + r/C of the raw iterate at fine-only vertices
     {
         const bool rc = a.rescorr != 0;
@@ -1845,13 +1877,12 @@ __global__ __launch_bounds__(64 * PASS_NW) void k_tile_pass(StreamArgs<T> a)
         for (int k = 0; k < TILE_RPW; ++k) {
             const Row<T> &bl = k == 0 ? dn : rw[k - 1];
             const Row<T> &ab = k == TILE_RPW - 1 ? up : rw[k + 1];
-            T d;
-            T r = res_odd<T, NPT>(bl, rw[k], ab, d);
-            q1[k] = rc ? r / d : T(0);
+            T r = res_odd<T, NPT>(bl, rw[k], ab);
+            q1[k] = rc ? div_by(r, rw[k].d1, rw[k].y1) : T(0);
             q0[k] = T(0);
             if (k & 1) {
-                r = res_even<T, NPT>(bl, rw[k], ab, d);
-                q0[k] = rc ? r / d : T(0);
+                r = res_even<T, NPT>(bl, rw[k], ab);
+                q0[k] = rc ? div_by(r, rw[k].d0, rw[k].y0) : T(0);
             }
         }
 #pragma unroll
@@ -1904,9 +1935,8 @@ __global__ __launch_bounds__(64 * PASS_NW) void k_tile_pass(StreamArgs<T> a)
                 for (int k = 0; k < TILE_RPW; ++k) {
                     const Row<T> &bl = k == 0 ? b0 : rw[k - 1];
                     const Row<T> &ab = k == TILE_RPW - 1 ? a3 : rw[k + 1];
-                    T d;
-                    const T re = res_even<T, NPT>(bl, rw[k], ab, d);
-                    const T ro = res_odd<T, NPT>(bl, rw[k], ab, d);
+                    const T re = res_even<T, NPT>(bl, rw[k], ab);
+                    const T ro = res_odd<T, NPT>(bl, rw[k], ab);
                     const int j = jw0 + k;
                     const bool rr = own && j >= 2 * s0 && j <= 2 * s1 - 1 && j >= 1 && j <= ny - 2;
                     if (rr && ie) acc += (double)re * re;
@@ -1958,9 +1988,8 @@ __global__ __launch_bounds__(64 * PASS_NW) void k_tile_pass(StreamArgs<T> a)
         for (int k = 0; k < TILE_RPW; ++k) {
             const Row<T> &bl = k == 0 ? b0 : rw[k - 1];
             const Row<T> &ab = k == TILE_RPW - 1 ? a3 : rw[k + 1];
-            T d;
-            res_e[k] = res_even<T, NPT>(bl, rw[k], ab, d);
-            res_o[k] = res_odd<T, NPT>(bl, rw[k], ab, d);
+            res_e[k] = res_even<T, NPT>(bl, rw[k], ab);
+            res_o[k] = res_odd<T, NPT>(bl, rw[k], ab);
             const int j = jw0 + k;
             const bool rr = j >= 1 && j <= ny - 2;
             if (!(rr && ie)) res_e[k] = T(0);
