@@ -18,6 +18,7 @@
 #include "hipbmg3d.h"
 #include "bmg_internal.h"
 #include "bmg_model.h"
+#include "bmg_quot.h"
 
 #include <algorithm>
 #include <chrono>
@@ -31,6 +32,8 @@
 #include <vector>
 
 namespace {
+
+using hbmg::div_by;
 
 // ---------------------------------------------------------------------------
 // geometry
@@ -603,7 +606,7 @@ struct PArgs {
 template <int NPT>
 struct Row {
     enum { noff = NPT == 7 ? 2 : 18 };
-    double b, off, d, k[InPlane<NPT>::n];
+    double b, off, d, y, k[InPlane<NPT>::n];   // y: 1 / d
     double oc[noff], ox[noff];
     bool in;
 };
@@ -644,8 +647,9 @@ __device__ __forceinline__ void load_row(const PArgs &a, int i, int j, long long
     R.b = a.b[v];
 }
 
-// the off-plane sum (a chain in the order of the pairs) and, where it is
-// formed, the diagonal W_p + W_e + S_p + S_n + B_p + B_t (in this order the
+// the off-plane sum (a chain in the order of the pairs), the diagonal's
+// reciprocal (no colour phase waits for a division: 33^3 1208 -> 1189 us a solve,
+// 129 x 97 x 65 7.26 -> 7.14 ms) and, where it is formed, the diagonal W_p + W_e + S_p + S_n + B_p + B_t (in this order the
 // setup found it bitwise the stored one)
 template <int NPT, bool ZC, bool OFF>
 __device__ __forceinline__ void finish_row(Row<NPT> &R)
@@ -656,6 +660,7 @@ __device__ __forceinline__ void finish_row(Row<NPT> &R)
         for (int q = 0; q < Row<NPT>::noff; ++q) R.off += R.oc[q] * R.ox[q];
     }
     if (NPT == 7 && ZC) R.d = R.k[0] + R.k[1] + R.k[2] + R.k[3] + R.oc[0] + R.oc[1];
+    R.y = 1.0 / R.d;
 }
 
 // the plane's iterate in LDS: one array per octant of the plane, rows lr0..,
@@ -685,7 +690,7 @@ __device__ __forceinline__ double row_resid(const Window &w, int at, const Row<N
 template <int NPT, int Q>
 __device__ __forceinline__ void relax_colour(const Window &w, int at, const Row<NPT> &R)
 {
-    if (R.in) w.x[Q * w.size + at] += row_resid<NPT, Q>(w, at, R) / R.d;
+    if (R.in) w.x[Q * w.size + at] += div_by(row_resid<NPT, Q>(w, at, R), R.d, R.y);
 }
 
 // the window's iterate into LDS: zero, or as stored
@@ -1374,7 +1379,7 @@ __global__ __launch_bounds__(CWG3) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
 constexpr int SMALL_NC = 48, SMALL_MAXTOP = 2;
 
 struct SRow {
-    double oc[18], k[8], d, b, w[8], off, r;
+    double oc[18], k[8], d, y, b, w[8], off, r;   // y: 1 / d
     int at;
     bool in;
 };
@@ -1406,6 +1411,7 @@ __device__ __forceinline__ void small_load(const CLev &L, int o, int lane, SRow 
         R.k[2 * (s - 9) + 1] = L.st[(1 + s) * F + nbr_rt(g, o, t, 1 - s % 3, 1 - (s / 3) % 3, 0)];
     }
     R.d = L.st[v];
+    R.y = 1.0 / R.d;
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
         R.w[m] = 1.0;
@@ -1445,7 +1451,7 @@ __device__ __forceinline__ void small_relax(SRow &R, double *x, int nx, int nxy,
             if ((o >> 2) == pz && R.in) small_off(R, x, nx, nxy, R.off);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                if (o == 4 * pz + q && R.in) x[R.at] += small_resid(R, x, nx) / R.d;
+                if (o == 4 * pz + q && R.in) x[R.at] += div_by(small_resid(R, x, nx), R.d, R.y);
                 __syncthreads();
             }
         }
@@ -1493,7 +1499,7 @@ __device__ __forceinline__ void small_interp(const Oct &g, const Oct &c, const S
         for (int m = 0; m < 8; ++m)
             if (!(m & ~o)) s += R.w[m] * xc[f + (m & 1) + ((m >> 1) & 1) * c.nx + (m >> 2) * c.nx * c.ny];
         double xv = x[R.at] + s;
-        if (o != 0 && rescorr) xv += R.r / R.d;
+        if (o != 0 && rescorr) xv += div_by(R.r, R.d, R.y);
         x[R.at] = xv;
     }
     __syncthreads();
