@@ -1055,17 +1055,41 @@ __global__ __launch_bounds__(256) void k3_fill0(double *p, long long n)
     for (long long t = blockIdx.x * 256LL + threadIdx.x; t < n; t += (long long)gridDim.x * 256) p[t] = 0.0;
 }
 
-// block b: out[b] = sum of partials [b*chunk, min(n, (b+1)*chunk))
-__global__ __launch_bounds__(256) void k3_reduce(const double *partials, long long n, long long chunk, double *out)
+// sum of partials [lo, hi) over a workgroup of 256; the result is thread 0's
+__device__ __forceinline__ double sum_range(const double *partials, long long lo, long long hi)
 {
     double s = 0.0;
-    const long long lo = blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
     for (long long t = lo + threadIdx.x; t < hi; t += 256) s += partials[t];
     for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
     __shared__ double ws[4];
     if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) out[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
+    return ws[0] + ws[1] + ws[2] + ws[3];
+}
+
+// block b: out[b] = sum of partials [b*chunk, min(n, (b+1)*chunk))
+__global__ __launch_bounds__(256) void k3_reduce(const double *partials, long long n, long long chunk, double *out)
+{
+    const long long lo = blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    const double s = sum_range(partials, lo, hi);
+    if (threadIdx.x == 0) out[blockIdx.x] = s;
+}
+
+// The sum of n partials to the host-mapped slot {sum, tag} the host polls.  The
+// tag is `set` (it starts a solve) or the last one plus 1: a captured launch has
+// no argument to carry it.  A copy to the host and a wait for the stream took
+// 10 us a cycle more than the poll.
+__global__ __launch_bounds__(256) void k3_sum_out(const double *partials, long long n, double *tag, double set,
+                                                  double *slot)
+{
+    const double s = sum_range(partials, 0, n);
+    if (threadIdx.x != 0) return;
+    const double t = set != 0.0 ? set : *tag + 1.0;
+    *tag = t;
+    volatile double *v = slot;
+    v[0] = s;
+    __threadfence_system();
+    v[1] = t;
 }
 
 // b_c = P^T r: each coarse vertex gathers its 27 fine support vertices
@@ -1649,7 +1673,8 @@ struct hipbmg3d_hier {
     double *d_part = nullptr;
     long long npart = 0;
     double *d_sum = nullptr;
-    double *h_sum = nullptr;   // pinned
+    double *slot = nullptr, *slot_dev = nullptr;   // host-mapped {sum, tag}
+    unsigned run_id = 0;       // solves so far: the tags' high bits
     double *d_nat = nullptr;   // plain-layout staging of the op_* entry points
     std::vector<void *> allocs;
     int cur = 0;                       // the finest iterate's buffer
@@ -1688,9 +1713,9 @@ hipbmg_status dalloc3(hipbmg3d_hier *h, double **p, long long n)
 void free3(hipbmg3d_hier *h)
 {
     hbmg::dev_free_all(h->allocs);
-    if (h->h_sum) {
+    if (h->slot) {
         (void)hipDeviceSynchronize();
-        hbmg::pinned_small_free(h->h_sum);
+        hbmg::pinned_small_free(h->slot);
     }
     for (hipEvent_t e : h->evpool) (void)hipEventDestroy(e);
     for (int k = 0; k < 2; ++k) {
@@ -1905,14 +1930,28 @@ hipbmg_status relax(hipbmg3d_hier *h, int l, int *cur, int sweeps, hipStream_t s
     return HIPBMG_OK;
 }
 
-// d_sum[0] = sum of n partials, in two stages of fixed shape (deterministic)
-hipbmg_status reduce_sum(hipbmg3d_hier *h, const double *partials, long long n, hipStream_t s)
+// The sum of n partials into the slot, tagged `tag` (0: the last tag plus 1).
+// Up to 2048 in one launch, more in two stages of fixed shape (deterministic).
+hipbmg_status reduce_sum(hipbmg3d_hier *h, const double *partials, long long n, double tag, hipStream_t s)
 {
     const long long nb = std::min<long long>(256, (n + 2047) / 2048);
-    const long long chunk = (n + nb - 1) / nb;
-    hipLaunchKernelGGL(k3_reduce, dim3((unsigned)nb), dim3(256), 0, s, partials, n, chunk, h->d_sum + 8);
-    hipLaunchKernelGGL(k3_reduce, dim3(1), dim3(256), 0, s, (const double *)(h->d_sum + 8), nb, nb, h->d_sum);
+    if (nb > 1) {
+        const long long chunk = (n + nb - 1) / nb;
+        hipLaunchKernelGGL(k3_reduce, dim3((unsigned)nb), dim3(256), 0, s, partials, n, chunk, h->d_sum + 8);
+        partials = h->d_sum + 8;
+        n = nb;
+    }
+    hipLaunchKernelGGL(k3_sum_out, dim3(1), dim3(256), 0, s, partials, n, h->d_sum, tag, h->slot_dev);
     HIP3(hipGetLastError());
+    return HIPBMG_OK;
+}
+
+// wait for the sum tagged `tag`
+hipbmg_status wait_sum(hipbmg3d_hier *h, double tag, hipStream_t s, double *out)
+{
+    const hipError_t e = hbmg::wait_tag(h->slot + 1, tag, s);
+    if (e != hipSuccess) return fail3(HIPBMG_EHIP, "a norm did not arrive: %s", hipGetErrorString(e));
+    *out = h->slot[0];
     return HIPBMG_OK;
 }
 
@@ -1929,7 +1968,7 @@ hipbmg_status residual(hipbmg3d_hier *h, int l, int cur, hipStream_t s)
     return HIPBMG_OK;
 }
 
-// ||b - A x[cur]||^2 of the finest level into d_sum[0].  The block sums of the
+// ||b - A x[cur]||^2 of the finest level into the slot.  The block sums of the
 // planes of a parity that a half sweep has left in d_part already (have_odd,
 // have_even) are the same bits this forms.
 hipbmg_status norm(hipbmg3d_hier *h, int cur, bool have_odd, bool have_even, hipStream_t s)
@@ -1952,7 +1991,7 @@ hipbmg_status norm(hipbmg3d_hier *h, int cur, bool have_odd, bool have_even, hip
             HIP3(pz ? launch_tiles<27>(k3_plane_resid<27, 1, false, true>, a, s)
                     : launch_tiles<27>(k3_plane_resid<27, 0, false, true>, a, s));
     }
-    return reduce_sum(h, h->d_part, norm_partials(f), s);
+    return reduce_sum(h, h->d_part, norm_partials(f), 0.0, s);
 }
 
 // b_{l-1} = P^T r_l, and x_{l-1} = 0 if zero
@@ -2067,7 +2106,7 @@ hipbmg_status collapse(hipbmg3d_hier *h, int top, hipStream_t s)
 
 // Algorithm 1 on level l; the iterate starts in x[0] (on the finest level in
 // x[h->cur], and from zero on all others) and ends in x[*end].  begun: the
-// first half sweep has been done; norm_odd: the last one also leaves the odd
+// first sweep has been done; norm_odd: the last one also leaves the odd
 // planes' part of the norm in d_part.
 hipbmg_status vcycle(hipbmg3d_hier *h, int l, hipStream_t s, int *end = nullptr, bool begun = false,
                      bool norm_odd = false)
@@ -2079,8 +2118,10 @@ hipbmg_status vcycle(hipbmg3d_hier *h, int l, hipStream_t s, int *end = nullptr,
     const int nu1 = h->prm.nu1, nu2 = h->prm.nu2;
     for (int it = 0; it < nu1; ++it) {
         const bool zero = !fine && it == 0;
-        if (!(begun && it == 0)) ST3(half_sweep(h, l, cur, 0, zero, 0, s));
-        ST3(half_sweep(h, l, cur, 1, zero, it == nu1 - 1 ? 1 : 0, s));
+        if (!(begun && it == 0)) {
+            ST3(half_sweep(h, l, cur, 0, zero, 0, s));
+            ST3(half_sweep(h, l, cur, 1, zero, it == nu1 - 1 ? 1 : 0, s));
+        }
         cur = 1 - cur;
     }
     // the coarse iterate's zeros are stored only for what reads them: the
@@ -2104,22 +2145,29 @@ hipbmg_status vcycle(hipbmg3d_hier *h, int l, hipStream_t s, int *end = nullptr,
     return HIPBMG_OK;
 }
 
-// the finest level's cycles overlap: a cycle ends with the first half sweep of
-// the next one, which writes the other buffer (the iterate stays whole where a
-// cycle was the last) and sums the squares of the residual it starts from, so
-// the norm's even planes cost no pass of their own.  Not where kernel timing
-// is on, which times the norm as a launch of its own.
+// the finest level's cycles overlap: a cycle ends with the first sweep of the
+// next one, which writes the other buffer (the iterate stays whole where a cycle
+// was the last).  Its first half sums the squares of the residual it starts
+// from, so the norm's even planes cost no pass of their own; the second runs
+// while the host sees the norm and enqueues the next cycle.  Not where kernel
+// timing is on, which times the norm as a launch of its own.
 bool overlapped(const hipbmg3d_hier *h) { return h->L - 1 > h->lstar && h->prm.nu1 > 0 && !h->prof; }
+
+hipbmg_status second_half(hipbmg3d_hier *h, int cur, hipStream_t s)
+{
+    return half_sweep(h, h->L - 1, cur, 1, false, h->prm.nu1 == 1 ? 1 : 0, s);
+}
 
 hipbmg_status enqueue_cycle(hipbmg3d_hier *h, hipStream_t s, int *end)
 {
     const bool norm_odd = h->L - 1 > h->lstar && h->prm.nu2 > 0, over = overlapped(h);
     ST3(vcycle(h, h->L - 1, s, end, over, norm_odd));
     if (over) ST3(half_sweep(h, h->L - 1, *end, 0, false, 3, s));
-    return norm(h, *end, norm_odd, over, s);
+    ST3(norm(h, *end, norm_odd, over, s));
+    return over ? second_half(h, *end, s) : HIPBMG_OK;
 }
 
-// one cycle and the finest residual norm (into d_sum); replayed from a
+// one cycle and the finest residual norm (into the slot); replayed from a
 // captured graph (one per buffer the finest iterate starts from) unless
 // use_graph is 0 or kernel timing is on
 hipbmg_status cycle_and_norm(hipbmg3d_hier *h, hipStream_t s)
@@ -2147,14 +2195,6 @@ hipbmg_status cycle_and_norm(hipbmg3d_hier *h, hipStream_t s)
     }
     HIP3(hipGraphLaunch(h->exec[k], s));
     if (h->L - 1 > h->lstar) h->cur = k ^ ((h->prm.nu1 + h->prm.nu2) & 1);
-    return HIPBMG_OK;
-}
-
-hipbmg_status read_sum(hipbmg3d_hier *h, hipStream_t s, double *out)
-{
-    HIP3(hipMemcpyAsync(h->h_sum, h->d_sum, sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP3(hipStreamSynchronize(s));
-    *out = h->h_sum[0];
     return HIPBMG_OK;
 }
 
@@ -2402,9 +2442,10 @@ extern "C" hipbmg_status hipbmg3d_setup(int nx, int ny, int nz, int npt, const d
     h->npart = (long long)nblk(top.g.field) + norm_partials(top) + 8;
     if ((st = dalloc3(h, &h->d_part, h->npart)) != HIPBMG_OK) return bail(st);
     if ((st = dalloc3(h, &h->d_sum, 8 + 256)) != HIPBMG_OK) return bail(st);
-    if (hbmg::pinned_small((void **)&h->h_sum, nullptr, 8 * sizeof(double)) != hipSuccess) {
+    if (hbmg::pinned_small((void **)&h->slot, (void **)&h->slot_dev, 2 * sizeof(double)) != hipSuccess ||
+        !h->slot_dev) {
         (void)hipGetLastError();
-        return bail(fail3(HIPBMG_ENOMEM, "pinned allocation failed"));
+        return bail(fail3(HIPBMG_ENOMEM, "host-mapped allocation failed"));
     }
     // the finest operator in the octant layout
     const int nf = npt == 7 ? 4 : 14;
@@ -2529,12 +2570,16 @@ extern "C" hipbmg_status hipbmg3d_solve(hipbmg3d_handle h, const double *b, doub
     ST3(to_oct(f.g, b, f.b, 1, s));
     ST3(to_oct(f.g, u, f.x[0], 1, s));
     h->cur = 0;
-    if (overlapped(h)) ST3(half_sweep(h, h->L - 1, 0, 0, false, 0, s));
+    if (overlapped(h)) {
+        ST3(half_sweep(h, h->L - 1, 0, 0, false, 0, s));
+        ST3(second_half(h, 0, s));
+    }
     hipLaunchKernelGGL(k3_sumsq, dim3(nblk(f.g.field)), dim3(256), 0, s, f.g, (const double *)f.b, h->d_part);
     HIP3(hipGetLastError());
-    ST3(reduce_sum(h, h->d_part, (long long)nblk(f.g.field), s));
+    const double tag0 = (double)(++h->run_id & 0xfffffu) * 4294967296.0;
+    ST3(reduce_sum(h, h->d_part, (long long)nblk(f.g.field), tag0, s));
     double bb = 0.0;
-    ST3(read_sum(h, s, &bb));
+    ST3(wait_sum(h, tag0, s, &bb));
     const double bn = std::sqrt(bb);
     if (info) {
         std::memset(info, 0, sizeof *info);
@@ -2553,7 +2598,7 @@ extern "C" hipbmg_status hipbmg3d_solve(hipbmg3d_handle h, const double *b, doub
         while (cycles < h->prm.max_cycles) {
             ST3(cycle_and_norm(h, s));
             double rr = 0.0;
-            ST3(read_sum(h, s, &rr));
+            ST3(wait_sum(h, tag0 + cycles + 1, s, &rr));
             rel = std::sqrt(rr) / bn;
             if (info) info->relres_hist[cycles] = rel;
             ++cycles;

@@ -168,6 +168,23 @@ hipError_t hbmg::pinned_small(void **host, void **dev, size_t bytes)
     return hipSuccess;
 }
 
+hipError_t hbmg::wait_tag(const volatile double *v, double tag, hipStream_t s)
+{
+    for (unsigned spins = 1; *v != tag; ++spins) {
+        __builtin_ia32_pause();
+        if (spins % 4096) continue;
+        const hipError_t e = hipStreamQuery(s);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        if (e == hipSuccess && *v == tag) break;
+        return e == hipSuccess ? hipErrorUnknown : e;
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    return hipSuccess;
+}
+
 void hbmg::pinned_small_free(void *host)
 {
     if (!host) return;
@@ -1473,20 +1490,8 @@ static double next_tag(hipbmg_hier *h) { return (double)(++h->run_id & 0xfffffu)
 // on stream s, so a stream that has drained without it means a failed launch.
 static hipbmg_status wait_slot(hipbmg_hier *h, int idx, double tag, hipStream_t s)
 {
-    const volatile double *v = h->ring_host + 4 * idx;
-    for (unsigned spins = 1;; ++spins) {
-        if (v[3] == tag) break;
-        __builtin_ia32_pause();
-        if (spins % 4096) continue;
-        const hipError_t e = hipStreamQuery(s);
-        if (e == hipErrorNotReady) {
-            (void)hipGetLastError();
-            continue;
-        }
-        if (e == hipSuccess && v[3] == tag) break;
-        return fail(HIPBMG_EHIP, "a test's result did not arrive: %s", hipGetErrorString(e));
-    }
-    std::atomic_thread_fence(std::memory_order_acquire);
+    const hipError_t e = wait_tag(h->ring_host + 4 * idx + 3, tag, s);
+    if (e != hipSuccess) return fail(HIPBMG_EHIP, "a test's result did not arrive: %s", hipGetErrorString(e));
     return HIPBMG_OK;
 }
 

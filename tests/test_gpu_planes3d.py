@@ -78,3 +78,23 @@ def test_register_resident_collapse_is_the_general_one(shape, prm):
             ref = (u, info.history())
         assert torch.equal(u, ref[0]), ls
         assert info.history() == ref[1], ls
+
+
+# the last size's ||b||^2 has more block sums (2500) than one launch adds up
+@pytest.mark.parametrize("shape", [(5, 5, 5), (17, 17, 17), (33, 17, 9), (81, 81, 97)])
+@pytest.mark.parametrize("nu", [(2, 1), (1, 1), (1, 2), (0, 2)])
+@pytest.mark.parametrize("use_graph", [0, 1])
+def test_stopping_cycle_is_the_capped_one(shape, nu, use_graph):
+    # the sweep enqueued ahead of a cycle's test leaves the iterate the test is
+    # about: a solve that meets its tolerance after k cycles returns the bits of
+    # one capped at k, and so does a repeated solve (replayed cycles)
+    nz, ny, nx = shape
+    planes = planes_of(7, shape, 81)
+    b = g(inputs.load3_uniform(nx, ny, nz, seed=82))
+    h = HB.Hierarchy3(planes, nu1=nu[0], nu2=nu[1], use_graph=use_graph)
+    u, info = h.solve(b, tol=1e-7)
+    again, info2 = h.solve(b, tol=1e-7)
+    assert torch.equal(u, again) and info.history() == info2.history()
+    capped = HB.Hierarchy3(planes, nu1=nu[0], nu2=nu[1], use_graph=1 - use_graph, max_cycles=info.cycles)
+    v, info3 = capped.solve(b, tol=1e-30, check=False)
+    assert torch.equal(u, v) and info.history() == info3.history() and info3.cycles == info.cycles
