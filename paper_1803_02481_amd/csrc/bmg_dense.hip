@@ -14,15 +14,17 @@ namespace hbmg {
 
 namespace {
 
-constexpr int BWG = 256;   // threads of a column's workgroup
 
 // a level as a column's workgroup sees it: operator and weights in global
 // memory (every column reads them, so they sit in L2), iterate, residual and
 // right-hand side in LDS at compact pitch nx
+// the values of two columns at a vertex
+typedef double D2 __attribute__((ext_vector_type(2)));
+
 struct DV {
     int nx, ny, P;
     const double *C, *W, *S, *SW, *SE;
-    double *x, *r, *b;
+    D2 *x, *r, *b;
     const double *wt;
     int cpitch;
     size_t cplane;
@@ -30,7 +32,7 @@ struct DV {
 
 __device__ __forceinline__ DV dview(const DenseBuildArgs &a, int l)
 {
-    extern __shared__ __align__(16) double dsm[];
+    extern __shared__ __align__(16) D2 dsm[];
     const LevelDev<double> &g = a.levels[l];
     DV v;
     v.nx = g.nx;
@@ -52,13 +54,13 @@ __device__ __forceinline__ DV dview(const DenseBuildArgs &a, int l)
 }
 
 // residual (b - A x) at interior vertex (i, j)
-__device__ __forceinline__ double dres(const DV &L, int i, int j, double &diag)
+__device__ __forceinline__ D2 dres(const DV &L, int i, int j, double &diag)
 {
     const int P = L.P, n = L.nx, q = j * n + i;
     const size_t p = (size_t)j * P + i;
-    const double *x = L.x;
+    const D2 *x = L.x;
     diag = L.C[p];
-    const double s = L.b[q] + L.W[p] * x[q - 1] + L.W[p + 1] * x[q + 1] + L.S[p] * x[q - n] + L.S[p + P] * x[q + n] +
+    const D2 s = L.b[q] + L.W[p] * x[q - 1] + L.W[p + 1] * x[q + 1] + L.S[p] * x[q - n] + L.S[p + P] * x[q + n] +
                      L.SW[p] * x[q - n - 1] + L.SW[p + P + 1] * x[q + n + 1] + L.SE[p] * x[q - n + 1] +
                      L.SE[p + P - 1] * x[q + n - 1];
     return s - diag * x[q];
@@ -69,10 +71,10 @@ __device__ __forceinline__ void dsweep(const DV &L)
     for (int k = 0; k < 4; ++k) {
         const int i0 = (k & 1) ? 1 : 2, j0 = (k >> 1) ? 1 : 2;
         const int ni = L.nx - 2 >= i0 ? (L.nx - 2 - i0) / 2 + 1 : 0, nj = L.ny - 2 >= j0 ? (L.ny - 2 - j0) / 2 + 1 : 0;
-        for (int idx = threadIdx.x; idx < ni * nj; idx += BWG) {
+        for (int idx = threadIdx.x; idx < ni * nj; idx += blockDim.x) {
             const int jj = idx / ni, i = i0 + 2 * (idx - jj * ni), j = j0 + 2 * jj;
             double d;
-            const double r = dres(L, i, j, d);
+            const D2 r = dres(L, i, j, d);
             L.x[j * L.nx + i] += r / d;
         }
         __syncthreads();
@@ -84,8 +86,9 @@ __device__ __forceinline__ void drestrict(const DV &F, const DV &Cl)
 {
     const int ni = Cl.nx - 2, n = ni * (Cl.ny - 2), P = F.nx, WP = F.cpitch;
     const size_t cp = F.cplane;
-    const double *w = F.wt, *r = F.r;
-    for (int idx = threadIdx.x; idx < n; idx += BWG) {
+    const double *w = F.wt;
+    const D2 *r = F.r;
+    for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
         const int J = 1 + idx / ni, I = 1 + idx % ni;
         const int f = 2 * J * P + 2 * I;
         const size_t c = (size_t)J * WP + I, cW = c - 1, cS = c - WP, cSW = c - WP - 1;
@@ -101,12 +104,13 @@ __device__ __forceinline__ void dinterp(const DV &F, const DV &Cl, int rescorr)
 {
     const int ni = F.nx - 2, n = ni * (F.ny - 2), CP = Cl.nx;
     const size_t cp = F.cplane;
-    const double *w = F.wt, *xc = Cl.x;
-    for (int idx = threadIdx.x; idx < n; idx += BWG) {
+    const double *w = F.wt;
+    const D2 *xc = Cl.x;
+    for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
         const int j = 1 + idx / ni, i = 1 + idx % ni;
         const int c = (j >> 1) * CP + (i >> 1);
         const size_t cw = (size_t)(j >> 1) * F.cpitch + (i >> 1);
-        double v;
+        D2 v;
         if (!(i & 1) && !(j & 1)) {
             v = xc[c];
         } else {
@@ -125,26 +129,29 @@ __device__ __forceinline__ void dinterp(const DV &F, const DV &Cl, int rescorr)
 
 }  // namespace
 
-// Column blockIdx.x of M: the V-cycle of levels top..0 on e_c.  Bound by the
-// latency of the phases (operator reads from L2 between two barriers); small
-// workgroups with only x, r and b in LDS (36 KB at 33^2) let four of them hide
-// each other's on a CU, so the 961 columns of a 33^2 level run at once
-// (61 us for the whole matrix, two cycles' worth of what it saves).
-__global__ __launch_bounds__(BWG) void k_dense_build(DenseBuildArgs a)
+// Columns 2 blockIdx.x and 2 blockIdx.x + 1 of M: the V-cycle of levels top..0
+// on e_c.  Bound by the operator's reads from L2 (a column walks the top level
+// five times) and the latency of its phases; two columns share the reads and
+// write M 16 bytes at a time.  The whole matrix of 961 unknowns (33^2) takes
+// 53 us (62 with a column per workgroup), of 1833 (49 x 41) 232 us (261).
+__global__ __launch_bounds__(512) void k_dense_build(DenseBuildArgs a)
 {
-    extern __shared__ __align__(16) double dsm[];
-    const int col = blockIdx.x;
-    for (int t = threadIdx.x; t < a.lds_doubles; t += BWG) dsm[t] = 0.0;
+    extern __shared__ __align__(16) D2 dsm[];
+    const int col = 2 * blockIdx.x;
+    for (int t = threadIdx.x; t < a.lds_elems; t += blockDim.x) dsm[t] = 0.0;
     __syncthreads();
     const DV T = dview(a, a.top);
-    const int ni = T.nx - 2;
-    if (threadIdx.x == 0) T.b[(1 + col / ni) * T.nx + 1 + col % ni] = 1.0;
+    const int ni = T.nx - 2, n = ni * (T.ny - 2);
+    if (threadIdx.x < 2 && col + (int)threadIdx.x < n) {
+        const int c = col + threadIdx.x;
+        T.b[(1 + c / ni) * T.nx + 1 + c % ni][threadIdx.x] = 1.0;
+    }
     __syncthreads();
     for (int l = a.top; l >= 1; --l) {
         const DV F = dview(a, l), Cl = dview(a, l - 1);
         for (int s = 0; s < a.nu1; ++s) dsweep(F);
         const int m = F.nx - 2, n = m * (F.ny - 2);
-        for (int idx = threadIdx.x; idx < n; idx += BWG) {
+        for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
             const int j = 1 + idx / m, i = 1 + idx % m;
             double d;
             F.r[j * F.nx + i] = dres(F, i, j, d);
@@ -155,25 +162,25 @@ __global__ __launch_bounds__(BWG) void k_dense_build(DenseBuildArgs a)
     }
     {   // coarsest level: the Cholesky substitutions, unknown k at the k-th interior vertex
         const DV L0 = dview(a, 0);
-        double *y = dsm + a.lds_y;
+        D2 *y = dsm + a.lds_y;
         const int m = L0.nx - 2, nc = a.nc;
-        for (int k = threadIdx.x; k < nc; k += BWG) y[k] = L0.b[(1 + k / m) * L0.nx + 1 + k % m];
+        for (int k = threadIdx.x; k < nc; k += blockDim.x) y[k] = L0.b[(1 + k / m) * L0.nx + 1 + k % m];
         __syncthreads();
         for (int k = 0; k < nc; ++k) {
-            const double yk = y[k] / a.chol[(size_t)k * nc + k];
-            for (int q = k + 1 + threadIdx.x; q < nc; q += BWG) y[q] -= a.chol[(size_t)q * nc + k] * yk;
+            const D2 yk = y[k] / a.chol[(size_t)k * nc + k];
+            for (int q = k + 1 + threadIdx.x; q < nc; q += blockDim.x) y[q] -= a.chol[(size_t)q * nc + k] * yk;
             __syncthreads();
             if (threadIdx.x == 0) y[k] = yk;
             __syncthreads();
         }
         for (int k = nc - 1; k >= 0; --k) {
-            const double xk = y[k] / a.chol[(size_t)k * nc + k];
-            for (int q = threadIdx.x; q < k; q += BWG) y[q] -= a.chol[(size_t)k * nc + q] * xk;
+            const D2 xk = y[k] / a.chol[(size_t)k * nc + k];
+            for (int q = threadIdx.x; q < k; q += blockDim.x) y[q] -= a.chol[(size_t)k * nc + q] * xk;
             __syncthreads();
             if (threadIdx.x == 0) y[k] = xk;
             __syncthreads();
         }
-        for (int k = threadIdx.x; k < nc; k += BWG) L0.x[(1 + k / m) * L0.nx + 1 + k % m] = y[k];
+        for (int k = threadIdx.x; k < nc; k += blockDim.x) L0.x[(1 + k / m) * L0.nx + 1 + k % m] = y[k];
         __syncthreads();
     }
     for (int l = 1; l <= a.top; ++l) {
@@ -182,14 +189,18 @@ __global__ __launch_bounds__(BWG) void k_dense_build(DenseBuildArgs a)
         __syncthreads();
         for (int s = 0; s < a.nu2; ++s) dsweep(F);
     }
-    const int n = ni * (T.ny - 2);
-    for (int row = threadIdx.x; row < n; row += BWG)
-        a.M[(size_t)row * a.ld + col] = T.x[(1 + row / ni) * T.nx + 1 + row % ni];
+    // ld is even, and its columns from n on are zero
+    for (int row = threadIdx.x; row < n; row += blockDim.x)
+        *reinterpret_cast<D2 *>(a.M + (size_t)row * a.ld + col) = T.x[(1 + row / ni) * T.nx + 1 + row % ni];
 }
 
 hipError_t launch_dense_build(const DenseBuildArgs &a, int n, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dense_build, dim3(n), dim3(BWG), (size_t)a.lds_doubles * sizeof(double), s, a);
+    const int lds = a.lds_elems * (int)sizeof(D2);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_dense_build),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, DENSE_LDS);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_dense_build, dim3((n + 1) / 2), dim3(512), lds, s, a);
     return hipGetLastError();
 }
 
@@ -198,7 +209,9 @@ hipError_t launch_dense_build(const DenseBuildArgs &a, int n, hipStream_t s)
 // in LDS, so the launch costs one memory round trip and a wave reduction.
 // Bound by that latency up to about 1000 unknowns and by M's bytes beyond.
 // Measured (gfx950, FP64): 3.9 us for 961 unknowns (33^2, M 7.9 MB), where
-// the collapsed workgroup takes 31-38 us for the same levels.
+// the collapsed workgroup takes 31-38 us for the same levels; 8.4 us for 1833
+// (49 x 41, 28 MB), where the level's two kernels and the product for 25 x 21
+// below it take 14.9 us.
 // The sum's order is fixed; columns n..ld-1 of M and of the staged
 // right-hand side are zero.
 constexpr int DENSE_ROWS = 4;                // rows (waves) of a workgroup

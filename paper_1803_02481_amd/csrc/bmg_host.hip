@@ -664,7 +664,7 @@ static bool rc_on_the_fly(const hipbmg_hier *h, int nx, int ny, bool fine)
 }
 
 // LDS of a dense-operator column's workgroup with its highest level `top`:
-// offsets (in doubles) of x, r, b per level, then the coarse solve's vector
+// offsets (in pairs of doubles) of x, r, b per level, then the coarse solve's vector
 static size_t dense_lds(const std::vector<int> &sx, const std::vector<int> &sy, int top, int *off)
 {
     size_t t = 0;
@@ -676,13 +676,15 @@ static size_t dense_lds(const std::vector<int> &sx, const std::vector<int> &sy, 
 }
 
 // Highest level run as one dense operator with everything below it (-1: none):
-// the largest below the finest with at most DENSE_UNKNOWNS unknowns whose
-// columns' workgroups fit their LDS.  Only where the caller leaves the coarse
+// the largest below the finest with at most DENSE_MAX unknowns whose
+// columns' workgroups fit their LDS.  Half as many above a coarsest level of more
+// than 64, whose substitutions, a barrier per unknown, take most of the build:
+// 1935 unknowns above 110 took 1.3 ms more to form and saved 5 us a cycle (with
+// at most 1024: 75 us a cycle on 705 x 737); above 20, 1833 unknowns take 0.2 ms
+// and save 6-8 (769 x 641: 73 -> 67 us a cycle, 193 x 129: 37 -> 29).  Only where the caller leaves the coarse
 // levels to the library: a forced collapse level, forced stages or
 // cluster_wg = 0 (also what a batch uses: its problems' collapses run side by
 // side, one workgroup each) keep the collapsed workgroup.
-constexpr int DENSE_UNKNOWNS = 1024;
-
 static int choose_dense(const hipbmg_params &prm, const std::vector<int> &sx, const std::vector<int> &sy, int *n)
 {
     *n = 0;
@@ -690,8 +692,9 @@ static int choose_dense(const hipbmg_params &prm, const std::vector<int> &sx, co
     int top = -1;
     for (int l = 0; l + 1 < (int)sx.size() && l < COLLAPSE_MAX_LEVELS; ++l) {
         const long long m = (long long)(sx[l] - 2) * (sy[l] - 2);
-        const size_t lds = (dense_lds(sx, sy, l, nullptr) + (size_t)(sx[0] - 2) * (sy[0] - 2)) * sizeof(double);
-        if (m > DENSE_UNKNOWNS || lds > (size_t)DENSE_LDS) break;
+        const size_t lds = (dense_lds(sx, sy, l, nullptr) + (size_t)(sx[0] - 2) * (sy[0] - 2)) * 2 * sizeof(double);
+        const long long lim = (long long)(sx[0] - 2) * (sy[0] - 2) <= 64 ? DENSE_MAX : DENSE_MAX / 2;
+        if (m > lim || lds > (size_t)DENSE_LDS) break;
         top = l;
         *n = (int)m;
     }
@@ -1471,7 +1474,7 @@ static hipbmg_status ensure_dense(hipbmg_hier *h, hipStream_t s)
         sy[l] = h->lv[l].ny;
     }
     a.lds_y = (int)dense_lds(sx, sy, a.top, a.lds_off);
-    a.lds_doubles = a.lds_y + h->nc;
+    a.lds_elems = a.lds_y + h->nc;
     a.M = h->d_dense;
     a.ld = h->dense_ld;
     HIPCHK(launch_dense_build(a, h->dense_n, s));
@@ -3177,7 +3180,7 @@ static hipbmg_status time_stages(hipbmg_batch *B, BPlan &plan, hipStream_t s, st
 // coarse levels short ones.  On 64 problems of 1025^2 in FP64 one shape for all
 // kept a cap of 16 (finest pass 1250 us a cycle) where the pass alone takes
 // 1036 us at 128: forward and adjoint solve 57.8 -> 52.5 ms; 256 problems of
-// 128^2..512^2 in mixed precision 32.9 -> 30.9 ms.  The choice is remembered per batch signature (sizes, stencil,
+// 129^2..1025^2 in mixed precision 32.9 -> 30.9 ms.  The choice is remembered per batch signature (sizes, stencil,
 // precision, cycle) for the life of the process.  HIPBMG_BATCH_TUNE=0 keeps one
 // strip per workgroup and the single-problem rule; HIPBMG_BATCH_WPG=1, 2 or 4
 // fixes W.

@@ -233,14 +233,14 @@ hipError_t launch_collapse(const CollapseArgs<T> &a, hipStream_t s);
 // ld = n rounded up to 128, the columns past n zero) with x_top = M b_top, the
 // V-cycle of levels top..0 from zero; n = (nx-2)(ny-2) of level top.
 constexpr int DENSE_MAX = 2048;               // largest ld
-constexpr int DENSE_LDS = 64 * 1024;          // bytes of LDS a column's workgroup may take
+constexpr int DENSE_LDS = 150 * 1024;         // bytes of LDS the workgroup of two columns may take
 struct DenseBuildArgs {
     const LevelDev<double> *levels;           // device array, index = level
     int top, nu1, nu2, rescorr;
     const double *chol;                       // as in CollapseArgs
     int nc;
-    int lds_off[COLLAPSE_MAX_LEVELS];         // doubles: x, r, b of each level at compact pitch
-    int lds_y, lds_doubles;
+    int lds_off[COLLAPSE_MAX_LEVELS];         // pairs of doubles: x, r, b of each level at compact pitch
+    int lds_y, lds_elems;
     double *M;
     int ld;
 };
