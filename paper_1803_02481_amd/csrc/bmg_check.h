@@ -29,6 +29,24 @@ __device__ __forceinline__ void slot_write(double *slot, double v0, double v1, d
     v[3] = tag;
 }
 
+// thread 0, with the partials' sum: the test and its outcome
+__device__ __forceinline__ void check_sum(const CheckArgs &c, double sum)
+{
+    const double rel = sqrt(sum) / c.denom[0];
+    int run = 1;
+    if (!isfinite(rel)) {
+        run = 0;
+        c.flags[1] = c.k;
+        c.flags[2] = 2;
+    } else if (rel <= c.tol) {
+        run = 0;
+        c.flags[1] = c.k;
+        c.flags[2] = 1;
+    }
+    c.flags[0] = run;
+    slot_write(c.slot, rel, (double)run, (double)c.flags[1], c.tag);
+}
+
 // the whole workgroup (at least 256 threads) calls
 __device__ __forceinline__ void cycle_check(const CheckArgs &c)
 {
@@ -38,21 +56,22 @@ __device__ __forceinline__ void cycle_check(const CheckArgs &c)
     if (threadIdx.x < 256)
         for (int m = threadIdx.x; m < c.n; m += 256) acc += c.partials[m];
     const double sum = sum256(acc, sh);
-    if (threadIdx.x == 0) {
-        const double rel = sqrt(sum) / c.denom[0];
-        int run = 1;
-        if (!isfinite(rel)) {
-            run = 0;
-            c.flags[1] = c.k;
-            c.flags[2] = 2;
-        } else if (rel <= c.tol) {
-            run = 0;
-            c.flags[1] = c.k;
-            c.flags[2] = 1;
-        }
-        c.flags[0] = run;
-        slot_write(c.slot, rel, (double)run, (double)c.flags[1], c.tag);
-    }
+    if (threadIdx.x == 0) check_sum(c, sum);
+}
+
+// the same bits from one wave: each lane stands for four of the 256 threads
+__device__ __forceinline__ void cycle_check_wave(const CheckArgs &c)
+{
+    if (c.flags[0] == 0) return;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int m = threadIdx.x; m < c.n; m += 256)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) acc[w] += m + 64 * w < c.n ? c.partials[m + 64 * w] : 0.0;
+    for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) acc[w] += __shfl_xor(acc[w], off, 64);
+    if (threadIdx.x == 0) check_sum(c, ((acc[0] + acc[1]) + acc[2]) + acc[3]);
 }
 
 }  // namespace hbmg

@@ -1239,11 +1239,12 @@ static StreamArgs<T> base_args(const LevelDev<T> &A, int rb)
 
 template <typename T>
 static hipError_t run_stream(const LevelDev<T> &A, int variant, StreamArgs<T> a, hipStream_t s,
-                             int *ntiles_out = nullptr)
+                             int *ntiles_out = nullptr, const CheckArgs *chk = nullptr)
 {
     int g;
     stream_geometry(A.nx, A.ny, A.npt, variant, a.rb, &a.nstrips, &a.nblocks, &a.ntiles, &g);
     if (ntiles_out) *ntiles_out = a.ntiles;
+    if (chk && chk->partials) return launch_stream2_check<T>(variant, a, g, *chk, s);
     return launch_stream<T>(A.npt, variant, a, g, s);
 }
 
@@ -1363,7 +1364,7 @@ static hipError_t enqueue_vcycle(hipbmg_hier *h, const std::vector<LevelDev<T>> 
                 tile_geometry(A.nx, A.ny, A.npt, nw, 1, &a.nstrips, &nbl, &a.ntiles);
                 a.nblocks = nbl;
                 if ((e = launch_tile<T>(1, nw, a, s, l == L - 1 ? chk : nullptr)) != hipSuccess) return e;
-            } else if ((e = run_stream(A, v, a, s)) != hipSuccess) {
+            } else if ((e = run_stream(A, v, a, s, nullptr, l == L - 1 ? chk : nullptr)) != hipSuccess) {
                 return e;
             }
             prof_end(h, pk, s);
@@ -1507,18 +1508,21 @@ static hipbmg_status wait_bnorm(hipbmg_hier *h, double tag, hipStream_t s, doubl
     return HIPBMG_OK;
 }
 
-// Whether the first launch below the finest level can take the previous cycle's
-// test along as one more workgroup: the dense operator, or a tile kernel.  The
-// launch then runs once after the stopping cycle too (16 us at most, on 513^2),
-// where a test of its own costs 4 us and a gap of 4-5 us every cycle; a
-// streaming down leg of a larger level would be 28 us or more.  Nothing it
-// writes is read again: the stopping cycle's correction is in the level's
-// other buffer.
+// Whether the first launch below the finest level takes the previous cycle's
+// test along as one more workgroup: the dense operator, a tile kernel, or a
+// streaming down leg of up to 2^21 vertices.  The launch then runs once after
+// the stopping cycle too (16 us at most on 513^2; 24 us on 1025^2 in FP64, 16 in
+// FP32), where a test of its own costs 4-6 us and a gap every cycle (2049^2 in
+// mixed precision 11.96 -> 11.47 ms a solve of some 80 cycles); on 2049^2 it
+// would be 70 us, ten cycles' tests.  Nothing it writes is read again: the
+// stopping cycle's correction is in the level's other buffer.
 static bool check_rides(const hipbmg_hier *h)
 {
     const int top = h->L - 2;
     const int gtop = h->dense_top >= 0 ? h->dense_top : h->cl_nstage > 0 ? h->cl_hi[0] : h->lstar;
-    return gtop == top ? h->dense_top == top : h->tile_dn[top] != 0;
+    if (gtop == top) return h->dense_top == top;
+    const LevelDev<double> &A = h->lv[top];
+    return A.npt == 9 && (long long)A.nx * A.ny <= 1LL << 21;
 }
 
 // Run up to max_cycles V-cycles on the hierarchy lv (FP64 levels, or the FP32

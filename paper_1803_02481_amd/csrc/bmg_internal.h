@@ -160,6 +160,11 @@ struct CheckArgs {
     double *slot, tag;
 };
 
+// SV_SWEEP2_RQ_ZX or SV_SWEEP2_R_ZX of a 9-point level with the test of the
+// previous cycle as one more workgroup; grid as stream_geometry gives it
+template <typename T>
+hipError_t launch_stream2_check(int variant, const StreamArgs<T> &a, int grid, const CheckArgs &chk, hipStream_t s);
+
 // Tile kernels of the small 9-point coarse levels (V(2,1)): a workgroup of nw
 // waves (4 or 8) owns a strip by tile_steps(nw, down) row-pair steps.  down:
 // two relaxations from zero, residual, r/C and restriction (the work of

@@ -977,6 +977,36 @@ __global__ __launch_bounds__(64) void k_stream2(StreamArgs<T> a)
     stream2_tile<T, NPT, ZX, STOREQ, ZC9>(a, tile);
 }
 
+// k_stream2 of a 9-point coarse level from zero, with the previous cycle's test
+// as one more workgroup, the first (its XCD's seven neighbours in the grid are
+// empty, so that the others keep their tile order)
+template <typename T, bool STOREQ, bool ZC9>
+__global__ __launch_bounds__(64) void k_stream2_check(StreamArgs<T> a, CheckArgs chk)
+{
+    if (blockIdx.x < 8) {
+        if (blockIdx.x == 0) cycle_check_wave(chk);
+        return;
+    }
+    if (a.active && *a.active == 0) return;
+    const int b = blockIdx.x - 8, per = (gridDim.x - 8) >> 3;
+    const int tile = (b & 7) * per + (b >> 3);
+    if (tile >= a.ntiles) return;
+    stream2_tile<T, 9, true, STOREQ, ZC9>(a, tile);
+}
+
+template <typename T>
+hipError_t launch_stream2_check(int variant, const StreamArgs<T> &a, int grid, const CheckArgs &chk, hipStream_t s)
+{
+    const dim3 g(grid + 8), b(64);
+    if (variant == SV_SWEEP2_RQ_ZX) hipLaunchKernelGGL((k_stream2_check<T, true, false>), g, b, 0, s, a, chk);
+    else if (variant != SV_SWEEP2_R_ZX) return hipErrorInvalidValue;
+    else if (a.zexc) hipLaunchKernelGGL((k_stream2_check<T, false, true>), g, b, 0, s, a, chk);
+    else hipLaunchKernelGGL((k_stream2_check<T, false, false>), g, b, 0, s, a, chk);
+    return hipGetLastError();
+}
+template hipError_t launch_stream2_check<double>(int, const StreamArgs<double> &, int, const CheckArgs &, hipStream_t);
+template hipError_t launch_stream2_check<float>(int, const StreamArgs<float> &, int, const CheckArgs &, hipStream_t);
+
 // The up leg's first pass with the r/C term formed from the loaded rows
 // instead of read from a stored plane (section 3, interpolation with r/C):
 // the iterate this pass loads is the pre-relaxed one whose residual the down

@@ -90,3 +90,33 @@ def test_stopping_cycle_is_the_capped_one(shape, ahead, monkeypatch):
     assert e.value.status == HB.ENAN
     after, _ = h.solve(b, tol=1e-8)
     assert torch.equal(u, after)
+
+
+# the level below the finest: streaming with r/C stored (577 x 609), and with r/C
+# formed by the up leg (1025^2)
+@pytest.mark.parametrize("shape", [(1153, 1217), (2049, 2049)])
+@pytest.mark.parametrize("reaction", [False, True])
+def test_check_rides_a_streaming_leg(shape, reaction, monkeypatch):
+    ny, nx = shape
+    planes = HB.fv5_from_cells(g(inputs.cells_lognormal(nx, ny, 1.0, seed=15)))
+    if reaction:   # no zero row sums: the coarse diagonals are loaded
+        planes = planes.clone()
+        planes[0, 1:-1, 1:-1] *= 1.0 + 1e-6
+    b = g(inputs.load_uniform(nx, ny, seed=16))
+    h = HB.Hierarchy(planes)
+    u, info = h.solve(b, tol=1e-8)
+    capped = HB.Hierarchy(planes, max_cycles=info.cycles)
+    v, capped_info = capped.solve(b, tol=1e-30, check=False)
+    assert torch.equal(u, v)
+    assert info.history() == capped_info.history() and info.cycles >= 3
+    # mixed precision: every refinement step's inner cycles end by such tests
+    got = []
+    for ahead in ("0", "2", "7"):
+        monkeypatch.setenv("HIPBMG_AHEAD", ahead)
+        m = HB.Hierarchy(planes, precision=HB.MIXED)
+        w, minfo = m.solve(b, tol=1e-10)
+        got.append((w, minfo.cycles, minfo.history(), minfo.relres))
+        m.close()
+    assert got[0][3] <= 1e-10
+    for w, cyc, hist, _ in got[1:]:
+        assert torch.equal(w, got[0][0]) and cyc == got[0][1] and hist == got[0][2]
