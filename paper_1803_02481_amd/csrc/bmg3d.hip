@@ -1396,23 +1396,39 @@ __global__ __launch_bounds__(CWG3) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
 // operator and its interpolation weights in registers, loaded once for the
 // launch; the iterates and residuals live in LDS.  Such a launch is nothing but
 // dependent phases, so what a phase waits for is kept out of it: the off-plane
-// sums of four colours are formed together before their first, and no phase
-// reads memory.  Same terms and order as above, so the same bits; at 257^3
-// (levels 9^3, 5^3, 3^3) the launch takes 25-30 us instead of 153.
+// sums of four colours are formed together before their first, no phase reads
+// memory, and none computes an index: setup packs rows, weights and indices lane
+// by lane (k3_small_pack), so the launch starts with one round of coalesced
+// loads.  Same terms and order as above, so the same bits; at 257^3 (levels 9^3,
+// 5^3, 3^3) the launch took 153 us vertex by vertex, 24 with its indices (and
+// 6 us before the first phase) in the launch, 20.6 now.
 // ---------------------------------------------------------------------------
 constexpr int SMALL_NC = 48, SMALL_MAXTOP = 2;
 
 struct SRow {
     double oc[18], k[8], d, y, b, w[8], off, r;   // y: 1 / d
-    int at;
+    int at, f;                                    // its place in LDS, the coarse corner's
     bool in;
+};
+
+// a packed level: PACK_D doubles per thread (field by field), the restriction's
+// weights (27 x 64); PACK_I integers per thread: place in LDS (-1: no vertex),
+// coarse corner's place, and, of the level's interior vertices in order, place in
+// LDS and in the field (-1: fewer); then by coarse vertex (64) the restriction's
+// fine place and its own (-1: fewer)
+constexpr int PACK_D = 36, PACK_I = 4;
+constexpr int PACK_DBL = PACK_D * CWG3 + 27 * 64, PACK_INT = PACK_I * CWG3 + 2 * 64;
+
+struct SmallPack {
+    const double *d[SMALL_MAXTOP + 1];
+    const int *i[SMALL_MAXTOP + 1];
 };
 
 __device__ __forceinline__ int small_count(int n, int odd) { return odd ? (n - 1) / 2 : (n - 3) / 2; }
 
 // vertex `lane` of octant o of a level (odd sides): its row and weights, all
 // loads in flight
-__device__ __forceinline__ void small_load(const CLev &L, int o, int lane, SRow &R)
+__device__ __forceinline__ void small_load(const CLev &L, const Oct &cg, int o, int lane, SRow &R)
 {
     const Oct &g = L.g;
     const int na = small_count(g.nx, o & 1), nb = small_count(g.ny, (o >> 1) & 1), nc = small_count(g.nz, o >> 2);
@@ -1421,6 +1437,7 @@ __device__ __forceinline__ void small_load(const CLev &L, int o, int lane, SRow 
     const int a = na > 0 ? p % na : 0, q = na > 0 ? p / na : 0, b = nb > 0 ? q % nb : 0, c = nb > 0 ? q / nb : 0;
     const int i = 2 * a + ((o & 1) ? 1 : 2), j = 2 * b + (((o >> 1) & 1) ? 1 : 2), k = 2 * c + ((o >> 2) ? 1 : 2);
     R.at = (k * g.ny + j) * g.nx + i;
+    R.f = ((k >> 1) * cg.ny + (j >> 1)) * cg.nx + (i >> 1);
     if (!R.in) return;
     const int F = (int)g.field;
     const int t = (k >> 1) * (int)g.plane + (j >> 1) * g.px + (i >> 1), v = o * (int)g.oct + t;
@@ -1482,8 +1499,8 @@ __device__ __forceinline__ void small_relax(SRow &R, double *x, int nx, int nxy,
 }
 
 // the weights of fine level F towards its coarse vertex t, slot by slot in the
-// order of the restriction's sum, into LDS
-__device__ __forceinline__ void small_stage_weights(const CLev &F, const Oct &c, double *wr)
+// order of the restriction's sum
+__device__ __forceinline__ void small_weights(const CLev &F, const Oct &c, double *wr)
 {
     const Oct &g = F.g;
     const int ni = c.nx - 2, nj = c.ny - 2, n = ni * nj * (c.nz - 2);
@@ -1496,32 +1513,82 @@ __device__ __forceinline__ void small_stage_weights(const CLev &F, const Oct &c,
     }
 }
 
-// b_c = P^T r: coarse vertices on the first wave's lanes
-__device__ __forceinline__ void small_restrict(const Oct &g, const Oct &c, const double *r, const double *wr, double *bc)
+// pack level L (c: the level below; L.w null: the coarsest) into d and ii
+__global__ __launch_bounds__(CWG3) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3_small_pack(CLev L, Oct c,
+                                                                                                 double *d, int *ii)
 {
-    const int ni = c.nx - 2, nj = c.ny - 2, n = ni * nj * (c.nz - 2), t = threadIdx.x;
-    if (t < n) {
-        const int I = 1 + t % ni, J = 1 + (t / ni) % nj, K = 1 + t / (ni * nj);
-        const int f = (2 * K * g.ny + 2 * J) * g.nx + 2 * I;
+    const int o = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const Oct &g = L.g;
+    if (L.w) {
+        SRow R;
+        small_load(L, c, o, lane, R);
+        int q = 0;
+        auto put = [&](double v) { d[q++ * CWG3 + threadIdx.x] = R.in ? v : 0.0; };
+#pragma unroll
+        for (int s = 0; s < 18; ++s) put(R.oc[s]);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) put(R.k[s]);
+        put(R.d);
+        put(R.y);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) put(R.w[m]);
+        small_weights(L, c, d + PACK_D * CWG3);
+        ii[threadIdx.x] = R.in ? R.at : -1;
+        ii[CWG3 + threadIdx.x] = R.in ? R.f : 0;
+        if (threadIdx.x < 64) {
+            const int ni = c.nx - 2, nj = c.ny - 2, n = ni * nj * (c.nz - 2), t = threadIdx.x;
+            const int I = 1 + t % ni, J = 1 + (t / ni) % nj, K = 1 + t / (ni * nj);
+            ii[PACK_I * CWG3 + t] = t < n ? (2 * K * g.ny + 2 * J) * g.nx + 2 * I : 0;
+            ii[PACK_I * CWG3 + 64 + t] = t < n ? (K * c.ny + J) * c.nx + I : -1;
+        }
+    }
+    const int ni = g.nx - 2, nj = g.ny - 2, n = ni * nj * (g.nz - 2), e = threadIdx.x;
+    const int i = 1 + e % ni, j = 1 + (e / ni) % nj, k = 1 + e / (ni * nj);
+    ii[2 * CWG3 + e] = e < n ? (k * g.ny + j) * g.nx + i : -1;
+    ii[3 * CWG3 + e] = e < n ? (int)vid(g, i, j, k) : 0;
+}
+
+// this thread's vertex of a packed level, all loads in flight
+__device__ __forceinline__ void small_unpack(const double *d, const int *ii, SRow &R)
+{
+    const int at = ii[threadIdx.x];
+    R.f = ii[CWG3 + threadIdx.x];
+    int q = 0;
+    auto get = [&]() { return d[q++ * CWG3 + threadIdx.x]; };
+#pragma unroll
+    for (int s = 0; s < 18; ++s) R.oc[s] = get();
+#pragma unroll
+    for (int s = 0; s < 8; ++s) R.k[s] = get();
+    R.d = get();
+    R.y = get();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) R.w[m] = get();
+    R.in = at >= 0;
+    R.at = R.in ? at : 0;
+}
+
+// b_c = P^T r: coarse vertices on the first wave's lanes (f: the fine place of
+// this lane's, to: its own, -1 without one)
+__device__ __forceinline__ void small_restrict(const Oct &g, const double *r, const double *wr, double *bc, int f, int to)
+{
+    if (threadIdx.x < 64 && to >= 0) {
+        const int nx = g.nx, nxy = g.nx * g.ny;
         double s = 0.0;
 #pragma unroll
         for (int e = 0; e < 27; ++e)
-            s += wr[e * 64 + t] * r[f + e % 3 - 1 + ((e / 3) % 3 - 1) * g.nx + (e / 9 - 1) * g.nx * g.ny];
-        bc[(K * c.ny + J) * c.nx + I] = s;
+            s += wr[e * 64 + threadIdx.x] * r[f + e % 3 - 1 + ((e / 3) % 3 - 1) * nx + (e / 9 - 1) * nxy];
+        bc[to] = s;
     }
     __syncthreads();
 }
 
-__device__ __forceinline__ void small_interp(const Oct &g, const Oct &c, const SRow &R, double *x, const double *xc,
-                                             int o, int rescorr)
+__device__ __forceinline__ void small_interp(const Oct &c, const SRow &R, double *x, const double *xc, int o, int rescorr)
 {
     if (R.in) {
-        const int k = R.at / (g.nx * g.ny), j = (R.at / g.nx) % g.ny, i = R.at % g.nx;
-        const int f = ((k >> 1) * c.ny + (j >> 1)) * c.nx + (i >> 1);
         double s = 0.0;
 #pragma unroll
         for (int m = 0; m < 8; ++m)
-            if (!(m & ~o)) s += R.w[m] * xc[f + (m & 1) + ((m >> 1) & 1) * c.nx + (m >> 2) * c.nx * c.ny];
+            if (!(m & ~o)) s += R.w[m] * xc[R.f + (m & 1) + ((m >> 1) & 1) * c.nx + (m >> 2) * c.nx * c.ny];
         double xv = x[R.at] + s;
         if (o != 0 && rescorr) xv += div_by(R.r, R.d, R.y);
         x[R.at] = xv;
@@ -1529,13 +1596,13 @@ __device__ __forceinline__ void small_interp(const Oct &g, const Oct &c, const S
     __syncthreads();
 }
 
-// the Cholesky substitutions of at most 64 unknowns on one wave, an unknown per lane
-__device__ __forceinline__ void small_coarse(const Oct &g, const double *Lf, int n, const double *b, double *x)
+// the Cholesky substitutions of at most 64 unknowns on one wave, an unknown per
+// lane (at: its place, -1 without one)
+__device__ __forceinline__ void small_coarse(const double *Lf, int n, const double *b, double *x, int at)
 {
     if (threadIdx.x < 64) {
-        const int r = threadIdx.x, ni = g.nx - 2, nj = g.ny - 2;
-        const int at = r < n ? ((1 + r / (ni * nj)) * g.ny + 1 + (r / ni) % nj) * g.nx + 1 + r % ni : 0;
-        double y = r < n ? b[at] : 0.0;
+        const int r = threadIdx.x;
+        double y = at >= 0 ? b[at] : 0.0;
         for (int k = 0; k < n; ++k) {
             const double yk = __shfl(y, k, 64) / Lf[k * n + k];
             if (r > k && r < n) y -= Lf[r * n + k] * yk;
@@ -1546,7 +1613,7 @@ __device__ __forceinline__ void small_coarse(const Oct &g, const double *Lf, int
             if (r < k) y -= Lf[k * n + r] * yk;
             if (r == k) y = yk;
         }
-        if (r < n) x[at] = y;
+        if (at >= 0) x[at] = y;
     }
     __syncthreads();
 }
@@ -1556,30 +1623,45 @@ struct SmallLds {
 };
 
 template <int TOP>
-__global__ __launch_bounds__(CWG3) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3_collapse_small(CArgs a,
+__global__ __launch_bounds__(CWG3) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3_collapse_small(CArgs a, SmallPack pk,
                                                                                                      SmallLds s)
 {
     extern __shared__ double sm[];
+    constexpr int NR = TOP > 0 ? TOP : 1;
     const int o = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    SRow R[TOP > 0 ? TOP : 1];
+    SRow R[NR];
+    int rf[NR], rto[NR];
+    double wr[NR][4];
+    // every load of the launch
+    const int tq = pk.i[TOP][2 * CWG3 + threadIdx.x], tv = pk.i[TOP][3 * CWG3 + threadIdx.x];
 #pragma unroll
-    for (int l = TOP; l >= 1; --l) small_load(a.lv[l], o, lane, R[l - 1]);
-    for (int e = threadIdx.x; e < s.w[0]; e += CWG3) sm[e] = 0.0;   // iterates, residuals, right-hand sides
-    for (int e = threadIdx.x; e < a.nc * a.nc; e += CWG3) sm[s.chol + e] = a.chol[e];
+    for (int l = TOP; l >= 1; --l) {
+        rf[l - 1] = pk.i[l][PACK_I * CWG3 + lane];
+        rto[l - 1] = pk.i[l][PACK_I * CWG3 + 64 + lane];
+        small_unpack(pk.d[l], pk.i[l], R[l - 1]);
 #pragma unroll
-    for (int l = TOP; l >= 1; --l) small_stage_weights(a.lv[l], a.lv[l - 1].g, sm + s.w[l]);
-    __syncthreads();
-    {   // the top level's right-hand side and iterate
-        const CLev &T = a.lv[TOP];
-        const Oct &g = T.g;
-        const int ni = g.nx - 2, nj = g.ny - 2, n = ni * nj * (g.nz - 2);
-        for (int e = threadIdx.x; e < n; e += CWG3) {
-            const int i = 1 + e % ni, j = 1 + (e / ni) % nj, k = 1 + e / (ni * nj);
-            const int q = (k * g.ny + j) * g.nx + i, v = (int)vid(g, i, j, k);
-            sm[s.x[TOP] + q] = T.x[v];
-            sm[s.b[TOP] + q] = T.b[v];
+        for (int q = 0; q < 4; ++q) {
+            const int e = threadIdx.x + q * CWG3;
+            wr[l - 1][q] = e < 27 * 64 ? pk.d[l][PACK_D * CWG3 + e] : 0.0;
         }
     }
+    const int cat = lane < a.nc ? pk.i[0][2 * CWG3 + lane] : -1;
+    const CLev &T = a.lv[TOP];
+    const double tx = T.x[tv], tb = T.b[tv];
+    for (int e = threadIdx.x; e < s.w[0]; e += CWG3) sm[e] = 0.0;   // iterates, residuals, right-hand sides
+    for (int e = threadIdx.x; e < a.nc * a.nc; e += CWG3) sm[s.chol + e] = a.chol[e];
+    __syncthreads();
+    if (tq >= 0) {   // the top level's right-hand side and iterate
+        sm[s.x[TOP] + tq] = tx;
+        sm[s.b[TOP] + tq] = tb;
+    }
+#pragma unroll
+    for (int l = TOP; l >= 1; --l)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = threadIdx.x + q * CWG3;
+            if (e < 27 * 64) sm[s.w[l] + e] = wr[l - 1][q];
+        }
     __syncthreads();
 #pragma unroll
     for (int l = TOP; l >= 1; --l) {
@@ -1595,26 +1677,18 @@ __global__ __launch_bounds__(CWG3) __attribute__((amdgpu_waves_per_eu(2, 2))) vo
             sm[s.r[l] + Q.at] = Q.r;
         }
         __syncthreads();
-        small_restrict(g, a.lv[l - 1].g, sm + s.r[l], sm + s.w[l], sm + s.b[l - 1]);
+        small_restrict(g, sm + s.r[l], sm + s.w[l], sm + s.b[l - 1], rf[l - 1], rto[l - 1]);
     }
-    small_coarse(a.lv[0].g, sm + s.chol, a.nc, sm + s.b[0], sm + s.x[0]);
+    small_coarse(sm + s.chol, a.nc, sm + s.b[0], sm + s.x[0], cat);
 #pragma unroll
     for (int l = 1; l <= TOP; ++l) {
         const Oct &g = a.lv[l].g;
         SRow &Q = R[l - 1];
         double *x = sm + s.x[l];
-        small_interp(g, a.lv[l - 1].g, Q, x, sm + s.x[l - 1], o, a.rescorr);
+        small_interp(a.lv[l - 1].g, Q, x, sm + s.x[l - 1], o, a.rescorr);
         small_relax(Q, x, g.nx, g.nx * g.ny, o, a.nu2);
     }
-    {
-        const CLev &T = a.lv[TOP];
-        const Oct &g = T.g;
-        const int ni = g.nx - 2, nj = g.ny - 2, n = ni * nj * (g.nz - 2);
-        for (int e = threadIdx.x; e < n; e += CWG3) {
-            const int i = 1 + e % ni, j = 1 + (e / ni) % nj, k = 1 + e / (ni * nj);
-            T.x[vid(g, i, j, k)] = sm[s.x[TOP] + (k * g.ny + j) * g.nx + i];
-        }
-    }
+    if (tq >= 0) T.x[tv] = sm[s.x[TOP] + tq];
 }
 
 // ---------------------------------------------------------------------------
@@ -1670,6 +1744,7 @@ struct hipbmg3d_hier {
     int nc = 0;
     double *d_chol = nullptr;
     long long *d_cidx = nullptr;
+    SmallPack pack{};                  // the levels k3_collapse_small may run (null: not packed)
     double *d_part = nullptr;
     long long npart = 0;
     double *d_sum = nullptr;
@@ -2073,6 +2148,24 @@ bool small_collapse(const hipbmg3d_hier *h, int top, SmallLds *s)
     return (size_t)s->total * sizeof(double) <= 64 * 1024;
 }
 
+// pack the levels that k3_collapse_small may run, once their operators are complete
+hipbmg_status small_pack(hipbmg3d_hier *h, hipStream_t s)
+{
+    SmallLds sl;
+    for (int l = 0; l < h->L && small_collapse(h, l, &sl); ++l) {
+        const Lev3 &v = h->lv[l];
+        double *d = nullptr, *i = nullptr;
+        if (l > 0) ST3(dalloc3(h, &d, PACK_DBL));
+        ST3(dalloc3(h, &i, (PACK_INT + 1) / 2));
+        const CLev c{v.g, v.npt, v.st, l > 0 ? v.w : nullptr, v.x[0], v.b, v.r};
+        hipLaunchKernelGGL(k3_small_pack, dim3(1), dim3(CWG3), 0, s, c, h->lv[l > 0 ? l - 1 : 0].g, d, (int *)i);
+        HIP3(hipGetLastError());
+        h->pack.d[l] = d;
+        h->pack.i[l] = (const int *)i;
+    }
+    return HIPBMG_OK;
+}
+
 // levels 0..top in one workgroup (top = 0: the coarse solve alone)
 hipbmg_status collapse(hipbmg3d_hier *h, int top, hipStream_t s)
 {
@@ -2093,9 +2186,9 @@ hipbmg_status collapse(hipbmg3d_hier *h, int top, hipStream_t s)
     if (small_collapse(h, top, &sl)) {
         const dim3 one(1), wg(CWG3);
         const size_t lds = (size_t)sl.total * sizeof(double);
-        if (top == 0) hipLaunchKernelGGL(k3_collapse_small<0>, one, wg, lds, s, a, sl);
-        else if (top == 1) hipLaunchKernelGGL(k3_collapse_small<1>, one, wg, lds, s, a, sl);
-        else hipLaunchKernelGGL(k3_collapse_small<2>, one, wg, lds, s, a, sl);
+        if (top == 0) hipLaunchKernelGGL(k3_collapse_small<0>, one, wg, lds, s, a, h->pack, sl);
+        else if (top == 1) hipLaunchKernelGGL(k3_collapse_small<1>, one, wg, lds, s, a, h->pack, sl);
+        else hipLaunchKernelGGL(k3_collapse_small<2>, one, wg, lds, s, a, h->pack, sl);
         HIP3(hipGetLastError());
         return HIPBMG_OK;
     }
@@ -2485,6 +2578,7 @@ extern "C" hipbmg_status hipbmg3d_setup(int nx, int ny, int nz, int npt, const d
         if (hipGetLastError() != hipSuccess) return bail(fail3(HIPBMG_EHIP, "setup kernel launch failed"));
     }
     if ((st = factor_coarsest(h, s)) != HIPBMG_OK) return bail(st);
+    if ((st = small_pack(h, s)) != HIPBMG_OK) return bail(st);
     // the collapse level: forced, or the model's argmin (section 3's model
     // with 3D counts).  Its terms for the small levels are measured here on
     // the hierarchy's own launches; larger levels use the process-wide
