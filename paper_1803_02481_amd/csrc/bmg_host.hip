@@ -1710,7 +1710,7 @@ static void fill_info_common(hipbmg_hier *h, hipbmg_info *info)
         info->rb_down[l] = l < h->L ? h->rb[l] : 0;
         info->rb_up[l] = l < h->L ? h->rb_up[l] : 0;
     }
-    info->rb_pipelined = h->fused3 ? (h->pass_tile ? pass_tile_steps() : h->rb3) : 0;
+    info->rb_pipelined = h->fused3 ? (h->pass_tile ? pass_tile_steps(h->nx, h->ny) : h->rb3) : 0;
     info->setup_ms = h->setup_ms;
     info->cluster_stages = h->cl_nstage;
     for (int k = 0; k < 4; ++k) {

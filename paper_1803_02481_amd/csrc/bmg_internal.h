@@ -177,9 +177,9 @@ template <typename T>
 hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s, const CheckArgs *chk = nullptr);
 
 // The pipelined finest pass (SV_FUSED3, SV_FUSED3_PN) of a small grid as tiles: a workgroup
-// owns a strip by pass_tile_steps() row-pair steps and writes one norm partial.
+// owns a strip by pass_tile_steps row-pair steps and writes one norm partial.
 // a.wform is ignored (the stored weights are read, the same values).
-int pass_tile_steps();
+int pass_tile_steps(int nx, int ny);
 void pass_tile_geometry(int nx, int ny, int *nstrips, int *nblocks, int *ntiles);
 template <typename T>
 hipError_t launch_tile_pass(int variant, StreamArgs<T> a, hipStream_t s);

@@ -1802,20 +1802,18 @@ __global__ __launch_bounds__(64 * NW) void k_tile_up(StreamArgs<T> a)
 // streaming pass: iterates and restricted residuals are the same bits, only the
 // norm's partial sums are in another order.
 //
-// Bound by latency: load, eight phases of two dependent updates (a division
-// each) and barriers; tiles of 12 and 16 waves own more of their rows but
-// spill.  us a cycle of a solve, streaming pass -> this one:
+// Bound by the waves of a SIMD taking turns at two dozen dependent updates each,
+// load and barriers; tiles of 12 and 16 waves own more of their rows but spill.
+// us a cycle of a solve with 8 waves, streaming pass -> this one:
 //         65^2          257^2         513^2         769 x 641     1025^2
 //   FP64  20.6 -> 17.7  43.2 -> 41.5  60.5 -> 57.5  77.0 -> 76.7  91.7 -> 101
 //   FP32  30.8 -> 27.6  48.0 -> 44.7  64.1 -> 59.3  78.9 -> 74.5  84.7 -> 83.3
-constexpr int PASS_NW = 8;
-
 // PN: P and its norm alone, storing the iterate (SV_FUSED3_PN), in the same
 // tiles, so that a capped solve's last norm is summed as the others are.
-template <typename T, bool ZC, bool PN>
-__global__ __launch_bounds__(64 * PASS_NW) void k_tile_pass(StreamArgs<T> a)
+template <typename T, int NW, bool ZC, bool PN>
+__global__ __launch_bounds__(64 * NW) void k_tile_pass(StreamArgs<T> a)
 {
-    constexpr int NPT = 5, NW = PASS_NW;
+    constexpr int NPT = 5;
     constexpr int HL = 5, HR = 5, OWN = 64 - HL - HR;
     constexpr int R = (NW * TILE_RPW - 16) / 2;
     // x of each wave's first [0] and last [1] row after the sweeps, alternating
@@ -2053,32 +2051,46 @@ __global__ __launch_bounds__(64 * PASS_NW) void k_tile_pass(StreamArgs<T> a)
     }
 }
 
-int pass_tile_steps() { return (PASS_NW * TILE_RPW - 16) / 2; }
+// 6 waves (4 row-pair steps) while those tiles find a CU each, else 8 waves (8
+// steps): fewer waves share a SIMD, more rows are halo.  us a cycle of a solve
+// in FP64 with 8 waves -> 6: 65^2 16.7 -> 15.4, 129^2 27.9 -> 26.5, 257^2 39.7 ->
+// 38.4, 385^2 51.6 -> 49.7; 513^2 (320 tiles) 55.4 -> 60.9.
+static int pass_waves(int nx, int ny)
+{
+    const int own = stream_owned_pairs(5, SV_FUSED3), r = (6 * TILE_RPW - 16) / 2;
+    return (long long)(((nx + 1) / 2 + own - 1) / own) * (((ny - 1) / 2 + r - 1) / r) <= 256 ? 6 : 8;
+}
+
+int pass_tile_steps(int nx, int ny) { return (pass_waves(nx, ny) * TILE_RPW - 16) / 2; }
 
 void pass_tile_geometry(int nx, int ny, int *nstrips, int *nblocks, int *ntiles)
 {
-    const int own = stream_owned_pairs(5, SV_FUSED3), r = pass_tile_steps();
+    const int own = stream_owned_pairs(5, SV_FUSED3), r = pass_tile_steps(nx, ny);
     *nstrips = ((nx + 1) / 2 + own - 1) / own;
     *nblocks = ((ny - 1) / 2 + r - 1) / r;
     *ntiles = *nstrips * *nblocks;
 }
 
-template <typename T, bool PN>
+template <typename T, int NW, bool PN>
 static void launch_pass(const StreamArgs<T> &a, hipStream_t s)
 {
-    if (a.zexc) hipLaunchKernelGGL((k_tile_pass<T, true, PN>), dim3(a.ntiles), dim3(64 * PASS_NW), 0, s, a);
-    else hipLaunchKernelGGL((k_tile_pass<T, false, PN>), dim3(a.ntiles), dim3(64 * PASS_NW), 0, s, a);
+    if (a.zexc) hipLaunchKernelGGL((k_tile_pass<T, NW, true, PN>), dim3(a.ntiles), dim3(64 * NW), 0, s, a);
+    else hipLaunchKernelGGL((k_tile_pass<T, NW, false, PN>), dim3(a.ntiles), dim3(64 * NW), 0, s, a);
 }
 
 template <typename T>
 hipError_t launch_tile_pass(int variant, StreamArgs<T> a, hipStream_t s)
 {
     pass_tile_geometry(a.nx, a.ny, &a.nstrips, &a.nblocks, &a.ntiles);
-    a.rb = pass_tile_steps();
-    if (a.ntiles <= 0) return hipErrorInvalidValue;
-    if (variant == SV_FUSED3) launch_pass<T, false>(a, s);
-    else if (variant == SV_FUSED3_PN) launch_pass<T, true>(a, s);
-    else return hipErrorInvalidValue;
+    a.rb = pass_tile_steps(a.nx, a.ny);
+    if (a.ntiles <= 0 || (variant != SV_FUSED3 && variant != SV_FUSED3_PN)) return hipErrorInvalidValue;
+    if (pass_waves(a.nx, a.ny) == 6) {
+        if (variant == SV_FUSED3) launch_pass<T, 6, false>(a, s);
+        else launch_pass<T, 6, true>(a, s);
+    } else {
+        if (variant == SV_FUSED3) launch_pass<T, 8, false>(a, s);
+        else launch_pass<T, 8, true>(a, s);
+    }
     return hipGetLastError();
 }
 template hipError_t launch_tile_pass<double>(int, StreamArgs<double>, hipStream_t);

@@ -18,7 +18,7 @@ def g(a):
 
 
 # (ny, nx): one pair of coarse vertices; a strip of exactly 54 column pairs, one
-# pair less and one more; row blocks of exactly 8 steps, one less and one more;
+# pair less and one more; row blocks of exactly 4 and 8 steps, one less and one more;
 # three strips; a thin grid each way; just within the limits of FP64 and FP32
 @pytest.mark.parametrize("shape", [(5, 5), (17, 107), (15, 105), (19, 109), (33, 33), (65, 325), (9, 1025),
                                    (513, 5), (609, 641), (993, 1025)])
@@ -42,7 +42,7 @@ def test_tiles_equal_streaming_pass(shape, precision, reaction, rescorr, monkeyp
         h.close()
     (u0, c0, h0, r0), (u1, c1, h1, r1) = runs
     assert r0 == 5
-    assert r1 == 8 if nx * ny <= (3 << 17 if precision == "fp64" else 1 << 20) else r1 > 0
+    assert r1 in (4, 8) if nx * ny <= (3 << 17 if precision == "fp64" else 1 << 20) else r1 > 0
     assert c1 == c0
     assert torch.equal(u1, u0)
     assert np.all(np.abs(h1 - h0) <= 1e-12 * np.abs(h0))
