@@ -82,7 +82,8 @@ typedef struct {
                              /* run in one persistent workgroup (0 = coarsest solve only)   */
     int residual_correction; /* 1: add r/C at fine-only vertices after interpolation (sec 3) */
     int max_cycles;          /* FP64: V-cycles; mixed: total inner cycles cap, default 500  */
-    int precision;           /* hipbmg_precision, default HIPBMG_FP64                       */
+    int precision;           /* hipbmg_precision, default HIPBMG_FP64; a mixed solve runs   */
+                             /* in FP64 where a diagonal is below the normal range of FP32  */
     int inner_max_cycles;    /* mixed: FP32 cycles per refinement step, default 32          */
     double inner_tol;        /* mixed: inner relative residual target, default 1e-4; a step */
                              /* stops its inner solve already at tol / (2 relres) when that */
@@ -155,7 +156,10 @@ hipbmg_status hipbmg_set_allocator(hipbmg_alloc_fn alloc_fn, hipbmg_free_fn free
  * performance model (sections 3 and 4) unless params->collapse_level >= 0.  With
  * cluster_wg = -1 (the default) and collapse_level = -1, l* and any
  * agglomeration stages above it come from the model's A* search over
- * (level, workgroups) states (section 4); info reports the path.
+ * (level, workgroups) states (section 4); info reports the path.  A hierarchy
+ * with both at their defaults applies its coarse levels of at most 2048 unknowns
+ * (1024 above a coarsest level of more than 64) as one dense operator, formed by
+ * its first solve, in place of the collapsed workgroup or stages of those levels.
  * coeffs is copied and may be freed after return.  params may be NULL for the
  * defaults.  Returns HIPBMG_ENOTSPD if the coarsest factorisation fails. */
 hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coeffs,
@@ -375,7 +379,7 @@ hipbmg_status hipbmg_profile_read(hipbmg_handle h, int precision, int kernel,
 /* Per-level totals recorded with enable = 2, for one precision: for level l,
  * ms_host[3l] the down leg (pre-relaxations, residual, restriction),
  * ms_host[3l+1] the up leg (interpolation and post-relaxations), ms_host[3l+2]
- * the collapse launch whose top level is l; n_host the matching launch
+ * the collapse launch, or dense product, whose top level is l; n_host the matching launch
  * counts.  Both arrays hold 3 * HIPBMG_MAX_LEVELS entries (n_host may be
  * NULL).  For the pipelined finest level the single pass is counted in its
  * up leg. */

@@ -318,6 +318,7 @@ struct hipbmg_hier {
     bool pass_tile = false;     // the pass runs as tiles
     int zexc[2] = {0, 0};       // the pipelined pass forms the finest diagonal ([0] FP64, [1] FP32)
     int wform = 0;              // the FP64 pipelined pass forms the interpolation weights
+    int fp32_tiny = 0;          // a diagonal is below the FP32 normal range: mixed solves run in FP64
     double *x3_64 = nullptr;    // third iterate buffer of the pipelined finest level
     float *x3_32 = nullptr;
     // device-side stopping: run flag, and a ring of host-mapped slots through
@@ -943,12 +944,15 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
     if (st != HIPBMG_OK) return bail(st);
 
     // FP32 edge-form copy of every level for mixed precision
+    int *d_tiny = nullptr;
     if (prm.precision == HIPBMG_MIXED) {
         st = alloc_levels(h, h->lv32, sx, sy, s);
         if (st != HIPBMG_OK) return bail(st);
+        st = dalloc(h, &d_tiny, 1, s);
+        if (st != HIPBMG_OK) return bail(st);
         for (int l = 0; l < L; ++l) {
             int cnx = l ? sx[l - 1] : 0, cny = l ? sy[l - 1] : 0;
-            if (launch_demote_level(h->lv[l], h->lv32[l], cnx, cny, s) != hipSuccess)
+            if (launch_demote_level(h->lv[l], h->lv32[l], cnx, cny, d_tiny, s) != hipSuccess)
                 return bail(fail(HIPBMG_EHIP, "demote launch failed"));
             if (h->zc9[0][l]) {
                 // the FP32 copy's excess at the deep vertices: zero if the
@@ -1192,9 +1196,12 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
         h->dense_top = dense_top;
     }
     if (h->dense_top < 0 && h->lstar >= L - 1) h->fused3 = 0;   // the finest level itself is collapsed
+    if (d_tiny && hipMemcpyAsync(h->h_scal + 7, d_tiny, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess)
+        return bail(fail(HIPBMG_EHIP, "hipMemcpyAsync failed"));
     if (hipStreamSynchronize(s) != hipSuccess) return bail(fail(HIPBMG_EHIP, "setup failed: %s",
                                                              hipGetErrorString(hipGetLastError())));
     h->setup_ms = now_ms() - t0;
+    if (d_tiny) std::memcpy(&h->fp32_tiny, h->h_scal + 7, sizeof(int));
     *out = h;
     return HIPBMG_OK;
 }
@@ -1844,8 +1851,9 @@ extern "C" hipbmg_status hipbmg_solve(hipbmg_handle h, const double *b, double *
     HIPCHK(launch_finalize_norm(h->d_partials, nparts, h->d_scal, s, h->d_flags, h->ring_dev + 4 * RING, bn_tag));
     double bnorm = 1.0;
     const double *res = F.x[0];
-    hipbmg_status st = h->prm.precision == HIPBMG_MIXED ? solve_mixed(h, tol, s, info, bn_tag, &bnorm)
-                                                         : solve_fp64(h, tol, s, info, &res, bn_tag, &bnorm);
+    const bool mixed = h->prm.precision == HIPBMG_MIXED && !h->fp32_tiny;
+    hipbmg_status st = mixed ? solve_mixed(h, tol, s, info, bn_tag, &bnorm)
+                             : solve_fp64(h, tol, s, info, &res, bn_tag, &bnorm);
     if (!std::isfinite(bnorm)) return st;
     if (bnorm == 0.0 && st == HIPBMG_OK) {
         HIPCHK(hipMemsetAsync(u, 0, (size_t)nx * ny * sizeof(double), s));
@@ -3349,6 +3357,7 @@ extern "C" hipbmg_status hipbmg_setup_batched(int nprob, const int *nx, const in
                 return bail(sts[p]);
             }
         for (int p = 0; p < nprob; ++p) {
+            if (B->hs[p]->fp32_tiny) B->prm.precision = HIPBMG_FP64;
             B->max_nx = std::max(B->max_nx, nx[p]);
             B->max_ny = std::max(B->max_ny, ny[p]);
         }
@@ -3465,7 +3474,7 @@ extern "C" hipbmg_status hipbmg_setup_batched(int nprob, const int *nx, const in
         B->cc64.assign(nprob, 0);
         B->cc32.assign(nprob, 0);
         if (pipe) {
-            if (prm.precision == HIPBMG_MIXED) {
+            if (B->prm.precision == HIPBMG_MIXED) {
                 chk(balloc(B, &B->d_rb32, nprob, s));
                 chk(balloc(B, &B->d_eptr, nprob, s));
             } else {

@@ -14,7 +14,7 @@ hipError_t launch_stage_in(const double *b, const double *u, double *bdst, doubl
 hipError_t launch_stage_out(const double *src, double *u, int nx, int ny, int pitch, hipStream_t s);
 // FP64 level -> FP32 edge-form level (and its interpolation weights)
 hipError_t launch_demote_level(const LevelDev<double> &d, const LevelDev<float> &f, int cnx,
-                               int cny, hipStream_t s);
+                               int cny, int *tiny, hipStream_t s);
 // r32 = (float)(b - A u) with FP64 partial sums of squares; *nparts partials written
 hipError_t launch_ir_residual(const LevelDev<double> &d, const double *u, float *r32, int pitchf,
                               double *partials, int *nparts, hipStream_t s);

@@ -104,7 +104,9 @@ hipError_t launch_stage_out(const double *src, double *u, int nx, int ny, int pi
 // rounded to float.  The FP32 kernels form A x as
 //   sum_q conn_pq (x_p - x_q) + E_p x_p,
 // so the zero row sums of pure-diffusion rows survive the rounding exactly.
-__global__ void k_demote_level(LevelDev<double> d, LevelDev<float> f)
+// *tiny is set where an interior diagonal is below the normal range of a float:
+// the FP32 kernels divide by its reciprocal, which may overflow.
+__global__ void k_demote_level(LevelDev<double> d, LevelDev<float> f, int *tiny)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y;
@@ -120,6 +122,7 @@ __global__ void k_demote_level(LevelDev<double> d, LevelDev<float> f)
         double rs = d.W[p] + d.W[p + 1] + d.S[p] + d.S[p + P] + d.SW[p] + d.SW[p + P + 1] + d.SE[p] +
                     d.SE[p + P - 1];
         e = (float)(d.C[p] - rs);
+        if (fabs(d.C[p]) < 1.1754943508222875e-38) *tiny = 1;
     }
     f.C[pf] = e;
 }
@@ -135,9 +138,9 @@ __global__ void k_demote_weights(const double *__restrict__ wd, size_t pd, int p
 }
 
 hipError_t launch_demote_level(const LevelDev<double> &d, const LevelDev<float> &f, int cnx,
-                               int cny, hipStream_t s)
+                               int cny, int *tiny, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_demote_level, dim3((d.nx + 255) / 256, d.ny), dim3(256), 0, s, d, f);
+    hipLaunchKernelGGL(k_demote_level, dim3((d.nx + 255) / 256, d.ny), dim3(256), 0, s, d, f, tiny);
     if (d.wt)
         hipLaunchKernelGGL(k_demote_weights, dim3((cnx + 255) / 256, cny), dim3(256), 0, s, d.wt,
                            d.cplane, d.cpitch, f.wt, f.cplane, f.cpitch, cnx, cny);
