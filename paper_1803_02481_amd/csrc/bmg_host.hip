@@ -1517,19 +1517,17 @@ static hipbmg_status wait_bnorm(hipbmg_hier *h, double tag, hipStream_t s, doubl
 
 // Whether the first launch below the finest level takes the previous cycle's
 // test along as one more workgroup: the dense operator, a tile kernel, or a
-// streaming down leg of up to 2^21 vertices.  The launch then runs once after
-// the stopping cycle too (16 us at most on 513^2; 24 us on 1025^2 in FP64, 16 in
-// FP32), where a test of its own costs 4-6 us and a gap every cycle (2049^2 in
-// mixed precision 11.96 -> 11.47 ms a solve of some 80 cycles); on 2049^2 it
-// would be 70 us, ten cycles' tests.  Nothing it writes is read again: the
-// stopping cycle's correction is in the level's other buffer.
+// streaming down leg.  A test of its own costs 4-6 us and a gap every cycle
+// (2049^2 in mixed precision 11.96 -> 11.47 ms a solve of some 80 cycles, 4097^2
+// in FP64 46.54 -> 46.15); the launch runs once in vain after the stopping cycle,
+// 16-24 us at most: a larger leg's tiles look at the flag again on the way.
+// Nothing it writes is read again: the stopping cycle's correction is in the
+// level's other buffer.
 static bool check_rides(const hipbmg_hier *h)
 {
     const int top = h->L - 2;
     const int gtop = h->dense_top >= 0 ? h->dense_top : h->cl_nstage > 0 ? h->cl_hi[0] : h->lstar;
-    if (gtop == top) return h->dense_top == top;
-    const LevelDev<double> &A = h->lv[top];
-    return A.npt == 9 && (long long)A.nx * A.ny <= 1LL << 21;
+    return gtop == top ? h->dense_top == top : h->lv[top].npt == 9;
 }
 
 // Run up to max_cycles V-cycles on the hierarchy lv (FP64 levels, or the FP32

@@ -468,7 +468,13 @@ __device__ __forceinline__ void stream_tile(const StreamArgs<T> &a, const int ti
 // second colour-by-colour sweep.  A's results are correct on fewer lanes than
 // a loaded row, so the halo is the sum of both stages' halos, and each block
 // of rows starts with three A steps and two B steps of prologue.
-template <typename T, int NPT, bool ZX, bool STOREQ = true, bool ZC9 = false>
+// LOOK: the launch carries the test that may clear its own run flag; the flag is
+// read once more some steps in, when the test has had time, and a tile whose
+// solve is over ends there (nothing a launch past the stopping cycle writes is
+// read).
+constexpr int LOOK_STEPS = 8;
+
+template <typename T, int NPT, bool ZX, bool STOREQ = true, bool ZC9 = false, bool LOOK = false>
 __device__ __forceinline__ void stream2_tile(const StreamArgs<T> &a, const int tile)
 {
     constexpr int HA = 1 + (NPT == 9);          // lanes of A's garbage margin per side
@@ -556,6 +562,11 @@ __device__ __forceinline__ void stream2_tile(const StreamArgs<T> &a, const int t
     step(jfirst - 2, M1{}, M0{}, std::true_type{});
     step(jfirst, M1{}, M1{}, std::true_type{});
     int ja = jfirst + 2;
+    if (LOOK) {
+        const int jt = min(jfirst + 2 * LOOK_STEPS, jlast + 2);
+        for (; ja < jt; ja += 2) step(ja, M1{}, M2{}, std::true_type{});
+        if (a.active && __hip_atomic_load(a.active, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
+    }
     for (; ja < jlast + 2; ja += 2) step(ja, M1{}, M2{}, std::true_type{});
     step(ja, M1{}, M2{}, std::false_type{});
 }
@@ -980,7 +991,7 @@ __global__ __launch_bounds__(64) void k_stream2(StreamArgs<T> a)
 // k_stream2 of a 9-point coarse level from zero, with the previous cycle's test
 // as one more workgroup, the first (its XCD's seven neighbours in the grid are
 // empty, so that the others keep their tile order)
-template <typename T, bool STOREQ, bool ZC9>
+template <typename T, bool STOREQ, bool ZC9, bool LOOK>
 __global__ __launch_bounds__(64) void k_stream2_check(StreamArgs<T> a, CheckArgs chk)
 {
     if (blockIdx.x < 8) {
@@ -991,17 +1002,22 @@ __global__ __launch_bounds__(64) void k_stream2_check(StreamArgs<T> a, CheckArgs
     const int b = blockIdx.x - 8, per = (gridDim.x - 8) >> 3;
     const int tile = (b & 7) * per + (b >> 3);
     if (tile >= a.ntiles) return;
-    stream2_tile<T, 9, true, STOREQ, ZC9>(a, tile);
+    stream2_tile<T, 9, true, STOREQ, ZC9, LOOK>(a, tile);
 }
 
 template <typename T>
 hipError_t launch_stream2_check(int variant, const StreamArgs<T> &a, int grid, const CheckArgs &chk, hipStream_t s)
 {
     const dim3 g(grid + 8), b(64);
-    if (variant == SV_SWEEP2_RQ_ZX) hipLaunchKernelGGL((k_stream2_check<T, true, false>), g, b, 0, s, a, chk);
+    // the second look at the flag costs a launch 2 % (15.0 -> 15.3 us on 1025^2 in
+    // FP32) and ends a 70 us one after 15: levels beyond 2^21 vertices take it
+    const bool look = (long long)a.nx * a.ny > 1LL << 21;
+    if (variant == SV_SWEEP2_RQ_ZX) hipLaunchKernelGGL((k_stream2_check<T, true, false, false>), g, b, 0, s, a, chk);
     else if (variant != SV_SWEEP2_R_ZX) return hipErrorInvalidValue;
-    else if (a.zexc) hipLaunchKernelGGL((k_stream2_check<T, false, true>), g, b, 0, s, a, chk);
-    else hipLaunchKernelGGL((k_stream2_check<T, false, false>), g, b, 0, s, a, chk);
+    else if (a.zexc && look) hipLaunchKernelGGL((k_stream2_check<T, false, true, true>), g, b, 0, s, a, chk);
+    else if (a.zexc) hipLaunchKernelGGL((k_stream2_check<T, false, true, false>), g, b, 0, s, a, chk);
+    else if (look) hipLaunchKernelGGL((k_stream2_check<T, false, false, true>), g, b, 0, s, a, chk);
+    else hipLaunchKernelGGL((k_stream2_check<T, false, false, false>), g, b, 0, s, a, chk);
     return hipGetLastError();
 }
 template hipError_t launch_stream2_check<double>(int, const StreamArgs<double> &, int, const CheckArgs &, hipStream_t);

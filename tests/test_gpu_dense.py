@@ -120,3 +120,20 @@ def test_check_rides_a_streaming_leg(shape, reaction, monkeypatch):
     assert got[0][3] <= 1e-10
     for w, cyc, hist, _ in got[1:]:
         assert torch.equal(w, got[0][0]) and cyc == got[0][1] and hist == got[0][2]
+
+
+def test_check_rides_a_leg_that_looks_again():
+    # a level below the finest beyond 2^21 vertices: its tiles end early once the
+    # test they carry is met
+    ny, nx = 1025, 8321
+    planes = HB.fv5_from_cells(g(inputs.cells_lognormal(nx, ny, 1.0, seed=17)))
+    b = g(inputs.load_uniform(nx, ny, seed=18))
+    for scale in (1.0, 1.0 + 1e-6):   # formed and loaded diagonals
+        p = planes.clone()
+        p[0, 1:-1, 1:-1] *= scale
+        h = HB.Hierarchy(p)
+        u, info = h.solve(b, tol=1e-8)
+        again, _ = h.solve(b, tol=1e-8)
+        v, capped = HB.Hierarchy(p, max_cycles=info.cycles).solve(b, tol=1e-30, check=False)
+        assert torch.equal(u, v) and torch.equal(u, again)
+        assert info.history() == capped.history() and info.cycles >= 3
