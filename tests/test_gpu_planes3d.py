@@ -98,3 +98,21 @@ def test_stopping_cycle_is_the_capped_one(shape, nu, use_graph):
     capped = HB.Hierarchy3(planes, nu1=nu[0], nu2=nu[1], use_graph=1 - use_graph, max_cycles=info.cycles)
     v, info3 = capped.solve(b, tol=1e-30, check=False)
     assert torch.equal(u, v) and info.history() == info3.history() and info3.cycles == info.cycles
+
+
+# the level below the finest has planes of 64 cells (one launch a sweep) as 8 x 8,
+# 1 x 64, 32 x 2 (and a single odd plane), of 72 and 68 (two launches), of 4
+@pytest.mark.parametrize("shape", [(33, 33, 33), (17, 33, 33), (9, 257, 5), (5, 9, 129), (17, 37, 33), (17, 69, 17),
+                                   (17, 9, 9)])
+@pytest.mark.parametrize("nu", [(2, 1), (1, 2), (3, 3)])
+def test_whole_sweeps_are_the_single_workgroup(shape, nu):
+    nz, ny, nx = shape
+    planes = planes_of(7, shape, 91)
+    b = g(inputs.load3_uniform(nx, ny, nz, seed=92))
+    u0 = g(np.random.default_rng(93).standard_normal(shape))
+    got = []
+    for ls in (0, HB.Hierarchy3(planes).L - 1):
+        h = HB.Hierarchy3(planes, collapse_level=ls, nu1=nu[0], nu2=nu[1], max_cycles=3)
+        u, info = h.solve(b, u0=u0, tol=1e-30, check=False)
+        got.append((u, info.history()))
+    assert torch.equal(got[0][0], got[1][0]) and got[0][1] == got[1][1]
