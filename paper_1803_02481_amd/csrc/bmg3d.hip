@@ -2787,6 +2787,7 @@ extern "C" hipbmg_status hipbmg3d_solve(hipbmg3d_handle h, const double *b, doub
     hipStream_t s = (hipStream_t)stream;
     auto t0 = std::chrono::steady_clock::now();
     Lev3 &f = h->lv[h->L - 1];
+    hbmg::Drain drain{s};
     ST3(to_oct(f.g, b, f.b, 1, s));
     ST3(to_oct(f.g, u, f.x[0], 1, s));
     h->cur = 0;
@@ -2835,6 +2836,7 @@ extern "C" hipbmg_status hipbmg3d_solve(hipbmg3d_handle h, const double *b, doub
         HIP3(hipStreamSynchronize(s));
         if (rc == HIPBMG_ENOCONV) fail3(rc, "tolerance not reached in %d cycles", cycles);
     }
+    drain.done = true;   // both ways here have synchronised
     if (h->prof) ST3(prof_collect(h));
     if (info) {
         info->cycles = cycles;

@@ -1843,6 +1843,9 @@ extern "C" hipbmg_status hipbmg_solve(hipbmg_handle h, const double *b, double *
         memset(info, 0, sizeof *info);
         fill_info_common(h, info);
     }
+    // cycles may be on the stream when a solve ends early (||b|| is waited for
+    // behind them): every return leaves the handle idle
+    Drain drain{s};
     int nparts = 0;
     HIPCHK(launch_stage_in(b, u, F.b, F.x[0], nx, ny, F.pitch, h->d_partials, &nparts, s));
     const double bn_tag = next_tag(h);
@@ -1856,6 +1859,7 @@ extern "C" hipbmg_status hipbmg_solve(hipbmg_handle h, const double *b, double *
     if (bnorm == 0.0 && st == HIPBMG_OK) {
         HIPCHK(hipMemsetAsync(u, 0, (size_t)nx * ny * sizeof(double), s));
         HIPCHK(hipStreamSynchronize(s));
+        drain.done = true;
         if (info) info->solve_ms = now_ms() - t0;
         return HIPBMG_OK;
     }
@@ -1864,6 +1868,7 @@ extern "C" hipbmg_status hipbmg_solve(hipbmg_handle h, const double *b, double *
     std::string msg = g_err;
     HIPCHK(launch_stage_out(res, u, nx, ny, F.pitch, s));
     HIPCHK(hipStreamSynchronize(s));
+    drain.done = true;
     if (info) info->solve_ms = now_ms() - t0;
     g_err = msg;
     return st;
@@ -2106,12 +2111,14 @@ extern "C" hipbmg_status hipbmg_op32_inner(hipbmg_handle h, const float *r, floa
     HIPCHK(hipStreamSynchronize(s));
     const float *res = nullptr;
     int done = 0;
+    Drain drain{s};
     HIPCHK(launch_flags_reset(h->d_flags, s));
     STCHK(run_cycles<float>(h, h->lv32, h->d_lv32, true, cycles, inner_tol, h->d_scal + 2, s, &res, &done, nullptr));
     if (hist_host)
         for (int m = 0; m < done; ++m) hist_host[m] = h->hist[m];
     STCHK(from_pitched(e, res, F.pitch, F.nx, F.ny, s));
     HIPCHK(hipStreamSynchronize(s));
+    drain.done = true;
     if (cycles_host) *cycles_host = done;
     return HIPBMG_OK;
 }

@@ -35,6 +35,15 @@ hipError_t pinned_small(void **host, void **dev, size_t bytes);
 // spins until *v, which a kernel on stream s writes, holds `tag`; a stream that
 // has drained without it, or failed, ends the wait with an error
 hipError_t wait_tag(const volatile double *v, double tag, hipStream_t s);
+// waits for the stream on every way out of a solve that has not done so itself
+struct Drain {
+    hipStream_t s;
+    bool done = false;
+    ~Drain()
+    {
+        if (!done) (void)hipStreamSynchronize(s);
+    }
+};
 void pinned_small_free(void *host);
 // a zeroed pinned host block of at least `bytes` (its size, a power of two of
 // at least 4 KiB, in *cap) from a per-size pool kept for the process;

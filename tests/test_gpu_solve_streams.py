@@ -1,0 +1,61 @@
+"""A solve leaves its handle idle whichever way it ends: the next one may come
+on another stream."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1803_02481_amd import hipbmg as HB
+from paper_1803_02481_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def g(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+# a right-hand side that is not finite ends a solve after its first cycle is
+# enqueued; as the handle's first one it also forms the dense coarse operator.
+# A level of 1833 unknowns takes the longest to form (769 x 641)
+@pytest.mark.parametrize("precision", [HB.FP64, HB.MIXED], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("prm", [{}, {"nu1": 1, "nu2": 2}])
+@pytest.mark.parametrize("shape", [(65, 65), (257, 257), (641, 769)])
+def test_a_failed_solve_then_one_on_another_stream(shape, prm, precision):
+    ny, nx = shape
+    planes = HB.fv5_from_cells(g(inputs.cells_lognormal(nx, ny, 1.0, seed=31)))
+    b = g(inputs.load_uniform(nx, ny, seed=32))
+    bad = b.clone()
+    bad[ny // 2, nx // 2] = float("inf")
+    ref, iref = HB.Hierarchy(planes, precision=precision, **prm).solve(b, tol=1e-9)
+    h = HB.Hierarchy(planes, precision=precision, **prm)
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(3):
+        with torch.cuda.stream(one):
+            v = torch.zeros_like(b)
+            with pytest.raises(HB.HipBMGError) as e:
+                h.solve(bad, v, tol=1e-9)
+            assert e.value.status == HB.ENAN
+            assert one.query()   # nothing of the failed solve is left on its stream
+        with torch.cuda.stream(two):
+            u, info = h.solve(b, tol=1e-9)
+        assert torch.equal(u, ref) and info.history() == iref.history()
+
+
+def test_a_failed_3d_solve_then_one_on_another_stream():
+    planes = HB.fv7_from_cells(g(inputs.cells3_lognormal(33, 33, 33, sigma=1.0, seed=33)))
+    b = g(inputs.load3_uniform(33, 33, 33, seed=34))
+    bad = b.clone()
+    bad[16, 16, 16] = float("nan")
+    ref, iref = HB.Hierarchy3(planes).solve(b, tol=1e-9)
+    h = HB.Hierarchy3(planes)
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(3):
+        with torch.cuda.stream(one):
+            with pytest.raises(HB.HipBMGError) as e:
+                h.solve(bad, tol=1e-9)
+            assert e.value.status == HB.ENAN and one.query()
+        with torch.cuda.stream(two):
+            u, info = h.solve(b, tol=1e-9)
+        assert torch.equal(u, ref) and info.history() == iref.history()
