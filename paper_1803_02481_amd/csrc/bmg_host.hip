@@ -1462,9 +1462,10 @@ static hipError_t enqueue_vcycle(hipbmg_hier *h, const std::vector<LevelDev<T>> 
 
 // Form the dense operator of levels 0..dense_top from the FP64 levels (the
 // FP32 cycles of a mixed solve use the same one), on the first solve's stream:
-// a hierarchy that is never solved with does not pay for it.  Every solve
-// synchronises its stream before it returns, so later solves on other streams
-// see it complete.
+// a hierarchy that is never solved with does not pay for it.  run_cycles marks it
+// as formed once a test launched behind it has arrived: a launch that was
+// captured, or failed, is not taken for a matrix.  Every solve synchronises its
+// stream before it returns, so later solves on other streams see it complete.
 static hipbmg_status ensure_dense(hipbmg_hier *h, hipStream_t s)
 {
     if (h->dense_top < 0 || h->dense_built) return HIPBMG_OK;
@@ -1486,7 +1487,6 @@ static hipbmg_status ensure_dense(hipbmg_hier *h, hipStream_t s)
     a.M = h->d_dense;
     a.ld = h->dense_ld;
     HIPCHK(launch_dense_build(a, h->dense_n, s));
-    h->dense_built = 1;
     return HIPBMG_OK;
 }
 
@@ -1668,6 +1668,7 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
         }
     }
     while (!stopped && seen < k) STCHK(look());
+    h->dense_built = h->dense_top >= 0;
     if (!stopped) kdone = k;
     if (h->prof_on) HIPCHK(hipStreamSynchronize(s));
     prof_collect(h, true, kdone);

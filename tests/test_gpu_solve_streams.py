@@ -1,5 +1,7 @@
 """A solve leaves its handle idle whichever way it ends: the next one may come
 on another stream."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -59,3 +61,37 @@ def test_a_failed_3d_solve_then_one_on_another_stream():
         with torch.cuda.stream(two):
             u, info = h.solve(b, tol=1e-9)
         assert torch.equal(u, ref) and info.history() == iref.history()
+
+
+def hip_runtime():
+    for line in open("/proc/self/maps"):
+        if "libamdhip64" in line:
+            return ctypes.CDLL(line.split()[-1])
+    raise RuntimeError("no HIP runtime in this process")
+
+
+# a first solve on a stream that is being captured is refused (it waits for its
+# results), and what it captured has not run: the next solve forms the dense
+# operator itself
+@pytest.mark.parametrize("shape", [(33, 65), (129, 129)])
+def test_a_solve_after_one_refused_under_capture(shape):
+    ny, nx = shape
+    planes = HB.fv5_from_cells(g(inputs.cells_lognormal(nx, ny, 1.0, seed=35)))
+    b = g(inputs.load_uniform(nx, ny, seed=36))
+    ref, iref = HB.Hierarchy(planes).solve(b, tol=1e-9)
+    h = HB.Hierarchy(planes)
+    u = torch.zeros_like(b)
+    hip, s, graph = hip_runtime(), torch.cuda.Stream(), ctypes.c_void_p()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        stream = ctypes.c_void_p(s.cuda_stream)
+        assert hip.hipStreamBeginCapture(stream, 2) == 0   # relaxed
+        with pytest.raises(HB.HipBMGError) as e:
+            h.solve(b, u, tol=1e-9)
+        assert e.value.status == HB.EHIP
+        hip.hipStreamEndCapture(stream, ctypes.byref(graph))
+        if graph.value:
+            hip.hipGraphDestroy(graph)
+        hip.hipGetLastError()
+    v, info = h.solve(b, tol=1e-9)
+    assert torch.equal(v, ref) and info.history() == iref.history()
