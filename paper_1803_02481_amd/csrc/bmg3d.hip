@@ -19,6 +19,7 @@
 #include "bmg_internal.h"
 #include "bmg_model.h"
 #include "bmg_quot.h"
+#include "bmg_tags.h"
 
 #include <algorithm>
 #include <chrono>
@@ -1842,7 +1843,7 @@ struct hipbmg3d_hier {
     long long npart = 0;
     double *d_sum = nullptr;
     double *slot = nullptr, *slot_dev = nullptr;   // host-mapped {sum, tag}
-    unsigned run_id = 0;       // solves so far: the tags' high bits
+    hbmg::Tags tags;
     double *d_nat = nullptr;   // plain-layout staging of the op_* entry points
     std::vector<void *> allocs;
     int cur = 0;                       // the finest iterate's buffer
@@ -2797,7 +2798,8 @@ extern "C" hipbmg_status hipbmg3d_solve(hipbmg3d_handle h, const double *b, doub
     }
     hipLaunchKernelGGL(k3_sumsq, dim3(nblk(f.g.field)), dim3(256), 0, s, f.g, (const double *)f.b, h->d_part);
     HIP3(hipGetLastError());
-    const double tag0 = (double)(++h->run_id & 0xfffffu) * 4294967296.0;
+    // ||b||'s tag, and one a cycle behind it
+    const double tag0 = h->tags.take(1 + (std::uint64_t)std::max(h->prm.max_cycles, 0));
     ST3(reduce_sum(h, h->d_part, (long long)nblk(f.g.field), tag0, s));
     double bb = 0.0;
     ST3(wait_sum(h, tag0, s, &bb));

@@ -5,6 +5,7 @@
 #include "bmg_internal.h"
 #include "bmg_misc.h"
 #include "bmg_model.h"
+#include "bmg_tags.h"
 
 #include <atomic>
 #include <thread>
@@ -326,10 +327,9 @@ struct hipbmg_hier {
     int *d_flags = nullptr;               // [0] run, [1] stopping cycle, [2] reason
     std::vector<double> hist;             // relres after each cycle of the current run
     int stop_reason = 0;                  // of that run: 1 test met, 2 not finite, 0 neither
-    // RING x {relres, run, stopping cycle, tag}, then one {norm, -, -, tag};
-    // a tag names a run and a cycle, so a slot of an earlier one never matches
+    // RING x {relres, run, stopping cycle, tag}, then one {norm, -, -, tag}
     double *ring_host = nullptr, *ring_dev = nullptr;
-    unsigned run_id = 0;
+    Tags tags;
     int ahead = 2;                        // cycles enqueued beyond the last test seen
     // live timing of the finest-level streaming kernels (HIP events on the
     // solve stream), kept in a ring and collected in order once complete
@@ -1494,9 +1494,6 @@ template <typename T> static T *&x3_of(hipbmg_hier *h);
 template <> double *&x3_of<double>(hipbmg_hier *h) { return h->x3_64; }
 template <> float *&x3_of<float>(hipbmg_hier *h) { return h->x3_32; }
 
-// A fresh tag: the run's number in the high bits, room for a cycle number below
-static double next_tag(hipbmg_hier *h) { return (double)(++h->run_id & 0xfffffu) * 4294967296.0; }
-
 // Wait until slot `idx` of the ring carries `tag`.  The kernel that writes it is
 // on stream s, so a stream that has drained without it means a failed launch.
 static hipbmg_status wait_slot(hipbmg_hier *h, int idx, double tag, hipStream_t s)
@@ -1558,7 +1555,7 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
     T *xb[3] = {F.x[0], F.x[1], pipe ? x3_of<T>(h) : nullptr};
     h->hist.clear();
     h->stop_reason = 0;
-    const double tag0 = next_tag(h);
+    const double tag0 = h->tags.take(max_cycles) - 1.0;   // cycle k's is tag0 + k
 
     std::vector<const T *> res_after((size_t)max_cycles + 1, F.x[0]);
     // pipelined: the inputs of each cycle's finest pass (iterate buffer,
@@ -1791,7 +1788,7 @@ static hipbmg_status solve_mixed(hipbmg_hier *h, double tol, hipStream_t s, hipb
             if (bnorm == 0.0) return HIPBMG_OK;
         }
         // the norm's launch starts the inner run's flags as well
-        const double tag = next_tag(h);
+        const double tag = h->tags.next();
         HIPCHK(launch_finalize_norm(h->d_partials, np, h->d_scal + 2, s, h->d_flags, h->ring_dev + 4 * RING, tag));
         STCHK(wait_slot(h, RING, tag, s));
         const double rnorm = h->ring_host[4 * RING];
@@ -1849,7 +1846,7 @@ extern "C" hipbmg_status hipbmg_solve(hipbmg_handle h, const double *b, double *
     Drain drain{s};
     int nparts = 0;
     HIPCHK(launch_stage_in(b, u, F.b, F.x[0], nx, ny, F.pitch, h->d_partials, &nparts, s));
-    const double bn_tag = next_tag(h);
+    const double bn_tag = h->tags.next();
     HIPCHK(launch_finalize_norm(h->d_partials, nparts, h->d_scal, s, h->d_flags, h->ring_dev + 4 * RING, bn_tag));
     double bnorm = 1.0;
     const double *res = F.x[0];
