@@ -29,6 +29,14 @@ __device__ __forceinline__ void slot_write(double *slot, double v0, double v1, d
     v[3] = tag;
 }
 
+// The run flag in a launch whose extra workgroup may clear it meanwhile.  Two
+// reads may differ, so a workgroup acts on one: a lone wave on its first lane's, a
+// larger one on thread 0's, handed round in LDS.
+__device__ __forceinline__ int run_flag(const int *active)
+{
+    return active ? __hip_atomic_load(active, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1;
+}
+
 // thread 0, with the partials' sum: the test and its outcome
 __device__ __forceinline__ void check_sum(const CheckArgs &c, double sum)
 {
@@ -43,7 +51,7 @@ __device__ __forceinline__ void check_sum(const CheckArgs &c, double sum)
         c.flags[1] = c.k;
         c.flags[2] = 1;
     }
-    c.flags[0] = run;
+    __hip_atomic_store(c.flags, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     slot_write(c.slot, rel, (double)run, (double)c.flags[1], c.tag);
 }
 

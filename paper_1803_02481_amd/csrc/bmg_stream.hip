@@ -565,7 +565,7 @@ __device__ __forceinline__ void stream2_tile(const StreamArgs<T> &a, const int t
     if (LOOK) {
         const int jt = min(jfirst + 2 * LOOK_STEPS, jlast + 2);
         for (; ja < jt; ja += 2) step(ja, M1{}, M2{}, std::true_type{});
-        if (a.active && __hip_atomic_load(a.active, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
+        if (__builtin_amdgcn_readfirstlane(run_flag(a.active)) == 0) return;
     }
     for (; ja < jlast + 2; ja += 2) step(ja, M1{}, M2{}, std::true_type{});
     step(ja, M1{}, M2{}, std::false_type{});
@@ -998,7 +998,7 @@ __global__ __launch_bounds__(64) void k_stream2_check(StreamArgs<T> a, CheckArgs
         if (blockIdx.x == 0) cycle_check_wave(chk);
         return;
     }
-    if (a.active && *a.active == 0) return;
+    if (__builtin_amdgcn_readfirstlane(run_flag(a.active)) == 0) return;
     const int b = blockIdx.x - 8, per = (gridDim.x - 8) >> 3;
     const int tile = (b & 7) * per + (b >> 3);
     if (tile >= a.ntiles) return;
@@ -1546,12 +1546,15 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArg
     constexpr int R = (NW * TILE_RPW - 10) / 2;
     __shared__ T xs[2][NW][64][2];   // x of each wave's first [0] and last [1] row
     __shared__ T rs[NW][64][2];      // residual of each wave's last row
+    __shared__ int go;
     const int tile = blockIdx.x;
     if (tile >= a.ntiles) {   // the extra workgroup
         cycle_check(chk);
         return;
     }
-    if (a.active && *a.active == 0) return;
+    // with the test along, the flag is looked at behind the first barrier
+    const bool rides = chk.partials != nullptr;
+    if (!rides && a.active && *a.active == 0) return;
     const int strip = tile % a.nstrips, blk = tile / a.nstrips;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int t = strip * OWN + lane - HL;
@@ -1615,6 +1618,7 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArg
         }
         return r;
     };
+    if (rides && threadIdx.x == 0) go = run_flag(a.active);
 #pragma unroll
     for (int sweep = 0; sweep < 2; ++sweep) {
         {   // even rows: colours 0 and 1 (the first sweep starts from x = 0)
@@ -1625,6 +1629,7 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArg
             xs[0][w][lane][1] = rw[0].x1;
         }
         __syncthreads();
+        if (sweep == 0 && rides && go == 0) return;
         {   // odd rows: colours 2 and 3
             tile_relax_row(rw[0], rw[1], rw[2], jw0 + 1, L);
             const Row<T> a3 = above();
