@@ -1146,8 +1146,10 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
             h->cl_wg[0] = K;
             h->cl_hi[0] = top;
         } else if (prm.cluster_wg == -1 && prm.collapse_level < 0 && std::isfinite(path.t_us)) {
+            // where the dense operator is used, it takes the place of the path's
+            // stages as of its collapse, whatever the calibration made of them
             h->lstar = path.lstar;
-            h->cl_nstage = std::min(path.nstage, CLUSTER_MAX_STAGES);
+            h->cl_nstage = dense_top >= 0 ? 0 : std::min(path.nstage, CLUSTER_MAX_STAGES);
             for (int k = 0; k < h->cl_nstage; ++k) {
                 h->cl_wg[k] = path.wg[k];
                 h->cl_hi[k] = path.hi[k];
@@ -1190,7 +1192,7 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
     } else {
         h->path_us = h->model_us[h->lstar];
     }
-    if (dense_top >= 0 && h->cl_nstage == 0) {
+    if (dense_top >= 0) {
         st = dalloc(h, &h->d_dense, (size_t)h->dense_n * h->dense_ld, s);
         if (st != HIPBMG_OK) return bail(st);
         h->dense_top = dense_top;
