@@ -312,7 +312,10 @@ def main():
     hier.profile(False)
     lv_ms = hier.profile_levels(0)
     mod = hier.model_levels()
-    ls_ = info_l.collapse_level
+    # the highest level below the grid-wide kernels: of the dense operator, or
+    # of the collapsed workgroup
+    dense = info_l.dense_levels
+    ls_ = dense - 1 if dense else info_l.collapse_level
     table = []
     for l in range(info_l.levels):
         ny_l, nx_l = hier.size(l)
@@ -320,6 +323,10 @@ def main():
         if l > ls_:
             row.update(mode="grid", measured_us_per_cycle=1e3 * (lv_ms[l][0] + lv_ms[l][1]) / info_l.cycles,
                        model_us_per_cycle=mod["grid_us"][l])
+        elif l == ls_ and dense:
+            row.update(mode="dense product (levels 0..%d)" % ls_,
+                       measured_us_per_cycle=1e3 * lv_ms[l][2] / info_l.cycles,
+                       model_us_per_cycle=info_l.path_us - sum(mod["grid_us"][l + 1: info_l.levels]))
         elif l == ls_:
             row.update(mode="collapse launch (levels 0..%d)" % ls_,
                        measured_us_per_cycle=1e3 * lv_ms[l][2] / info_l.cycles,
@@ -702,8 +709,8 @@ def main():
                                "V(2,1) to rel. residual 1e-10, Galerkin coarsening to a %dx%d direct solve, FP64"
                                % (n, n, hier.params.coarsest_n, hier.params.coarsest_n),
                    "n": n, "cycles": cycles, "levels": info.levels, "coarsest_n": hier.params.coarsest_n,
-                   "collapse_level": info.collapse_level, "setup_ms": info0.setup_ms,
-                   "relres": info.relres,
+                   "collapse_level": info.collapse_level, "dense_levels": info.dense_levels,
+                   "setup_ms": info0.setup_ms, "relres": info.relres,
                    "row_blocks": {"down": list(info.rb_down)[: info.levels],
                                   "up": list(info.rb_up)[: info.levels],
                                   "pipelined_finest": info.rb_pipelined}},

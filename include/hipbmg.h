@@ -103,7 +103,8 @@ typedef struct {
     int outer_steps;         /* mixed: refinement steps; FP64: equals cycles                */
     double relres;           /* final ||b - A u||_2 / ||b||_2, FP64, interior vertices      */
     int levels;              /* number of levels L                                          */
-    int collapse_level;      /* l* in use                                                   */
+    int collapse_level;      /* l*: levels 0..l* in one workgroup.  Where dense_levels > 0 it */
+                             /* and the stages are not run: the model's choice for them      */
     double model_us[HIPBMG_MAX_LEVELS]; /* model time of one cycle for each l*, microseconds */
     double setup_ms;         /* wall time of hipbmg_setup                                   */
     double solve_ms;         /* wall time of the solve call                                 */
@@ -118,8 +119,10 @@ typedef struct {
     int cluster_hi[4];       /* highest level of each stage                                  */
     double search_us;        /* model time of one cycle along the path the search found     */
     int search_expanded;     /* states the A* search expanded                                */
-    double path_us;          /* model time of one cycle of the configuration in use (l* and */
-                             /* stages, searched or forced)                                   */
+    int dense_levels;        /* levels 0..dense_levels - 1 are applied as one dense operator */
+                             /* (0: none)                                                     */
+    double path_us;          /* model time of one cycle of the configuration in use (the     */
+                             /* dense operator, or l* and stages, searched or forced)        */
 } hipbmg_info;
 
 /* Fill *p with the defaults above. */

@@ -1196,6 +1196,8 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
         st = dalloc(h, &h->d_dense, (size_t)h->dense_n * h->dense_ld, s);
         if (st != HIPBMG_OK) return bail(st);
         h->dense_top = dense_top;
+        h->path_us = model_dense_path_us(ml, L, prm.nu1, prm.nu2, prm.precision == HIPBMG_MIXED ? 4 : 8, h->mp,
+                                         dense_top, h->dense_n, h->dense_ld);
     }
     if (h->dense_top < 0 && h->lstar >= L - 1) h->fused3 = 0;   // the finest level itself is collapsed
     if (d_tiny && hipMemcpyAsync(h->h_scal + 7, d_tiny, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess)
@@ -1725,6 +1727,7 @@ static void fill_info_common(hipbmg_hier *h, hipbmg_info *info)
     info->search_us = h->search_us;
     info->search_expanded = h->search_expanded;
     info->path_us = h->path_us;
+    info->dense_levels = h->dense_top + 1;
 }
 
 // A stage barrier that gave up waiting (its workgroups were not all resident)

@@ -362,6 +362,15 @@ double model_path_us(const ModelLevel *lv, int L, int nu1, int nu2, int nc, int 
     return t + p.alpha_launch_us;
 }
 
+double model_dense_path_us(const ModelLevel *lv, int L, int nu1, int nu2, int word, const ModelParams &p, int top,
+                           int n, int ld)
+{
+    double t = 0.0;
+    for (int l = L - 1; l > top; --l) t += model_grid_level_us(lv[l], l == L - 1, nu1, nu2, word, p);
+    t += p.t0_up_us[word == 4 ? 1 : 0] + 8.0 * n * ld * p.beta_cache_us_per_B;
+    return t + p.alpha_launch_us;
+}
+
 // ---------------------------------------------------------------------------
 // 3D levels
 // ---------------------------------------------------------------------------

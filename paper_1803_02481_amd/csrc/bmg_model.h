@@ -133,6 +133,11 @@ ModelPath model_search_exhaustive(const ModelLevel *lv, int L, int nu1, int nu2,
 // model time of one cycle with the given stages above collapse level lstar
 double model_path_us(const ModelLevel *lv, int L, int nu1, int nu2, int nc, int word, const ModelParams &p,
                      int lstar, int nstage, const int *wg, const int *hi);
+// model time of one cycle with levels 0..top as a product with a matrix of
+// n rows of ld columns: the grid-wide levels above, a kernel that moves the
+// matrix from the last-level cache, and the test
+double model_dense_path_us(const ModelLevel *lv, int L, int nu1, int nu2, int word, const ModelParams &p, int top,
+                           int n, int ld);
 
 // the two parts of the model for one level (exposed for reporting)
 double model_grid_level_us(const ModelLevel &lv, bool finest, int nu1, int nu2, int word,

@@ -41,7 +41,7 @@ class Info(ctypes.Structure):
                 ("rb_pipelined", ctypes.c_int), ("cluster_stages", ctypes.c_int),
                 ("cluster_wg", ctypes.c_int * 4), ("cluster_hi", ctypes.c_int * 4),
                 ("search_us", ctypes.c_double), ("search_expanded", ctypes.c_int),
-                ("path_us", ctypes.c_double)]
+                ("dense_levels", ctypes.c_int), ("path_us", ctypes.c_double)]
 
     def history(self):
         n = self.outer_steps if self.outer_steps else self.cycles
