@@ -156,23 +156,25 @@ __device__ void load27(const Sten &s, int i, int j, int k, double e[27])
 // ---------------------------------------------------------------------------
 // layout conversion and finite volumes
 // ---------------------------------------------------------------------------
-__global__ void k3_to_oct(const double *nat, double *out, Oct g, int interior_only)
+// times scale; *tiny (or null) is set where an interior value is tiny_diag
+__global__ void k3_to_oct(const double *nat, double *out, Oct g, int interior_only, double scale, int *tiny)
 {
     const long long n = (long long)g.nx * g.ny * g.nz;
     const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     if (t >= n) return;
     const int i = (int)(t % g.nx), j = (int)((t / g.nx) % g.ny), k = (int)(t / ((long long)g.nx * g.ny));
     const bool keep = !interior_only || inner(g, i, j, k);
-    out[vid(g, i, j, k)] = keep ? nat[t] : 0.0;
+    out[vid(g, i, j, k)] = keep ? scale * nat[t] : 0.0;
+    if (tiny && hbmg::tiny_diag(nat[t]) && inner(g, i, j, k)) *tiny = 1;
 }
 
-__global__ void k3_from_oct(const double *in, double *nat, Oct g)
+__global__ void k3_from_oct(const double *in, double *nat, Oct g, double scale)
 {
     const long long n = (long long)g.nx * g.ny * g.nz;
     const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     if (t >= n) return;
     const int i = (int)(t % g.nx), j = (int)((t / g.nx) % g.ny), k = (int)(t / ((long long)g.nx * g.ny));
-    nat[t] = inner(g, i, j, k) ? in[vid(g, i, j, k)] : 0.0;
+    nat[t] = inner(g, i, j, k) ? scale * in[vid(g, i, j, k)] : 0.0;
 }
 
 __device__ inline double cellv3(const double *D, int nx, int ny, int nz, int ci, int cj, int ck)
@@ -400,7 +402,7 @@ __global__ __launch_bounds__(256) void k3_rap(RArgs a)
 }
 
 // level operator in the plain layout: 27 entries per vertex, zero towards the boundary
-__global__ void k3_stencil_out(Sten s, double *out)
+__global__ void k3_stencil_out(Sten s, double *out, double scale)
 {
     const Oct &g = s.g;
     const long long n = (long long)g.nx * g.ny * g.nz;
@@ -415,7 +417,7 @@ __global__ void k3_stencil_out(Sten s, double *out)
     } else {
         for (int o = 0; o < 27; ++o) e[o] = 0.0;
     }
-    for (int o = 0; o < 27; ++o) out[o * n + t] = e[o];
+    for (int o = 0; o < 27; ++o) out[o * n + t] = scale * e[o];
 }
 
 __global__ void k3_interp_out(Oct g, const double *w, double *out)
@@ -1835,6 +1837,7 @@ struct hipbmg3d_hier {
     double model_us[HIPBMG_MAX_LEVELS] = {0};
     Lev3 lv[HIPBMG_MAX_LEVELS];
     hipbmg_params prm;
+    double scale = 1.0;                // the stored operator is the caller's times this power of two
     int nc = 0;
     double *d_chol = nullptr;
     long long *d_cidx = nullptr;
@@ -2418,17 +2421,19 @@ hipbmg_status cycle_and_norm(hipbmg3d_hier *h, hipStream_t s)
     return HIPBMG_OK;
 }
 
-hipbmg_status to_oct(const Oct &g, const double *nat, double *out, int interior_only, hipStream_t s)
+hipbmg_status to_oct(const Oct &g, const double *nat, double *out, int interior_only, hipStream_t s,
+                     double scale = 1.0, int *tiny = nullptr)
 {
     hipLaunchKernelGGL(k3_to_oct, dim3(nblk((long long)g.nx * g.ny * g.nz)), dim3(256), 0, s, nat, out, g,
-                       interior_only);
+                       interior_only, scale, tiny);
     HIP3(hipGetLastError());
     return HIPBMG_OK;
 }
 
-hipbmg_status from_oct(const Oct &g, const double *in, double *nat, hipStream_t s)
+hipbmg_status from_oct(const Oct &g, const double *in, double *nat, hipStream_t s, double scale = 1.0)
 {
-    hipLaunchKernelGGL(k3_from_oct, dim3(nblk((long long)g.nx * g.ny * g.nz)), dim3(256), 0, s, in, nat, g);
+    hipLaunchKernelGGL(k3_from_oct, dim3(nblk((long long)g.nx * g.ny * g.nz)), dim3(256), 0, s, in, nat, g,
+                       scale);
     HIP3(hipGetLastError());
     return HIPBMG_OK;
 }
@@ -2601,22 +2606,11 @@ extern "C" hipbmg_status hipbmg3d_fv7_from_cells(int nx, int ny, int nz, const d
     return HIPBMG_OK;
 }
 
-extern "C" hipbmg_status hipbmg3d_setup(int nx, int ny, int nz, int npt, const double *planes,
-                                        const hipbmg_params *params, void *stream, hipbmg3d_handle *out)
+// Build a hierarchy whose stored operator is the caller's times scale; *tiny is
+// set where scale = 1 leaves reciprocals of its diagonal out of range.
+static hipbmg_status build_hierarchy3(int nx, int ny, int nz, int npt, const double *planes, const hipbmg_params &prm,
+                                      hipStream_t s, double scale, int *tiny, hipbmg3d_hier **out)
 {
-    if (!out || !planes) return fail3(HIPBMG_EINVAL, "null argument");
-    *out = nullptr;
-    if (!odd_ok(nx) || !odd_ok(ny) || !odd_ok(nz)) return fail3(HIPBMG_EINVAL, "sizes must be odd and >= 3");
-    if (npt != 7 && npt != 27) return fail3(HIPBMG_EINVAL, "npt must be 7 or 27");
-    hipbmg_params prm;
-    hipbmg_default_params(&prm);
-    if (params) prm = *params;
-    if (prm.nu1 < 0 || prm.nu2 < 0 || prm.nu1 + prm.nu2 < 1 || prm.coarsest_n < 3 || prm.max_cycles < 1 ||
-        prm.max_cycles > HIPBMG_MAX_HIST)
-        return fail3(HIPBMG_EINVAL, "bad parameters");
-    if (prm.precision != HIPBMG_FP64) return fail3(HIPBMG_EINVAL, "the 3D path runs in FP64 only");
-    hipStream_t s = (hipStream_t)stream;
-
     int sx[HIPBMG_MAX_LEVELS], sy[HIPBMG_MAX_LEVELS], sz[HIPBMG_MAX_LEVELS], L = 1;
     sx[0] = nx;
     sy[0] = ny;
@@ -2639,6 +2633,7 @@ extern "C" hipbmg_status hipbmg3d_setup(int nx, int ny, int nz, int npt, const d
     hipbmg3d_hier *h = new hipbmg3d_hier();
     h->L = L;
     h->prm = prm;
+    h->scale = scale;
     auto bail = [&](hipbmg_status st) {
         free3(h);
         return st;
@@ -2662,15 +2657,19 @@ extern "C" hipbmg_status hipbmg3d_setup(int nx, int ny, int nz, int npt, const d
     h->npart = (long long)nblk(top.g.field) + norm_partials(top) + 8;
     if ((st = dalloc3(h, &h->d_part, h->npart)) != HIPBMG_OK) return bail(st);
     if ((st = dalloc3(h, &h->d_sum, 8 + 256)) != HIPBMG_OK) return bail(st);
-    if (hbmg::pinned_small((void **)&h->slot, (void **)&h->slot_dev, 2 * sizeof(double)) != hipSuccess ||
+    if (hbmg::pinned_small((void **)&h->slot, (void **)&h->slot_dev, 3 * sizeof(double)) != hipSuccess ||
         !h->slot_dev) {
         (void)hipGetLastError();
         return bail(fail3(HIPBMG_ENOMEM, "host-mapped allocation failed"));
     }
+    h->slot[0] = h->slot[1] = h->slot[2] = 0.0;
+    int *const d_tiny = reinterpret_cast<int *>(h->slot_dev + 2);   // read after the setup's last wait
     // the finest operator in the octant layout
     const int nf = npt == 7 ? 4 : 14;
     for (int q = 0; q < nf; ++q)
-        if ((st = to_oct(top.g, planes + q * nnat, top.st + q * top.g.field, 0, s)) != HIPBMG_OK) return bail(st);
+        if ((st = to_oct(top.g, planes + q * nnat, top.st + q * top.g.field, 0, s, scale, q == 0 ? d_tiny : nullptr)) !=
+            HIPBMG_OK)
+            return bail(st);
     // a 7-point finest operator whose diagonal is the sum of its six
     // connections (finite volumes of pure diffusion): its relaxation and
     // residual kernels form the diagonal instead of loading it
@@ -2729,8 +2728,37 @@ extern "C" hipbmg_status hipbmg3d_setup(int nx, int ny, int nz, int npt, const d
     }
     if (hipStreamSynchronize(s) != hipSuccess) return bail(fail3(HIPBMG_EHIP, "setup failed on the device"));
     (void)t0;
+    *tiny = *reinterpret_cast<const volatile int *>(h->slot + 2);
     *out = h;
     return HIPBMG_OK;
+}
+
+extern "C" hipbmg_status hipbmg3d_setup(int nx, int ny, int nz, int npt, const double *planes,
+                                        const hipbmg_params *params, void *stream, hipbmg3d_handle *out)
+{
+    if (!out || !planes) return fail3(HIPBMG_EINVAL, "null argument");
+    *out = nullptr;
+    if (!odd_ok(nx) || !odd_ok(ny) || !odd_ok(nz)) return fail3(HIPBMG_EINVAL, "sizes must be odd and >= 3");
+    if (npt != 7 && npt != 27) return fail3(HIPBMG_EINVAL, "npt must be 7 or 27");
+    hipbmg_params prm;
+    hipbmg_default_params(&prm);
+    if (params) prm = *params;
+    if (prm.nu1 < 0 || prm.nu2 < 0 || prm.nu1 + prm.nu2 < 1 || prm.coarsest_n < 3 || prm.max_cycles < 1 ||
+        prm.max_cycles > HIPBMG_MAX_HIST)
+        return fail3(HIPBMG_EINVAL, "bad parameters");
+    if (prm.precision != HIPBMG_FP64) return fail3(HIPBMG_EINVAL, "the 3D path runs in FP64 only");
+    // as in 2D, an operator with diagonals so small that their reciprocals
+    // overflow is built again, scaled by a power of two
+    for (double scale = 1.0;; scale = hbmg::TINY_SCALE) {
+        hipbmg3d_hier *h = nullptr;
+        int tiny = 0;
+        ST3(build_hierarchy3(nx, ny, nz, npt, planes, prm, (hipStream_t)stream, scale, &tiny, &h));
+        if (!tiny || scale != 1.0) {
+            *out = h;
+            return HIPBMG_OK;
+        }
+        free3(h);
+    }
 }
 
 extern "C" hipbmg_status hipbmg3d_destroy(hipbmg3d_handle h)
@@ -2763,7 +2791,7 @@ extern "C" hipbmg_status hipbmg3d_get_stencil(hipbmg3d_handle h, int l, double *
     const Lev3 &v = h->lv[l];
     const long long n = (long long)v.g.nx * v.g.ny * v.g.nz;
     hipLaunchKernelGGL(k3_stencil_out, dim3(nblk(n)), dim3(256), 0, (hipStream_t)stream, Sten{v.st, v.npt, v.g},
-                       out);
+                       out, 1.0 / h->scale);
     HIP3(hipGetLastError());
     return HIPBMG_OK;
 }
@@ -2789,7 +2817,7 @@ extern "C" hipbmg_status hipbmg3d_solve(hipbmg3d_handle h, const double *b, doub
     auto t0 = std::chrono::steady_clock::now();
     Lev3 &f = h->lv[h->L - 1];
     hbmg::Drain drain{s};
-    ST3(to_oct(f.g, b, f.b, 1, s));
+    ST3(to_oct(f.g, b, f.b, 1, s, h->scale));
     ST3(to_oct(f.g, u, f.x[0], 1, s));
     h->cur = 0;
     if (overlapped(h)) {
@@ -2856,7 +2884,7 @@ extern "C" hipbmg_status hipbmg3d_op_smooth(hipbmg3d_handle h, int l, const doub
     if (l < 0 || l >= h->L || sweeps < 0) return fail3(HIPBMG_EINVAL, "bad level or sweeps");
     hipStream_t s = (hipStream_t)stream;
     Lev3 &v = h->lv[l];
-    ST3(to_oct(v.g, b, v.b, 1, s));
+    ST3(to_oct(v.g, b, v.b, 1, s, h->scale));
     ST3(to_oct(v.g, x, v.x[0], 1, s));
     int cur = 0;
     ST3(relax(h, l, &cur, sweeps, s));
@@ -2873,10 +2901,10 @@ extern "C" hipbmg_status hipbmg3d_op_residual(hipbmg3d_handle h, int l, const do
     if (l < 0 || l >= h->L) return fail3(HIPBMG_EINVAL, "bad level");
     hipStream_t s = (hipStream_t)stream;
     Lev3 &v = h->lv[l];
-    ST3(to_oct(v.g, b, v.b, 1, s));
+    ST3(to_oct(v.g, b, v.b, 1, s, h->scale));
     ST3(to_oct(v.g, x, v.x[0], 1, s));
     ST3(residual(h, l, 0, s));
-    ST3(from_oct(v.g, v.r, r, s));
+    ST3(from_oct(v.g, v.r, r, s, 1.0 / h->scale));
     HIP3(hipStreamSynchronize(s));
     h->marks.clear();
     return HIPBMG_OK;
@@ -2904,7 +2932,7 @@ extern "C" hipbmg_status hipbmg3d_op_interp_correct(hipbmg3d_handle h, int l, do
     hipStream_t s = (hipStream_t)stream;
     Lev3 &v = h->lv[l];
     ST3(to_oct(v.g, x, v.x[0], 1, s));
-    ST3(to_oct(v.g, r, v.r, 1, s));
+    ST3(to_oct(v.g, r, v.r, 1, s, h->scale));
     ST3(to_oct(h->lv[l - 1].g, xc, h->lv[l - 1].x[0], 1, s));
     ST3(interp_from(h, l, 0, 0, rescorr, s));
     ST3(from_oct(v.g, v.x[0], x, s));
@@ -2918,7 +2946,7 @@ extern "C" hipbmg_status hipbmg3d_op_coarse_solve(hipbmg3d_handle h, const doubl
     if (!h || !b || !x) return fail3(HIPBMG_EINVAL, "null argument");
     hipStream_t s = (hipStream_t)stream;
     Lev3 &c = h->lv[0];
-    ST3(to_oct(c.g, b, c.b, 1, s));
+    ST3(to_oct(c.g, b, c.b, 1, s, h->scale));
     hipLaunchKernelGGL(k3_fill0, dim3((unsigned)std::min<long long>(nblk(c.g.field), 2048)), dim3(256), 0, s,
                        c.x[0], c.g.field);
     HIP3(hipGetLastError());

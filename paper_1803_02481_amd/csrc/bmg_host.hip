@@ -5,6 +5,7 @@
 #include "bmg_internal.h"
 #include "bmg_misc.h"
 #include "bmg_model.h"
+#include "bmg_quot.h"
 #include "bmg_tags.h"
 
 #include <atomic>
@@ -320,6 +321,7 @@ struct hipbmg_hier {
     int zexc[2] = {0, 0};       // the pipelined pass forms the finest diagonal ([0] FP64, [1] FP32)
     int wform = 0;              // the FP64 pipelined pass forms the interpolation weights
     int fp32_tiny = 0;          // a diagonal is below the FP32 normal range: mixed solves run in FP64
+    double scale = 1.0;         // the stored operators are the caller's times this power of two
     double *x3_64 = nullptr;    // third iterate buffer of the pipelined finest level
     float *x3_32 = nullptr;
     // device-side stopping: run flag, and a ring of host-mapped slots through
@@ -797,31 +799,11 @@ static double now_ms()
     return duration<double, std::milli>(steady_clock::now().time_since_epoch()).count();
 }
 
-extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coeffs,
-                                      const hipbmg_params *params, void *stream,
-                                      hipbmg_handle *out)
+// Build a hierarchy whose stored operators are the caller's times scale; *tiny is
+// set where a diagonal of the caller's is tiny_diag.
+static hipbmg_status build_hierarchy(int nx, int ny, int npt, const double *coeffs, const hipbmg_params &prm,
+                                     hipStream_t s, double scale, int *tiny, hipbmg_hier **out)
 {
-    const double t0 = now_ms();
-    if (!out) return fail(HIPBMG_EINVAL, "out is NULL");
-    *out = nullptr;
-    if (!coeffs) return fail(HIPBMG_EINVAL, "coeffs is NULL");
-    if (nx < 3 || ny < 3 || !(nx & 1) || !(ny & 1))
-        return fail(HIPBMG_EINVAL, "grid %d x %d: sizes must be odd and >= 3", nx, ny);
-    if (npt != 5 && npt != 9) return fail(HIPBMG_EINVAL, "npt must be 5 or 9 (got %d)", npt);
-    hipbmg_params prm;
-    hipbmg_default_params(&prm);
-    if (params) prm = *params;
-    if (prm.nu1 < 1 || prm.nu2 < 1 || prm.nu1 > 16 || prm.nu2 > 16)
-        return fail(HIPBMG_EINVAL, "nu1 and nu2 must be in [1, 16]");
-    if (prm.coarsest_n < 3) return fail(HIPBMG_EINVAL, "coarsest_n must be >= 3");
-    if (prm.max_cycles < 1) return fail(HIPBMG_EINVAL, "max_cycles must be >= 1");
-    if (prm.precision != HIPBMG_FP64 && prm.precision != HIPBMG_MIXED)
-        return fail(HIPBMG_EINVAL, "unknown precision %d", prm.precision);
-    if (prm.precision == HIPBMG_MIXED && (prm.inner_max_cycles < 1 || !(prm.inner_tol > 0.0)))
-        return fail(HIPBMG_EINVAL, "mixed precision needs inner_max_cycles >= 1 and inner_tol > 0");
-    if ((long long)nx * ny > (1LL << 31)) return fail(HIPBMG_EINVAL, "grid too large");
-    hipStream_t s = (hipStream_t)stream;
-
     std::vector<int> sx{nx}, sy{ny};
     // every other vertex is kept; a side with an even number of vertices ends
     // in a boundary vertex at an odd index and cannot be coarsened again
@@ -848,6 +830,7 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
     h->ny = ny;
     h->npt = npt;
     h->prm = prm;
+    h->scale = scale;
     auto bail = [&](hipbmg_status st) {
         delete h;
         return st;
@@ -866,10 +849,18 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
     }
     hipbmg_status st = alloc_levels(h, h->lv, sx, sy, s);
     if (st != HIPBMG_OK) return bail(st);
+    // host-mapped: the slots of the solves' tests and norms, and two flags of the
+    // setup (an FP64, an FP32 diagonal out of range), read after its last wait
+    if (pinned_small((void **)&h->ring_host, (void **)&h->ring_dev, ((RING + 1) * 4 + 1) * sizeof(double)) !=
+            hipSuccess ||
+        !h->ring_dev)
+        return bail(fail(HIPBMG_ENOMEM, "host-mapped allocation failed"));
+    for (int k = 0; k <= (RING + 1) * 4; ++k) h->ring_host[k] = 0.0;
+    int *const d_tiny = reinterpret_cast<int *>(h->ring_dev + (RING + 1) * 4);
     // finest operator, as given
     LevelDev<double> &F = h->lv[L - 1];
     const int nplanes = npt == 5 ? 3 : 5;
-    if (launch_planes_in(coeffs, nx, ny, nplanes, F.C, F.pitch, F.plane, s) != hipSuccess)
+    if (launch_planes_in(coeffs, nx, ny, nplanes, F.C, F.pitch, F.plane, scale, d_tiny, s) != hipSuccess)
         return bail(fail(HIPBMG_EHIP, "copy of the stencil planes failed"));
     // coarse operators: interpolation weights and Galerkin products.  On the
     // large coarse levels whose up leg forms r/C from its rows, a vertex at
@@ -944,15 +935,12 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
     if (st != HIPBMG_OK) return bail(st);
 
     // FP32 edge-form copy of every level for mixed precision
-    int *d_tiny = nullptr;
     if (prm.precision == HIPBMG_MIXED) {
         st = alloc_levels(h, h->lv32, sx, sy, s);
         if (st != HIPBMG_OK) return bail(st);
-        st = dalloc(h, &d_tiny, 1, s);
-        if (st != HIPBMG_OK) return bail(st);
         for (int l = 0; l < L; ++l) {
             int cnx = l ? sx[l - 1] : 0, cny = l ? sy[l - 1] : 0;
-            if (launch_demote_level(h->lv[l], h->lv32[l], cnx, cny, d_tiny, s) != hipSuccess)
+            if (launch_demote_level(h->lv[l], h->lv32[l], cnx, cny, 0x1p-126 * scale, d_tiny + 1, s) != hipSuccess)
                 return bail(fail(HIPBMG_EHIP, "demote launch failed"));
             if (h->zc9[0][l]) {
                 // the FP32 copy's excess at the deep vertices: zero if the
@@ -1050,13 +1038,9 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
     if (st != HIPBMG_OK) return bail(st);
     if (pinned_small((void **)&h->h_scal, nullptr, 8 * sizeof(double)) != hipSuccess)
         return bail(fail(HIPBMG_ENOMEM, "pinned host allocation failed"));
-    // device-side stopping: run flag, host-mapped test slots
+    // device-side stopping: the run flag
     st = dalloc(h, &h->d_flags, 4, s);
     if (st != HIPBMG_OK) return bail(st);
-    if (pinned_small((void **)&h->ring_host, (void **)&h->ring_dev, (RING + 1) * 4 * sizeof(double)) != hipSuccess ||
-        !h->ring_dev)
-        return bail(fail(HIPBMG_ENOMEM, "host-mapped allocation failed"));
-    for (int k = 0; k < (RING + 1) * 4; ++k) h->ring_host[k] = 0.0;
     if (const char *e = std::getenv("HIPBMG_AHEAD")) {   // cycles enqueued ahead of the last test seen
         const int v = std::atoi(e);
         if (v >= 0 && v < RING) h->ahead = v;
@@ -1200,14 +1184,52 @@ extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coe
                                          dense_top, h->dense_n, h->dense_ld);
     }
     if (h->dense_top < 0 && h->lstar >= L - 1) h->fused3 = 0;   // the finest level itself is collapsed
-    if (d_tiny && hipMemcpyAsync(h->h_scal + 7, d_tiny, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess)
-        return bail(fail(HIPBMG_EHIP, "hipMemcpyAsync failed"));
     if (hipStreamSynchronize(s) != hipSuccess) return bail(fail(HIPBMG_EHIP, "setup failed: %s",
                                                              hipGetErrorString(hipGetLastError())));
-    h->setup_ms = now_ms() - t0;
-    if (d_tiny) std::memcpy(&h->fp32_tiny, h->h_scal + 7, sizeof(int));
+    const volatile int *flags = reinterpret_cast<const int *>(h->ring_host + (RING + 1) * 4);
+    *tiny = flags[0];
+    h->fp32_tiny = flags[1];
     *out = h;
     return HIPBMG_OK;
+}
+
+extern "C" hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coeffs,
+                                      const hipbmg_params *params, void *stream,
+                                      hipbmg_handle *out)
+{
+    if (!out) return fail(HIPBMG_EINVAL, "out is NULL");
+    *out = nullptr;
+    if (!coeffs) return fail(HIPBMG_EINVAL, "coeffs is NULL");
+    if (nx < 3 || ny < 3 || !(nx & 1) || !(ny & 1))
+        return fail(HIPBMG_EINVAL, "grid %d x %d: sizes must be odd and >= 3", nx, ny);
+    if (npt != 5 && npt != 9) return fail(HIPBMG_EINVAL, "npt must be 5 or 9 (got %d)", npt);
+    hipbmg_params prm;
+    hipbmg_default_params(&prm);
+    if (params) prm = *params;
+    if (prm.nu1 < 1 || prm.nu2 < 1 || prm.nu1 > 16 || prm.nu2 > 16)
+        return fail(HIPBMG_EINVAL, "nu1 and nu2 must be in [1, 16]");
+    if (prm.coarsest_n < 3) return fail(HIPBMG_EINVAL, "coarsest_n must be >= 3");
+    if (prm.max_cycles < 1) return fail(HIPBMG_EINVAL, "max_cycles must be >= 1");
+    if (prm.precision != HIPBMG_FP64 && prm.precision != HIPBMG_MIXED)
+        return fail(HIPBMG_EINVAL, "unknown precision %d", prm.precision);
+    if (prm.precision == HIPBMG_MIXED && (prm.inner_max_cycles < 1 || !(prm.inner_tol > 0.0)))
+        return fail(HIPBMG_EINVAL, "mixed precision needs inner_max_cycles >= 1 and inner_tol > 0");
+    if ((long long)nx * ny > (1LL << 31)) return fail(HIPBMG_EINVAL, "grid too large");
+    // the usual operator is stored as it is; one with diagonals so small that
+    // FP64 reciprocals, or those of an FP32 copy, overflow is built again, scaled
+    const double t0 = now_ms();
+    for (double scale = 1.0;;) {
+        hipbmg_hier *h = nullptr;
+        int tiny = 0;
+        STCHK(build_hierarchy(nx, ny, npt, coeffs, prm, (hipStream_t)stream, scale, &tiny, &h));
+        if (scale != 1.0 || !(tiny || h->fp32_tiny)) {
+            h->setup_ms = now_ms() - t0;
+            *out = h;
+            return HIPBMG_OK;
+        }
+        scale = tiny ? TINY_SCALE : TINY_SCALE32;
+        hipbmg_destroy(h);
+    }
 }
 
 extern "C" hipbmg_status hipbmg_destroy(hipbmg_handle h)
@@ -1850,7 +1872,7 @@ extern "C" hipbmg_status hipbmg_solve(hipbmg_handle h, const double *b, double *
     // behind them): every return leaves the handle idle
     Drain drain{s};
     int nparts = 0;
-    HIPCHK(launch_stage_in(b, u, F.b, F.x[0], nx, ny, F.pitch, h->d_partials, &nparts, s));
+    HIPCHK(launch_stage_in(b, u, F.b, F.x[0], nx, ny, F.pitch, h->scale, h->d_partials, &nparts, s));
     const double bn_tag = h->tags.next();
     HIPCHK(launch_finalize_norm(h->d_partials, nparts, h->d_scal, s, h->d_flags, h->ring_dev + 4 * RING, bn_tag));
     double bnorm = 1.0;
@@ -1890,6 +1912,7 @@ extern "C" hipbmg_status hipbmg_get_stencil(hipbmg_handle h, int l, double *out,
         HIPCHK(hipMemcpy2DAsync(out + (size_t)k * A.nx * A.ny, A.nx * sizeof(double), A.C + k * A.plane,
                                 A.pitch * sizeof(double), A.nx * sizeof(double), A.ny,
                                 hipMemcpyDeviceToDevice, s));
+    HIPCHK(launch_scale(out, A.nx, 5 * A.ny, A.nx, 1.0 / h->scale, s));
     HIPCHK(hipStreamSynchronize(s));
     return HIPBMG_OK;
 }
@@ -1949,6 +1972,7 @@ static hipbmg_status op_smooth(hipbmg_hier *h, int l, const T *b, T *x, int swee
     STCHK(op_levels(h, &lv));
     const LevelDev<T> &A = (*lv)[l];
     STCHK(to_pitched(A.b, A.pitch, b, A.nx, A.ny, s));
+    HIPCHK(launch_scale(A.b, A.nx, A.ny, A.pitch, h->scale, s));
     STCHK(to_pitched(A.x[0], A.pitch, x, A.nx, A.ny, s));
     int xb = 0;
     for (int k = 0; k < sweeps; ++k) {
@@ -1974,6 +1998,7 @@ static hipbmg_status op_smooth_restrict(hipbmg_hier *h, int l, const T *b, T *x,
     STCHK(op_levels(h, &lv));
     const LevelDev<T> &A = (*lv)[l], &C = (*lv)[l - 1];
     STCHK(to_pitched(A.b, A.pitch, b, A.nx, A.ny, s));
+    HIPCHK(launch_scale(A.b, A.nx, A.ny, A.pitch, h->scale, s));
     STCHK(to_pitched(A.x[0], A.pitch, x, A.nx, A.ny, s));
     HIPCHK(hipMemsetAsync(A.q, 0, A.plane * sizeof(T), s));
     HIPCHK(hipMemsetAsync(C.b, 0, C.plane * sizeof(T), s));
@@ -1991,6 +2016,7 @@ static hipbmg_status op_smooth_restrict(hipbmg_hier *h, int l, const T *b, T *x,
     STCHK(from_pitched(x, A.x[1], A.pitch, A.nx, A.ny, s));
     STCHK(from_pitched(q, A.q, A.pitch, A.nx, A.ny, s));
     STCHK(from_pitched(bc, C.b, C.pitch, C.nx, C.ny, s));
+    HIPCHK(launch_scale(bc, C.nx, C.ny, C.nx, 1.0 / h->scale, s));
     HIPCHK(hipStreamSynchronize(s));
     return HIPBMG_OK;
 }
@@ -2005,6 +2031,7 @@ static hipbmg_status op_interp_smooth(hipbmg_hier *h, int l, const T *b, T *x, c
     STCHK(op_levels(h, &lv));
     const LevelDev<T> &A = (*lv)[l], &C = (*lv)[l - 1];
     STCHK(to_pitched(A.b, A.pitch, b, A.nx, A.ny, s));
+    HIPCHK(launch_scale(A.b, A.nx, A.ny, A.pitch, h->scale, s));
     STCHK(to_pitched(A.x[0], A.pitch, x, A.nx, A.ny, s));
     STCHK(to_pitched(A.q, A.pitch, q, A.nx, A.ny, s));
     STCHK(to_pitched(C.x[1], C.pitch, xc, C.nx, C.ny, s));
@@ -2025,7 +2052,8 @@ static hipbmg_status op_interp_smooth(hipbmg_hier *h, int l, const T *b, T *x, c
     if (sumsq_host) {
         HIPCHK(launch_finalize_norm(h->d_partials, nt, h->d_scal + 5, s));
         STCHK(read_scalars(h, 5, 1, s));
-        *sumsq_host = h->h_scal[5] * h->h_scal[5];
+        const double norm = h->h_scal[5] / h->scale;
+        *sumsq_host = norm * norm;
     }
     STCHK(from_pitched(x, A.x[1], A.pitch, A.nx, A.ny, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -2067,6 +2095,7 @@ extern "C" hipbmg_status hipbmg_get_level32(hipbmg_handle h, int l, float *stenc
     for (int k = 0; k < 5; ++k)
         HIPCHK(hipMemcpy2DAsync(stencil_out + (size_t)k * A.nx * A.ny, A.nx * sizeof(float), A.C + k * A.plane,
                                 A.pitch * sizeof(float), A.nx * sizeof(float), A.ny, hipMemcpyDeviceToDevice, s));
+    HIPCHK(launch_scale(stencil_out, A.nx, 5 * A.ny, A.nx, 1.0 / h->scale, s));
     if (interp_out) {
         const LevelDev<float> &C = (*lv)[l - 1];
         for (int k = 0; k < 8; ++k)
@@ -2109,7 +2138,8 @@ extern "C" hipbmg_status hipbmg_op32_inner(hipbmg_handle h, const float *r, floa
     hipStream_t s = (hipStream_t)stream;
     const LevelDev<float> &F = (*lv)[h->L - 1];
     STCHK(to_pitched(F.b, F.pitch, r, F.nx, F.ny, s));
-    h->h_scal[2] = rnorm;
+    HIPCHK(launch_scale(F.b, F.nx, F.ny, F.pitch, h->scale, s));
+    h->h_scal[2] = rnorm * h->scale;
     HIPCHK(hipMemcpyAsync(h->d_scal + 2, h->h_scal + 2, sizeof(double), hipMemcpyHostToDevice, s));
     HIPCHK(hipStreamSynchronize(s));
     const float *res = nullptr;
@@ -3607,6 +3637,10 @@ extern "C" hipbmg_status hipbmg_solve_batched(hipbmg_batch_handle B, const doubl
     }
     HIPCHK(hipMemcpyAsync(B->d_user, B->h_user, 2 * n * sizeof(double *), hipMemcpyHostToDevice, s));
     HIPCHK(launch_stage_batched(B->d_user, B->d_bptr, B->d_xptr, B->d_dims, B->d_rowoff, n, B->rows, 0, s));
+    for (hipbmg_hier *h : B->hs) {
+        const LevelDev<double> &F = h->lv[h->L - 1];
+        HIPCHK(launch_scale(F.b, F.nx, F.ny, F.pitch, h->scale, s));
+    }
     for (int p = 0; p < n; ++p) {
         hipbmg_hier *h = B->hs[p];
         const LevelDev<double> &F = h->lv[h->L - 1];

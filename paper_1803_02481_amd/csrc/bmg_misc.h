@@ -8,13 +8,14 @@ hipError_t launch_zero_ring(double *v, int nx, int ny, int pitch, hipStream_t s)
 hipError_t launch_zero_ring(float *v, int nx, int ny, int pitch, hipStream_t s);
 // the caller's b and u ([ny][nx]) into a level's padded planes, 0 on the boundary
 // ring, with block sums of b^2 (interior) to partials (*nparts of them, at most
-// 4096 + ceil(nx / 256)); and a padded plane back to the caller's array
+// 4096 + ceil(nx / 256)), b times `scale`; and a padded plane back to the caller's array
 hipError_t launch_stage_in(const double *b, const double *u, double *bdst, double *xdst, int nx, int ny, int pitch,
-                           double *partials, int *nparts, hipStream_t s);
+                           double scale, double *partials, int *nparts, hipStream_t s);
 hipError_t launch_stage_out(const double *src, double *u, int nx, int ny, int pitch, hipStream_t s);
-// FP64 level -> FP32 edge-form level (and its interpolation weights)
+// FP64 level -> FP32 edge-form level (and its interpolation weights);
+// *tiny is set where an interior diagonal is below normal
 hipError_t launch_demote_level(const LevelDev<double> &d, const LevelDev<float> &f, int cnx,
-                               int cny, int *tiny, hipStream_t s);
+                               int cny, double normal, int *tiny, hipStream_t s);
 // r32 = (float)(b - A u) with FP64 partial sums of squares; *nparts partials written
 hipError_t launch_ir_residual(const LevelDev<double> &d, const double *u, float *r32, int pitchf,
                               double *partials, int *nparts, hipStream_t s);
@@ -38,9 +39,13 @@ hipError_t launch_ir_residual_batched(const LevelDev<double> *d, const LevelDev<
 hipError_t launch_ir_update_batched(const LevelDev<double> *d, const LevelDev<float> *f, const float *const *eptr,
                                     const int *active, const int *rowoff, int nrows, int nprob, hipStream_t s);
 // planes [nplanes][ny][nx] (contiguous) into a level's padded planes
-// (dst + k * plane, rows of `pitch`); the padding is left as it is
+// (dst + k * plane, rows of `pitch`) times scale; the padding is left as it is.
+// *tiny is set where an interior diagonal is tiny_diag
 hipError_t launch_planes_in(const double *src, int nx, int ny, int nplanes, double *dst, int pitch, size_t plane,
-                            hipStream_t s);
+                            double scale, int *tiny, hipStream_t s);
+// v ([ny] rows of pitch) *= f, a power of two; nothing for 1
+template <typename T>
+hipError_t launch_scale(T *v, int nx, int ny, int pitch, double f, hipStream_t s);
 // the caller's arrays of a batch to and from the finest levels' padded planes,
 // one wave per row over all problems (rowoff[p]: the first row of problem p in
 // the batch, rowoff[nprob] the rows of all; dims[p] = (nx, ny, pitch)).

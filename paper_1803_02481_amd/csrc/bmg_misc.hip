@@ -4,6 +4,7 @@
 // arrays to and from its finest levels.
 #include "bmg_misc.h"
 #include "bmg_check.h"
+#include "bmg_quot.h"
 
 #include <algorithm>
 
@@ -43,7 +44,8 @@ hipError_t launch_zero_ring(float *v, int nx, int ny, int pitch, hipStream_t s)
 // and 92 us, at 2.9 TB/s for the copies).
 __global__ __launch_bounds__(256) void k_stage_in(const double *__restrict__ b, const double *__restrict__ u,
                                                   double *__restrict__ bdst, double *__restrict__ xdst, int nx,
-                                                  int ny, int pitch, int rows, double *__restrict__ partials)
+                                                  int ny, int pitch, int rows, double scale,
+                                                  double *__restrict__ partials)
 {
     __shared__ double sh[4];
     const int i = blockIdx.x * 256 + threadIdx.x, j0 = blockIdx.y * rows, j1 = min(j0 + rows, ny);
@@ -54,7 +56,7 @@ __global__ __launch_bounds__(256) void k_stage_in(const double *__restrict__ b, 
         for (int j = j0; j < j1; ++j) {
             const size_t q = (size_t)j * nx + i, p = (size_t)j * pitch + i;
             const bool in = ci && j >= 1 && j <= ny - 2;
-            const double bv = in ? b[q] : 0.0, uv = in ? u[q] : 0.0;
+            const double bv = in ? scale * b[q] : 0.0, uv = in ? u[q] : 0.0;
             bdst[p] = bv;
             xdst[p] = uv;
             acc += bv * bv;
@@ -82,12 +84,13 @@ static dim3 stage_grid(int nx, int ny, int *rows)
 }
 
 hipError_t launch_stage_in(const double *b, const double *u, double *bdst, double *xdst, int nx, int ny, int pitch,
-                           double *partials, int *nparts, hipStream_t s)
+                           double scale, double *partials, int *nparts, hipStream_t s)
 {
     int rows = 1;
     const dim3 g = stage_grid(nx, ny, &rows);
     *nparts = (int)(g.x * g.y);
-    hipLaunchKernelGGL(k_stage_in, g, dim3(256), 0, s, b, u, bdst, xdst, nx, ny, pitch, rows, partials);
+    hipLaunchKernelGGL(k_stage_in, g, dim3(256), 0, s, b, u, bdst, xdst, nx, ny, pitch, rows, scale,
+                       partials);
     return hipGetLastError();
 }
 
@@ -104,9 +107,9 @@ hipError_t launch_stage_out(const double *src, double *u, int nx, int ny, int pi
 // rounded to float.  The FP32 kernels form A x as
 //   sum_q conn_pq (x_p - x_q) + E_p x_p,
 // so the zero row sums of pure-diffusion rows survive the rounding exactly.
-// *tiny is set where an interior diagonal is below the normal range of a float:
-// the FP32 kernels divide by its reciprocal, which may overflow.
-__global__ void k_demote_level(LevelDev<double> d, LevelDev<float> f, int *tiny)
+// *tiny is set where an interior diagonal is below `normal`: the FP32 kernels
+// divide by its reciprocal, which may overflow.
+__global__ void k_demote_level(LevelDev<double> d, LevelDev<float> f, double normal, int *tiny)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y;
@@ -122,7 +125,7 @@ __global__ void k_demote_level(LevelDev<double> d, LevelDev<float> f, int *tiny)
         double rs = d.W[p] + d.W[p + 1] + d.S[p] + d.S[p + P] + d.SW[p] + d.SW[p + P + 1] + d.SE[p] +
                     d.SE[p + P - 1];
         e = (float)(d.C[p] - rs);
-        if (fabs(d.C[p]) < 1.1754943508222875e-38) *tiny = 1;
+        if (fabs(d.C[p]) < normal) *tiny = 1;
     }
     f.C[pf] = e;
 }
@@ -138,9 +141,9 @@ __global__ void k_demote_weights(const double *__restrict__ wd, size_t pd, int p
 }
 
 hipError_t launch_demote_level(const LevelDev<double> &d, const LevelDev<float> &f, int cnx,
-                               int cny, int *tiny, hipStream_t s)
+                               int cny, double normal, int *tiny, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_demote_level, dim3((d.nx + 255) / 256, d.ny), dim3(256), 0, s, d, f, tiny);
+    hipLaunchKernelGGL(k_demote_level, dim3((d.nx + 255) / 256, d.ny), dim3(256), 0, s, d, f, normal, tiny);
     if (d.wt)
         hipLaunchKernelGGL(k_demote_weights, dim3((cnx + 255) / 256, cny), dim3(256), 0, s, d.wt,
                            d.cplane, d.cpitch, f.wt, f.cplane, f.cpitch, cnx, cny);
@@ -323,20 +326,40 @@ hipError_t launch_ir_update_batched(const LevelDev<double> *d, const LevelDev<fl
 }
 
 __global__ void k_planes_in(const double *__restrict__ src, int nx, int ny, double *__restrict__ dst, int pitch,
-                            size_t plane)
+                            size_t plane, double scale, int *tiny)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int j = blockIdx.y, k = blockIdx.z;
-    if (i < nx) dst[k * plane + (size_t)j * pitch + i] = src[((size_t)k * ny + j) * nx + i];
+    if (i >= nx) return;
+    const double v = src[((size_t)k * ny + j) * nx + i];
+    dst[k * plane + (size_t)j * pitch + i] = scale * v;
+    if (k == 0 && tiny_diag(v) && i >= 1 && i <= nx - 2 && j >= 1 && j <= ny - 2) *tiny = 1;
 }
 
 hipError_t launch_planes_in(const double *src, int nx, int ny, int nplanes, double *dst, int pitch, size_t plane,
-                            hipStream_t s)
+                            double scale, int *tiny, hipStream_t s)
 {
     hipLaunchKernelGGL(k_planes_in, dim3((nx + 255) / 256, ny, nplanes), dim3(256), 0, s, src, nx, ny, dst, pitch,
-                       plane);
+                       plane, scale, tiny);
     return hipGetLastError();
 }
+
+template <typename T>
+__global__ void k_scale(T *v, int nx, int pitch, T f)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nx) v[(size_t)blockIdx.y * pitch + i] *= f;
+}
+
+template <typename T>
+hipError_t launch_scale(T *v, int nx, int ny, int pitch, double f, hipStream_t s)
+{
+    if (f == 1.0) return hipSuccess;
+    hipLaunchKernelGGL((k_scale<T>), dim3((nx + 255) / 256, ny), dim3(256), 0, s, v, nx, pitch, (T)f);
+    return hipGetLastError();
+}
+template hipError_t launch_scale<double>(double *, int, int, int, double, hipStream_t);
+template hipError_t launch_scale<float>(float *, int, int, int, double, hipStream_t);
 
 // one wave per row of the batch; the row's problem by bisection of the row
 // offsets (the same for all lanes of the wave)

@@ -17,4 +17,12 @@ __device__ __forceinline__ T div_by(T r, T d, T y)
     return __builtin_elementwise_fma(e, y, q);
 }
 
+// Reciprocals of diagonals d, and the entries of a coarse inverse, which grow to
+// about 1e4 / d, are finite from here up.  Where a finest diagonal is smaller the
+// setup stores the operator times TINY_SCALE, and solves take b times the same:
+// a power of two, so the iterates are those of the operator itself.  A smaller
+// one serves FP32 copies with diagonals below the normal range of a float.
+constexpr double TINY_SCALE = 0x1p80, TINY_SCALE32 = 0x1p64;
+__host__ __device__ inline bool tiny_diag(double d) { return d != 0.0 && __builtin_fabs(d) < 0x1p-1000; }
+
 }  // namespace hbmg
