@@ -82,8 +82,9 @@ typedef struct {
                              /* run in one persistent workgroup (0 = coarsest solve only)   */
     int residual_correction; /* 1: add r/C at fine-only vertices after interpolation (sec 3) */
     int max_cycles;          /* FP64: V-cycles; mixed: total inner cycles cap, default 500  */
-    int precision;           /* hipbmg_precision, default HIPBMG_FP64; a mixed solve runs   */
-                             /* in FP64 where a diagonal is below the normal range of FP32  */
+    int precision;           /* hipbmg_precision, default HIPBMG_FP64; a mixed solve, and a */
+                             /* whole mixed batch, runs in FP64 where a diagonal is below   */
+                             /* the normal range of FP32 (outer_steps then equals cycles)   */
     int inner_max_cycles;    /* mixed: FP32 cycles per refinement step, default 32          */
     double inner_tol;        /* mixed: inner relative residual target, default 1e-4; a step */
                              /* stops its inner solve already at tol / (2 relres) when that */
@@ -163,6 +164,11 @@ hipbmg_status hipbmg_set_allocator(hipbmg_alloc_fn alloc_fn, hipbmg_free_fn free
  * with both at their defaults applies its coarse levels of at most 2048 unknowns
  * (1024 above a coarsest level of more than 64) as one dense operator, formed by
  * its first solve, in place of the collapsed workgroup or stages of those levels.
+ * The operator (8 bytes times its unknowns squared: 8 MB for 33^2, 34 MB at most)
+ * is part of the hierarchy's memory from setup on; cluster_wg = 0 does without it.
+ * Its product rounds differently from the workgroup's phases, which batches keep:
+ * a default solve and the same problem in a batch agree to rounding, and cycle by
+ * cycle bit for bit where the single hierarchy has cluster_wg = 0.
  * coeffs is copied and may be freed after return.  params may be NULL for the
  * defaults.  Returns HIPBMG_ENOTSPD if the coarsest factorisation fails. */
 hipbmg_status hipbmg_setup(int nx, int ny, int npt, const double *coeffs,

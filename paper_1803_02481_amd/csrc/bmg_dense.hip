@@ -14,13 +14,12 @@ namespace hbmg {
 
 namespace {
 
-
-// a level as a column's workgroup sees it: operator and weights in global
-// memory (every column reads them, so they sit in L2), iterate, residual and
-// right-hand side in LDS at compact pitch nx
 // the values of two columns at a vertex
 typedef double D2 __attribute__((ext_vector_type(2)));
 
+// a level as a workgroup's two columns see it: operator and weights in global
+// memory (every column reads them, so they sit in L2), iterate, residual and
+// right-hand side in LDS at compact pitch nx
 struct DV {
     int nx, ny, P;
     const double *C, *W, *S, *SW, *SE;
