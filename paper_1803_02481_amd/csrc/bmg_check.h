@@ -29,12 +29,10 @@ __device__ __forceinline__ void slot_write(double *slot, double v0, double v1, d
     v[3] = tag;
 }
 
-// The run flag in a launch whose extra workgroup may clear it meanwhile.  Two
-// reads may differ, so a workgroup acts on one: a lone wave on its first lane's, a
-// larger one on thread 0's, handed round in LDS.
-__device__ __forceinline__ int run_flag(const int *active)
+// test k's flag; a large streaming leg's tiles may read it on the way
+__device__ __forceinline__ void set_flag(const CheckArgs &c, int run)
 {
-    return active ? __hip_atomic_load(active, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1;
+    __hip_atomic_store(c.flags + (c.k & 1), run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // thread 0, with the partials' sum: the test and its outcome
@@ -42,24 +40,24 @@ __device__ __forceinline__ void check_sum(const CheckArgs &c, double sum)
 {
     const double rel = sqrt(sum) / c.denom[0];
     int run = 1;
-    if (!isfinite(rel)) {
-        run = 0;
-        c.flags[1] = c.k;
-        c.flags[2] = 2;
-    } else if (rel <= c.tol) {
-        run = 0;
-        c.flags[1] = c.k;
-        c.flags[2] = 1;
-    }
-    __hip_atomic_store(c.flags, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    slot_write(c.slot, rel, (double)run, (double)c.flags[1], c.tag);
+    if (!isfinite(rel) || rel <= c.tol) run = 0;
+    set_flag(c, run);
+    slot_write(c.slot, rel, (double)run, (double)(run ? 0 : c.k), c.tag);
+}
+
+// whether an earlier cycle met the test: then so does this one (no slot is written)
+__device__ __forceinline__ bool check_over(const CheckArgs &c)
+{
+    if (c.flags[(c.k - 1) & 1]) return false;
+    if (threadIdx.x == 0) set_flag(c, 0);
+    return true;
 }
 
 // the whole workgroup (at least 256 threads) calls
 __device__ __forceinline__ void cycle_check(const CheckArgs &c)
 {
     __shared__ double sh[4];
-    if (c.flags[0] == 0) return;   // an earlier cycle met the test
+    if (check_over(c)) return;
     double acc = 0.0;
     if (threadIdx.x < 256)
         for (int m = threadIdx.x; m < c.n; m += 256) acc += c.partials[m];
@@ -70,7 +68,7 @@ __device__ __forceinline__ void cycle_check(const CheckArgs &c)
 // the same bits from one wave: each lane stands for four of the 256 threads
 __device__ __forceinline__ void cycle_check_wave(const CheckArgs &c)
 {
-    if (c.flags[0] == 0) return;
+    if (check_over(c)) return;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
     for (int m = threadIdx.x; m < c.n; m += 256)

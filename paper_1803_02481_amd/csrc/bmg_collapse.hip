@@ -629,8 +629,7 @@ __global__ __launch_bounds__(256) void k_finalize(const double *__restrict__ par
         const double v = sqrt(sum);
         out[0] = v;
         if (flags) {
-            flags[0] = 1;
-            flags[1] = flags[2] = 0;
+            flags[0] = flags[1] = 1;
         }
         if (slot) slot_write(slot, v, 0.0, 0.0, tag);
     }
@@ -653,7 +652,7 @@ hipError_t launch_finalize_check(const CheckArgs &c, hipStream_t s)
 
 __global__ void k_flags_reset(int *flags)
 {
-    if (threadIdx.x < 4) flags[threadIdx.x] = threadIdx.x == 0 ? 1 : 0;
+    if (threadIdx.x < 2) flags[threadIdx.x] = 1;
 }
 
 hipError_t launch_flags_reset(int *flags, hipStream_t s)

@@ -222,14 +222,11 @@ __global__ __launch_bounds__(64 * DENSE_ROWS) void k_dense_apply(const double *_
                                                                 int pitch, const int *active, CheckArgs chk)
 {
     __shared__ __align__(16) double bs[DENSE_MAX];
-    __shared__ int go;
     if ((int)blockIdx.x * DENSE_ROWS >= n) {   // the extra workgroup
         cycle_check(chk);
         return;
     }
-    // with the test along, the flag is looked at behind the barrier
-    const bool rides = chk.partials != nullptr;
-    if (!rides && active && *active == 0) return;
+    if (active && *active == 0) return;
     const int lane = threadIdx.x & 63, row = blockIdx.x * DENSE_ROWS + (threadIdx.x >> 6);
     const int nch = ld >> 7, mine = row < n ? row : n - 1;
     const double2 *m = reinterpret_cast<const double2 *>(M + (size_t)mine * ld) + lane;
@@ -241,9 +238,7 @@ __global__ __launch_bounds__(64 * DENSE_ROWS) void k_dense_apply(const double *_
         const int jj = idx / ni;
         bs[idx] = idx < n ? (double)b[(size_t)(1 + jj) * pitch + 1 + idx - jj * ni] : 0.0;
     }
-    if (rides && threadIdx.x == 0) go = run_flag(active);
     __syncthreads();
-    if (rides && go == 0) return;
     double s0 = 0.0, s1 = 0.0;
 #pragma unroll
     for (int c = 0; c < DENSE_PRE; ++c)
@@ -267,7 +262,8 @@ hipError_t launch_dense_apply(const double *M, int n, int ld, const LevelDev<T> 
     static_assert(64 * DENSE_ROWS >= 256, "cycle_check needs 256 threads");
     const int extra = chk && chk->partials ? 1 : 0;
     hipLaunchKernelGGL((k_dense_apply<T>), dim3((n + DENSE_ROWS - 1) / DENSE_ROWS + extra), dim3(64 * DENSE_ROWS), 0,
-                       s, M, n, ld, lv.b, lv.x[xb], lv.nx, lv.pitch, active, extra ? *chk : CheckArgs{});
+                       s, M, n, ld, lv.b, lv.x[xb], lv.nx, lv.pitch, extra ? chk->before() : active,
+                       extra ? *chk : CheckArgs{});
     return hipGetLastError();
 }
 template hipError_t launch_dense_apply<double>(const double *, int, int, const LevelDev<double> &, int, const int *,

@@ -326,7 +326,7 @@ struct hipbmg_hier {
     float *x3_32 = nullptr;
     // device-side stopping: run flag, and a ring of host-mapped slots through
     // which the host sees each cycle's test
-    int *d_flags = nullptr;               // [0] run, [1] stopping cycle, [2] reason
+    int *d_flags = nullptr;               // run flags of the tests of even and of odd cycles
     std::vector<double> hist;             // relres after each cycle of the current run
     int stop_reason = 0;                  // of that run: 1 test met, 2 not finite, 0 neither
     // RING x {relres, run, stopping cycle, tag}, then one {norm, -, -, tag}
@@ -1575,7 +1575,6 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
 {
     const int L = h->L;
     const LevelDev<T> &F = lv[L - 1];
-    const int *act = h->d_flags;
     const bool pipe = h->fused3 != 0;
     STCHK(ensure_dense(h, s));
     T *xb[3] = {F.x[0], F.x[1], pipe ? x3_of<T>(h) : nullptr};
@@ -1633,6 +1632,7 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
     while (k < max_cycles && !stopped) {
         ++k;
         h->prof_cycle = k;
+        const int *act = h->d_flags + ((k - 1) & 1);   // the last cycle's test's
         int np = 0;
         if (pipe) {
             const LevelDev<T> &Cl = lv[L - 2];

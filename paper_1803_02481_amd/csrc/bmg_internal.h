@@ -155,11 +155,12 @@ hipError_t launch_rowsum_diag(const LevelDev<double> &A, int *flag, int set, hip
 hipError_t launch_zero_excess9(const LevelDev<float> &A, int *flag, hipStream_t s);
 
 // Convergence test after cycle k of a solve: ||r|| / denom[0] from the n norm
-// partials goes, with the flag state, to the slot {relres, run flag, stopping
-// cycle, tag} (host-mapped memory the host polls for the tag).
-// When relres <= tol, or is not finite, the run flag flags[0] is cleared and
-// flags[1] = k, flags[2] = 1 (met) or 2 (not finite).  Nothing is written once
-// the flag is clear.
+// partials goes, with the run flag, to the slot {relres, run flag, stopping
+// cycle, tag} (host-mapped memory the host polls for the tag).  The run flag is
+// cleared when relres <= tol, or is not finite.  Test k leaves it in flags[k & 1],
+// so a launch that carries test k along goes by test k-1's, which nothing
+// writes meanwhile, and the launches behind it by test k's.  Once the flag is
+// clear a later test clears its own and writes nothing else.
 struct CheckArgs {
     const double *partials;   // null: no test in this launch
     int n, k;
@@ -167,12 +168,13 @@ struct CheckArgs {
     double tol;
     int *flags;
     double *slot, tag;
+    const int *before() const { return flags + ((k - 1) & 1); }
 };
 
 // SV_SWEEP2_RQ_ZX or SV_SWEEP2_R_ZX of a 9-point level with the test of the
 // previous cycle as one more workgroup; grid as stream_geometry gives it
 template <typename T>
-hipError_t launch_stream2_check(int variant, const StreamArgs<T> &a, int grid, const CheckArgs &chk, hipStream_t s);
+hipError_t launch_stream2_check(int variant, StreamArgs<T> a, int grid, const CheckArgs &chk, hipStream_t s);
 
 // Tile kernels of the small 9-point coarse levels (V(2,1)): a workgroup of nw
 // waves (4 or 8) owns a strip by tile_steps(nw, down) row-pair steps.  down:
@@ -183,7 +185,7 @@ int tile_steps(int nw, int down);
 void tile_geometry(int nx, int ny, int npt, int nw, int down, int *nstrips, int *nblocks, int *ntiles);
 // chk: the test of the previous cycle, as one more workgroup (down only).
 template <typename T>
-hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s, const CheckArgs *chk = nullptr);
+hipError_t launch_tile(int down, int nw, StreamArgs<T> a, hipStream_t s, const CheckArgs *chk = nullptr);
 
 // The pipelined finest pass (SV_FUSED3, SV_FUSED3_PN) of a small grid as tiles: a workgroup
 // owns a strip by pass_tile_steps row-pair steps and writes one norm partial.
@@ -308,12 +310,12 @@ hipError_t launch_finalize_batched(const double *partials, const int *off, const
                                    const double *tol_dev, int nprob, hipStream_t s, int tol_stride = 0);
 hipError_t launch_count_active(const int *active, int n, int *count, hipStream_t s);
 
-// out[0] = sqrt(sum(partials)).  flags (or null): starts a solve, flags[0] = 1
-// (run), flags[1] = flags[2] = 0.  slot (or null): host-mapped {norm, -, -, tag}.
+// out[0] = sqrt(sum(partials)).  flags (or null): starts a solve, both run
+// flags set.  slot (or null): host-mapped {norm, -, -, tag}.
 hipError_t launch_finalize_norm(const double *partials, int n, double *out, hipStream_t s, int *flags = nullptr,
                                 double *slot = nullptr, double tag = 0.0);
 hipError_t launch_finalize_check(const CheckArgs &c, hipStream_t s);
-// flags[0] = 1 (run), flags[1] = flags[2] = 0: the start of a solve
+// both run flags set: the start of a solve
 hipError_t launch_flags_reset(int *flags, hipStream_t s);
 
 }  // namespace hbmg

@@ -468,14 +468,13 @@ __device__ __forceinline__ void stream_tile(const StreamArgs<T> &a, const int ti
 // second colour-by-colour sweep.  A's results are correct on fewer lanes than
 // a loaded row, so the halo is the sum of both stages' halos, and each block
 // of rows starts with three A steps and two B steps of prologue.
-// LOOK: the launch carries the test that may clear its own run flag; the flag is
-// read once more some steps in, when the test has had time, and a tile whose
-// solve is over ends there (nothing a launch past the stopping cycle writes is
-// read).
+// LOOK: the launch carries a test; its flag (look) is read some steps in, when the
+// test has had time, and a tile whose solve is over ends there (nothing a launch
+// past the stopping cycle writes is read).
 constexpr int LOOK_STEPS = 8;
 
 template <typename T, int NPT, bool ZX, bool STOREQ = true, bool ZC9 = false, bool LOOK = false>
-__device__ __forceinline__ void stream2_tile(const StreamArgs<T> &a, const int tile)
+__device__ __forceinline__ void stream2_tile(const StreamArgs<T> &a, const int tile, const int *look = nullptr)
 {
     constexpr int HA = 1 + (NPT == 9);          // lanes of A's garbage margin per side
     constexpr int HL = HA + halo_left(NPT, 1);
@@ -565,7 +564,8 @@ __device__ __forceinline__ void stream2_tile(const StreamArgs<T> &a, const int t
     if (LOOK) {
         const int jt = min(jfirst + 2 * LOOK_STEPS, jlast + 2);
         for (; ja < jt; ja += 2) step(ja, M1{}, M2{}, std::true_type{});
-        if (__builtin_amdgcn_readfirstlane(run_flag(a.active)) == 0) return;
+        if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(look, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0)
+            return;
     }
     for (; ja < jlast + 2; ja += 2) step(ja, M1{}, M2{}, std::true_type{});
     step(ja, M1{}, M2{}, std::false_type{});
@@ -998,16 +998,17 @@ __global__ __launch_bounds__(64) void k_stream2_check(StreamArgs<T> a, CheckArgs
         if (blockIdx.x == 0) cycle_check_wave(chk);
         return;
     }
-    if (__builtin_amdgcn_readfirstlane(run_flag(a.active)) == 0) return;
+    if (a.active && *a.active == 0) return;
     const int b = blockIdx.x - 8, per = (gridDim.x - 8) >> 3;
     const int tile = (b & 7) * per + (b >> 3);
     if (tile >= a.ntiles) return;
-    stream2_tile<T, 9, true, STOREQ, ZC9, LOOK>(a, tile);
+    stream2_tile<T, 9, true, STOREQ, ZC9, LOOK>(a, tile, LOOK ? chk.flags + (chk.k & 1) : nullptr);
 }
 
 template <typename T>
-hipError_t launch_stream2_check(int variant, const StreamArgs<T> &a, int grid, const CheckArgs &chk, hipStream_t s)
+hipError_t launch_stream2_check(int variant, StreamArgs<T> a, int grid, const CheckArgs &chk, hipStream_t s)
 {
+    a.active = chk.before();
     const dim3 g(grid + 8), b(64);
     // the second look at the flag costs a launch 2 % (15.0 -> 15.3 us on 1025^2 in
     // FP32) and ends a 70 us one after 15: levels beyond 2^21 vertices take it
@@ -1020,8 +1021,8 @@ hipError_t launch_stream2_check(int variant, const StreamArgs<T> &a, int grid, c
     else hipLaunchKernelGGL((k_stream2_check<T, false, false, false>), g, b, 0, s, a, chk);
     return hipGetLastError();
 }
-template hipError_t launch_stream2_check<double>(int, const StreamArgs<double> &, int, const CheckArgs &, hipStream_t);
-template hipError_t launch_stream2_check<float>(int, const StreamArgs<float> &, int, const CheckArgs &, hipStream_t);
+template hipError_t launch_stream2_check<double>(int, StreamArgs<double>, int, const CheckArgs &, hipStream_t);
+template hipError_t launch_stream2_check<float>(int, StreamArgs<float>, int, const CheckArgs &, hipStream_t);
 
 // The up leg's first pass with the r/C term formed from the loaded rows
 // instead of read from a stored plane (section 3, interpolation with r/C):
@@ -1546,15 +1547,12 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArg
     constexpr int R = (NW * TILE_RPW - 10) / 2;
     __shared__ T xs[2][NW][64][2];   // x of each wave's first [0] and last [1] row
     __shared__ T rs[NW][64][2];      // residual of each wave's last row
-    __shared__ int go;
     const int tile = blockIdx.x;
     if (tile >= a.ntiles) {   // the extra workgroup
         cycle_check(chk);
         return;
     }
-    // with the test along, the flag is looked at behind the first barrier
-    const bool rides = chk.partials != nullptr;
-    if (!rides && a.active && *a.active == 0) return;
+    if (a.active && *a.active == 0) return;
     const int strip = tile % a.nstrips, blk = tile / a.nstrips;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int t = strip * OWN + lane - HL;
@@ -1618,7 +1616,6 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArg
         }
         return r;
     };
-    if (rides && threadIdx.x == 0) go = run_flag(a.active);
 #pragma unroll
     for (int sweep = 0; sweep < 2; ++sweep) {
         {   // even rows: colours 0 and 1 (the first sweep starts from x = 0)
@@ -1629,7 +1626,6 @@ __global__ __launch_bounds__(64 * NW) void k_tile_down(StreamArgs<T> a, CheckArg
             xs[0][w][lane][1] = rw[0].x1;
         }
         __syncthreads();
-        if (sweep == 0 && rides && go == 0) return;
         {   // odd rows: colours 2 and 3
             tile_relax_row(rw[0], rw[1], rw[2], jw0 + 1, L);
             const Row<T> a3 = above();
@@ -2118,11 +2114,12 @@ template hipError_t launch_tile_pass<double>(int, StreamArgs<double>, hipStream_
 template hipError_t launch_tile_pass<float>(int, StreamArgs<float>, hipStream_t);
 
 template <typename T>
-hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s, const CheckArgs *chk)
+hipError_t launch_tile(int down, int nw, StreamArgs<T> a, hipStream_t s, const CheckArgs *chk)
 {
     if (a.ntiles <= 0) return hipErrorInvalidValue;
     const int extra = down && chk && chk->partials ? 1 : 0;
     const CheckArgs c = extra ? *chk : CheckArgs{};
+    if (extra) a.active = c.before();
     if (nw == 8) {
         if (down) hipLaunchKernelGGL((k_tile_down<T, 8>), dim3(a.ntiles + extra), dim3(512), 0, s, a, c);
         else hipLaunchKernelGGL((k_tile_up<T, 8>), dim3(a.ntiles), dim3(512), 0, s, a);
@@ -2134,7 +2131,7 @@ hipError_t launch_tile(int down, int nw, const StreamArgs<T> &a, hipStream_t s, 
     }
     return hipGetLastError();
 }
-template hipError_t launch_tile<double>(int, int, const StreamArgs<double> &, hipStream_t, const CheckArgs *);
-template hipError_t launch_tile<float>(int, int, const StreamArgs<float> &, hipStream_t, const CheckArgs *);
+template hipError_t launch_tile<double>(int, int, StreamArgs<double>, hipStream_t, const CheckArgs *);
+template hipError_t launch_tile<float>(int, int, StreamArgs<float>, hipStream_t, const CheckArgs *);
 
 }  // namespace hbmg
