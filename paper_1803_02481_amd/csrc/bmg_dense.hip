@@ -132,15 +132,25 @@ __device__ __forceinline__ void dinterp(const DV &F, const DV &Cl, int rescorr)
 // on e_c.  Bound by the operator's reads from L2 (a column walks the top level
 // five times) and the latency of its phases; two columns share the reads and
 // write M 16 bytes at a time.  The whole matrix of 961 unknowns (33^2) takes
-// 53 us (62 with a column per workgroup), of 1833 (49 x 41) 232 us (261).
+// 52 us (62 with a column per workgroup), of 1833 (49 x 41) 205 us: 232 with its
+// coarse factor of 20 unknowns read from memory, a barrier per unknown.  Rows
+// kept in registers over a level's colours change nothing: the iterate's reads
+// from LDS and the divisions take the time.
 __global__ __launch_bounds__(512) void k_dense_build(DenseBuildArgs a)
 {
     extern __shared__ __align__(16) D2 dsm[];
     const int col = 2 * blockIdx.x;
     for (int t = threadIdx.x; t < a.lds_elems; t += blockDim.x) dsm[t] = 0.0;
+    if (a.lds_chol >= 0)
+        for (int t = threadIdx.x; t < a.nc * a.nc; t += blockDim.x)
+            reinterpret_cast<double *>(dsm + a.lds_chol)[t] = a.chol[t];
     __syncthreads();
     const DV T = dview(a, a.top);
     const int ni = T.nx - 2, n = ni * (T.ny - 2);
+    // ld is even, and its columns from n on are zero (an odd n's column n is this
+    // workgroup's second)
+    for (int row = blockIdx.x; row < n; row += gridDim.x)
+        for (int c = n + (n & 1) + threadIdx.x; c < a.ld; c += blockDim.x) a.M[(size_t)row * a.ld + c] = 0.0;
     if (threadIdx.x < 2 && col + (int)threadIdx.x < n) {
         const int c = col + threadIdx.x;
         T.b[(1 + c / ni) * T.nx + 1 + c % ni][threadIdx.x] = 1.0;
@@ -163,24 +173,46 @@ __global__ __launch_bounds__(512) void k_dense_build(DenseBuildArgs a)
         const DV L0 = dview(a, 0);
         D2 *y = dsm + a.lds_y;
         const int m = L0.nx - 2, nc = a.nc;
-        for (int k = threadIdx.x; k < nc; k += blockDim.x) y[k] = L0.b[(1 + k / m) * L0.nx + 1 + k % m];
-        __syncthreads();
-        for (int k = 0; k < nc; ++k) {
-            const D2 yk = y[k] / a.chol[(size_t)k * nc + k];
-            for (int q = k + 1 + threadIdx.x; q < nc; q += blockDim.x) y[q] -= a.chol[(size_t)q * nc + k] * yk;
+        if (a.lds_chol >= 0) {
+            // one wave, an unknown per lane, the factor in LDS: the same operations
+            // without a barrier and a memory latency per unknown
+            if (threadIdx.x < 64) {
+                const double *ch = reinterpret_cast<const double *>(dsm + a.lds_chol);
+                const int r = threadIdx.x, at = r < nc ? (1 + r / m) * L0.nx + 1 + r % m : 0;
+                D2 v = r < nc ? L0.b[at] : D2(0.0);
+                for (int k = 0; k < nc; ++k) {
+                    const D2 vk = D2{__shfl(v.x, k, 64), __shfl(v.y, k, 64)} / ch[k * nc + k];
+                    if (r > k && r < nc) v -= ch[r * nc + k] * vk;
+                    if (r == k) v = vk;
+                }
+                for (int k = nc - 1; k >= 0; --k) {
+                    const D2 vk = D2{__shfl(v.x, k, 64), __shfl(v.y, k, 64)} / ch[k * nc + k];
+                    if (r < k) v -= ch[k * nc + r] * vk;
+                    if (r == k) v = vk;
+                }
+                if (r < nc) L0.x[at] = v;
+            }
             __syncthreads();
-            if (threadIdx.x == 0) y[k] = yk;
+        } else {
+            for (int k = threadIdx.x; k < nc; k += blockDim.x) y[k] = L0.b[(1 + k / m) * L0.nx + 1 + k % m];
+            __syncthreads();
+            for (int k = 0; k < nc; ++k) {
+                const D2 yk = y[k] / a.chol[(size_t)k * nc + k];
+                for (int q = k + 1 + threadIdx.x; q < nc; q += blockDim.x) y[q] -= a.chol[(size_t)q * nc + k] * yk;
+                __syncthreads();
+                if (threadIdx.x == 0) y[k] = yk;
+                __syncthreads();
+            }
+            for (int k = nc - 1; k >= 0; --k) {
+                const D2 xk = y[k] / a.chol[(size_t)k * nc + k];
+                for (int q = threadIdx.x; q < k; q += blockDim.x) y[q] -= a.chol[(size_t)k * nc + q] * xk;
+                __syncthreads();
+                if (threadIdx.x == 0) y[k] = xk;
+                __syncthreads();
+            }
+            for (int k = threadIdx.x; k < nc; k += blockDim.x) L0.x[(1 + k / m) * L0.nx + 1 + k % m] = y[k];
             __syncthreads();
         }
-        for (int k = nc - 1; k >= 0; --k) {
-            const D2 xk = y[k] / a.chol[(size_t)k * nc + k];
-            for (int q = threadIdx.x; q < k; q += blockDim.x) y[q] -= a.chol[(size_t)k * nc + q] * xk;
-            __syncthreads();
-            if (threadIdx.x == 0) y[k] = xk;
-            __syncthreads();
-        }
-        for (int k = threadIdx.x; k < nc; k += blockDim.x) L0.x[(1 + k / m) * L0.nx + 1 + k % m] = y[k];
-        __syncthreads();
     }
     for (int l = 1; l <= a.top; ++l) {
         const DV F = dview(a, l), Cl = dview(a, l - 1);
@@ -188,14 +220,13 @@ __global__ __launch_bounds__(512) void k_dense_build(DenseBuildArgs a)
         __syncthreads();
         for (int s = 0; s < a.nu2; ++s) dsweep(F);
     }
-    // ld is even, and its columns from n on are zero
     for (int row = threadIdx.x; row < n; row += blockDim.x)
         *reinterpret_cast<D2 *>(a.M + (size_t)row * a.ld + col) = T.x[(1 + row / ni) * T.nx + 1 + row % ni];
 }
 
 hipError_t launch_dense_build(const DenseBuildArgs &a, int n, hipStream_t s)
 {
-    const int lds = a.lds_elems * (int)sizeof(D2);
+    const int lds = (a.lds_elems + (a.lds_chol >= 0 ? (a.nc * a.nc + 1) / 2 : 0)) * (int)sizeof(D2);
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_dense_build),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, DENSE_LDS);
     if (e != hipSuccess) return e;

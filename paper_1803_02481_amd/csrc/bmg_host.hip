@@ -435,17 +435,19 @@ constexpr size_t ARENA_CHUNK = size_t(16) << 20;
 
 static size_t dalloc_bytes(size_t n, size_t elem) { return (n * elem + 256 + 255) / 256 * 256; }
 
-static hipbmg_status arena_reserve(hipbmg_hier *h, size_t bytes, hipStream_t s)
+// `raw` more bytes behind them, not zeroed, for the dense operator
+static hipbmg_status arena_reserve(hipbmg_hier *h, size_t bytes, size_t raw, hipStream_t s)
 {
     void *q = nullptr;
-    if (dev_malloc(&q, bytes) != hipSuccess) {
+    if (dev_malloc(&q, bytes + raw) != hipSuccess) {
         (void)hipGetLastError();
-        return fail(HIPBMG_ENOMEM, "device allocation of %zu bytes failed", bytes);
+        return fail(HIPBMG_ENOMEM, "device allocation of %zu bytes failed", bytes + raw);
     }
     h->allocs.push_back(q);
     HIPCHK(hipMemsetAsync(q, 0, bytes, s));
     h->arena = static_cast<char *>(q);
     h->arena_left = bytes;
+    if (raw) h->d_dense = reinterpret_cast<double *>(h->arena + bytes);
     return HIPBMG_OK;
 }
 
@@ -843,8 +845,9 @@ static hipbmg_status build_hierarchy(int nx, int ny, int npt, const double *coef
         size_t need = levels_bytes<double>(sx, sy) + (mixed ? levels_bytes<float>(sx, sy) : 0) + (size_t(1) << 20);
         if (npt == 5 && prm.nu1 == 2 && prm.nu2 == 1 && L >= 2)
             need += dalloc_bytes(fplane, sizeof(double)) + (mixed ? dalloc_bytes(fplane, sizeof(float)) : 0);
-        if (dense_top >= 0) need += dalloc_bytes((size_t)h->dense_n * h->dense_ld, sizeof(double));
-        const hipbmg_status rs = arena_reserve(h, need, s);
+        need = (need + 255) / 256 * 256;
+        const size_t raw = dense_top >= 0 ? (size_t)h->dense_n * h->dense_ld * sizeof(double) : 0;
+        const hipbmg_status rs = arena_reserve(h, need, raw, s);
         if (rs != HIPBMG_OK) return bail(rs);
     }
     hipbmg_status st = alloc_levels(h, h->lv, sx, sy, s);
@@ -1177,8 +1180,6 @@ static hipbmg_status build_hierarchy(int nx, int ny, int npt, const double *coef
         h->path_us = h->model_us[h->lstar];
     }
     if (dense_top >= 0) {
-        st = dalloc(h, &h->d_dense, (size_t)h->dense_n * h->dense_ld, s);
-        if (st != HIPBMG_OK) return bail(st);
         h->dense_top = dense_top;
         h->path_us = model_dense_path_us(ml, L, prm.nu1, prm.nu2, prm.precision == HIPBMG_MIXED ? 4 : 8, h->mp,
                                          dense_top, h->dense_n, h->dense_ld);
@@ -1510,6 +1511,9 @@ static hipbmg_status ensure_dense(hipbmg_hier *h, hipStream_t s)
     }
     a.lds_y = (int)dense_lds(sx, sy, a.top, a.lds_off);
     a.lds_elems = a.lds_y + h->nc;
+    // the factor of at most 64 unknowns goes to LDS where it still fits
+    const size_t with = (size_t)a.lds_elems * 16 + ((size_t)h->nc * h->nc + 1) / 2 * 16;
+    a.lds_chol = h->nc <= 64 && with <= (size_t)DENSE_LDS ? a.lds_elems : -1;
     a.M = h->d_dense;
     a.ld = h->dense_ld;
     HIPCHK(launch_dense_build(a, h->dense_n, s));

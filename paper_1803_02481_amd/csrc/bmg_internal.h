@@ -257,6 +257,7 @@ struct DenseBuildArgs {
     int nc;
     int lds_off[COLLAPSE_MAX_LEVELS];         // pairs of doubles: x, r, b of each level at compact pitch
     int lds_y, lds_elems;
+    int lds_chol;                             // the factor's place behind lds_elems, or -1: it stays in global memory
     double *M;
     int ld;
 };
