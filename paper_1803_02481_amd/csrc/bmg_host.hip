@@ -3191,7 +3191,7 @@ static hipbmg_status build_plans(hipbmg_batch *B, hipStream_t s)
     return st;
 }
 
-// Time (us, best of three) of every launch of one V-cycle of the batch, every
+// Time (us, best of two) of every launch of one V-cycle of the batch, every
 // problem active; ev holds one event more than the plan has launches.
 template <typename T>
 static hipbmg_status time_stages(hipbmg_batch *B, BPlan &plan, hipStream_t s, std::vector<hipEvent_t> &ev,
@@ -3205,7 +3205,7 @@ static hipbmg_status time_stages(hipbmg_batch *B, BPlan &plan, hipStream_t s, st
     }
     us.assign(n, 1e30);
     HIPCHK(run_plan_launches<T>(B, plan, B->d_active, s));   // warm-up
-    for (int r = 0; r < 3; ++r) {
+    for (int r = 0; r < 2; ++r) {
         HIPCHK(hipEventRecord(ev[0], s));
         for (size_t k = 0; k < n; ++k) {
             HIPCHK(run_launch<T>(B, plan.launches[k], B->d_active, s));
@@ -3283,9 +3283,12 @@ static hipbmg_status tune_batch(hipbmg_batch *B, hipStream_t s)
     std::vector<double> us;
     std::map<int, std::pair<double, TileShape>> best;
     hipbmg_status st = HIPBMG_OK;
+    int steps = 0;   // of the tallest problem: a longer tile than that is the same one
+    for (hipbmg_hier *h : B->hs) steps = std::max(steps, (h->ny - 1) / 2);
     for (int w : {1, 2, 4}) {
         if (wfix && w != wfix) continue;
         for (int cap : {0, 2, 4, 8, 16, 32, 64, 128}) {
+            if (cap / 2 >= steps) break;
             B->base = TileShape{cap, w};
             if ((st = build_plans(B, s)) != HIPBMG_OK) break;
             BPlan *plan;
