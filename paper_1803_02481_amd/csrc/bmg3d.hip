@@ -2817,20 +2817,22 @@ extern "C" hipbmg_status hipbmg3d_solve(hipbmg3d_handle h, const double *b, doub
     auto t0 = std::chrono::steady_clock::now();
     Lev3 &f = h->lv[h->L - 1];
     hbmg::Drain drain{s};
+    // the first sweep waits for ||b||, which comes while u is on its way in: a
+    // solve of b = 0 does not pay for it
     ST3(to_oct(f.g, b, f.b, 1, s, h->scale));
-    ST3(to_oct(f.g, u, f.x[0], 1, s));
-    h->cur = 0;
-    if (overlapped(h)) {
-        ST3(half_sweep(h, h->L - 1, 0, 0, false, 0, s));
-        ST3(second_half(h, 0, s));
-    }
     hipLaunchKernelGGL(k3_sumsq, dim3(nblk(f.g.field)), dim3(256), 0, s, f.g, (const double *)f.b, h->d_part);
     HIP3(hipGetLastError());
     // ||b||'s tag, and one a cycle behind it
     const double tag0 = h->tags.take(1 + (std::uint64_t)std::max(h->prm.max_cycles, 0));
     ST3(reduce_sum(h, h->d_part, (long long)nblk(f.g.field), tag0, s));
+    ST3(to_oct(f.g, u, f.x[0], 1, s));
+    h->cur = 0;
     double bb = 0.0;
     ST3(wait_sum(h, tag0, s, &bb));
+    if (bb != 0.0 && overlapped(h)) {
+        ST3(half_sweep(h, h->L - 1, 0, 0, false, 0, s));
+        ST3(second_half(h, 0, s));
+    }
     const double bn = std::sqrt(bb);
     if (info) {
         std::memset(info, 0, sizeof *info);

@@ -629,7 +629,7 @@ __global__ __launch_bounds__(256) void k_finalize(const double *__restrict__ par
         const double v = sqrt(sum);
         out[0] = v;
         if (flags) {
-            flags[0] = flags[1] = 1;
+            flags[0] = flags[1] = v > 0.0 && isfinite(v);
         }
         if (slot) slot_write(slot, v, 0.0, 0.0, tag);
     }

@@ -139,6 +139,7 @@ __device__ __forceinline__ void dinterp(const DV &F, const DV &Cl, int rescorr)
 __global__ __launch_bounds__(512) void k_dense_build(DenseBuildArgs a)
 {
     extern __shared__ __align__(16) D2 dsm[];
+    if (*a.active == 0) return;
     const int col = 2 * blockIdx.x;
     for (int t = threadIdx.x; t < a.lds_elems; t += blockDim.x) dsm[t] = 0.0;
     if (a.lds_chol >= 0)

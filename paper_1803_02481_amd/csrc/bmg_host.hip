@@ -1516,6 +1516,7 @@ static hipbmg_status ensure_dense(hipbmg_hier *h, hipStream_t s)
     a.lds_chol = h->nc <= 64 && with <= (size_t)DENSE_LDS ? a.lds_elems : -1;
     a.M = h->d_dense;
     a.ld = h->dense_ld;
+    a.active = h->d_flags;
     HIPCHK(launch_dense_build(a, h->dense_n, s));
     return HIPBMG_OK;
 }
@@ -1560,15 +1561,15 @@ static bool check_rides(const hipbmg_hier *h)
 // Run up to max_cycles V-cycles on the hierarchy lv (FP64 levels, or the FP32
 // levels of a mixed solve) from its finest iterate x[0] (or from zero), with
 // the convergence test ||r|| / denom[0] <= tol after every cycle taken on the
-// device.  The caller has set the run flag.  The host enqueues up to `ahead`
+// device.  The caller has set the run flags (a norm of 0 leaves them clear, and
+// every launch here returns at once).  The host enqueues up to `ahead`
 // cycles beyond the last test it has seen; once a test is met the device clears
 // the run flag and every launch of later cycles returns at once, so the iterate
 // stays the one of the stopping cycle.  The host polls host-mapped slots for
 // the tests and never waits for the stream.  With the finest level pipelined,
 // cycle k's post-relaxation, norm and cycle k+1's pre-relaxations and
 // restriction are one pass over three iterate buffers.  gate (or null) is
-// called once the first cycle is enqueued and ends the run unless it returns
-// OK.  On return *result is the finest buffer that holds the iterate after the
+// called once the first launch is out and ends the run unless it returns OK.  On return *result is the finest buffer that holds the iterate after the
 // last cycle run (once the stream gets there), *cycles_done their number,
 // h->hist the residual history and h->stop_reason why it stopped.
 template <typename T>
@@ -1595,6 +1596,7 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
         // pre-relaxations of cycle 1 and the restriction of its residual
         const LevelDev<T> &Cl = lv[L - 2];
         StreamArgs<T> a = base_args(F, h->rb[L - 1]);
+        a.active = h->d_flags;
         a.x_in = xb[0];
         a.x_out = xb[1];
         a.q_out = F.q;
@@ -1606,6 +1608,7 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
         a.cplane = (long long)Cl.plane;
         HIPCHK(run_stream(F, zero_start ? SV_SWEEP2_RQ_ZX : SV_SWEEP2_RQ, a, s));
     }
+    if (gate) STCHK(gate());
     int k = 0, seen = 0, i = 1, cur = 0, kdone = 0;
     bool stopped = false;
     const bool ride = pipe && check_rides(h);
@@ -1687,7 +1690,6 @@ static hipbmg_status run_cycles(hipbmg_hier *h, const std::vector<LevelDev<T>> &
             HIPCHK(launch_finalize_check(pending, s));
             pending = CheckArgs{};
         }
-        if (k == 1 && gate) STCHK(gate());
         // the tests of earlier cycles, `ahead` cycles behind the newest
         while (seen < k - ahead && !stopped) {
             STCHK(look());
@@ -1775,7 +1777,8 @@ static hipbmg_status solve_fp64(hipbmg_hier *h, double tol, hipStream_t s, hipbm
                                 const double **res_out, double bn_tag, double *bnorm)
 {
     int cycles = 0;
-    // ||b|| is waited for once the first relaxations are under way
+    // ||b|| is waited for once the first relaxations are under way (which a norm
+    // of 0 ends at once)
     auto gate = [&]() -> hipbmg_status {
         STCHK(wait_bnorm(h, bn_tag, s, bnorm));
         return *bnorm == 0.0 ? HIPBMG_EINVAL : HIPBMG_OK;   // nothing to solve: ends the run
@@ -1812,7 +1815,9 @@ static hipbmg_status solve_mixed(hipbmg_hier *h, double tol, hipStream_t s, hipb
     double bnorm = 0.0;
     for (;;) {
         int np = 0;
-        HIPCHK(launch_ir_residual(F, F.x[0], F32.b, F32.pitch, h->d_partials, &np, s));
+        // the first is out before ||b|| is seen, and returns at once where it is 0
+        HIPCHK(launch_ir_residual(F, F.x[0], F32.b, F32.pitch, h->d_partials, &np, steps == 0 ? h->d_flags : nullptr,
+                                  s));
         if (steps == 0) {
             STCHK(wait_bnorm(h, bn_tag, s, bnorm_out));
             bnorm = *bnorm_out;
@@ -1872,8 +1877,8 @@ extern "C" hipbmg_status hipbmg_solve(hipbmg_handle h, const double *b, double *
         memset(info, 0, sizeof *info);
         fill_info_common(h, info);
     }
-    // cycles may be on the stream when a solve ends early (||b|| is waited for
-    // behind them): every return leaves the handle idle
+    // launches may be on the stream when a solve ends early (||b|| is waited for
+    // behind the first of them): every return leaves the handle idle
     Drain drain{s};
     int nparts = 0;
     HIPCHK(launch_stage_in(b, u, F.b, F.x[0], nx, ny, F.pitch, h->scale, h->d_partials, &nparts, s));

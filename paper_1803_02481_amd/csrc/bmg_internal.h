@@ -260,6 +260,7 @@ struct DenseBuildArgs {
     int lds_chol;                             // the factor's place behind lds_elems, or -1: it stays in global memory
     double *M;
     int ld;
+    const int *active;                        // a run flag: nothing is formed where it is clear
 };
 hipError_t launch_dense_build(const DenseBuildArgs &a, int n, hipStream_t s);
 template <typename T>
@@ -312,7 +313,7 @@ hipError_t launch_finalize_batched(const double *partials, const int *off, const
 hipError_t launch_count_active(const int *active, int n, int *count, hipStream_t s);
 
 // out[0] = sqrt(sum(partials)).  flags (or null): starts a solve, both run
-// flags set.  slot (or null): host-mapped {norm, -, -, tag}.
+// flags set unless the norm is 0 or not finite (no cycle is to run).  slot (or null): host-mapped {norm, -, -, tag}.
 hipError_t launch_finalize_norm(const double *partials, int n, double *out, hipStream_t s, int *flags = nullptr,
                                 double *slot = nullptr, double tag = 0.0);
 hipError_t launch_finalize_check(const CheckArgs &c, hipStream_t s);

@@ -18,7 +18,7 @@ hipError_t launch_demote_level(const LevelDev<double> &d, const LevelDev<float> 
                                int cny, double normal, int *tiny, hipStream_t s);
 // r32 = (float)(b - A u) with FP64 partial sums of squares; *nparts partials written
 hipError_t launch_ir_residual(const LevelDev<double> &d, const double *u, float *r32, int pitchf,
-                              double *partials, int *nparts, hipStream_t s);
+                              double *partials, int *nparts, const int *active, hipStream_t s);
 // u += (double) e
 hipError_t launch_ir_update(double *u, int pitch, const float *e, int pitchf, int nx, int ny,
                             hipStream_t s);

@@ -160,9 +160,10 @@ constexpr int IR_ROWS = 16;
 template <int NPT>
 __global__ __launch_bounds__(256) void k_ir_residual(LevelDev<double> d, const double *__restrict__ u,
                                                      float *__restrict__ r32, int pitchf,
-                                                     double *__restrict__ partials)
+                                                     double *__restrict__ partials, const int *active)
 {
     __shared__ double sh[4];
+    if (active && *active == 0) return;
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int j0 = blockIdx.y * IR_ROWS, j1 = min(j0 + IR_ROWS, d.ny);
     double acc = 0.0;
@@ -191,14 +192,14 @@ __global__ __launch_bounds__(256) void k_ir_residual(LevelDev<double> d, const d
 }
 
 hipError_t launch_ir_residual(const LevelDev<double> &d, const double *u, float *r32, int pitchf,
-                              double *partials, int *nparts, hipStream_t s)
+                              double *partials, int *nparts, const int *active, hipStream_t s)
 {
     dim3 g((d.nx + 255) / 256, (d.ny + IR_ROWS - 1) / IR_ROWS);
     *nparts = g.x * g.y;
     if (d.npt == 9)
-        hipLaunchKernelGGL(k_ir_residual<9>, g, dim3(256), 0, s, d, u, r32, pitchf, partials);
+        hipLaunchKernelGGL(k_ir_residual<9>, g, dim3(256), 0, s, d, u, r32, pitchf, partials, active);
     else
-        hipLaunchKernelGGL(k_ir_residual<5>, g, dim3(256), 0, s, d, u, r32, pitchf, partials);
+        hipLaunchKernelGGL(k_ir_residual<5>, g, dim3(256), 0, s, d, u, r32, pitchf, partials, active);
     return hipGetLastError();
 }
 

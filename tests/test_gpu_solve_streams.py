@@ -16,9 +16,9 @@ def g(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
 
 
-# a right-hand side that is not finite ends a solve after its first cycle is
-# enqueued; as the handle's first one it also forms the dense coarse operator.
-# A level of 1833 unknowns takes the longest to form (769 x 641)
+# a right-hand side that is not finite ends a solve after its first launches are
+# out, among them, on a new handle, the one that forms the dense coarse operator:
+# 1833 unknowns take the longest (769 x 641)
 @pytest.mark.parametrize("precision", [HB.FP64, HB.MIXED], ids=["fp64", "mixed"])
 @pytest.mark.parametrize("prm", [{}, {"nu1": 1, "nu2": 2}])
 @pytest.mark.parametrize("shape", [(65, 65), (257, 257), (641, 769)])
@@ -95,3 +95,31 @@ def test_a_solve_after_one_refused_under_capture(shape):
         hip.hipGetLastError()
     v, info = h.solve(b, tol=1e-9)
     assert torch.equal(v, ref) and info.history() == iref.history()
+
+
+# b = 0 ends a solve after its launches are out: they return at once (on a new
+# handle the dense operator is not formed either), and the next solve is a first one
+@pytest.mark.parametrize("shape", [(65, 65), (641, 769), (17, 17, 17), (65, 33, 49)])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_a_zero_right_hand_side_then_another(shape, mixed):
+    if len(shape) == 2:
+        planes = HB.fv5_from_cells(g(inputs.cells_lognormal(shape[1], shape[0], 1.0, seed=37)))
+        b = g(inputs.load_uniform(shape[1], shape[0], seed=38))
+        new = lambda: HB.Hierarchy(planes, precision=HB.MIXED if mixed else HB.FP64)
+        solve = lambda h, f, u0: h.solve(f, u0.clone(), tol=1e-9)
+    else:
+        if mixed:
+            pytest.skip("3D runs in FP64")
+        nz, ny, nx = shape
+        planes = HB.fv7_from_cells(g(inputs.cells3_lognormal(nx, ny, nz, sigma=1.0, seed=37)))
+        b = g(inputs.load3_uniform(nx, ny, nz, seed=38))
+        new = lambda: HB.Hierarchy3(planes)
+        solve = lambda h, f, u0: h.solve(f, u0=u0, tol=1e-9)
+    u0 = g(np.random.default_rng(39).standard_normal(shape))
+    ref, iref = solve(new(), b, u0)
+    h = new()
+    for _ in range(2):
+        z, zinfo = solve(h, torch.zeros_like(b), u0)
+        assert zinfo.cycles == 0 and float(z.abs().max()) == 0.0
+        u, info = solve(h, b, u0)
+        assert torch.equal(u, ref) and info.history() == iref.history()
